@@ -11,10 +11,10 @@ N = 512 vectors filtered in 4 blocks of 128, Chebyshev degree 24, Gamma point.
 Printed JSON (one line, rank 0):
   value        FP64 filter throughput, TFLOP/s, in the 4M count of the dense complex
                cell product (a complex multiply-add = 8 flops) over the filter sections
-               of the timed passes; filter_tflops_real_work counts the Pauli form's own
-               products (0.75 of the 4M cell count at Gamma)
+               of the timed passes; filter_tflops_real_work counts the kernel's own
+               products (0.5 of the 4M cell count at Gamma)
   ms_per_step  wall time per FP64 pass (filter + CholGS + RR), the K timed passes
-  roofline     the FP64 cell-product kernel (dominant): the Pauli form's real flops per
+  roofline     the FP64 cell-product kernel (dominant): the kernel's real flops per
                launch / mean launch time from HIP events, against 78.6 TFLOP/s (the 4M
                and issued-MFMA rates beside it), with the counter-measured HBM traffic
   mixed, mixed_resid   the FP32 filter forms (plain: FP32 cell/projector products in
@@ -282,14 +282,18 @@ def cpu_baseline(s_name):
             "apply_s": t_apply}
 
 
-def cell_roofline(flops_4m, exec_flops, ms, gamma, peak):
+KERNEL_PRODUCTS = (8, 12)   # real n x n products per column of the cell kernel: at Gamma, with the k-term
+
+
+def cell_roofline(flops_4m, exec_flops, ms, gamma, peak, products=(12, 16)):
     """Roofline figures of one cell-product launch.  flops_4m is the 4M count of
-    the dense complex 2n x 2n cell product (8 (2n)^2 flops per column and cell);
-    the Pauli form needs 12 real n x n products per column at Gamma (16 with the
-    k-term) where that count assumes 16, so the method's own work is 0.75 (1.0) of
-    it.  achieved / frac use that real work; the issued MFMA count (row padding
-    included) and the dense-equivalent rate are reported beside them."""
-    real = flops_4m * (0.75 if gamma else 1.0)
+    the dense complex 2n x 2n cell product (8 (2n)^2 flops per column and cell),
+    which assumes 16 real n x n products per column; products are those of the form
+    at hand, at Gamma and with the k-term (entry by entry the Pauli form takes 12
+    and 16, as a sum of rank-one spin terms 8 and 12), so the method's own work is
+    products / 16 of it.  achieved / frac use that real work; the issued MFMA count
+    (row padding included) and the dense-equivalent rate are reported beside them."""
+    real = flops_4m * products[0 if gamma else 1] / 16.0
     sec = ms * 1e-3
     if sec <= 0:
         return {"achieved": 0.0, "frac": 0.0, "real_flops_per_launch": real}
@@ -801,12 +805,13 @@ def bench_scale(args, torch):
     total = time.perf_counter() - t0
     filt_tflops = fst["flops"] / sum(ftimes) / 1e12
     gamma = all(float(x) == 0.0 for x in np.ravel(s.kpts))
-    # the filter's real work: the cell part at 0.75 of its 4M count at Gamma
-    real_filt = (fst["flops"] - (0.25 if gamma else 0.0) * fst["cell_flops"]) / sum(ftimes) / 1e12
+    # the filter's real work: the cell part at the kernel's products of the 16 of its 4M count
+    cell_part = KERNEL_PRODUCTS[0 if gamma else 1] / 16.0
+    real_filt = (fst["flops"] - (1.0 - cell_part) * fst["cell_flops"]) / sum(ftimes) / 1e12
     n_l = max(1, fst["cell_launches"])
     cell_per_launch = fst["cell_flops"] / n_l
     cell_ms = fst["cell_ms"] / n_l
-    roof = cell_roofline(cell_per_launch, fst["cell_exec"] / n_l, cell_ms, gamma, PEAK_FP64)
+    roof = cell_roofline(cell_per_launch, fst["cell_exec"] / n_l, cell_ms, gamma, PEAK_FP64, KERNEL_PRODUCTS)
     # filter launches: one colour of cells x row tiles x column tiles of 64
     n_colour_cells = int(np.prod(s.n_cells)) // 8
     nloc = (s.p + 1) ** 3
@@ -834,7 +839,8 @@ def bench_scale(args, torch):
                      "traffic_unit": "HBM bytes per launch (calibrated FETCH_SIZE + WRITE_SIZE)",
                      "algorithmic_bytes_per_launch": cell_alg_bytes(s),
                      "kernel": "cell_apply_kernel<double, 2, false> (gather + Pauli-form cell products + scatter-add, 64-column tiles)",
-                     "flops_counting": "real work of the Pauli form (12 real n x n products per column at Gamma)",
+                     "flops_counting": "real work of the kernel (8 real n x n products per column at Gamma: the spin matrices as "
+                                       "four rank-one terms)",
                      "flops_per_launch": roof["real_flops_per_launch"], "mean_launch_ms": round(cell_ms, 4),
                      "dense_4M_flops_per_launch": cell_per_launch,
                      "dense_4M_equivalent_tflops": roof.get("dense_4M_equivalent_tflops"),

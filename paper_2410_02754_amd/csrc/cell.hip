@@ -10,10 +10,13 @@
 // with A = kinetic + |k|^2/2 mass + V-weighted mass and B_d the B_d-weighted
 // masses (real symmetric) and S the skew-symmetrised k-gradient term (real
 // antisymmetric, zero at Gamma).  Each cell stores the real matrices
-// Hp = A + Bz, Hm = A - Bz, Bx, By (and S when k != 0) instead of the complex
-// 2n x 2n matrix: half the bytes, and 12 instead of 16 real MFMAs per complex
-// multiply-add block at Gamma.  Matrices are stored pre-tiled in MFMA
-// A-operand order: [cell][row block of 16][k-step of 4][matrix][64 lanes].
+// Pu = A + Bz - Bx - By, Pd = A - Bz - Bx - By, Bx, By (and S when k != 0)
+// instead of the complex
+// 2n x 2n matrix: half the bytes, and 8 instead of 16 real MFMAs per complex
+// multiply-add block at Gamma (the sum of four rank-one spin terms below).
+// Matrices are stored pre-tiled in MFMA A-operand order: [cell][row block of
+// 16][k-step of 4], each tile [64 lanes][Pu, Pd, Bx, By] (one 16- or two 16-byte
+// loads per lane) and then [64 lanes] of S.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -80,15 +83,16 @@ __global__ __launch_bounds__(256) void cell_setup_kernel(
     if (valid) {
       const double s = sS[i] * sS[j];
       const double a0 = U0[(size_t)i * nloc + j] + mv;
-      vals[0] = s * (a0 + mbz);
-      vals[1] = s * (a0 - mbz);
+      vals[0] = s * (a0 + mbz - mbx - mby);
+      vals[1] = s * (a0 - mbz - mbx - mby);
       vals[2] = s * mbx;
       vals[3] = s * mby;
       vals[4] = (nmat > 4) ? s * Sk[(size_t)i * nloc + j] : 0.0;
     }
     const int kb = j / 4, lane = (j % 4) * 16 + il;
-    double* dst = out + (((size_t)e * nrb + rb) * nkb + kb) * nmat * 64 + lane;
-    for (int m = 0; m < nmat; ++m) dst[m * 64] = vals[m];
+    double* dst = out + (((size_t)e * nrb + rb) * nkb + kb) * nmat * 64;
+    for (int m = 0; m < 4; ++m) dst[lane * 4 + m] = vals[m];
+    if (nmat > 4) dst[256 + lane] = vals[4];
   }
 }
 
@@ -123,38 +127,62 @@ void launch_cell_to_f32(chfsi_ctx* c, KPoint& kp) {
 // ============================================================================
 // Fused gather / cell product / scatter-add, one launch per colour
 // ============================================================================
-// Block = 4 waves as 2 (row blocks) x 2 (column halves).  Block tile: 32 local
-// rows x BN = 32*CB columns of one cell.  K loop over the cell's local nodes in
-// stages of 8 nodes: the gathered spinor rows (X_up = a + ib, X_dn = c + id)
-// are staged in LDS as four planar real arrays, double-buffered, with the
-// next stage's global loads issued before the current stage's MFMAs.  Each
-// wave reads its A fragments (Hp, Hm, Bx, By, S) straight from the pre-tiled
-// cell operator.  Per 4-node k-step and 16-column block the products are
-//   Yup_r += Hp a + Bx c + By d - S b      Yup_i += Hp b + Bx d - By c + S a
-//   Ydn_r += Hm c + Bx a - By b - S d      Ydn_i += Hm d + Bx b + By a + S c
-template <class T, int CB>
+// Block = 2 (row blocks) x WC (column groups) waves of 16 rows x 16*CB columns:
+// block tile 32 local rows x BN = 16*CB*WC columns of one cell.  K loop over
+// the cell's local nodes in stages of 8 nodes: the gathered spinor rows (u, d) =
+// (X_up, X_dn) are staged in LDS as complex pairs, double-buffered, with the
+// next stage's global loads issued before the current stage's MFMAs.  Each wave
+// reads its A fragments straight from the pre-tiled cell operator.  The spin
+// structure is a sum of four rank-one terms,
+//   A + B.sigma = Pu |up><up| + Pd |dn><dn| + Bx |1,1><1,1| + By |1,i><1,i|
+//   Pu = A + Bz - Bx - By,  Pd = A - Bz - Bx - By,
+// so that per 4-node k-step and 16-column block 8 real products do
+//   yu = Pu u,  yd = Pd d,  tx = Bx (u + d),  ty = By (u - i d)     (+ S: 4 more)
+//   Y_up = yu + tx + ty,    Y_dn = yd + tx + i ty
+// instead of the 12 of the products entry by entry.  The MFMAs bound the kernel
+// (80 % of its wave cycles wait for them), so the four extra accumulators and the
+// additions on the fragments are paid for.  FP64 filter of 128 columns on 8^3
+// cells, p = 6, degree 24: 97.2 -> 74.0 ms; with FP32 products and the k-term, 200
+// columns on 10^3 cells, p = 5, degree 16: 80.5 -> 68.7 ms.
+template <class T> struct CellC2;
+template <> struct CellC2<double> { typedef double2 type; };
+template <> struct CellC2<float> { typedef float2 type; };
+
+// Shape of a tile of 32 TW columns (TW = 1, 2, 4): column groups of waves and
+// 16-column blocks per wave.  FP64: one block per wave up to 64 columns (eight
+// waves, 128 VGPRs, 16 waves per CU; two blocks per wave leave 8 per CU and run
+// 4 % slower); FP32: two (its accumulators are half as wide, 4 % faster than one).
+template <class T, int TW> constexpr int cell_wc() { return sizeof(T) == 8 ? (TW == 1 ? 2 : 4) : (TW == 4 ? 4 : 2); }
+template <class T, int TW> constexpr int cell_cb() { return 2 * TW / cell_wc<T, TW>(); }
+template <class T, int TW> constexpr int cell_threads() { return 128 * cell_wc<T, TW>(); }
+// waves per SIMD that the registers are limited for
+template <class T, int TW> constexpr int cell_min_waves() { return sizeof(T) == 8 && cell_cb<T, TW>() > 1 ? 2 : 4; }
+
+template <class T, int TW>
 struct CellSmem {
-  static constexpr int BN = 32 * CB;
+  static constexpr int BN = 32 * TW;
   static constexpr int BK = 8;
-  static constexpr int PAD = 16;          // row pad: 4 k-rows of a fragment hit disjoint banks
-  T sB[2][4][BK][BN + PAD];
+  static constexpr int PAD = 2;
+  typename CellC2<T>::type sB[2][2][BK][BN + PAD];      // [buffer][spin][node][column]
   int32_t sNode[(kMaxP + 1) * (kMaxP + 1) * (kMaxP + 1)];
 };
 
 // One block tile of the fused gather / cell product / scatter-add for cell e,
 // row tile rt (two 16-row blocks) and column tile ct.  Starts and ends with
 // the block synchronised, so it can be called repeatedly by a persistent block.
-template <class T, int CB, bool HAS_S>
-__device__ __forceinline__ void cell_tile(CellSmem<T, CB>& sm, const T* __restrict__ cm,
+template <class T, int TW, bool HAS_S>
+__device__ __forceinline__ void cell_tile(CellSmem<T, TW>& sm, const T* __restrict__ cm,
                                           const int32_t* __restrict__ cell_nodes, int e, int rt, int ct,
                                           int nloc, int nrb, int nkb, int nmat,
                                           const double2* __restrict__ X, int64_t ldx,
                                           double2* __restrict__ W, int64_t ldw, int n_vec, double alpha) {
   typedef typename Vec4<T>::type V4;
-  constexpr int BN = 32 * CB;
+  typedef typename CellC2<T>::type C2;
+  constexpr int CB = cell_cb<T, TW>();
+  constexpr int NT = cell_threads<T, TW>();
+  constexpr int BN = 32 * TW;
   constexpr int BK = 8;
-  constexpr int NPRE = (BK * 2 * BN) / 256;
-  constexpr int NM = HAS_S ? 5 : 4;
+  constexpr int NPRE = (BK * 2 * BN) / NT;
   auto& sB = sm.sB;
   auto& sNode = sm.sNode;
   __syncthreads();                        // previous tile's LDS reads are done
@@ -168,27 +196,30 @@ __device__ __forceinline__ void cell_tile(CellSmem<T, CB>& sm, const T* __restri
   // so the stage loop below has no branches and loads overlap the MFMAs
   const int rb_eff = row_active ? rb : nrb - 1;
   const int col0 = ct * BN;
+  // waves past the last column only stage and wait (a block of 130 columns costs 144, not 192)
+  const bool cols_active = col0 + wc * (CB * 16) < n_vec;
 
-  for (int i = tid; i < nloc; i += 256) sNode[i] = cell_nodes[(size_t)e * nloc + i];
+  for (int i = tid; i < nloc; i += NT) sNode[i] = cell_nodes[(size_t)e * nloc + i];
   __syncthreads();
 
-  V4 acc[CB][4];
+  V4 acc[CB][8];                          // yu, yd, tx, ty: real and imaginary parts
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) acc[cb][k] = V4{0, 0, 0, 0};
+    for (int k = 0; k < 8; ++k) acc[cb][k] = V4{0, 0, 0, 0};
 
-  const T* Abase = cm + ((size_t)(e * nrb + rb_eff) * nkb) * nmat * 64 + lane;
+  const T* Abase = cm + ((size_t)(e * nrb + rb_eff) * nkb) * nmat * 64;
   const int nstage = nkb / 2;
   double2 pre[NPRE];
-  T aC[2][NM], aN[2][NM];
+  V4 aC[2], aN[2];                        // Pu, Pd, Bx, By of the stage's two k-steps
+  T sC[2], sN[2];
 
   // per-thread constants of the gather: (k node, spin, column) of each prefetch slot
   int g_kk[NPRE], g_sp[NPRE], g_col[NPRE];
   bool g_cv[NPRE];
 #pragma unroll
   for (int j = 0; j < NPRE; ++j) {
-    const int idx = tid + 256 * j;
+    const int idx = tid + NT * j;
     g_col[j] = idx % BN;
     g_sp[j] = (idx / BN) & 1;
     g_kk[j] = idx / (2 * BN);
@@ -209,81 +240,79 @@ __device__ __forceinline__ void cell_tile(CellSmem<T, CB>& sm, const T* __restri
   };
   auto lstore = [&](int buf) {
 #pragma unroll
-    for (int j = 0; j < NPRE; ++j) {
-      sB[buf][2 * g_sp[j]][g_kk[j]][g_col[j]] = (T)pre[j].x;
-      sB[buf][2 * g_sp[j] + 1][g_kk[j]][g_col[j]] = (T)pre[j].y;
-    }
+    for (int j = 0; j < NPRE; ++j) sB[buf][g_sp[j]][g_kk[j]][g_col[j]] = C2{(T)pre[j].x, (T)pre[j].y};
   };
-  auto aload = [&](int s, T (&dst)[2][NM]) {
+  // tile of one k-step: [64 lanes][Pu, Pd, Bx, By], then [64 lanes] of S
+  auto aload = [&](int s, V4 (&dst)[2], T (&ds)[2]) {
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
       const T* Ap = Abase + (size_t)(s * 2 + kk) * nmat * 64;
-#pragma unroll
-      for (int m = 0; m < NM; ++m) dst[kk][m] = Ap[m * 64];
+      dst[kk] = *reinterpret_cast<const V4*>(Ap + lane * 4);
+      ds[kk] = HAS_S ? Ap[256 + lane] : (T)0;
     }
   };
 
-  aload(0, aC);
   gload(0);
   lstore(0);
+  if (!cols_active) {
+    __syncthreads();
+    for (int s = 0; s < nstage; ++s) {
+      gload(s + 1 < nstage ? s + 1 : s);
+      lstore((s & 1) ^ 1);
+      __syncthreads();
+    }
+    return;                               // (no barrier follows inside the tile)
+  }
+  aload(0, aC, sC);
   __syncthreads();
   for (int s = 0; s < nstage; ++s) {
     const int buf = s & 1;
     const int sn = s + 1 < nstage ? s + 1 : s;      // the last stage reloads itself (unused)
     gload(sn);
-    aload(sn, aN);
+    aload(sn, aN, sN);
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
-      const T hp = aC[kk][0], hm = aC[kk][1], bx = aC[kk][2], by = aC[kk][3];
-      const T sv = HAS_S ? aC[kk][NM - 1] : (T)0;
-      const T nby = -by, nsv = -sv;
+      const T pu = aC[kk][0], pd = aC[kk][1], bx = aC[kk][2], by = aC[kk][3];
+      const T sv = sC[kk], nsv = -sC[kk];
       const int krow = kk * 4 + (lane >> 4);
-      T ba[CB], bb[CB], bc[CB], bd[CB];
+      C2 u[CB], d[CB];
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
         const int col = wc * (CB * 16) + cb * 16 + (lane & 15);
-        ba[cb] = sB[buf][0][krow][col];
-        bb[cb] = sB[buf][1][krow][col];
-        bc[cb] = sB[buf][2][krow][col];
-        bd[cb] = sB[buf][3][krow][col];
+        u[cb] = sB[buf][0][krow][col];
+        d[cb] = sB[buf][1][krow][col];
       }
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
-        acc[cb][0] = mfma(hp, ba[cb], acc[cb][0]);
-        acc[cb][1] = mfma(hp, bb[cb], acc[cb][1]);
-        acc[cb][2] = mfma(hm, bc[cb], acc[cb][2]);
-        acc[cb][3] = mfma(hm, bd[cb], acc[cb][3]);
+        acc[cb][0] = mfma(pu, u[cb].x, acc[cb][0]);
+        acc[cb][1] = mfma(pu, u[cb].y, acc[cb][1]);
+        acc[cb][2] = mfma(pd, d[cb].x, acc[cb][2]);
+        acc[cb][3] = mfma(pd, d[cb].y, acc[cb][3]);
       }
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
-        acc[cb][0] = mfma(bx, bc[cb], acc[cb][0]);
-        acc[cb][1] = mfma(bx, bd[cb], acc[cb][1]);
-        acc[cb][2] = mfma(bx, ba[cb], acc[cb][2]);
-        acc[cb][3] = mfma(bx, bb[cb], acc[cb][3]);
-      }
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) {
-        acc[cb][0] = mfma(by, bd[cb], acc[cb][0]);
-        acc[cb][1] = mfma(nby, bc[cb], acc[cb][1]);
-        acc[cb][2] = mfma(nby, bb[cb], acc[cb][2]);
-        acc[cb][3] = mfma(by, ba[cb], acc[cb][3]);
+        acc[cb][4] = mfma(bx, u[cb].x + d[cb].x, acc[cb][4]);
+        acc[cb][5] = mfma(bx, u[cb].y + d[cb].y, acc[cb][5]);
+        acc[cb][6] = mfma(by, u[cb].x + d[cb].y, acc[cb][6]);
+        acc[cb][7] = mfma(by, u[cb].y - d[cb].x, acc[cb][7]);
       }
       if (HAS_S) {
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
-          acc[cb][0] = mfma(nsv, bb[cb], acc[cb][0]);
-          acc[cb][1] = mfma(sv, ba[cb], acc[cb][1]);
-          acc[cb][2] = mfma(nsv, bd[cb], acc[cb][2]);
-          acc[cb][3] = mfma(sv, bc[cb], acc[cb][3]);
+          acc[cb][0] = mfma(nsv, u[cb].y, acc[cb][0]);
+          acc[cb][1] = mfma(sv, u[cb].x, acc[cb][1]);
+          acc[cb][2] = mfma(nsv, d[cb].y, acc[cb][2]);
+          acc[cb][3] = mfma(sv, d[cb].x, acc[cb][3]);
         }
       }
     }
     lstore(buf ^ 1);       // the other buffer was last read before the previous barrier
     __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-      for (int m = 0; m < NM; ++m) aC[kk][m] = aN[kk][m];
+    for (int kk = 0; kk < 2; ++kk) {
+      aC[kk] = aN[kk];
+      sC[kk] = sN[kk];
+    }
   }
 
   if (!row_active) return;                // (no barrier follows inside the tile)
@@ -299,24 +328,27 @@ __device__ __forceinline__ void cell_tile(CellSmem<T, CB>& sm, const T* __restri
     for (int cb = 0; cb < CB; ++cb) {
       const int gcol = col0 + wc * (CB * 16) + cb * 16 + (lane & 15);
       if (gcol >= n_vec) continue;
+      const T tx = acc[cb][4][j], ti = acc[cb][5][j], yx = acc[cb][6][j], yi = acc[cb][7][j];
+      const C2 y0 = {acc[cb][0][j] + (tx + yx), acc[cb][1][j] + (ti + yi)};
+      const C2 y1 = {acc[cb][2][j] + (tx - yi), acc[cb][3][j] + (ti + yx)};
       double2 o0 = w0[gcol], o1 = w1[gcol];
-      o0.x += alpha * (double)acc[cb][0][j];
-      o0.y += alpha * (double)acc[cb][1][j];
-      o1.x += alpha * (double)acc[cb][2][j];
-      o1.y += alpha * (double)acc[cb][3][j];
+      o0.x = fma(alpha, (double)y0.x, o0.x);
+      o0.y = fma(alpha, (double)y0.y, o0.y);
+      o1.x = fma(alpha, (double)y1.x, o1.x);
+      o1.y = fma(alpha, (double)y1.y, o1.y);
       w0[gcol] = o0;
       w1[gcol] = o1;
     }
   }
 }
 
-template <class T, int CB, bool HAS_S>
-__global__ __launch_bounds__(256) void cell_apply_kernel(
+template <class T, int TW, bool HAS_S>
+__global__ __launch_bounds__((cell_threads<T, TW>()), (cell_min_waves<T, TW>())) void cell_apply_kernel(
     const T* __restrict__ cm, const int32_t* __restrict__ cell_nodes,
     const int32_t* __restrict__ cells, int nloc, int nrb, int nkb, int nmat, int n_rowtiles,
     int n_coltiles, int n_work, const double2* __restrict__ X, int64_t ldx, double2* __restrict__ W,
     int64_t ldw, int n_vec, double alpha) {
-  __shared__ CellSmem<T, CB> sm;
+  __shared__ CellSmem<T, TW> sm;
   // Workgroups are dispatched round-robin over the 8 XCDs; remap so that each
   // XCD gets a contiguous range of (cell, row tile, column tile) work and the
   // row tiles of one cell share that XCD's L2 for the gathered rows.
@@ -326,39 +358,33 @@ __global__ __launch_bounds__(256) void cell_apply_kernel(
   const int ct = bid % n_coltiles;
   const int rt = (bid / n_coltiles) % n_rowtiles;
   const int ci = bid / (n_coltiles * n_rowtiles);
-  cell_tile<T, CB, HAS_S>(sm, cm, cell_nodes, cells[ci], rt, ct, nloc, nrb, nkb, nmat, X, ldx, W, ldw, n_vec,
-                          alpha);
+  cell_tile<T, TW, HAS_S>(sm, cm, cell_nodes, cells[ci], rt, ct, nloc, nrb, nkb, nmat, X, ldx, W, ldw,
+                          n_vec, alpha);
 }
 
 // Batched form: one persistent grid walks a static list of (task, cell, row
 // tile, column tile) items of one colour phase across many independent
 // operators (k-points, systems).  Items were ordered on the host so that item
 // i runs on XCD i % 8 and the row tiles of a cell share an XCD.
-
-// Resident workgroups per CU the persistent form is compiled for: what the
-// per-colour kernel reaches, so the item walk costs no occupancy.
-template <int CB>
-constexpr int cell_min_blocks() { return CB == 4 ? 1 : CB == 2 ? 3 : 4; }
-
-template <class T, int CB, bool HAS_S>
-__global__ __launch_bounds__(256, cell_min_blocks<CB>()) void cell_batch_kernel(const BatchTaskArgs tasks,
+template <class T, int TW, bool HAS_S>
+__global__ __launch_bounds__((cell_threads<T, TW>()), (cell_min_waves<T, TW>())) void cell_batch_kernel(const BatchTaskArgs tasks,
                                                          const int4* __restrict__ items, int n_items,
                                                          const double* __restrict__ alpha, int src) {
-  __shared__ CellSmem<T, CB> sm;
+  __shared__ CellSmem<T, TW> sm;
   for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
     const int4 w = items[it];
     if (w.x < 0) continue;                // padding item (uniform over the block)
     const BatchTaskDev& t = tasks.t[w.x];
     const T* cm = sizeof(T) == 8 ? (const T*)t.cm64 : (const T*)t.cm32;
-    cell_tile<T, CB, HAS_S>(sm, cm, t.cell_nodes, w.y, w.z, w.w, t.nloc, t.nrb, t.nkb, t.nmat, t.buf[src],
-                            t.ld[src], t.buf[src ^ 1], t.ld[src ^ 1], t.n_vec, alpha[w.x]);
+    cell_tile<T, TW, HAS_S>(sm, cm, t.cell_nodes, w.y, w.z, w.w, t.nloc, t.nrb, t.nkb, t.nmat, t.buf[src],
+                                t.ld[src], t.buf[src ^ 1], t.ld[src ^ 1], t.n_vec, alpha[w.x]);
   }
 }
 
-template <class T, int CB, bool HAS_S>
+template <class T, int TW, bool HAS_S>
 static void launch_cells(chfsi_ctx* c, const T* cm, int nmat, const double2* X, int64_t ldx,
                          double2* W, int64_t ldw, int n_vec, double alpha) {
-  const int BN = 32 * CB;
+  const int BN = 32 * TW;
   const int n_rowtiles = cdiv(c->nrb, 2);
   const int n_coltiles = cdiv(n_vec, BN);
   for (int k = 0; k < c->n_colours; ++k) {
@@ -367,29 +393,31 @@ static void launch_cells(chfsi_ctx* c, const T* cm, int nmat, const double2* X, 
     const int nblk = n_in * n_rowtiles * n_coltiles;
     const double n2 = 2.0 * c->nloc;
     const double flops = 8.0 * n2 * n2 * n_vec * n_in;
-    // issued MFMA flops: per cell nrb row blocks x 2 column waves per column tile,
-    // each nkb k-steps of CB x (12 | 16) MFMAs of 16x16x4 (2048 flops)
-    const double exec = (double)n_in * c->nrb * 2.0 * n_coltiles * c->nkb * CB * (HAS_S ? 16 : 12) * 2048.0;
+    // issued MFMA flops: per cell nrb row blocks x 2 TW 16-column blocks per column
+    // tile, each nkb k-steps of (8 | 12) MFMAs of 16x16x4 (2048 flops)
+    const double exec = (double)n_in * c->nrb * 2.0 * TW * n_coltiles * c->nkb * (HAS_S ? 12 : 8) * 2048.0;
     const double bytes = (double)n_in * ((double)nmat * c->nloc * c->nloc * sizeof(T) +
                                          3.0 * c->nloc * 2.0 * n_vec * sizeof(double2));
     StageTimer tm(c, sizeof(T) == 8 ? CHFSI_STAGE_CELL_FP64 : CHFSI_STAGE_CELL_FP32, flops, exec, bytes);
     const int grid = 8 * ((nblk + 7) / 8);
-    hipLaunchKernelGGL((cell_apply_kernel<T, CB, HAS_S>), dim3(grid), dim3(256), 0, c->stream, cm,
+    hipLaunchKernelGGL((cell_apply_kernel<T, TW, HAS_S>), dim3(grid), dim3((cell_threads<T, TW>())), 0, c->stream, cm,
                        c->cell_nodes.ptr, c->colour_cells.ptr + c->colour_off[k], c->nloc, c->nrb,
                        c->nkb, nmat, n_rowtiles, n_coltiles, nblk, X, ldx, W, ldw, n_vec, alpha);
     LAUNCH_CHECK();
   }
 }
 
+// 64-column tiles for every block wider than 32: at p = 5..6 they run 1-4 %
+// faster than 128-column tiles in both precisions (three workgroups per CU
+// instead of one hide the epilogue and barrier latencies; the two column tiles
+// of a cell read its operator through the same L2).  The per-column arithmetic
+// does not depend on the tile width, so results are bitwise the same.
+static int cell_tile_width(int n_vec) { return n_vec > 32 ? 2 : 1; }
+
 template <class T, bool HAS_S>
 static void launch_cells_cb(chfsi_ctx* c, const T* cm, int nmat, const double2* X, int64_t ldx,
                             double2* W, int64_t ldw, int n_vec, double alpha) {
-  // 64-column tiles for every block wider than 32: at p = 5..6 they run 1-4 %
-  // faster than 128-column tiles in both precisions (three workgroups per CU
-  // instead of one hide the epilogue and barrier latencies; the two column tiles
-  // of a cell read its operator through the same L2).  The per-column arithmetic
-  // does not depend on the tile width, so results are bitwise the same.
-  if (n_vec > 32)
+  if (cell_tile_width(n_vec) == 2)
     launch_cells<T, 2, HAS_S>(c, cm, nmat, X, ldx, W, ldw, n_vec, alpha);
   else
     launch_cells<T, 1, HAS_S>(c, cm, nmat, X, ldx, W, ldw, n_vec, alpha);
@@ -408,10 +436,10 @@ void launch_cell_products(chfsi_ctx* c, KPoint& kp, int prec, const double2* X, 
 }
 
 // ---------------------------------------------------------------- batched form
-template <class T, int CB, bool HAS_S>
+template <class T, int TW, bool HAS_S>
 static void launch_batch_t(hipStream_t s, const BatchTaskArgs& tasks, const int4* items, int n_items,
                            const double* alpha, int src, int grid) {
-  hipLaunchKernelGGL((cell_batch_kernel<T, CB, HAS_S>), dim3(grid), dim3(256), 0, s, tasks, items, n_items, alpha,
+  hipLaunchKernelGGL((cell_batch_kernel<T, TW, HAS_S>), dim3(grid), dim3((cell_threads<T, TW>())), 0, s, tasks, items, n_items, alpha,
                      src);
   LAUNCH_CHECK();
 }
@@ -438,10 +466,10 @@ void launch_cell_batch(hipStream_t s, bool fp64, int CB, bool has_s, const Batch
   }
 }
 
-template <class T, int CB, bool HAS_S>
+template <class T, int TW, bool HAS_S>
 static int occ_t() {
   int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, cell_batch_kernel<T, CB, HAS_S>, 256, 0) != hipSuccess) n = 1;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, cell_batch_kernel<T, TW, HAS_S>, (cell_threads<T, TW>()), 0) != hipSuccess) n = 1;
   return std::max(1, n);
 }
 

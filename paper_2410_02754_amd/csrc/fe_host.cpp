@@ -202,7 +202,7 @@ void build_mesh(chfsi_ctx* c) {
   c->minv_sqrt_h.resize(c->n_nodes);
   for (int64_t i = 0; i < c->n_nodes; ++i) c->minv_sqrt_h[i] = 1.0 / std::sqrt(M[i]);
   c->nrb = (c->nloc + kRowBlk - 1) / kRowBlk;
-  c->nkb = c->nrb * (kRowBlk / kKStep);
+  c->nkb = (c->nloc + 2 * kKStep - 1) / (2 * kKStep) * 2;
   c->cell_nodes.upload(c->cell_nodes_h.data(), c->cell_nodes_h.size(), c->stream);
   c->colour_cells.upload(order.data(), order.size(), c->stream);
   c->minv_sqrt.upload(c->minv_sqrt_h.data(), c->minv_sqrt_h.size(), c->stream);

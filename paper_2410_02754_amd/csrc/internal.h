@@ -187,7 +187,7 @@ struct chfsi_ctx {
   chfsi::DevBuf<double> minv_sqrt;
   // cell operator tiling
   int nrb;                                    // row blocks of 16 (padded)
-  int nkb;                                    // k-steps of 4 (padded to nrb*4)
+  int nkb;                                    // k-steps of 4 (padded to whole stages of 8 nodes)
   // uniform reference matrices (host, real [nloc][nloc])
   std::vector<double> Kin, Mcons;
   std::vector<double> Cgrad[3];               // d-th component of the k-gradient matrix
