@@ -470,7 +470,7 @@ size_t chfsi_workspace_bytes(const chfsi_ctx* c, int ik, int n_vec, int op) {
   prow = (prow + 127) / 128 * 128;
   const size_t rot_b = ((size_t)prow * n + n * n) * sizeof(double2);
   const size_t resid_b = (256 * n + n) * sizeof(double);
-  const size_t nl_b = nonlocal_scratch_bytes(*c->kp[ik], n_vec);
+  const size_t nl_b = nonlocal_scratch_bytes(*c->kp[ik], n_vec) + products_scratch_bytes(c, n_vec, true);
   switch (op) {
     case CHFSI_OP_APPLY:
     case CHFSI_OP_FILTER:

@@ -175,7 +175,8 @@ __device__ __forceinline__ void cell_tile(CellSmem<T, TW>& sm, const T* __restri
                                           const int32_t* __restrict__ cell_nodes, int e, int rt, int ct,
                                           int nloc, int nrb, int nkb, int nmat,
                                           const double2* __restrict__ X, int64_t ldx,
-                                          double2* __restrict__ W, int64_t ldw, int n_vec, double alpha) {
+                                          double2* __restrict__ W, int64_t ldw, int n_vec, double alpha,
+                                          typename CellC2<T>::type* __restrict__ ye) {
   typedef typename Vec4<T>::type V4;
   typedef typename CellC2<T>::type C2;
   constexpr int CB = cell_cb<T, TW>();
@@ -324,6 +325,7 @@ __device__ __forceinline__ void cell_tile(CellSmem<T, TW>& sm, const T* __restri
     const int64_t node = sNode[rl];
     double2* w0 = W + (2 * node) * ldw;
     double2* w1 = W + (2 * node + 1) * ldw;
+    C2* ye0 = ye + ((size_t)e * nloc + rl) * 2 * n_vec;
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
       const int gcol = col0 + wc * (CB * 16) + cb * 16 + (lane & 15);
@@ -331,6 +333,11 @@ __device__ __forceinline__ void cell_tile(CellSmem<T, TW>& sm, const T* __restri
       const T tx = acc[cb][4][j], ti = acc[cb][5][j], yx = acc[cb][6][j], yi = acc[cb][7][j];
       const C2 y0 = {acc[cb][0][j] + (tx + yx), acc[cb][1][j] + (ti + yi)};
       const C2 y1 = {acc[cb][2][j] + (tx - yi), acc[cb][3][j] + (ti + yx)};
+      if (ye) {
+        ye0[gcol] = y0;
+        ye0[n_vec + gcol] = y1;
+        continue;
+      }
       double2 o0 = w0[gcol], o1 = w1[gcol];
       o0.x = fma(alpha, (double)y0.x, o0.x);
       o0.y = fma(alpha, (double)y0.y, o0.y);
@@ -347,7 +354,7 @@ __global__ __launch_bounds__((cell_threads<T, TW>()), (cell_min_waves<T, TW>()))
     const T* __restrict__ cm, const int32_t* __restrict__ cell_nodes,
     const int32_t* __restrict__ cells, int nloc, int nrb, int nkb, int nmat, int n_rowtiles,
     int n_coltiles, int n_work, const double2* __restrict__ X, int64_t ldx, double2* __restrict__ W,
-    int64_t ldw, int n_vec, double alpha) {
+    int64_t ldw, int n_vec, double alpha, typename CellC2<T>::type* __restrict__ ye) {
   __shared__ CellSmem<T, TW> sm;
   // Workgroups are dispatched round-robin over the 8 XCDs; remap so that each
   // XCD gets a contiguous range of (cell, row tile, column tile) work and the
@@ -358,8 +365,8 @@ __global__ __launch_bounds__((cell_threads<T, TW>()), (cell_min_waves<T, TW>()))
   const int ct = bid % n_coltiles;
   const int rt = (bid / n_coltiles) % n_rowtiles;
   const int ci = bid / (n_coltiles * n_rowtiles);
-  cell_tile<T, TW, HAS_S>(sm, cm, cell_nodes, cells[ci], rt, ct, nloc, nrb, nkb, nmat, X, ldx, W, ldw,
-                          n_vec, alpha);
+  cell_tile<T, TW, HAS_S>(sm, cm, cell_nodes, cells ? cells[ci] : ci, rt, ct, nloc, nrb, nkb, nmat, X, ldx, W, ldw,
+                          n_vec, alpha, ye);
 }
 
 // Batched form: one persistent grid walks a static list of (task, cell, row
@@ -377,18 +384,18 @@ __global__ __launch_bounds__((cell_threads<T, TW>()), (cell_min_waves<T, TW>()))
     const BatchTaskDev& t = tasks.t[w.x];
     const T* cm = sizeof(T) == 8 ? (const T*)t.cm64 : (const T*)t.cm32;
     cell_tile<T, TW, HAS_S>(sm, cm, t.cell_nodes, w.y, w.z, w.w, t.nloc, t.nrb, t.nkb, t.nmat, t.buf[src],
-                                t.ld[src], t.buf[src ^ 1], t.ld[src ^ 1], t.n_vec, alpha[w.x]);
+                                t.ld[src], t.buf[src ^ 1], t.ld[src ^ 1], t.n_vec, alpha[w.x], nullptr);
   }
 }
 
 template <class T, int TW, bool HAS_S>
 static void launch_cells(chfsi_ctx* c, const T* cm, int nmat, const double2* X, int64_t ldx,
-                         double2* W, int64_t ldw, int n_vec, double alpha) {
+                         double2* W, int64_t ldw, int n_vec, double alpha, void* ye = nullptr) {
   const int BN = 32 * TW;
   const int n_rowtiles = cdiv(c->nrb, 2);
   const int n_coltiles = cdiv(n_vec, BN);
-  for (int k = 0; k < c->n_colours; ++k) {
-    const int n_in = c->colour_off[k + 1] - c->colour_off[k];
+  for (int k = 0; k < (ye ? 1 : c->n_colours); ++k) {
+    const int n_in = ye ? c->n_cells : c->colour_off[k + 1] - c->colour_off[k];
     if (n_in == 0) continue;
     const int nblk = n_in * n_rowtiles * n_coltiles;
     const double n2 = 2.0 * c->nloc;
@@ -401,8 +408,9 @@ static void launch_cells(chfsi_ctx* c, const T* cm, int nmat, const double2* X, 
     StageTimer tm(c, sizeof(T) == 8 ? CHFSI_STAGE_CELL_FP64 : CHFSI_STAGE_CELL_FP32, flops, exec, bytes);
     const int grid = 8 * ((nblk + 7) / 8);
     hipLaunchKernelGGL((cell_apply_kernel<T, TW, HAS_S>), dim3(grid), dim3((cell_threads<T, TW>())), 0, c->stream, cm,
-                       c->cell_nodes.ptr, c->colour_cells.ptr + c->colour_off[k], c->nloc, c->nrb,
-                       c->nkb, nmat, n_rowtiles, n_coltiles, nblk, X, ldx, W, ldw, n_vec, alpha);
+                       c->cell_nodes.ptr, ye ? nullptr : c->colour_cells.ptr + c->colour_off[k], c->nloc, c->nrb,
+                       c->nkb, nmat, n_rowtiles, n_coltiles, nblk, X, ldx, W, ldw, n_vec, alpha,
+                       (typename CellC2<T>::type*)ye);
     LAUNCH_CHECK();
   }
 }
@@ -414,24 +422,29 @@ static void launch_cells(chfsi_ctx* c, const T* cm, int nmat, const double2* X, 
 // does not depend on the tile width, so results are bitwise the same.
 static int cell_tile_width(int n_vec) { return n_vec > 32 ? 2 : 1; }
 
-template <class T, bool HAS_S>
-static void launch_cells_cb(chfsi_ctx* c, const T* cm, int nmat, const double2* X, int64_t ldx,
-                            double2* W, int64_t ldw, int n_vec, double alpha) {
-  if (cell_tile_width(n_vec) == 2)
-    launch_cells<T, 2, HAS_S>(c, cm, nmat, X, ldx, W, ldw, n_vec, alpha);
-  else
-    launch_cells<T, 1, HAS_S>(c, cm, nmat, X, ldx, W, ldw, n_vec, alpha);
+int64_t cell_items_per_cell(const chfsi_ctx* c, int n_vec) {
+  return (int64_t)cdiv(c->nrb, 2) * cdiv(n_vec, 32 * cell_tile_width(n_vec));
 }
 
-// Local (cell) part of H_hat for all colours: W += alpha * sum_e R_e^T H_e R_e X.
+template <class T, bool HAS_S>
+static void launch_cells_cb(chfsi_ctx* c, const T* cm, int nmat, const double2* X, int64_t ldx,
+                            double2* W, int64_t ldw, int n_vec, double alpha, void* ye) {
+  if (cell_tile_width(n_vec) == 2)
+    launch_cells<T, 2, HAS_S>(c, cm, nmat, X, ldx, W, ldw, n_vec, alpha, ye);
+  else
+    launch_cells<T, 1, HAS_S>(c, cm, nmat, X, ldx, W, ldw, n_vec, alpha, ye);
+}
+
+// Local (cell) part of H_hat: W += alpha * sum_e R_e^T H_e R_e X colour by colour,
+// or the products of all cells to ye.
 void launch_cell_products(chfsi_ctx* c, KPoint& kp, int prec, const double2* X, int64_t ldx, double2* W,
-                          int64_t ldw, int n_vec, double alpha) {
+                          int64_t ldw, int n_vec, double alpha, void* ye) {
   if (prec == CHFSI_PREC_MIXED) {
-    if (kp.gamma) launch_cells_cb<float, false>(c, kp.cell32.ptr, kp.nmat, X, ldx, W, ldw, n_vec, alpha);
-    else launch_cells_cb<float, true>(c, kp.cell32.ptr, kp.nmat, X, ldx, W, ldw, n_vec, alpha);
+    if (kp.gamma) launch_cells_cb<float, false>(c, kp.cell32.ptr, kp.nmat, X, ldx, W, ldw, n_vec, alpha, ye);
+    else launch_cells_cb<float, true>(c, kp.cell32.ptr, kp.nmat, X, ldx, W, ldw, n_vec, alpha, ye);
   } else {
-    if (kp.gamma) launch_cells_cb<double, false>(c, kp.cell64.ptr, kp.nmat, X, ldx, W, ldw, n_vec, alpha);
-    else launch_cells_cb<double, true>(c, kp.cell64.ptr, kp.nmat, X, ldx, W, ldw, n_vec, alpha);
+    if (kp.gamma) launch_cells_cb<double, false>(c, kp.cell64.ptr, kp.nmat, X, ldx, W, ldw, n_vec, alpha, ye);
+    else launch_cells_cb<double, true>(c, kp.cell64.ptr, kp.nmat, X, ldx, W, ldw, n_vec, alpha, ye);
   }
 }
 

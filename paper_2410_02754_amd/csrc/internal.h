@@ -204,6 +204,7 @@ struct chfsi_ctx {
   // columns per launch as fit (the allocation-free filter entry point)
   void* nl_fixed = nullptr;
   size_t nl_fixed_bytes = 0;
+  chfsi::DevBuf<double> ye;                   // cell products of one apply, cell by cell (small applies)
   chfsi::DevBuf<double> panel;                // row panel for in-place rotations
   chfsi::DevBuf<double> cd_partial;           // adjoint cross densities per column group
   chfsi::DevBuf<int32_t> den_order;           // cell order of the density kernels (4x4x4 tiles)
@@ -255,8 +256,15 @@ void hermitian_eig(const std::vector<cplx>& A, int n, std::vector<double>& w, st
 void launch_cell_setup(chfsi_ctx* c, KPoint& kp, const double* V, const double* B,
                        const double* U0, const double* S);
 void launch_cell_to_f32(chfsi_ctx* c, KPoint& kp);
+// W += alpha sum_e R_e^T H_e R_e X by colours; or, ye non-null, the products H_e R_e X
+// of all cells to ye[cell][local node][spin][n_vec] (the precision's complex type)
 void launch_cell_products(chfsi_ctx* c, KPoint& kp, int prec, const double2* X, int64_t ldx, double2* W,
-                          int64_t ldw, int n_vec, double alpha);
+                          int64_t ldw, int n_vec, double alpha, void* ye = nullptr);
+// workgroups per cell of the two forms' products
+int64_t cell_items_per_cell(const chfsi_ctx* c, int n_vec);
+int64_t mf_items_per_cell(const chfsi_ctx* c, int n_vec, bool fp64);
+// bytes of ye that an apply of this width uses (0: it runs by colours)
+size_t products_scratch_bytes(const chfsi_ctx* c, int n_vec, bool fp64);
 int check_finite(chfsi_ctx* c, const double* p, int64_t n);
 // W <- alpha H_hat X + beta W + gamma X   (W is not read when beta == 0)
 void apply_H(chfsi_ctx* c, KPoint& kp, const double2* X, int64_t ldx, double2* W, int64_t ldw,
@@ -282,8 +290,9 @@ void mf_prepare(chfsi_ctx* c);
 void mf_set_local(chfsi_ctx* c, const double* V, const double* B);
 // W += alpha H_loc X with the matrix-free operator; alpha_d (device, or NULL)
 // overrides alpha at run time (graph replays with new filter bounds)
+// (ye as in launch_cell_products: the products without the output's M^{-1/2})
 void launch_mf_products(chfsi_ctx* c, const KPoint& kp, int prec, const double2* X, int64_t ldx, double2* W,
-                        int64_t ldw, int n_vec, double alpha, const double* alpha_d = nullptr);
+                        int64_t ldw, int n_vec, double alpha, const double* alpha_d = nullptr, void* ye = nullptr);
 void densities(chfsi_ctx* c, const double2* X, int64_t ldx, int n_vec, const double* occ_d, double* rho,
                double* mag);
 void launch_axpby_rows(chfsi_ctx* c, double2* W, int64_t ldw, const double2* X, int64_t ldx,

@@ -107,30 +107,42 @@ constexpr int nl_col_blocks() { return sizeof(T) == 8 ? 1 : 2; }
 //   Re c = (p_r x_r)[chi] + (p_i x_i)[chi + 8],  Im c = (p_r x_i)[chi] - (p_i x_r)[chi + 8];
 // row chi + 8 is accumulator register j + 2 of the same lane (FP64) or register
 // j of the lane 32 above (FP32).
-template <class T, bool REALP, bool PACK = false>
-__global__ __launch_bounds__(256) void nl_contract_kernel(
-    const typename C2<T>::type* __restrict__ proj, const int32_t* __restrict__ sup_node,
-    const int32_t* __restrict__ chunk_atom, const int32_t* __restrict__ chunk_begin,
-    const int32_t* __restrict__ chunk_end, const int32_t* __restrict__ chunk_order,
-    const int32_t* __restrict__ atom_npj, int max_pj, int n_work, int n_coltiles,
-    const double2* __restrict__ X, int64_t ldx, int n_vec, typename C2<T>::type* __restrict__ partial) {
+// A chunk is cut into nsub parts (partial[chunk * nsub + part]) where whole
+// chunks are too few waves to fill the GPU: a wave walks its entries 16 at a
+// time, each step a trip to memory, so 512 entries of a narrow block were a
+// 97 us chain (16 atoms, one column) that eight parts cut to 17 us.
+template <class T>
+struct NlContractArgs {
+  const typename C2<T>::type* proj;
+  const int32_t *sup_node, *chunk_atom, *chunk_begin, *chunk_end, *chunk_order, *atom_npj;
+  int max_pj, nsub, n_work, n_coltiles;
+  const double2* X;
+  int64_t ldx;
+  int n_vec;
+  typename C2<T>::type* partial;
+};
+
+template <class T, bool REALP, bool PACK>
+__device__ __forceinline__ void nl_contract_wave(const NlContractArgs<T>& g, int wid) {
   typedef typename C2<T>::type CT;
   typedef typename Vec4<T>::type V4;
   static_assert(!PACK || !REALP, "packed rows: complex projector values only");
   constexpr int U = 4;                    // k-steps per batch
   constexpr int NCB = nl_col_blocks<T>();
-  // each XCD takes a contiguous range of the (window, atom)-ordered chunks, so the
-  // chunks of different atoms over the same rows meet in that XCD's L2
-  const int per_xcd = (int)((gridDim.x + 7) / 8);
-  const int bid = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
-  const int wid = __builtin_amdgcn_readfirstlane(bid * 4 + (int)(threadIdx.x >> 6));
-  if (wid >= n_work) return;              // no barrier in this kernel
+  const CT* __restrict__ proj = g.proj;
+  const double2* __restrict__ X = g.X;
+  const int32_t* __restrict__ sup_node = g.sup_node;
+  const int64_t ldx = g.ldx;
+  const int n_vec = g.n_vec, max_pj = g.max_pj;
   const int lane = threadIdx.x & 63;
   const int kl = lane >> 4, il = lane & 15;
-  const int oi = wid / n_coltiles, ct = wid - oi * n_coltiles;
-  const int ch = chunk_order[oi];
-  const int a = chunk_atom[ch], b = chunk_begin[ch], e = chunk_end[ch];
-  const int npj = atom_npj[a];
+  const int oi = wid / (g.n_coltiles * g.nsub), rem = wid - oi * g.n_coltiles * g.nsub;
+  const int sub = rem / g.n_coltiles, ct = rem - sub * g.n_coltiles;
+  const int ch = g.chunk_order[oi];
+  const int a = g.chunk_atom[ch], cb0 = g.chunk_begin[ch], ce0 = g.chunk_end[ch];
+  const int part = ((ce0 - cb0 + g.nsub - 1) / g.nsub + 15) / 16 * 16;   // whole batches per part
+  const int b = cb0 + sub * part, e = min(ce0, b + part);                // b >= e: an empty part
+  const int npj = g.atom_npj[a];
   const int chi = PACK ? (il & 7) : il;   // projector of this lane's A row
   const bool rv = chi < npj;              // ... and whether it is in use
   int col[NCB];
@@ -189,7 +201,7 @@ __global__ __launch_bounds__(256) void nl_contract_kernel(
       }
     }
   }
-  CT* out = partial + (size_t)ch * 2 * max_pj * n_vec;
+  CT* out = g.partial + ((size_t)ch * g.nsub + sub) * 2 * max_pj * n_vec;
   if constexpr (PACK) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -235,83 +247,103 @@ __global__ __launch_bounds__(256) void nl_contract_kernel(
   }
 }
 
-// Csum[a][r][n] = sum over the chunks of atom a of partial[chunk][r][n] (chunk order fixed)
-// (a column group: partial holds n_vec columns, written to Csum columns col0.. of
-// its ldc-wide rows)
-template <class T>
-__global__ __launch_bounds__(64) void nl_reduce_kernel(const typename C2<T>::type* __restrict__ partial,
-                                                       const int32_t* __restrict__ atom_chunk0,
-                                                       const int32_t* __restrict__ atom_npj, int max_pj,
-                                                       int n_vec, int ldc, int col0,
-                                                       typename C2<T>::type* __restrict__ Csum) {
-  typedef typename C2<T>::type CT;
-  const int a = blockIdx.x, r = blockIdx.y;
-  const int col = blockIdx.z * 64 + threadIdx.x;
-  const int mr = 2 * max_pj;
-  if (r >= 2 * atom_npj[a] || col >= n_vec) return;
-  T sr = 0, si = 0;
-  const int c0 = atom_chunk0[a], c1 = atom_chunk0[a + 1];
-  int ch = c0;
-  for (; ch + 3 < c1; ch += 4) {
-    CT v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = partial[((size_t)(ch + u) * mr + r) * n_vec + col];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      sr += v[u].x;
-      si += v[u].y;
-    }
-  }
-  for (; ch < c1; ++ch) {
-    const CT v = partial[((size_t)ch * mr + r) * n_vec + col];
-    sr += v.x;
-    si += v.y;
-  }
-  CT o;
-  o.x = sr;
-  o.y = si;
-  Csum[((size_t)a * mr + r) * ldc + col0 + col] = o;
+template <class T, bool REALP, bool PACK = false>
+__global__ __launch_bounds__(256) void nl_contract_kernel(const NlContractArgs<T> g) {
+  // each XCD takes a contiguous range of the (window, atom)-ordered chunks, so the
+  // chunks of different atoms over the same rows meet in that XCD's L2
+  const int per_xcd = (int)((gridDim.x + 7) / 8);
+  const int bid = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+  const int wid = __builtin_amdgcn_readfirstlane(bid * 4 + (int)(threadIdx.x >> 6));
+  if (wid >= g.n_work) return;            // no barrier in this kernel
+  nl_contract_wave<T, REALP, PACK>(g, wid);
 }
 
-// C'[a][r][n] = alpha sum_r' Delta_a[r][r'] Csum[a][r'][n]; alpha_d (device, or
-// null) overrides alpha at run time (graph replays with new filter bounds)
+// Coefficients of one atom and 16 columns: the sum over the atom's parts,
+//   C[r][n] = sum_part partial[part][r][n],
+// and the coupling C'[r][n] = alpha sum_r' Delta[r][r'] C[r'][n] (r = 2 chi + spin).
+// 16 threads per column take every 16th part (in a fixed order), meet by lane
+// exchange and in LDS, and each then forms its rows of C'.  Serial chains of
+// loads set its time: the sum over parts is 16 times shorter than with one
+// thread per row, and one launch takes the place of two (together 103 us for 33
+// atoms, 128 columns and 9200 parts).  alpha_d (device, or null) overrides alpha
+// at run time (graph replays with new filter bounds).
 template <class T>
-__global__ __launch_bounds__(64) void nl_delta_kernel(const typename C2<T>::type* __restrict__ Csum,
-                                                      const int32_t* __restrict__ atom_npj,
-                                                      const double2* __restrict__ delta, int max_pj, int n_vec,
-                                                      double alpha, const double* __restrict__ alpha_d,
-                                                      typename C2<T>::type* __restrict__ Cp) {
+struct NlCoefArgs {
+  const typename C2<T>::type* partial;
+  const int32_t *atom_chunk0, *atom_npj;
+  const double2* delta;
+  int max_pj, nsub, n_part, col0, n_vec;      // the parts hold n_part columns: columns col0 .. of C'
+  double alpha;
+  const double* alpha_d;
+  typename C2<T>::type* Cp;
+};
+constexpr int kCoefCols = 16;
+
+template <class T>
+struct NlCoefSmem {
+  typename C2<T>::type w[4][2 * kMaxPj][kCoefCols];
+};
+
+template <class T>
+__device__ __forceinline__ void nl_coef_block(NlCoefSmem<T>& sm, const NlCoefArgs<T>& g, int a, int ctile) {
   typedef typename C2<T>::type CT;
-  if (alpha_d) alpha = *alpha_d;
-  const int a = blockIdx.x;
-  const int col = blockIdx.y * 64 + threadIdx.x;
-  if (col >= n_vec) return;
-  const int nr = 2 * atom_npj[a];
-  const int mr = 2 * max_pj;
-  T cr[2 * kMaxPj], cim[2 * kMaxPj];
+  const int tid = threadIdx.x, il = tid & 15, slot = tid >> 4, wave = tid >> 6;
+  const int col = ctile * kCoefCols + il;
+  const int mr = 2 * g.max_pj, nr = 2 * g.atom_npj[a];
+  const int p0 = g.atom_chunk0[a] * g.nsub, p1 = g.atom_chunk0[a + 1] * g.nsub;
+  const CT* __restrict__ part = g.partial + min(col, g.n_part - 1);
+  T sr[2 * kMaxPj], si[2 * kMaxPj];
 #pragma unroll
-  for (int q = 0; q < 2 * kMaxPj; ++q) {
-    cr[q] = cim[q] = (T)0;
-    if (q < nr) {
-      const CT v = Csum[((size_t)a * mr + q) * n_vec + col];
-      cr[q] = v.x;
-      cim[q] = v.y;
+  for (int r = 0; r < 2 * kMaxPj; ++r) sr[r] = si[r] = (T)0;
+  for (int p = p0 + slot; p < p1; p += 16) {
+    CT v[2 * kMaxPj];
+#pragma unroll
+    for (int r = 0; r < 2 * kMaxPj; ++r)
+      if (r < nr) v[r] = part[((size_t)p * mr + r) * g.n_part];
+#pragma unroll
+    for (int r = 0; r < 2 * kMaxPj; ++r)
+      if (r < nr) {
+        sr[r] += v[r].x;
+        si[r] += v[r].y;
+      }
+  }
+#pragma unroll
+  for (int r = 0; r < 2 * kMaxPj; ++r) {
+    sr[r] += __shfl_xor(sr[r], 16);
+    si[r] += __shfl_xor(si[r], 16);
+    sr[r] += __shfl_xor(sr[r], 32);
+    si[r] += __shfl_xor(si[r], 32);
+    if ((tid & 63) < 16) {
+      CT o;
+      o.x = sr[r];
+      o.y = si[r];
+      sm.w[wave][r][il] = o;
     }
   }
-  for (int r = 0; r < nr; ++r) {
-    T sr = 0, si = 0;
-#pragma unroll
-    for (int q = 0; q < 2 * kMaxPj; ++q)
-      if (q < nr) {
-        const double2 d = delta[((size_t)a * mr + r) * mr + q];
-        sr += (T)d.x * cr[q] - (T)d.y * cim[q];
-        si += (T)d.x * cim[q] + (T)d.y * cr[q];
-      }
-    CT o;
-    o.x = (T)alpha * sr;
-    o.y = (T)alpha * si;
-    Cp[((size_t)a * mr + r) * n_vec + col] = o;
+  __syncthreads();
+  const double alpha = g.alpha_d ? *g.alpha_d : g.alpha;
+  for (int r = slot; r < nr; r += 16) {
+    T xr = 0, xi = 0;
+    for (int q = 0; q < nr; ++q) {
+      const double2 d = g.delta[((size_t)a * mr + r) * mr + q];
+      const T cr = (sm.w[0][q][il].x + sm.w[1][q][il].x) + (sm.w[2][q][il].x + sm.w[3][q][il].x);
+      const T ci = (sm.w[0][q][il].y + sm.w[1][q][il].y) + (sm.w[2][q][il].y + sm.w[3][q][il].y);
+      xr += (T)d.x * cr - (T)d.y * ci;
+      xi += (T)d.x * ci + (T)d.y * cr;
+    }
+    if (col < g.n_part) {
+      CT o;
+      o.x = (T)alpha * xr;
+      o.y = (T)alpha * xi;
+      g.Cp[((size_t)a * mr + r) * g.n_vec + g.col0 + col] = o;
+    }
   }
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void nl_coef_kernel(const NlCoefArgs<T> g) {
+  __shared__ NlCoefSmem<T> sm;
+  nl_coef_block<T>(sm, g, blockIdx.x, blockIdx.y);
 }
 
 // Recurrence initialisation fused with the nonlocal back-product, one wave per
@@ -327,29 +359,75 @@ __global__ __launch_bounds__(64) void nl_delta_kernel(const typename C2<T>::type
 // the residual term (FL: which terms are present).  REALP: real projector values
 // (Gamma point), two real MFMAs per step instead of four.  bg_d (device, or null)
 // overrides (beta, gamma) at run time; FL still selects which terms are read.
+// GATHER: the cell products were written cell by cell (ye[cell][local node][spin][n])
+// and every node adds alpha (msc: alpha M^{-1/2}) times the values of the up to
+// eight cells that hold it, in the colour order of the assembly: bit for bit the
+// sum that the per-colour launches leave.  The cells of a node follow from its
+// position in the mesh.
 constexpr int kInitBeta = 1, kInitGamma = 2, kInitRs = 4;
 
-template <class T, int FL, bool REALP>
-__global__ __launch_bounds__(256) void init_nl_kernel(
-    const typename C2<T>::type* __restrict__ proj, const int32_t* __restrict__ run_off,
-    const int32_t* __restrict__ pair_atom, const int32_t* __restrict__ pair_ent,
-    const int32_t* __restrict__ atom_npj, int max_pj, const typename C2<T>::type* __restrict__ Cp,
-    int has_nl, const double2* __restrict__ X, int64_t ldx, double2* W, int64_t ldw,
-    const double2* Wold, int64_t ldo, const double2* __restrict__ Rs, int64_t ldr,
-    const double* __restrict__ rscale, int64_t n_nodes, int n_work, int n_coltiles, int n_vec, double beta,
-    double gamma, const double* __restrict__ bg_d) {
+struct MeshShape {
+  int p, np1, nx, ny, nz, Nx, Ny;       // degree, cells and nodes per direction
+};
+
+template <class T>
+struct InitArgs {
+  const typename C2<T>::type* proj;
+  const int32_t *run_off, *pair_atom, *pair_ent, *atom_npj;
+  int max_pj, has_nl;
+  const typename C2<T>::type* Cp;
+  const double2* X;
+  int64_t ldx;
+  double2* W;
+  int64_t ldw;
+  const double2* Wold;
+  int64_t ldo;
+  const double2* Rs;
+  int64_t ldr;
+  const double* rscale;
+  int64_t n_nodes;
+  int n_work, n_coltiles, n_vec;
+  double beta, gamma, alpha;
+  const double *bg_d, *alpha_d;
+  const typename C2<T>::type* ye;
+  const double* msc;
+  MeshShape mesh;
+};
+
+// The cells along one direction that hold node coordinate i, in colour order, as
+// their part of the row of ye: cell * cell_rows + local index * loc_rows; returns
+// how many (1 or 2).
+__device__ __forceinline__ int dir_rows(int i, int p, int n, int cell_rows, int loc_rows, int (&row)[2]) {
+  const int c = i / p, a = i - c * p;
+  row[0] = row[1] = c * cell_rows + a * loc_rows;
+  if (a != 0) return 1;
+  const int l = c == 0 ? n - 1 : c - 1;               // the cell that ends at this node
+  const int kc = (n % 2 != 0 && c == n - 1) ? 2 : c % 2, kl = (n % 2 != 0 && l == n - 1) ? 2 : l % 2;
+  row[kl < kc ? 0 : 1] = l * cell_rows + p * loc_rows;
+  return 2;
+}
+
+template <class T, int FL, bool REALP, bool GATHER>
+__device__ __forceinline__ void init_nl_wave(const InitArgs<T>& g, int wid) {
   typedef typename C2<T>::type CT;
   typedef typename Vec4<T>::type V4;
   static_assert(kNlRun == 16, "one MFMA row block per run");
-  if (bg_d) {
-    beta = bg_d[0];
-    gamma = bg_d[1];
+  double beta = g.beta, gamma = g.gamma;
+  if (g.bg_d) {
+    beta = g.bg_d[0];
+    gamma = g.bg_d[1];
   }
   constexpr int KS = (kMaxPj + 3) / 4;    // k-steps per atom
   constexpr int NCB = nl_col_blocks<T>();
-  const int wid = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
-  if (wid >= n_work) return;              // no barrier in this kernel
-  const int run = wid / n_coltiles, ct = wid - run * n_coltiles;
+  const double2* __restrict__ X = g.X;
+  const double2* Wold = g.Wold;
+  double2* W = g.W;
+  const double2* __restrict__ Rs = g.Rs;
+  const double* __restrict__ rscale = g.rscale;
+  const CT* __restrict__ proj = g.proj;
+  const int64_t ldx = g.ldx, ldw = g.ldw, ldo = g.ldo, ldr = g.ldr, n_nodes = g.n_nodes;
+  const int n_vec = g.n_vec, max_pj = g.max_pj;
+  const int run = wid / g.n_coltiles, ct = wid - run * g.n_coltiles;
   const int lane = threadIdx.x & 63;
   const int kl = lane >> 4, il = lane & 15;
   int col[NCB];
@@ -399,13 +477,13 @@ __global__ __launch_bounds__(256) void init_nl_kernel(
         }
       }
     }
-  if (has_nl) {
-    const int p0 = run_off[run], p1 = run_off[run + 1];
+  if (g.has_nl) {
+    const int p0 = g.run_off[run], p1 = g.run_off[run + 1];
     for (int pr = p0; pr < p1; ++pr) {
-      const int a = pair_atom[pr];
-      const int npj = atom_npj[a];
-      const int ent = pair_ent[(size_t)pr * kNlRun + il];      // A row = node il of the run
-      const CT* cpa = Cp + (size_t)a * 2 * max_pj * n_vec;
+      const int a = g.pair_atom[pr];
+      const int npj = g.atom_npj[a];
+      const int ent = g.pair_ent[(size_t)pr * kNlRun + il];    // A row = node il of the run
+      const CT* __restrict__ cpa = g.Cp + (size_t)a * 2 * max_pj * n_vec;
       CT pa[KS];
       CT bv[KS][2][NCB];
 #pragma unroll
@@ -476,6 +554,37 @@ __global__ __launch_bounds__(256) void init_nl_kernel(
         }
         v[cb][sp] = t;
       }
+    if constexpr (GATHER) {
+      const MeshShape& ms = g.mesh;
+      const int nd = (int)nodec, nloc = ms.np1 * ms.np1 * ms.np1;
+      const double alpha = g.alpha_d ? *g.alpha_d : g.alpha;
+      const double sc = g.msc ? alpha * g.msc[nd] : alpha;
+      const int iyz = nd / ms.Nx, ix = nd - iyz * ms.Nx;
+      const int iz = iyz / ms.Ny, iy = iyz - iz * ms.Ny;
+      int rx[2], ry[2], rz[2];
+      const int kx = dir_rows(ix, ms.p, ms.nx, nloc, 1, rx);
+      const int ky = dir_rows(iy, ms.p, ms.ny, nloc * ms.nx, ms.np1, ry);
+      const int kz = dir_rows(iz, ms.p, ms.nz, nloc * ms.nx * ms.ny, ms.np1 * ms.np1, rz);
+#pragma unroll
+      for (int z = 0; z < 2; ++z)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+          if (z < kz && y < ky) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+              if (x < kx) {
+                const CT* __restrict__ yr = g.ye + (size_t)(rx[x] + ry[y] + rz[z]) * 2 * n_vec;
+#pragma unroll
+                for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+                  for (int sp = 0; sp < 2; ++sp) {
+                    const CT yv = yr[(size_t)sp * n_vec + col[cb]];
+                    v[cb][sp].x = fma(sc, (double)yv.x, v[cb][sp].x);
+                    v[cb][sp].y = fma(sc, (double)yv.y, v[cb][sp].y);
+                  }
+              }
+          }
+    }
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
@@ -484,13 +593,58 @@ __global__ __launch_bounds__(256) void init_nl_kernel(
   }
 }
 
-// Nonlocal coefficients C' = alpha Delta P^H X for every atom; returns the
-// device array [n_atoms][2 max_pj][n_vec] (in the scratch buffer), or null.
-// Scratch: the caller's buffer (scratch, at least nonlocal_scratch_bytes(nl,
-// n_vec) bytes) or the context's growable buffer.  alpha_d as in nl_delta_kernel.
+template <class T, int FL, bool REALP, bool GATHER>
+__global__ __launch_bounds__(256) void init_nl_kernel(const InitArgs<T> g) {
+  const int wid = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  if (wid >= g.n_work) return;            // no barrier in this kernel
+  init_nl_wave<T, FL, REALP, GATHER>(g, wid);
+}
+
 // the packed complex contraction applies (at most 8 projectors per atom)
 static bool pack_rows(const NonlocalK& nl) { return nl.max_pj <= 8; }
 
+// Parts per chunk of the contraction: enough waves for the GPU (16384 = 16 per
+// SIMD; above that whole chunks are the better work items, since each part writes
+// its own rows of partial sums), and 64 entries or more in a full chunk's part.  A
+// function of the whole block's width, so that a contraction over column groups
+// splits alike; whole chunks where the parts of a column would not fit the fixed
+// scratch that takes the whole ones.
+static int nl_parts(const NonlocalK& nl, int n_vec) {
+  const int64_t waves = (int64_t)std::max(1, nl.n_chunks) * cdiv(n_vec, 16);
+  const int s = (int)std::max<int64_t>(1, std::min<int64_t>(kNlChunk / 64, 16384 / waves));
+  const size_t mr = 2 * nl.max_pj;
+  const size_t need = ((size_t)nl.n_chunks * s * mr + (size_t)nl.n_atoms * mr * n_vec) * sizeof(double2);
+  return need <= (size_t)CHFSI_NOALLOC_SCRATCH_BYTES ? s : 1;
+}
+
+template <class T>
+static NlContractArgs<T> contract_args(const NonlocalK& nl, const typename C2<T>::type* proj, const double2* X,
+                                       int64_t ldx, int n_vec, int nsub, typename C2<T>::type* partial) {
+  NlContractArgs<T> g;
+  g.proj = proj;
+  g.sup_node = nl.sup_node.ptr;
+  g.chunk_atom = nl.chunk_atom.ptr;
+  g.chunk_begin = nl.chunk_begin.ptr;
+  g.chunk_end = nl.chunk_end.ptr;
+  g.chunk_order = nl.chunk_order.ptr;
+  g.atom_npj = nl.atom_npj.ptr;
+  g.max_pj = nl.max_pj;
+  g.nsub = nsub;
+  g.n_coltiles = cdiv(n_vec, 16 * nl_col_blocks<T>());
+  const int64_t work = (int64_t)nl.n_chunks * nsub * g.n_coltiles;
+  CHFSI_CHECK(work < (int64_t)1 << 30, CHFSI_EINVAL, "nonlocal contraction: too many work items");
+  g.n_work = (int)work;
+  g.X = X;
+  g.ldx = ldx;
+  g.n_vec = n_vec;
+  g.partial = partial;
+  return g;
+}
+
+// Nonlocal coefficients C' = alpha Delta P^H X for every atom; returns the
+// device array [n_atoms][2 max_pj][n_vec] (in the scratch buffer), or null.
+// Scratch: the caller's buffer (scratch, at least nonlocal_scratch_bytes(nl,
+// n_vec) bytes) or the context's growable buffer.  alpha_d as in nl_coef_kernel.
 template <class T>
 static const typename C2<T>::type* nonlocal_coeffs(chfsi_ctx* c, NonlocalK& nl,
                                                    const typename C2<T>::type* proj, const double2* X,
@@ -499,15 +653,16 @@ static const typename C2<T>::type* nonlocal_coeffs(chfsi_ctx* c, NonlocalK& nl,
   typedef typename C2<T>::type CT;
   if (nl.n_atoms == 0 || nl.n_entries == 0) return nullptr;
   const int mr = 2 * nl.max_pj;
-  const size_t n_part = (size_t)nl.n_chunks * mr * n_vec;
+  const int nsub = nl_parts(nl, n_vec);
+  const size_t n_part = (size_t)nl.n_chunks * nsub * mr * n_vec;
   const size_t n_cp = (size_t)nl.n_atoms * mr * n_vec;
-  const size_t bytes = (n_part + 2 * n_cp) * sizeof(CT);
+  const size_t bytes = (n_part + n_cp) * sizeof(CT);
   int group = n_vec;                      // columns per contraction launch
   if (!scratch && c->nl_fixed) {
     // fixed buffer: whole coefficient arrays, then as many columns of
     // partials per contraction launch as fit (the caller checked that one does)
-    const size_t per_col = (size_t)nl.n_chunks * mr * sizeof(CT);
-    const size_t head = 2 * n_cp * sizeof(CT);
+    const size_t per_col = (size_t)nl.n_chunks * nsub * mr * sizeof(CT);
+    const size_t head = n_cp * sizeof(CT);
     CHFSI_CHECK(c->nl_fixed_bytes >= head + per_col, CHFSI_EINVAL, "fixed nonlocal scratch too small");
     group = (int)std::min<size_t>(n_vec, (c->nl_fixed_bytes - head) / per_col);
     scratch = c->nl_fixed;
@@ -515,68 +670,85 @@ static const typename C2<T>::type* nonlocal_coeffs(chfsi_ctx* c, NonlocalK& nl,
     c->scratch.alloc((bytes + sizeof(double) - 1) / sizeof(double));
     scratch = c->scratch.ptr;
   }
-  CT* Csum = reinterpret_cast<CT*>(scratch);
-  CT* Cp = Csum + n_cp;
+  CT* Cp = reinterpret_cast<CT*>(scratch);
   CT* partial = Cp + n_cp;
   double nl_flops = 0.0;
   for (const auto& at : nl.atoms)
     nl_flops += 2.0 * 8.0 * at.n_sup * at.n_pj * 2.0 * n_vec + 8.0 * 4.0 * at.n_pj * at.n_pj * n_vec;
   const double nl_bytes = (double)nl.n_entries * (2.0 * n_vec * sizeof(double2) + nl.max_pj * sizeof(CT));
   StageTimer tm(c, CHFSI_STAGE_NONLOCAL, nl_flops, nl_flops, nl_bytes);
-  const int nct = cdiv(n_vec, 64);
   for (int c0 = 0; c0 < n_vec; c0 += group) {
-    const int g = std::min(group, n_vec - c0);
-    const int nct32 = cdiv(g, 16 * nl_col_blocks<T>());
-    const int n_work = nl.n_chunks * nct32;
-    const dim3 cgrid(8 * cdiv(cdiv(n_work, 4), 8));
+    const int gc = std::min(group, n_vec - c0);
+    const NlContractArgs<T> ca = contract_args<T>(nl, proj, X + c0, ldx, gc, nsub, partial);
+    const dim3 cgrid(8 * cdiv(cdiv(ca.n_work, 4), 8));
     if (nl.real_proj)
-      hipLaunchKernelGGL((nl_contract_kernel<T, true>), cgrid, dim3(256), 0, c->stream, proj, nl.sup_node.ptr,
-                         nl.chunk_atom.ptr, nl.chunk_begin.ptr, nl.chunk_end.ptr, nl.chunk_order.ptr,
-                         nl.atom_npj.ptr, nl.max_pj, n_work, nct32, X + c0, ldx, g, partial);
+      hipLaunchKernelGGL((nl_contract_kernel<T, true>), cgrid, dim3(256), 0, c->stream, ca);
     else if (pack_rows(nl))
-      hipLaunchKernelGGL((nl_contract_kernel<T, false, true>), cgrid, dim3(256), 0, c->stream, proj,
-                         nl.sup_node.ptr, nl.chunk_atom.ptr, nl.chunk_begin.ptr, nl.chunk_end.ptr,
-                         nl.chunk_order.ptr, nl.atom_npj.ptr, nl.max_pj, n_work, nct32, X + c0, ldx, g, partial);
+      hipLaunchKernelGGL((nl_contract_kernel<T, false, true>), cgrid, dim3(256), 0, c->stream, ca);
     else
-      hipLaunchKernelGGL((nl_contract_kernel<T, false>), cgrid, dim3(256), 0, c->stream, proj, nl.sup_node.ptr,
-                         nl.chunk_atom.ptr, nl.chunk_begin.ptr, nl.chunk_end.ptr, nl.chunk_order.ptr,
-                         nl.atom_npj.ptr, nl.max_pj, n_work, nct32, X + c0, ldx, g, partial);
+      hipLaunchKernelGGL((nl_contract_kernel<T, false>), cgrid, dim3(256), 0, c->stream, ca);
     LAUNCH_CHECK();
-    hipLaunchKernelGGL(nl_reduce_kernel<T>, dim3(nl.n_atoms, mr, cdiv(g, 64)), dim3(64), 0, c->stream, partial,
-                       nl.atom_chunk0.ptr, nl.atom_npj.ptr, nl.max_pj, g, n_vec, c0, Csum);
+    const NlCoefArgs<T> co{partial, nl.atom_chunk0.ptr, nl.atom_npj.ptr, nl.delta.ptr, nl.max_pj, nsub,
+                           gc,      c0,                 n_vec,           alpha,        alpha_d,   Cp};
+    hipLaunchKernelGGL((nl_coef_kernel<T>), dim3(nl.n_atoms, cdiv(gc, kCoefCols)), dim3(256), 0, c->stream, co);
     LAUNCH_CHECK();
   }
-  hipLaunchKernelGGL(nl_delta_kernel<T>, dim3(nl.n_atoms, nct), dim3(64), 0, c->stream, Csum,
-                     nl.atom_npj.ptr, nl.delta.ptr, nl.max_pj, n_vec, alpha, alpha_d, Cp);
-  LAUNCH_CHECK();
   return Cp;
 }
 
+static MeshShape mesh_shape(const chfsi_ctx* c) {
+  return MeshShape{c->p, c->np1, c->nc[0], c->nc[1], c->nc[2], c->Nd[0], c->Nd[1]};
+}
+
 template <class T>
-static void init_and_backproduct(chfsi_ctx* c, NonlocalK& nl, const typename C2<T>::type* proj,
-                                 const typename C2<T>::type* Cp, const double2* X, int64_t ldx,
-                                 double2* W, int64_t ldw, const double2* Wold, int64_t ldo, int n_vec,
-                                 double beta, double gamma, const double2* Rs = nullptr, int64_t ldr = 0,
-                                 const double* rscale = nullptr, const double* bg_d = nullptr) {
-  const int64_t rows = 2 * c->n_nodes;
-  StageTimer tm(c, CHFSI_STAGE_AXPY, Cp ? 8.0 * 2.0 * nl.n_entries * nl.max_pj * n_vec : 0.0, 0.0,
-                (double)rows * n_vec * sizeof(double2) * (1.0 + (beta != 0.0) + (gamma != 0.0)));
-  const int has = Cp != nullptr;
-  const int64_t n_runs = (c->n_nodes + kNlRun - 1) / kNlRun;
-  const int nct = cdiv(n_vec, 16 * nl_col_blocks<T>());
-  const int n_work = (int)(n_runs * nct);
-  const int fl = (beta != 0.0 ? kInitBeta : 0) | (gamma != 0.0 ? kInitGamma : 0) | (Rs ? kInitRs : 0);
-  const dim3 grid(cdiv(n_work, 4)), blk(256);
-#define INIT_NL_ARGS                                                                                      \
-  proj, has ? nl.run_off.ptr : nullptr, has ? nl.pair_atom.ptr : nullptr, has ? nl.pair_ent.ptr : nullptr, \
-      has ? nl.atom_npj.ptr : nullptr, nl.max_pj, Cp, has, X, ldx, W, ldw, Wold, ldo, Rs, ldr, rscale,    \
-      c->n_nodes, n_work, nct, n_vec, beta, gamma, bg_d
-#define INIT_NL_CASE(F)                                                                        \
-  case F:                                                                                      \
-    if (has && nl.real_proj)                                                                   \
-      hipLaunchKernelGGL((init_nl_kernel<T, F, true>), grid, blk, 0, c->stream, INIT_NL_ARGS);  \
-    else                                                                                       \
-      hipLaunchKernelGGL((init_nl_kernel<T, F, false>), grid, blk, 0, c->stream, INIT_NL_ARGS); \
+static InitArgs<T> init_args(chfsi_ctx* c, NonlocalK& nl, const typename C2<T>::type* proj,
+                             const typename C2<T>::type* Cp, const double2* X, int64_t ldx, double2* W, int64_t ldw,
+                             const double2* Wold, int64_t ldo, int n_vec, double beta, double gamma) {
+  const bool has = Cp != nullptr;
+  InitArgs<T> g{};
+  g.proj = proj;
+  g.run_off = has ? nl.run_off.ptr : nullptr;
+  g.pair_atom = has ? nl.pair_atom.ptr : nullptr;
+  g.pair_ent = has ? nl.pair_ent.ptr : nullptr;
+  g.atom_npj = has ? nl.atom_npj.ptr : nullptr;
+  g.max_pj = nl.max_pj;
+  g.has_nl = has;
+  g.Cp = Cp;
+  g.X = X;
+  g.ldx = ldx;
+  g.W = W;
+  g.ldw = ldw;
+  g.Wold = Wold;
+  g.ldo = ldo;
+  g.n_nodes = c->n_nodes;
+  g.n_coltiles = cdiv(n_vec, 16 * nl_col_blocks<T>());
+  g.n_work = (int)((c->n_nodes + kNlRun - 1) / kNlRun * g.n_coltiles);
+  g.n_vec = n_vec;
+  g.beta = beta;
+  g.gamma = gamma;
+  g.mesh = mesh_shape(c);
+  return g;
+}
+
+template <class T>
+static void launch_init(chfsi_ctx* c, const InitArgs<T>& g, const NonlocalK& nl) {
+  const bool realp = g.has_nl && nl.real_proj;
+  StageTimer tm(c, CHFSI_STAGE_AXPY, g.has_nl ? 8.0 * 2.0 * nl.n_entries * nl.max_pj * g.n_vec : 0.0, 0.0,
+                2.0 * (double)g.n_nodes * g.n_vec * sizeof(double2) *
+                    (1.0 + (g.beta != 0.0) + (g.gamma != 0.0)));
+  const int fl = (g.beta != 0.0 ? kInitBeta : 0) | (g.gamma != 0.0 ? kInitGamma : 0) | (g.Rs ? kInitRs : 0);
+  const dim3 grid(cdiv(g.n_work, 4)), blk(256);
+#define INIT_NL_LAUNCH(F, RP, GA) hipLaunchKernelGGL((init_nl_kernel<T, F, RP, GA>), grid, blk, 0, c->stream, g)
+#define INIT_NL_CASE(F)                     \
+  case F:                                   \
+    if (realp && g.ye)                      \
+      INIT_NL_LAUNCH(F, true, true);        \
+    else if (realp)                         \
+      INIT_NL_LAUNCH(F, true, false);       \
+    else if (g.ye)                          \
+      INIT_NL_LAUNCH(F, false, true);       \
+    else                                    \
+      INIT_NL_LAUNCH(F, false, false);      \
     break;
   switch (fl) {
     INIT_NL_CASE(0)
@@ -590,27 +762,82 @@ static void init_and_backproduct(chfsi_ctx* c, NonlocalK& nl, const typename C2<
     INIT_NL_CASE(7)
   }
 #undef INIT_NL_CASE
-#undef INIT_NL_ARGS
+#undef INIT_NL_LAUNCH
   LAUNCH_CHECK();
+}
+
+// Where the cell products of one apply go.  Per-colour launches add them into
+// the output; each needs enough workgroups, or its tail (and at the 27 colours of
+// an odd mesh the number of launches) sets the time.  Otherwise one launch over all
+// cells writes them to ye, and the initialisation pass gathers them: the same
+// sums to the bit.  The line is drawn at kYeWork workgroups per colour on the mean
+// and kYeMax bytes of ye.  Filters by colours and by cells: 3^3 cells, p = 4, one
+// apply of 32 columns 500 and 47 us; 9^3, p = 5 (27 colours), matrix-free, 130
+// columns 23.5 and 18.8 ms; 8^3, p = 5, matrix-free adjoint, 128 columns (4096
+// workgroups per colour) 46.2 and 43.2 ms; 8^3, p = 6, cell matrices, 128 columns
+// 72.6 and 68.8 ms; 16^3, p = 6, matrix-free, 128 columns (32768 per colour) 226
+// and 233 ms.
+constexpr int64_t kYeWork = 8192;
+constexpr size_t kYeMax = (size_t)2 << 30;
+
+size_t products_scratch_bytes(const chfsi_ctx* c, int n_vec, bool fp64) {
+  const int64_t per_cell = c->form == CHFSI_FORM_MATRIX_FREE ? mf_items_per_cell(c, n_vec, fp64)
+                                                             : cell_items_per_cell(c, n_vec);
+  const size_t bytes = (size_t)c->n_cells * c->nloc * 2 * n_vec * (fp64 ? sizeof(double2) : sizeof(float2));
+  return per_cell * c->n_cells <= kYeWork * c->n_colours && bytes <= kYeMax ? bytes : 0;
+}
+
+// The context's ye for this apply, or null: per-colour launches (which also serve
+// where nothing may be allocated, the fixed-scratch filter or a capture that
+// comes before the first such apply).
+static void* ye_for_call(chfsi_ctx* c, int n_vec, bool fp64) {
+  const size_t bytes = c->nl_fixed ? 0 : products_scratch_bytes(c, n_vec, fp64);
+  if (bytes == 0) return nullptr;
+  const size_t n = (bytes + sizeof(double) - 1) / sizeof(double);
+  if (c->ye.n < n) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    CHFSI_HIP(hipStreamIsCapturing(c->stream, &st));
+    if (st != hipStreamCaptureStatusNone) return nullptr;
+    c->ye.alloc(n);
+  }
+  return c->ye.ptr;
+}
+
+template <class T>
+static void apply_t(chfsi_ctx* c, KPoint& kp, const typename C2<T>::type* proj, const double2* X, int64_t ldx,
+                    double2* W, int64_t ldw, const double2* Wold, int64_t ldo, int n_vec, int prec, double alpha,
+                    double beta, double gamma, const double2* Rs, int64_t ldr, const double* rscale) {
+  typedef typename C2<T>::type CT;
+  const bool mf = c->form == CHFSI_FORM_MATRIX_FREE;
+  const CT* Cp = nonlocal_coeffs<T>(c, kp.nl, proj, X, ldx, n_vec, alpha);
+  InitArgs<T> g = init_args<T>(c, kp.nl, proj, Cp, X, ldx, W, ldw, Wold, ldo, n_vec, beta, gamma);
+  g.Rs = Rs;
+  g.ldr = ldr;
+  g.rscale = rscale;
+  CT* ye = reinterpret_cast<CT*>(ye_for_call(c, n_vec, sizeof(T) == 8));
+  if (ye) {
+    g.ye = ye;
+    g.alpha = alpha;
+    g.msc = mf ? c->minv_sqrt.ptr : nullptr;
+    if (mf) launch_mf_products(c, kp, prec, X, ldx, nullptr, 0, n_vec, 1.0, nullptr, ye);
+    else launch_cell_products(c, kp, prec, X, ldx, nullptr, 0, n_vec, 1.0, ye);
+    launch_init<T>(c, g, kp.nl);
+    return;
+  }
+  launch_init<T>(c, g, kp.nl);
+  if (mf) launch_mf_products(c, kp, prec, X, ldx, W, ldw, n_vec, alpha);
+  else launch_cell_products(c, kp, prec, X, ldx, W, ldw, n_vec, alpha);
 }
 
 void apply_H3(chfsi_ctx* c, KPoint& kp, const double2* X, int64_t ldx, double2* W, int64_t ldw,
               const double2* Wold, int64_t ldo, int n_vec, int prec, double alpha, double beta, double gamma,
               const double2* Rs, int64_t ldr, const double* rscale) {
-  if (prec == CHFSI_PREC_MIXED) {
-    const float2* Cp = nonlocal_coeffs<float>(c, kp.nl, kp.nl.proj32.ptr, X, ldx, n_vec, alpha);
-    init_and_backproduct<float>(c, kp.nl, kp.nl.proj32.ptr, Cp, X, ldx, W, ldw, Wold, ldo, n_vec, beta, gamma,
-                                Rs, ldr, rscale);
-  } else {
-    const double2* Cp = nonlocal_coeffs<double>(c, kp.nl, kp.nl.proj.ptr, X, ldx, n_vec, alpha);
-    init_and_backproduct<double>(c, kp.nl, kp.nl.proj.ptr, Cp, X, ldx, W, ldw, Wold, ldo, n_vec, beta, gamma,
-                                 Rs, ldr, rscale);
-  }
-  if (c->form == CHFSI_FORM_MATRIX_FREE) {
-    launch_mf_products(c, kp, prec, X, ldx, W, ldw, n_vec, alpha);
-  } else {
-    launch_cell_products(c, kp, prec, X, ldx, W, ldw, n_vec, alpha);
-  }
+  if (prec == CHFSI_PREC_MIXED)
+    apply_t<float>(c, kp, kp.nl.proj32.ptr, X, ldx, W, ldw, Wold, ldo, n_vec, prec, alpha, beta, gamma, Rs, ldr,
+                   rscale);
+  else
+    apply_t<double>(c, kp, kp.nl.proj.ptr, X, ldx, W, ldw, Wold, ldo, n_vec, prec, alpha, beta, gamma, Rs, ldr,
+                    rscale);
 }
 
 void apply_H2(chfsi_ctx* c, KPoint& kp, const double2* X, int64_t ldx, double2* W, int64_t ldw,
@@ -648,18 +875,23 @@ void apply_H(chfsi_ctx* c, KPoint& kp, const double2* X, int64_t ldx, double2* W
 }
 
 // ---------------------------------------------------------------- batched support
+template <class T>
+static void nonlocal_init_t(chfsi_ctx* c, KPoint& kp, const typename C2<T>::type* proj, const double2* X, int64_t ldx,
+                            double2* W, int64_t ldw, int n_vec, double alpha, double beta, double gamma,
+                            const double* alpha_d, const double* bg_d, void* scratch) {
+  const typename C2<T>::type* Cp = nonlocal_coeffs<T>(c, kp.nl, proj, X, ldx, n_vec, alpha, alpha_d, scratch);
+  InitArgs<T> g = init_args<T>(c, kp.nl, proj, Cp, X, ldx, W, ldw, W, ldw, n_vec, beta, gamma);
+  g.bg_d = bg_d;
+  launch_init<T>(c, g, kp.nl);
+}
+
 void apply_nonlocal_init(chfsi_ctx* c, KPoint& kp, const double2* X, int64_t ldx, double2* W, int64_t ldw,
                          int n_vec, int prec, double alpha, double beta, double gamma, const double* alpha_d,
                          const double* bg_d, void* scratch) {
-  if (prec == CHFSI_PREC_MIXED) {
-    const float2* Cp = nonlocal_coeffs<float>(c, kp.nl, kp.nl.proj32.ptr, X, ldx, n_vec, alpha, alpha_d, scratch);
-    init_and_backproduct<float>(c, kp.nl, kp.nl.proj32.ptr, Cp, X, ldx, W, ldw, W, ldw, n_vec, beta, gamma,
-                                nullptr, 0, nullptr, bg_d);
-  } else {
-    const double2* Cp = nonlocal_coeffs<double>(c, kp.nl, kp.nl.proj.ptr, X, ldx, n_vec, alpha, alpha_d, scratch);
-    init_and_backproduct<double>(c, kp.nl, kp.nl.proj.ptr, Cp, X, ldx, W, ldw, W, ldw, n_vec, beta, gamma,
-                                 nullptr, 0, nullptr, bg_d);
-  }
+  if (prec == CHFSI_PREC_MIXED)
+    nonlocal_init_t<float>(c, kp, kp.nl.proj32.ptr, X, ldx, W, ldw, n_vec, alpha, beta, gamma, alpha_d, bg_d, scratch);
+  else
+    nonlocal_init_t<double>(c, kp, kp.nl.proj.ptr, X, ldx, W, ldw, n_vec, alpha, beta, gamma, alpha_d, bg_d, scratch);
 }
 
 size_t nonlocal_scratch_bytes_min(const KPoint& kp, int n_vec) {
@@ -673,7 +905,7 @@ size_t nonlocal_scratch_bytes(const KPoint& kp, int n_vec) {
   const NonlocalK& nl = kp.nl;
   if (nl.n_atoms == 0 || nl.n_entries == 0) return 0;
   const size_t mr = 2 * nl.max_pj;
-  const size_t n = (size_t)nl.n_chunks * mr * n_vec + 2 * (size_t)nl.n_atoms * mr * n_vec;
+  const size_t n = (size_t)nl.n_chunks * nl_parts(nl, n_vec) * mr * n_vec + (size_t)nl.n_atoms * mr * n_vec;
   return n * sizeof(double2);  // the larger of the two precisions
 }
 

@@ -130,7 +130,7 @@ __global__ __launch_bounds__(MfT<T>::NT) void mf_apply_kernel(
     const int32_t* __restrict__ cells, int total, int n_chunks, const double* __restrict__ minv_sqrt,
     const double2* __restrict__ X, int64_t ldx, double2* __restrict__ Y, int64_t ldy, int n_vec, double alpha,
     T J, T half_k2, T a0, T a1, T a2, T b0, T b1, T b2, const T* __restrict__ kin,
-    const double* __restrict__ alpha_d) {
+    const double* __restrict__ alpha_d, typename MfT<T>::C2* __restrict__ ye) {
   typedef typename MfT<T>::C2 C2;
   typedef typename MfT<T>::Q4 Q4;
   constexpr int NT = MfT<T>::NT;
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(MfT<T>::NT) void mf_apply_kernel(
   // neighbouring lanes read one row
   const bool edge = tid < 2 * CW * N2;
   const int tc = tid % CW, ts = (tid / CW) % 2, tl = tid / (2 * CW);
-  const int e = cells[item / n_chunks];
+  const int e = cells ? cells[item / n_chunks] : item / n_chunks;
   const int col = (item % n_chunks) * CW + tc;
   const int32_t* nodes = cell_nodes + (size_t)e * N3;
   const bool ok = edge && col < n_vec;
@@ -226,6 +226,11 @@ __global__ __launch_bounds__(MfT<T>::NT) void mf_apply_kernel(
 #pragma unroll
     for (int z = 0; z < NP; ++z) v[z] = in[z * N2];
     sf_eo<T, NP, false>(eoBb, v, y);
+    if (ye) {                             // all cells in one launch: gathered by the caller
+#pragma unroll
+      for (int o = 0; o < NP; ++o) ye[(((size_t)e * N3 + tl + o * N2) * 2 + ts) * n_vec + col] = y[o];
+      return;
+    }
 #pragma unroll
     for (int o = 0; o < NP; ++o) r[o] = double2{(double)y[o].x, (double)y[o].y};
     int64_t I[NP];
@@ -261,7 +266,7 @@ __global__ void mf_qdata_kernel(const double* __restrict__ V, const double* __re
 
 template <class T, int NP, bool KT>
 void launch_mf_t(chfsi_ctx* c, const KPoint& kp, const double2* X, int64_t ldx, double2* W, int64_t ldw, int n_vec,
-                 double alpha, const double* alpha_d) {
+                 double alpha, const double* alpha_d, void* ye) {
   typedef typename MfT<T>::C2 C2;
   typedef typename MfT<T>::Q4 Q4;
   constexpr int CW = mf_cw<T>(NP);
@@ -287,8 +292,8 @@ void launch_mf_t(chfsi_ctx* c, const KPoint& kp, const double2* X, int64_t ldx, 
     kin = c->mf_kin32.ptr;
   }
   const double np3 = (double)NP * NP * NP;
-  for (int k = 0; k < c->n_colours; ++k) {
-    const int n_in = c->colour_off[k + 1] - c->colour_off[k];
+  for (int k = 0; k < (ye ? 1 : c->n_colours); ++k) {
+    const int n_in = ye ? c->n_cells : c->colour_off[k + 1] - c->colour_off[k];
     if (n_in == 0) continue;
     const int64_t total = (int64_t)n_in * n_chunks;
     CHFSI_CHECK(total < (int64_t)1 << 30, CHFSI_EINVAL, "matrix-free apply: too many work items");
@@ -302,28 +307,32 @@ void launch_mf_t(chfsi_ctx* c, const KPoint& kp, const double2* X, int64_t ldx, 
     StageTimer tm(c, sizeof(T) == 8 ? CHFSI_STAGE_CELL_FP64 : CHFSI_STAGE_CELL_FP32, flops, exec, bytes);
     const int grid = (int)(8 * ((total + 7) / 8));
     hipLaunchKernelGGL((mf_apply_kernel<T, NP, KT>), dim3(grid), dim3(MfT<T>::NT), sh, c->stream, tab, qd,
-                       c->cell_nodes.ptr, c->colour_cells.ptr + c->colour_off[k], (int)total, n_chunks,
+                       c->cell_nodes.ptr, ye ? nullptr : c->colour_cells.ptr + c->colour_off[k], (int)total, n_chunks,
                        c->minv_sqrt.ptr, X, ldx, W, ldw, n_vec, alpha, (T)c->J, half_k2, a[0], a[1], a[2], b[0],
-                       b[1], b[2], kin, alpha_d);
+                       b[1], b[2], kin, alpha_d, (C2*)ye);
     LAUNCH_CHECK();
   }
 }
 
 template <int NP>
 void launch_mf_np(chfsi_ctx* c, const KPoint& kp, bool fp64, const double2* X, int64_t ldx, double2* W, int64_t ldw,
-                  int n_vec, double alpha, const double* alpha_d) {
+                  int n_vec, double alpha, const double* alpha_d, void* ye) {
   if (fp64) {
-    if (kp.gamma) launch_mf_t<double, NP, false>(c, kp, X, ldx, W, ldw, n_vec, alpha, alpha_d);
-    else launch_mf_t<double, NP, true>(c, kp, X, ldx, W, ldw, n_vec, alpha, alpha_d);
+    if (kp.gamma) launch_mf_t<double, NP, false>(c, kp, X, ldx, W, ldw, n_vec, alpha, alpha_d, ye);
+    else launch_mf_t<double, NP, true>(c, kp, X, ldx, W, ldw, n_vec, alpha, alpha_d, ye);
   } else {
-    if (kp.gamma) launch_mf_t<float, NP, false>(c, kp, X, ldx, W, ldw, n_vec, alpha, alpha_d);
-    else launch_mf_t<float, NP, true>(c, kp, X, ldx, W, ldw, n_vec, alpha, alpha_d);
+    if (kp.gamma) launch_mf_t<float, NP, false>(c, kp, X, ldx, W, ldw, n_vec, alpha, alpha_d, ye);
+    else launch_mf_t<float, NP, true>(c, kp, X, ldx, W, ldw, n_vec, alpha, alpha_d, ye);
   }
 }
 
 }  // namespace
 
 bool mf_supported(const chfsi_ctx* c) { return c->nq == c->np1 && c->np1 >= 2 && c->np1 <= 9; }
+
+int64_t mf_items_per_cell(const chfsi_ctx* c, int n_vec, bool fp64) {
+  return cdiv(n_vec, fp64 ? mf_cw<double>(c->np1) : mf_cw<float>(c->np1));
+}
 
 void mf_prepare(chfsi_ctx* c) {
   CHFSI_CHECK(mf_supported(c), CHFSI_EINVAL, "matrix-free apply needs n_q = p + 1 and 1 <= p <= 8");
@@ -458,17 +467,17 @@ void mf_set_local(chfsi_ctx* c, const double* V, const double* B) {
 }
 
 void launch_mf_products(chfsi_ctx* c, const KPoint& kp, int prec, const double2* X, int64_t ldx, double2* W,
-                        int64_t ldw, int n_vec, double alpha, const double* alpha_d) {
+                        int64_t ldw, int n_vec, double alpha, const double* alpha_d, void* ye) {
   const bool fp64 = prec != CHFSI_PREC_MIXED;
   switch (c->np1) {
-    case 2: launch_mf_np<2>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d); break;
-    case 3: launch_mf_np<3>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d); break;
-    case 4: launch_mf_np<4>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d); break;
-    case 5: launch_mf_np<5>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d); break;
-    case 6: launch_mf_np<6>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d); break;
-    case 7: launch_mf_np<7>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d); break;
-    case 8: launch_mf_np<8>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d); break;
-    case 9: launch_mf_np<9>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d); break;
+    case 2: launch_mf_np<2>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d, ye); break;
+    case 3: launch_mf_np<3>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d, ye); break;
+    case 4: launch_mf_np<4>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d, ye); break;
+    case 5: launch_mf_np<5>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d, ye); break;
+    case 6: launch_mf_np<6>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d, ye); break;
+    case 7: launch_mf_np<7>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d, ye); break;
+    case 8: launch_mf_np<8>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d, ye); break;
+    case 9: launch_mf_np<9>(c, kp, fp64, X, ldx, W, ldw, n_vec, alpha, alpha_d, ye); break;
     default: throw Error{CHFSI_EINVAL, "matrix-free apply: unsupported p"};
   }
 }

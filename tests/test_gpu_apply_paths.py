@@ -1,0 +1,63 @@
+"""The two routes of the cell products and the split contraction.
+
+A small apply runs all cells in one launch and gathers them in the initialisation
+pass; the fixed-scratch filter always runs colour by colour.  Both add the cells
+of a node in the colour order, so the filters agree bit for bit, on even and odd
+cell counts, at every order of basis, in both forms and precisions.
+
+The contraction cuts its chunks into more parts the narrower the block is, which
+only reorders sums of at most 512 terms: a column alone and inside a wide block
+agree to 64 units in the last place of the block's scale (the random-walk growth
+of a 4096-term sum).
+"""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _op(cells, p, k, form, lmax=2):
+    from paper_2410_02754_amd import Operator
+    s = synth.make_system("paths", n_cells=cells, box=tuple(1.3 * c for c in cells), p=p, kpts=[(k, -k, 0.5 * k)],
+                          n_atoms=2, lmax=lmax, rcut_sigmas=5.0, n_vec=1)
+    op = Operator(s.n_cells, s.box, s.p, s.quad, s.n_q, s.kpts, form=form)
+    pts = op.quad_points().reshape(-1, 3)
+    op.set_local(torch.tensor(synth.veff(s, pts).reshape(op.n_cells, op.nq3), device="cuda"),
+                 torch.tensor(synth.bxc(s, pts).reshape(op.n_cells, op.nq3, 3), device="cuda"))
+    op.set_atoms(s.atoms)
+    return op
+
+
+@pytest.mark.parametrize("cells,p,n,k,form,prec", [
+    ((2, 2, 2), 1, 3, 0.0, "matrix_free", "fp64"),
+    ((3, 2, 4), 4, 33, 0.2, "cell", "fp64"),
+    ((3, 3, 3), 3, 17, 0.0, "matrix_free", "fp64"),
+    ((2, 5, 3), 5, 65, 0.1, "cell", "mixed"),
+    ((4, 3, 2), 6, 130, 0.1, "matrix_free", "mixed"),
+    ((5, 2, 2), 7, 1, 0.0, "cell", "fp64"),
+    ((2, 3, 2), 8, 20, 0.0, "matrix_free", "fp64"),
+])
+def test_one_launch_equals_colours(cells, p, n, k, form, prec):
+    op = _op(cells, p, k, form)
+    X = torch.tensor(synth.random_block(5, op.n_dof, n), device="cuda")
+    W, Y, Z = torch.empty_like(X), X.clone(), X.clone()
+    op.cheb_filter(Y, W, 3, 8.0, 900.0, -6.0, prec=prec)
+    op.cheb_filter_noalloc(Z, W, 3, 8.0, 900.0, -6.0, prec=prec)
+    assert torch.isfinite(torch.view_as_real(Y)).all() and torch.equal(Y, Z)
+    op.close()
+
+
+@pytest.mark.parametrize("lmax,k", [(0, 0.0), (1, 0.2), (2, 0.2), (2, 0.0)])
+def test_split_contraction_matches_whole_chunks(lmax, k):
+    op = _op((4, 4, 3), 5, k, "cell", lmax)
+    X = torch.tensor(synth.random_block(6, op.n_dof, 1500), device="cuda")
+    Y = op.apply_H(X, torch.empty_like(X))
+    for c in (0, 7, 1499):
+        x = X[:, c:c + 1].contiguous()
+        y = op.apply_H(x, torch.empty_like(x))
+        err = (y[:, 0] - Y[:, c]).abs().max() / Y[:, c].abs().max()
+        assert float(err) <= 64 * np.finfo(float).eps, float(err)
+    op.close()
