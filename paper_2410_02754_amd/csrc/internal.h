@@ -214,9 +214,9 @@ struct chfsi_ctx {
   // or CHFSI_FORM_MATRIX_FREE (sum factorisation from the quadrature data)
   int form = 0;
   chfsi::DevBuf<double> mf_tab;               // [B: np1^2][Dq: np1^2][w: np1]
-  chfsi::DevBuf<double> mf_qd;                // [E][nq^3][4]: w_q J (V, Bx, By, Bz)
+  chfsi::DevBuf<double> mf_qd;                // [E][x][y + nq z][4]: w_q J (V, Bx, By, Bz)
   chfsi::DevBuf<float> mf_tab32, mf_qd32;     // FP32 copies for mixed precision
-  chfsi::DevBuf<float> mf_kin32;              // [3][nq^3] FP32 kinetic weights per point
+  chfsi::DevBuf<float> mf_kin32;              // [3][point on the line][line] FP32 kinetic weights
   // tables and work vectors of the SCF field solves (built on first use)
   std::shared_ptr<chfsi::FieldOps> fields;
   // stage timing

@@ -7,7 +7,7 @@
 //   1. U = (B (x) B (x) B)^T u        values at the quadrature points (3 passes)
 //   2. W = w_q J [(V + |k|^2/2) U + (B_xc . sigma) U]          pointwise
 //   3. for each direction d: G_d = D_d U (collocation derivative along d),
-//        W += D_d^T (w_q J G_d / 2) - i k_d w_q J G_d              (2 passes each)
+//        W += D_d^T (w_q J G_d / 2) - i k_d w_q J G_d
 //   4. y = (B (x) B (x) B) W            back to the nodes (3 passes)
 // and y, scaled by M_D^{-1/2}, is added into the output rows of the cell's nodes.
 // B[a][q] = l_a(x_q) is the 1-D GLL-node Lagrange basis at the quadrature points
@@ -16,9 +16,10 @@
 // are exact for the degree-p fields of the cell, so the result equals the
 // product with the assembled cell matrices (kinetic K, mass, k-gradient C,
 // potential and field matrices) up to rounding: same quadrature, different
-// order of summation.  Work per cell and column is 12 line contractions of
-// n_p^4 complex-by-real multiply-adds per spin, against 4 (2 n_p^3)^2 for the
-// dense cell product, and no cell matrices are stored.
+// order of summation.  Work per cell and column is 9 line contractions of
+// n_p^4 complex-by-real multiply-adds per spin in FP64 at k = 0 (12 with the k-term
+// and in FP32), against 4 (2 n_p^3)^2 for the dense cell product, and no cell
+// matrices are stored.
 //
 // FP64, or FP32 (mixed precision: tables, quadrature data, LDS fields and
 // arithmetic in FP32, rows converted on gather and added into the FP64 output).
@@ -49,84 +50,102 @@ template <> struct MfT<float> {
   typedef float4 Q4;
   static constexpr int NT = 512;
 };
+
+struct MfMesh {
+  int nx, ny;               // cells along x, y
+  int Nx, Ny, Nz, Nxy;      // nodes
+};
+// waves per SIMD that the registers are limited for: what the LDS lets share a CU, as
+// far as the registers do not spill much (FP64 at n_p = 6 and five waves: 54 ms for
+// an adjoint that takes 42 at four)
+template <class T>
+constexpr int mf_waves(int NP) { return sizeof(T) == 8 ? (NP <= 6 ? 4 : NP == 7 ? 3 : 2) : (NP <= 7 ? 6 : 3); }
 // columns per workgroup: the same LDS bytes in both precisions
 template <class T>
 constexpr int mf_cw(int NP) { return sizeof(T) == 8 ? sf_cols(NP) : 2 * sf_cols(NP); }
 
-// Kinetic and k-gradient terms along DIM, added into W:
-//   G = Dq U,  W += a_d Dq^T (wJ G) - i b_d wJ G,
-// a_d = (2/h_d)^2 / 2, b_d = k_d (2/h_d), wJ = J w_x w_y w_z at each point.
-// BWD: W along the line is then complete (the other directions ran before), so
-// the backward interpolation along DIM (W -> B W) is applied in place.
-// eo: even-odd tables of Dq (G = Dq U), Dq^T (the transposed contraction) and
-// B^T (points -> nodes), see sf_eo.
-// In FP32 the kinetic weights a_d wJ come per point from kin (formed in FP64 and
-// rounded once): products of the shared 1-D weights rounded in FP32 would bias
-// the operator the same way in every cell.
-template <class T, int NP, int CW, int DIM, bool KT, bool BWD>
-__device__ __forceinline__ void grad_pass(const T* __restrict__ eoDf, const T* __restrict__ eoDb,
-                                          const T* __restrict__ eoBb, const T* __restrict__ w1, T J, T a_d, T b_d,
-                                          const T* __restrict__ kin, const typename MfT<T>::C2* __restrict__ U,
-                                          typename MfT<T>::C2* __restrict__ W) {
+// Kinetic and k-gradient terms of one line u along direction d, added into w:
+//   w += a_d Dq^T (wJ Dq u) - i b_d wJ Dq u,
+// a_d = (2/h_d)^2 / 2, b_d = k_d (2/h_d), wJ = wl w1[q] with wl = J times the two
+// weights held fixed along the line.  FP64: wl comes out of the first term, which is
+// one contraction with K = Dq^T diag(w1) Dq (eoK) instead of two (with the second
+// term, K and Dq: two as before).  FP32 keeps Dq and Dq^T: their rounded tables hold
+// the identities listed in mf_prepare, and the kinetic weights a_d wJ come per point
+// from kin (formed in FP64 and rounded once), since products of the shared 1-D
+// weights rounded in FP32 would bias the operator the same way in every cell.
+template <class T, int NP, bool KT>
+__device__ __forceinline__ void grad_line(const T* __restrict__ eoDf, const T* __restrict__ eoDb,
+                                          const T* __restrict__ eoK, const T* __restrict__ w1, T wl, T a_d, T b_d,
+                                          const T* __restrict__ kin, const typename MfT<T>::C2 (&u)[NP],
+                                          typename MfT<T>::C2 (&w)[NP]) {
   typedef typename MfT<T>::C2 C2;
-  constexpr int NT = MfT<T>::NT;
-  constexpr int N2 = NP * NP, N3 = N2 * NP;
-  constexpr int S = DIM == 0 ? 1 : DIM == 1 ? NP : N2;
-  for (int t = threadIdx.x; t < N2 * 2 * CW; t += NT) {
-    const int l = t % N2, f = t / N2;
-    const int lb = sf_line_base<NP, DIM>(l);
-    const int base = f * N3 + lb;
-    // the two coordinates held fixed along the line are l % NP and l / NP
-    const T wl = J * w1[l % NP] * w1[l / NP];
-    T kw[NP];
+  C2 g[NP], dw[NP];
+  if constexpr (sizeof(T) == 8) {
+    sf_eo<T, NP, false>(eoK, u, dw);
+    const T c = a_d * wl;
 #pragma unroll
-    for (int q = 0; q < NP; ++q) kw[q] = (sizeof(T) == 4) ? kin[lb + q * S] : a_d * wl * w1[q];
-    C2 u[NP], g[NP];
-#pragma unroll
-    for (int j = 0; j < NP; ++j) u[j] = U[base + j * S];
+    for (int r = 0; r < NP; ++r) w[r] = C2{fma(c, dw[r].x, w[r].x), fma(c, dw[r].y, w[r].y)};
+    if constexpr (KT) sf_eo<T, NP, true>(eoDf, u, g);
+  } else {
     sf_eo<T, NP, true>(eoDf, u, g);
-    C2 fk[NP], dw[NP];
+    C2 fk[NP];
 #pragma unroll
-    for (int q = 0; q < NP; ++q) fk[q] = C2{kw[q] * g[q].x, kw[q] * g[q].y};
+    for (int q = 0; q < NP; ++q) {
+      const T k = kin[q * NP * NP];
+      fk[q] = C2{k * g[q].x, k * g[q].y};
+    }
     sf_eo<T, NP, true>(eoDb, fk, dw);
-    C2 wv[NP];
+#pragma unroll
+    for (int r = 0; r < NP; ++r) w[r] = C2{w[r].x + dw[r].x, w[r].y + dw[r].y};
+  }
+  if constexpr (KT) {
 #pragma unroll
     for (int r = 0; r < NP; ++r) {
-      C2 acc = W[base + r * S];
-      acc.x += dw[r].x;
-      acc.y += dw[r].y;
-      if constexpr (KT) {
-        // -i b wJ g = b wJ g.y - i b wJ g.x
-        const T s = b_d * wl * w1[r];
-        acc.x = fma(s, g[r].y, acc.x);
-        acc.y = fma(-s, g[r].x, acc.y);
-      }
-      wv[r] = acc;
-    }
-    if constexpr (BWD) {
-      C2 o[NP];
-      sf_eo<T, NP, false>(eoBb, wv, o);
-#pragma unroll
-      for (int r = 0; r < NP; ++r) W[base + r * S] = o[r];
-    } else {
-#pragma unroll
-      for (int r = 0; r < NP; ++r) W[base + r * S] = wv[r];
+      // -i b wJ g = b wJ g.y - i b wJ g.x
+      const T s = b_d * wl * w1[r];
+      w[r].x = fma(s, g[r].y, w[r].x);
+      w[r].y = fma(-s, g[r].x, w[r].y);
     }
   }
 }
 
-// tab: [B: NP*NP][Dq: NP*NP][w: NP][even-odd tables of B, B^T, Dq, Dq^T], qd:
-// [E][NP^3] of (wJ V, wJ Bx, wJ By, wJ Bz), both in the arithmetic type T.
+// Lines of a pass along y: groups of 8 lanes share one z, so that the lanes of a
+// 128-bit LDS access hit distinct banks (consecutive lines of n_p = 6, 7 overlap by
+// the pitch of a plane: 37 % of the kernel's LDS cycles were conflicts); other
+// orders keep consecutive lines.
+template <int NP>
+constexpr int mf_ypitch() { return NP == 6 || NP == 7 ? 8 : NP; }
+
+// tab: [B: NP*NP][Dq: NP*NP][w: NP][even-odd tables of B, B^T, Dq, Dq^T, K], qd:
+// [E][x][y + NP z] of (wJ V, wJ Bx, wJ By, wJ Bz), kin: [3][point on the line][line],
+// all in the arithmetic type T.  Both run along the lines' index first, so that the
+// lanes of a load share cache lines (point after point along x, every lane was on a
+// line of its own, and the lookups cost more than the rows').
 //
 // One workgroup per work item (cell of the colour, chunk of CW columns); items
 // are cell major and consecutive items run on one XCD (workgroup b on XCD b % 8),
-// so the column chunks of a cell share its rows in that XCD's L2.  Each thread
-// owns at most one (column, spin, z-line) task of the first and last phases
-// (2 CW n_p^2 <= NT for every n_p) and issues all of that task's global loads
-// before it uses any of them.
+// so the column chunks of a cell share its rows in that XCD's L2.  Seven phases,
+// a thread owning one line in each:
+//   1. z-lines of x gathered, B            5. + kinetic z, then B^T along z
+//   2. y: B                                6. B^T along y
+//   3. x: B -> U; potential, kinetic x     7. B^T along x, y scattered
+//   4. + kinetic y
+// (phase 3 takes the x-lines of both spins together, as the field couples them).
+// Nothing saturates: the vector units (38 % busy), the requests of 32-byte row
+// pieces to L2 (45 %), the LDS and the waits for rows each take a share at the
+// three workgroups per CU that 44 KB of LDS allow, so each is kept short: one
+// contraction per kinetic term (FP64), one 64-bit multiplication per line's
+// addresses, quadrature data in the order of the lanes, the old values of the
+// output rows loaded right after phase 3 and used in phase 7, barriers that order
+// LDS only.  Per colour launch of 512 cells, p = 6, 128 columns: 0.73 -> 0.61 ms; filter
+// of 16^3 cells, degree 24: 225 -> 205 ms.
+// Slower here (whole filter, 16^3 cells): the y and z kinetic terms carried along the
+// interpolation as one more field (five phases, 11 contractions for 9, a fifth of
+// the LDS traffic less) 217 ms, the spins of phase 3 in neighbouring lanes 207 ms, x
+// and z exchanged 207 ms; field pitches without bank conflicts changed nothing.
 template <class T, int NP, bool KT>
-__global__ __launch_bounds__(MfT<T>::NT) void mf_apply_kernel(
-    const T* __restrict__ tab, const typename MfT<T>::Q4* __restrict__ qd, const int32_t* __restrict__ cell_nodes,
+__global__ __launch_bounds__(MfT<T>::NT, mf_waves<T>(NP)) void mf_apply_kernel(
+    const T* __restrict__ tab, const typename MfT<T>::Q4* __restrict__ qd, const MfMesh mesh,
     const int32_t* __restrict__ cells, int total, int n_chunks, const double* __restrict__ minv_sqrt,
     const double2* __restrict__ X, int64_t ldx, double2* __restrict__ Y, int64_t ldy, int n_vec, double alpha,
     T J, T half_k2, T a0, T a1, T a2, T b0, T b1, T b2, const T* __restrict__ kin,
@@ -136,120 +155,206 @@ __global__ __launch_bounds__(MfT<T>::NT) void mf_apply_kernel(
   constexpr int NT = MfT<T>::NT;
   constexpr int CW = mf_cw<T>(NP);
   constexpr int N2 = NP * NP, N3 = N2 * NP;
+  constexpr int YP = mf_ypitch<NP>(), NY = YP * NP;
   static_assert(2 * CW * N2 <= NT, "one edge task per thread");
   extern __shared__ double2 mf_sm_raw[];
-  C2* bufA = reinterpret_cast<C2*>(mf_sm_raw);   // [CW][2][N3]
-  C2* bufB = bufA + CW * 2 * N3;                 // [CW][2][N3]
+  C2* bufU = reinterpret_cast<C2*>(mf_sm_raw);   // [CW][2][N3]
+  C2* bufW = bufU + CW * 2 * N3;
+  T* w2 = reinterpret_cast<T*>(bufW + CW * 2 * N3);  // [N2] J w_a w_b
   const T* w1 = tab + 2 * N2;
   const T* eoBf = tab + 2 * N2 + NP;
   const T* eoBb = eoBf + sf_eo_size(NP);
   const T* eoDf = eoBb + sf_eo_size(NP);
   const T* eoDb = eoDf + sf_eo_size(NP);
+  const T* eoK = eoDb + sf_eo_size(NP);
   const int tid = threadIdx.x;
 
   const int per_xcd = (total + 7) / 8;
   const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (item >= total) return;
-  // edge task: column fastest, then spin, then the z-line (x, y), so that
-  // neighbouring lanes read one row
+  // edge task: column fastest, then spin, then the line, so that neighbouring
+  // lanes read one row
   const bool edge = tid < 2 * CW * N2;
   const int tc = tid % CW, ts = (tid / CW) % 2, tl = tid / (2 * CW);
+  const int ta = tl % NP, tb = tl / NP;          // the line's two fixed indices
+  const int tf = (tc * 2 + ts) * N3;
   const int e = cells ? cells[item / n_chunks] : item / n_chunks;
   const int col = (item % n_chunks) * CW + tc;
-  const int32_t* nodes = cell_nodes + (size_t)e * N3;
+  const int cx = e % mesh.nx, cyz = e / mesh.nx;
+  const int cy = cyz % mesh.ny, cz = cyz / mesh.ny;
   const bool ok = edge && col < n_vec;
+  // nodes of a line along d: the first, and a step that wraps at the line's end
+  // where the cell is the last of its row (uniform over the workgroup)
+  const int fx = cx * (NP - 1), fy = cy * (NP - 1), fz = cz * (NP - 1);
+  const auto wrap = [](int i, int n) { return i >= n ? i - n : i; };
+  const int last_x = fx + NP - 1 == mesh.Nx ? -fx : NP - 1;
+  const int last_z = fz + NP - 1 == mesh.Nz ? -fz : NP - 1;
 
-  // gather M^{-1/2} x along the task's z-line (addresses clamped in bounds) and
-  // interpolate along z into bufB
+  // 1. gather M^{-1/2} x along the task's z-line (addresses clamped in bounds)
   if (edge) {
     const int cc = ok ? col : 0;
-    int64_t I[NP];
-#pragma unroll
-    for (int z = 0; z < NP; ++z) I[z] = nodes[tl + z * N2];
+    const int I0 = wrap(fx + ta, mesh.Nx) + mesh.Nx * wrap(fy + tb, mesh.Ny) + mesh.Nxy * fz;
+    const double2* __restrict__ x0 = X + ((2 * (int64_t)I0 + ts) * ldx + cc);
+    const int64_t zs = 2 * mesh.Nxy * ldx;
     double xs[NP];
     double2 xr[NP];
 #pragma unroll
     for (int z = 0; z < NP; ++z) {
-      xs[z] = minv_sqrt[I[z]];
-      xr[z] = X[(2 * I[z] + ts) * ldx + cc];
+      const int k = z == NP - 1 ? last_z : z;
+      xs[z] = minv_sqrt[I0 + mesh.Nxy * k];
+      xr[z] = x0[zs * k];
     }
-    C2 u[NP];
+    if (tid < N2) w2[tid] = J * w1[tid % NP] * w1[tid / NP];
+    C2 u[NP], r[NP];
 #pragma unroll
     for (int z = 0; z < NP; ++z) {
       const double f = ok ? xs[z] : 0.0;
       u[z] = C2{(T)(f * xr[z].x), (T)(f * xr[z].y)};
     }
-    C2* out = bufB + (tc * 2 + ts) * N3 + tl;
-    C2 r[NP];
     sf_eo<T, NP, false>(eoBf, u, r);
 #pragma unroll
-    for (int o = 0; o < NP; ++o) out[o * N2] = r[o];
+    for (int o = 0; o < NP; ++o) bufU[tf + tl + o * N2] = r[o];
   }
   lds_barrier();
-  sf_line_pass<NP, 2 * CW, 1, NT, T>(eoBf, bufB, bufB);   // in place: a thread owns its line
-  lds_barrier();
-  sf_line_pass<NP, 2 * CW, 0, NT, T>(eoBf, bufB, bufB);   // U in bufB
-  lds_barrier();
 
-  // potential and field terms at the points
-  for (int t = tid; t < N3 * CW; t += NT) {
-    const int q = t % N3, c = t / N3;
-    const T wj = J * w1[q % NP] * w1[(q / NP) % NP] * w1[q / N2];
-    const Q4 d = qd[(size_t)e * N3 + q];
-    const C2 u0 = bufB[(c * 2) * N3 + q], u1 = bufB[(c * 2 + 1) * N3 + q];
-    const T s = d.x + half_k2 * wj;
-    // up:   (s + Bz) u0 + (Bx - i By) u1;  down: (s - Bz) u1 + (Bx + i By) u0
-    C2 w0, w2;
-    w0.x = (s + d.w) * u0.x + d.y * u1.x + d.z * u1.y;
-    w0.y = (s + d.w) * u0.y + d.y * u1.y - d.z * u1.x;
-    w2.x = (s - d.w) * u1.x + d.y * u0.x - d.z * u0.y;
-    w2.y = (s - d.w) * u1.y + d.y * u0.y + d.z * u0.x;
-    bufA[(c * 2) * N3 + q] = w0;
-    bufA[(c * 2 + 1) * N3 + q] = w2;
-  }
-  lds_barrier();
-  grad_pass<T, NP, CW, 2, KT, false>(eoDf, eoDb, eoBb, w1, J, a2, b2, kin + 2 * N3, bufB, bufA);
-  lds_barrier();
-  grad_pass<T, NP, CW, 1, KT, false>(eoDf, eoDb, eoBb, w1, J, a1, b1, kin + 1 * N3, bufB, bufA);
-  lds_barrier();
-  grad_pass<T, NP, CW, 0, KT, true>(eoDf, eoDb, eoBb, w1, J, a0, b0, kin + 0 * N3, bufB, bufA);   // and W -> B W along x
-  lds_barrier();
-  sf_line_pass<NP, 2 * CW, 1, NT, T>(eoBb, bufA, bufA);
-  lds_barrier();
-
-  // last backward contraction along z, then Y[rows] += alpha M^{-1/2} y (the
-  // rows' indices, factors and old values loaded together before the stores)
-  if (ok) {
-    const C2* in = bufA + (tc * 2 + ts) * N3 + tl;
-    C2 v[NP], y[NP];
-    double2 r[NP];
+  // a line of a y phase: field and first point; false for the lanes that pad a group
+  const auto yline = [&](int t, int& f, int& l) {
+    const int g = t % NY, fi = t / NY, x = g % YP, z = g / YP;
+    l = x + NP * z;
+    f = fi * N3 + x + z * N2;
+    return x < NP;
+  };
+  // 2. y
+  for (int t = tid; t < NY * 2 * CW; t += NT) {
+    int p, l;
+    if (!yline(t, p, l)) continue;
+    C2 v[NP], r[NP];
 #pragma unroll
-    for (int z = 0; z < NP; ++z) v[z] = in[z * N2];
+    for (int j = 0; j < NP; ++j) v[j] = bufU[p + j * NP];
+    sf_eo<T, NP, false>(eoBf, v, r);
+#pragma unroll
+    for (int o = 0; o < NP; ++o) bufU[p + o * NP] = r[o];
+  }
+  lds_barrier();
+
+  // 3. x-lines of both spins: U, potential and field, kinetic x
+  for (int t = tid; t < N2 * CW; t += NT) {
+    const int l = t % N2, base = (t / N2) * 2 * N3 + l * NP;
+    const Q4* __restrict__ dq = qd + (size_t)e * N3 + l;
+    const T wl = w2[l];
+    C2 u0[NP], u1[NP], s0[NP], s1[NP];
+    {
+      C2 v[NP];
+#pragma unroll
+      for (int j = 0; j < NP; ++j) v[j] = bufU[base + j];
+      sf_eo<T, NP, false>(eoBf, v, u0);
+#pragma unroll
+      for (int j = 0; j < NP; ++j) v[j] = bufU[base + N3 + j];
+      sf_eo<T, NP, false>(eoBf, v, u1);
+    }
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      bufU[base + q] = u0[q];
+      bufU[base + N3 + q] = u1[q];
+      // up:   (s + Bz) u0 + (Bx - i By) u1;  down: (s - Bz) u1 + (Bx + i By) u0
+      const Q4 d = dq[q * N2];
+      const T s = KT ? d.x + half_k2 * (wl * w1[q]) : d.x;
+      s0[q].x = (s + d.w) * u0[q].x + d.y * u1[q].x + d.z * u1[q].y;
+      s0[q].y = (s + d.w) * u0[q].y + d.y * u1[q].y - d.z * u1[q].x;
+      s1[q].x = (s - d.w) * u1[q].x + d.y * u0[q].x - d.z * u0[q].y;
+      s1[q].y = (s - d.w) * u1[q].y + d.y * u0[q].y + d.z * u0[q].x;
+    }
+    grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, wl, a0, b0, kin + l, u0, s0);
+    grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, wl, a0, b0, kin + l, u1, s1);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      bufW[base + q] = s0[q];
+      bufW[base + N3 + q] = s1[q];
+    }
+  }
+
+  // the output rows of phase 7's x-line, in flight while the next phases run
+  const int I7 = fx + mesh.Nx * wrap(fy + ta, mesh.Ny) + mesh.Nxy * wrap(fz + tb, mesh.Nz);
+  double2* __restrict__ y0 = Y + ((2 * (int64_t)I7 + ts) * ldy + col);
+  // (FP64; in FP32 their registers would cost a resident workgroup)
+  constexpr bool kEarly = sizeof(T) == 8;
+  double2 yo[NP];
+  if (kEarly && ok && !ye) {
+#pragma unroll
+    for (int o = 0; o < NP; ++o) yo[o] = y0[2 * ldy * (o == NP - 1 ? last_x : o)];
+  }
+  lds_barrier();
+
+  // 4. kinetic y
+  for (int t = tid; t < NY * 2 * CW; t += NT) {
+    int p, l;
+    if (!yline(t, p, l)) continue;
+    C2 u[NP], w[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) u[j] = bufU[p + j * NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) w[j] = bufW[p + j * NP];
+    grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, w2[l], a1, b1, kin + N3 + l, u, w);
+#pragma unroll
+    for (int j = 0; j < NP; ++j) bufW[p + j * NP] = w[j];
+  }
+  lds_barrier();
+
+  // 5. kinetic z; W is then complete, and goes back along z
+  for (int t = tid; t < N2 * 2 * CW; t += NT) {
+    const int l = t % N2, base = (t / N2) * N3 + l;
+    C2 u[NP], w[NP], r[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) u[j] = bufU[base + j * N2];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) w[j] = bufW[base + j * N2];
+    grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, w2[l], a2, b2, kin + 2 * N3 + l, u, w);
+    sf_eo<T, NP, false>(eoBb, w, r);
+#pragma unroll
+    for (int j = 0; j < NP; ++j) bufW[base + j * N2] = r[j];
+  }
+  lds_barrier();
+
+  // 6. back along y
+  for (int t = tid; t < NY * 2 * CW; t += NT) {
+    int p, l;
+    if (!yline(t, p, l)) continue;
+    C2 v[NP], r[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) v[j] = bufW[p + j * NP];
+    sf_eo<T, NP, false>(eoBb, v, r);
+#pragma unroll
+    for (int o = 0; o < NP; ++o) bufW[p + o * NP] = r[o];
+  }
+  lds_barrier();
+
+  // 7. back along x, then Y[rows] += alpha M^{-1/2} y
+  if (ok) {
+    C2 v[NP], y[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) v[j] = bufW[tf + tl * NP + j];
     sf_eo<T, NP, false>(eoBb, v, y);
     if (ye) {                             // all cells in one launch: gathered by the caller
+      C2* __restrict__ yr = ye + (((size_t)e * N3 + tl * NP) * 2 + ts) * n_vec + col;
 #pragma unroll
-      for (int o = 0; o < NP; ++o) ye[(((size_t)e * N3 + tl + o * N2) * 2 + ts) * n_vec + col] = y[o];
+      for (int o = 0; o < NP; ++o) yr[(size_t)2 * n_vec * o] = y[o];
       return;
     }
+    const double al = alpha_d ? *alpha_d : alpha;
+    if (!kEarly) {
 #pragma unroll
-    for (int o = 0; o < NP; ++o) r[o] = double2{(double)y[o].x, (double)y[o].y};
-    int64_t I[NP];
-#pragma unroll
-    for (int o = 0; o < NP; ++o) I[o] = nodes[tl + o * N2];
-    double sc[NP];
-    double2 yo[NP];
-#pragma unroll
-    for (int o = 0; o < NP; ++o) {
-      sc[o] = (alpha_d ? *alpha_d : alpha) * minv_sqrt[I[o]];
-      yo[o] = Y[(2 * I[o] + ts) * ldy + col];
+      for (int o = 0; o < NP; ++o) yo[o] = y0[2 * ldy * (o == NP - 1 ? last_x : o)];
     }
 #pragma unroll
-    for (int o = 0; o < NP; ++o)
-      Y[(2 * I[o] + ts) * ldy + col] = double2{fma(sc[o], r[o].x, yo[o].x), fma(sc[o], r[o].y, yo[o].y)};
+    for (int o = 0; o < NP; ++o) {
+      const int k = o == NP - 1 ? last_x : o;
+      const double sc = al * minv_sqrt[I7 + k];
+      y0[2 * ldy * k] = double2{fma(sc, (double)y[o].x, yo[o].x), fma(sc, (double)y[o].y, yo[o].y)};
+    }
   }
 }
 
-// qd[e][q] = w_q J (V, Bx, By, Bz), in FP64 and FP32
+// qd[e][x][y + nq z] = w_q J (V, Bx, By, Bz), in FP64 and FP32
 __global__ void mf_qdata_kernel(const double* __restrict__ V, const double* __restrict__ B,
                                 const double* __restrict__ w1, double J, int nq, int64_t n_points,
                                 double4* __restrict__ qd, float4* __restrict__ qd32) {
@@ -259,8 +364,9 @@ __global__ void mf_qdata_kernel(const double* __restrict__ V, const double* __re
     const int q = (int)(p % nq3);
     const double wj = J * w1[q % nq] * w1[(q / nq) % nq] * w1[q / (nq * nq)];
     const double4 v = double4{wj * V[p], wj * B[3 * p], wj * B[3 * p + 1], wj * B[3 * p + 2]};
-    qd[p] = v;
-    qd32[p] = float4{(float)v.x, (float)v.y, (float)v.z, (float)v.w};
+    const int64_t o = p - q + (q % nq) * (nq * nq) + q / nq;
+    qd[o] = v;
+    qd32[o] = float4{(float)v.x, (float)v.y, (float)v.z, (float)v.w};
   }
 }
 
@@ -270,7 +376,8 @@ void launch_mf_t(chfsi_ctx* c, const KPoint& kp, const double2* X, int64_t ldx, 
   typedef typename MfT<T>::C2 C2;
   typedef typename MfT<T>::Q4 Q4;
   constexpr int CW = mf_cw<T>(NP);
-  const size_t sh = 2 * (size_t)CW * 2 * NP * NP * NP * sizeof(C2);
+  const size_t sh = 2 * (size_t)CW * 2 * NP * NP * NP * sizeof(C2) + NP * NP * sizeof(T);
+  const MfMesh mesh{c->nc[0], c->nc[1], c->Nd[0], c->Nd[1], c->Nd[2], c->Nd[0] * c->Nd[1]};
   const int n_chunks = cdiv(n_vec, CW);
   T a[3], b[3];
   for (int d = 0; d < 3; ++d) {
@@ -298,7 +405,7 @@ void launch_mf_t(chfsi_ctx* c, const KPoint& kp, const double2* X, int64_t ldx, 
     const int64_t total = (int64_t)n_in * n_chunks;
     CHFSI_CHECK(total < (int64_t)1 << 30, CHFSI_EINVAL, "matrix-free apply: too many work items");
     // algorithmic flops of the dense cell product (the filter's count), flops of
-    // 12 dense line contractions per spin (the even-odd form issues about half of
+    // 12 dense line contractions per spin (as by the formula; the even-odd form issues about half of
     // those multiply-adds), and the rows moved
     const double n2 = 2.0 * c->nloc;
     const double flops = 8.0 * n2 * n2 * n_vec * n_in;
@@ -307,7 +414,7 @@ void launch_mf_t(chfsi_ctx* c, const KPoint& kp, const double2* X, int64_t ldx, 
     StageTimer tm(c, sizeof(T) == 8 ? CHFSI_STAGE_CELL_FP64 : CHFSI_STAGE_CELL_FP32, flops, exec, bytes);
     const int grid = (int)(8 * ((total + 7) / 8));
     hipLaunchKernelGGL((mf_apply_kernel<T, NP, KT>), dim3(grid), dim3(MfT<T>::NT), sh, c->stream, tab, qd,
-                       c->cell_nodes.ptr, ye ? nullptr : c->colour_cells.ptr + c->colour_off[k], (int)total, n_chunks,
+                       mesh, ye ? nullptr : c->colour_cells.ptr + c->colour_off[k], (int)total, n_chunks,
                        c->minv_sqrt.ptr, X, ldx, W, ldw, n_vec, alpha, (T)c->J, half_k2, a[0], a[1], a[2], b[0],
                        b[1], b[2], kin, alpha_d, (C2*)ye);
     LAUNCH_CHECK();
@@ -345,7 +452,7 @@ void mf_prepare(chfsi_ctx* c) {
   for (int q = 0; q < n; ++q)
     for (int r = 0; r < n; ++r) tab[n * n + q * n + r] = Dlag[(size_t)r * n + q];
   for (int q = 0; q < n; ++q) tab[2 * n * n + q] = c->ref.wq[q];
-  // even-odd tables of B (nodes -> points), B^T, Dq (G = Dq U) and Dq^T, each as
+  // even-odd tables of B (nodes -> points), B^T, Dq (G = Dq U), Dq^T and K, each as
   // out[o] = sum_i M[i][o] in[i]
   const int h = n / 2, es = 2 * h * h + 2 * h + 1;
   auto Bm = [&](int i, int o) { return tab[i * n + o]; };
@@ -375,6 +482,26 @@ void mf_prepare(chfsi_ctx* c) {
   eo([&](int i, int o) { return Bm(o, i); }, false);
   eo([&](int i, int o) { return Dm(o, i); }, true);
   eo([&](int i, int o) { return Dm(i, o); }, true);
+  // K = Dq^T diag(w) Dq (centrosymmetric, for a symmetric rule), summed in extended
+  // precision; the closing entry of each sum over a constant's image is re-formed
+  // so that K maps constants to zero as Dq does
+  const int k0 = (int)tab.size();
+  eo([&](int i, int o) {
+    long double k = 0.0;
+    for (int q = 0; q < n; ++q) k += (long double)c->ref.wq[q] * Dm(q, i) * Dm(q, o);
+    return (double)k;
+  }, false);
+  for (int o = 0; o < h; ++o) {
+    long double sum = 0.0;                 // 2 sum_i A[i][o] + M[h][o] = 0
+    for (int i = 0; i < h - (n % 2 == 0); ++i) sum += tab[k0 + i * h + o];
+    if (n % 2) tab[k0 + 2 * h * h + o] = (double)(-2.0L * sum);
+    else tab[k0 + (h - 1) * h + o] = (double)-sum;
+  }
+  if (n % 2) {
+    long double sum = 0.0;                 // 2 sum_i M[i][h] + M[h][h] = 0
+    for (int i = 0; i < h; ++i) sum += tab[k0 + 2 * h * h + h + i];
+    tab[k0 + 2 * h * h + 2 * h] = (double)(-2.0L * sum);
+  }
   std::vector<float> tab32(tab.begin(), tab.end());
   // The FP32 tables keep identities of the exact ones, so that rounding them does
   // not perturb every cell the same way: the interpolation reproduces constants
@@ -436,14 +563,19 @@ void mf_prepare(chfsi_ctx* c) {
       tab32[db0 + 2 * h * h + 2 * h] = 0.0f;
     }
   }
-  // FP32 kinetic weights per point and direction: (2/h_d)^2 / 2 * J w_x w_y w_z
-  const int n3 = n * n * n;
+  // FP32 kinetic weights per direction, point i on the line and line l:
+  // (2/h_d)^2 / 2 * J w_x w_y w_z
+  const int n2 = n * n, n3 = n2 * n;
   std::vector<float> kin32(3 * (size_t)n3);
   for (int d = 0; d < 3; ++d) {
     const double sd = 2.0 / c->h[d];
-    for (int q = 0; q < n3; ++q)
-      kin32[(size_t)d * n3 + q] =
-          (float)(0.5 * sd * sd * c->J * c->ref.wq[q % n] * c->ref.wq[(q / n) % n] * c->ref.wq[q / (n * n)]);
+    for (int i = 0; i < n; ++i)
+      for (int l = 0; l < n2; ++l) {
+        const int a = l % n, b = l / n;      // the other two indices, in the order x, y, z
+        const int x = d == 0 ? i : a, y = d == 0 ? a : d == 1 ? i : b, z = d == 2 ? i : b;
+        kin32[(size_t)d * n3 + i * n2 + l] =
+            (float)(0.5 * sd * sd * c->J * c->ref.wq[x] * c->ref.wq[y] * c->ref.wq[z]);
+      }
   }
   c->mf_tab.upload(tab.data(), tab.size(), c->stream);
   c->mf_tab32.upload(tab32.data(), tab32.size(), c->stream);
