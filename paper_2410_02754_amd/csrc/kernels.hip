@@ -18,6 +18,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "internal.h"
 #include "mfma.h"
@@ -144,7 +145,6 @@ __device__ __forceinline__ void nl_contract_wave(const NlContractArgs<T>& g, int
   const int b = cb0 + sub * part, e = min(ce0, b + part);                // b >= e: an empty part
   const int npj = g.atom_npj[a];
   const int chi = PACK ? (il & 7) : il;   // projector of this lane's A row
-  const bool rv = chi < npj;              // ... and whether it is in use
   int col[NCB];
   bool cv[NCB];
 #pragma unroll
@@ -158,25 +158,46 @@ __device__ __forceinline__ void nl_contract_wave(const NlContractArgs<T>& g, int
   for (int sp = 0; sp < 2; ++sp)
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) cr[sp][cb] = ci[sp][cb] = V4{0, 0, 0, 0};
-  for (int j0 = b; j0 < e; j0 += 4 * U) {
+  // Entry 4 u + kl of a batch is this lane's k index of step u.  All loads of a batch
+  // are issued before its first use and without branches: the node numbers were
+  // fetched with the batch before, unused rows (chi >= npj) and columns read in
+  // bounds and are never stored.  Only the last, partial batch is masked (TAIL: its
+  // missing entries repeat the last one with both factors zeroed).
+  const int chi_c = min(chi, max_pj - 1);
+  int nd[U];
+  auto nodes = [&](int j0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) nd[u] = sup_node[min(j0 + 4 * u + kl, e - 1)];
+  };
+  auto batch = [&](int j0, auto tail) {
+    constexpr bool TAIL = decltype(tail)::value;
     CT pv[U];
     double2 xv[U][2][NCB];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int j = j0 + 4 * u + kl;      // entry of this lane's k index
-      const bool jv = j < e;
-      const int64_t nd = sup_node[jv ? j : b];
-      pv[u] = (jv && rv) ? proj[(size_t)j * max_pj + chi] : CT{(T)0, (T)0};
+      const int j = TAIL ? min(j0 + 4 * u + kl, e - 1) : j0 + 4 * u + kl;
+      pv[u] = proj[(size_t)j * max_pj + chi_c];
+      const double2* __restrict__ xr = X + 2 * (int64_t)nd[u] * ldx;
 #pragma unroll
       for (int sp = 0; sp < 2; ++sp)
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-          const double2 v = X[(2 * nd + sp) * ldx + col[cb]];
-          xv[u][sp][cb] = (jv && cv[cb]) ? v : double2{0.0, 0.0};
-        }
+        for (int cb = 0; cb < NCB; ++cb) xv[u][sp][cb] = xr[sp * ldx + col[cb]];
     }
+    if (!TAIL) nodes(j0 + 4 * U);
+    __builtin_amdgcn_sched_barrier(0);    // (the scheduler would pair loads and uses to save registers)
 #pragma unroll
     for (int u = 0; u < U; ++u) {
+      if constexpr (TAIL) {
+        const bool jv = j0 + 4 * u + kl < e;
+        pv[u] = CT{jv ? pv[u].x : (T)0, jv ? pv[u].y : (T)0};
+#pragma unroll
+        for (int sp = 0; sp < 2; ++sp)
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) {
+            xv[u][sp][cb].x = jv ? xv[u][sp][cb].x : 0.0;
+            xv[u][sp][cb].y = jv ? xv[u][sp][cb].y : 0.0;
+          }
+      }
       if constexpr (PACK) {
         const T av = il < 8 ? pv[u].x : pv[u].y;
 #pragma unroll
@@ -200,6 +221,12 @@ __device__ __forceinline__ void nl_contract_wave(const NlContractArgs<T>& g, int
           }
       }
     }
+  };
+  if (b < e) {                            // (an empty part stores zeros)
+    nodes(b);
+    int j0 = b;
+    for (; j0 + 4 * U <= e; j0 += 4 * U) batch(j0, std::false_type{});
+    if (j0 < e) batch(j0, std::true_type{});
   }
   CT* out = g.partial + ((size_t)ch * g.nsub + sub) * 2 * max_pj * n_vec;
   if constexpr (PACK) {
