@@ -48,6 +48,31 @@ static void check_block(const chfsi_ctx* c, const void* p, int64_t ld, int n_vec
   (void)c;
 }
 
+// Uniform parts of the cell operator at this k, kept on the device with the k-point:
+//   U0 = kinetic + |k|^2/2 mass;  S = -(C - C^T)/2 with C = sum_d k_d C_d
+// (the k-gradient term -i C of eqn:FEHloc, skew-symmetrised per cell; the
+// symmetric part of C sums to zero over the periodic mesh)
+static void uniform_parts(chfsi_ctx* c, KPoint& kp) {
+  if (kp.U0.n != 0) return;
+  const int N = c->nloc;
+  const double k2 = kp.k[0] * kp.k[0] + kp.k[1] * kp.k[1] + kp.k[2] * kp.k[2];
+  std::vector<double> U0((size_t)N * N), S((size_t)N * N, 0.0);
+  for (size_t t = 0; t < U0.size(); ++t) U0[t] = c->Kin[t] + 0.5 * k2 * c->Mcons[t];
+  if (!kp.gamma)
+    for (int i = 0; i < N; ++i)
+      for (int j = 0; j < N; ++j) {
+        double cij = 0.0, cji = 0.0;
+        for (int d = 0; d < 3; ++d) {
+          cij += kp.k[d] * c->Cgrad[d][(size_t)i * N + j];
+          cji += kp.k[d] * c->Cgrad[d][(size_t)j * N + i];
+        }
+        S[(size_t)i * N + j] = -0.5 * (cij - cji);
+      }
+  kp.S.upload(S.data(), S.size(), c->stream);
+  kp.U0.upload(U0.data(), U0.size(), c->stream);
+  CHFSI_HIP(hipStreamSynchronize(c->stream));   // the host arrays end here
+}
+
 static void require_operator(const chfsi_ctx* c) {
   CHFSI_CHECK(c->have_local, CHFSI_ESTATE, "chfsi_set_local has not been called");
 }
@@ -181,44 +206,25 @@ int chfsi_set_local(chfsi_ctx* c, const double* V, const double* B) {
   if (!c) return CHFSI_EINVAL;
   API_BEGIN(c)
   CHFSI_CHECK(V && B, CHFSI_EINVAL, "veff_d and bxc_d must be non-NULL");
-  CHFSI_CHECK(check_finite(c, V, (int64_t)c->n_cells * c->nq3), CHFSI_ENONFINITE, "veff has NaN/Inf");
-  CHFSI_CHECK(check_finite(c, B, (int64_t)c->n_cells * c->nq3 * 3), CHFSI_ENONFINITE, "bxc has NaN/Inf");
+  const int64_t np = (int64_t)c->n_cells * c->nq3;
+  const int bad = check_finite2(c, V, np, B, 3 * np);
+  CHFSI_CHECK(!(bad & 1), CHFSI_ENONFINITE, "veff has NaN/Inf");
+  CHFSI_CHECK(!(bad & 2), CHFSI_ENONFINITE, "bxc has NaN/Inf");
   ++c->gen;
   if (c->form == CHFSI_FORM_MATRIX_FREE) {
     mf_set_local(c, V, B);
     c->have_local = true;
     return CHFSI_OK;
   }
-  const int N = c->nloc;
   for (auto* kp : c->kp) {
-    // uniform parts of the cell operator for this k:
-    //   U0 = kinetic + |k|^2/2 mass;  S = -(C - C^T)/2 with C = sum_d k_d C_d
-    // (the k-gradient term -i C of eqn:FEHloc, skew-symmetrised per cell; the
-    // symmetric part of C sums to zero over the periodic mesh)
-    const double k2 = kp->k[0] * kp->k[0] + kp->k[1] * kp->k[1] + kp->k[2] * kp->k[2];
-    std::vector<double> U0((size_t)N * N), S((size_t)N * N, 0.0);
-    for (size_t t = 0; t < U0.size(); ++t) U0[t] = c->Kin[t] + 0.5 * k2 * c->Mcons[t];
-    if (!kp->gamma)
-      for (int i = 0; i < N; ++i)
-        for (int j = 0; j < N; ++j) {
-          double cij = 0.0, cji = 0.0;
-          for (int d = 0; d < 3; ++d) {
-            cij += kp->k[d] * c->Cgrad[d][(size_t)i * N + j];
-            cji += kp->k[d] * c->Cgrad[d][(size_t)j * N + i];
-          }
-          S[(size_t)i * N + j] = -0.5 * (cij - cji);
-        }
-    DevBuf<double> dU, dS;
-    dU.upload(U0.data(), U0.size(), c->stream);
-    dS.upload(S.data(), S.size(), c->stream);
-    launch_cell_setup(c, *kp, V, B, dU.ptr, dS.ptr);
-    launch_cell_to_f32(c, *kp);
-    CHFSI_HIP(hipStreamSynchronize(c->stream));
+    uniform_parts(c, *kp);
+    launch_cell_setup(c, *kp, V, B);
   }
   // the matrix-free quadrature data as well (w_q J (V, B) per point, 32 B): the
   // single-column applies of the Lanczos bounds use it instead of streaming the
   // cell operators for one column
   if (mf_supported(c)) mf_set_local(c, V, B);
+  CHFSI_HIP(hipStreamSynchronize(c->stream));
   c->have_local = true;
   API_END(c)
 }

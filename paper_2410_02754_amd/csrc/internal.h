@@ -134,6 +134,7 @@ struct KPoint {
   int nmat;                     // 4 at Gamma (Hp, Hm, Bx, By), 5 with the k-term S
   DevBuf<double> cell64;        // tiled cell operators, FP64
   DevBuf<float> cell32;         // FP32 copy
+  DevBuf<double> U0, S;         // uniform parts of the cell operator at this k (built by the first set_local)
   NonlocalK nl;
 };
 
@@ -253,9 +254,7 @@ void lower_inverse(const std::vector<cplx>& L, int n, std::vector<cplx>& Linv);
 void hermitian_eig(const std::vector<cplx>& A, int n, std::vector<double>& w, std::vector<cplx>& V);
 
 // device launchers (kernels.hip)
-void launch_cell_setup(chfsi_ctx* c, KPoint& kp, const double* V, const double* B,
-                       const double* U0, const double* S);
-void launch_cell_to_f32(chfsi_ctx* c, KPoint& kp);
+void launch_cell_setup(chfsi_ctx* c, KPoint& kp, const double* V, const double* B);
 // W += alpha sum_e R_e^T H_e R_e X by colours; or, ye non-null, the products H_e R_e X
 // of all cells to ye[cell][local node][spin][n_vec] (the precision's complex type)
 void launch_cell_products(chfsi_ctx* c, KPoint& kp, int prec, const double2* X, int64_t ldx, double2* W,
@@ -265,7 +264,8 @@ int64_t cell_items_per_cell(const chfsi_ctx* c, int n_vec);
 int64_t mf_items_per_cell(const chfsi_ctx* c, int n_vec, bool fp64);
 // bytes of ye that an apply of this width uses (0: it runs by colours)
 size_t products_scratch_bytes(const chfsi_ctx* c, int n_vec, bool fp64);
-int check_finite(chfsi_ctx* c, const double* p, int64_t n);
+// bit 0: p holds a NaN or infinity, bit 1: q does (one synchronisation)
+int check_finite2(chfsi_ctx* c, const double* p, int64_t n, const double* q, int64_t m);
 // W <- alpha H_hat X + beta W + gamma X   (W is not read when beta == 0)
 void apply_H(chfsi_ctx* c, KPoint& kp, const double2* X, int64_t ldx, double2* W, int64_t ldw,
              int n_vec, int prec, double alpha, double beta, double gamma);

@@ -1900,25 +1900,29 @@ void launch_fill_random(chfsi_ctx* c, double2* X, int64_t n_rows, int n_vec, int
   LAUNCH_CHECK();
 }
 
-__global__ void zero_int_kernel(int* __restrict__ f) { f[0] = 0; }
+__global__ void zero_int_kernel(int* __restrict__ f) { f[0] = f[1] = 0; }
 
-__global__ void nonfinite_kernel(const double* __restrict__ p, int64_t n, int* __restrict__ flag) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+__global__ void nonfinite_kernel(const double* __restrict__ p, int64_t n, const double* __restrict__ q, int64_t m,
+                                 int* __restrict__ flag) {
+  const int64_t step = (int64_t)gridDim.x * blockDim.x, i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  for (int64_t i = i0; i < n; i += step)
     if (!isfinite(p[i])) flag[0] = 1;
+  for (int64_t i = i0; i < m; i += step)
+    if (!isfinite(q[i])) flag[1] = 1;
 }
 
-int check_finite(chfsi_ctx* c, const double* p, int64_t n) {
+int check_finite2(chfsi_ctx* c, const double* p, int64_t n, const double* q, int64_t m) {
   c->scratch.alloc(1);
   int* flag = reinterpret_cast<int*>(c->scratch.ptr);
   hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, c->stream, flag);
   LAUNCH_CHECK();
-  const int blocks = (int)std::min<int64_t>(cdiv(n, 256), 4096);
-  hipLaunchKernelGGL(nonfinite_kernel, dim3(std::max(blocks, 1)), dim3(256), 0, c->stream, p, n, flag);
+  const int blocks = (int)std::min<int64_t>(cdiv(std::max(n, m), 256), 4096);
+  hipLaunchKernelGGL(nonfinite_kernel, dim3(std::max(blocks, 1)), dim3(256), 0, c->stream, p, n, q, m, flag);
   LAUNCH_CHECK();
-  int h = 0;
-  CHFSI_HIP(hipMemcpyAsync(&h, flag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+  int h[2] = {0, 0};
+  CHFSI_HIP(hipMemcpyAsync(h, flag, sizeof(h), hipMemcpyDeviceToHost, c->stream));
   CHFSI_HIP(hipStreamSynchronize(c->stream));
-  return h ? 0 : 1;
+  return (h[0] ? 1 : 0) | (h[1] ? 2 : 0);
 }
 
 }  // namespace chfsi

@@ -588,10 +588,8 @@ void mf_set_local(chfsi_ctx* c, const double* V, const double* B) {
   const int64_t n_points = (int64_t)c->n_cells * c->nq3;
   c->mf_qd.alloc((size_t)n_points * 4);
   c->mf_qd32.alloc((size_t)n_points * 4);
-  DevBuf<double> w1;
-  w1.upload(c->ref.wq.data(), c->ref.wq.size(), c->stream);
   hipLaunchKernelGGL(mf_qdata_kernel, dim3((unsigned)std::min<int64_t>(cdiv(n_points, 256), 8192)), dim3(256), 0,
-                     c->stream, V, B, w1.ptr, c->J, c->nq, n_points, reinterpret_cast<double4*>(c->mf_qd.ptr),
+                     c->stream, V, B, c->mf_tab.ptr + 2 * c->np1 * c->np1, c->J, c->nq, n_points, reinterpret_cast<double4*>(c->mf_qd.ptr),
                      reinterpret_cast<float4*>(c->mf_qd32.ptr));
   LAUNCH_CHECK();
   CHFSI_HIP(hipStreamSynchronize(c->stream));
