@@ -4,11 +4,13 @@
 // Fields live at the cell quadrature points ([E][nq^3], the order of
 // chfsi_quad_points) or at the global nodes ([M]).  The FE scalar operator
 // A = K_s + kappa^2 M_c (K_s = int grad N_I . grad N_J, M_c = int N_I N_J) has
-// the same cell matrix in every cell of the uniform mesh, so its action is
-// one shared dense cell matrix applied to the gathered nodal values, with a
-// colour-ordered scatter-add (no atomics, bitwise reproducible).  Screened
-// Poisson problems (kappa^2 - lap) u = g are solved in the FE space by
-// conjugate gradients preconditioned with the assembled diagonal of A.
+// the same tensor-product cell matrix in every cell of the uniform mesh, so the
+// assembled operator is a sum of Kronecker products of assembled 1-D matrices, whose
+// rows reach p nodes to either side: its action and its diagonal come from
+// two 1-D row tables, node by node, without assembly.  Screened Poisson problems
+// (kappa^2 - lap) u = g are solved in the FE space by conjugate gradients
+// preconditioned with the diagonal of A.  Sums have a fixed order (bitwise
+// reproducible).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -22,57 +24,274 @@ namespace chfsi {
 namespace {
 constexpr int kFieldRed = 256;      // fixed reduction grid (deterministic order)
 
-// y[I(e, i)] += sum_j A[i][j] x[I(e, j)] for the cells of one colour
-__global__ __launch_bounds__(256) void scal_cell_op_kernel(const double* __restrict__ A,
-                                                           const int32_t* __restrict__ cell_nodes,
-                                                           const int32_t* __restrict__ cells, int nloc,
-                                                           const double* __restrict__ x, double* __restrict__ y) {
-  extern __shared__ double xs[];
-  const int e = cells[blockIdx.x];
-  const int32_t* nd = cell_nodes + (size_t)e * nloc;
-  for (int j = threadIdx.x; j < nloc; j += blockDim.x) xs[j] = x[nd[j]];
+// The mesh and 1-D tables of the scalar kernels.
+struct ScalMesh {
+  int p, np1, nq, nx, ny, nz, Nx, Ny, Nz;
+  const double* B;      // [np1][nq] Lagrange basis at the quadrature points
+  const double* wq;     // [nq] weights
+  const double* rows;   // [2][p][2p + 1]: rows of the assembled 1-D stiffness and mass of the
+                        // nodes a = 0 .. p-1 of a cell, over the nodes -p .. p of the cell's frame
+  double J, sx, sy, sz; // A = J (sx S M M + sy M S M + sz M M S + kappa^2 M M M), s_d = (2/h_d)^2
+};
+
+// Sum of the 256 threads' values, to every thread, in a fixed order.
+__device__ __forceinline__ double block_sum(double v, double* sm) {
+#pragma unroll
+  for (int k = 32; k > 0; k >>= 1) v += __shfl_xor(v, k);
+  __syncthreads();                        // sm is free
+  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int i = threadIdx.x; i < nloc; i += blockDim.x) {
-    const double* Ai = A + (size_t)i * nloc;
-    double s = 0.0;
-    for (int j = 0; j < nloc; ++j) s += Ai[j] * xs[j];
-    y[nd[i]] += s;
+  return (sm[0] + sm[1]) + (sm[2] + sm[3]);
+}
+__device__ __forceinline__ double partial_sum(const double* __restrict__ p, int n, double* sm) {
+  double v = 0.0;
+  for (int i = threadIdx.x; i < n; i += 256) v += p[i];
+  return block_sum(v, sm);
+}
+
+// ---- Conjugate gradients, two kernels per step, scalars on the device.  A step was
+// a fill, a launch per colour, ten vector kernels and three round trips to the host
+// (about 130 us on 4^3 cells, p = 4); these two take 12.4 us.  red: [kCgDots][kFieldRed]
+// partial sums (p.Ap; r.r and r.z of even and odd steps; b.b), then the state: the
+// number of steps when r.r reached the tolerance, or -1.
+constexpr int kCgDots = 6, kCgPq = 0, kCgRr = 1, kCgRz = 3, kCgBb = 5;
+__device__ __forceinline__ const double* cg_dot(const double* red, int k) { return red + k * kFieldRed; }
+// whether a step before has stopped the iteration, the same for the whole workgroup
+__device__ __forceinline__ bool cg_stopped(const double* red, double* sm) {
+  if (threadIdx.x == 0) sm[0] = red[kCgDots * kFieldRed];
+  __syncthreads();
+  return sm[0] >= 0.0;
+}
+
+// 1 / diag(A) at node (ax, ay, az) of a cell's frame (a < p in each direction)
+__device__ __forceinline__ double inv_diag(const ScalMesh& m, double kappa2, int ax, int ay, int az) {
+  const int w = 2 * m.p + 1, c = m.p;     // the diagonal entry of row a is at column p + a
+  const double* S = m.rows;
+  const double* M = m.rows + m.p * w;
+  const double mx = M[ax * w + c + ax], my = M[ay * w + c + ay], mz = M[az * w + c + az];
+  const double s = m.sx * S[ax * w + c + ax] * my * mz + m.sy * mx * S[ay * w + c + ay] * mz +
+                   m.sz * mx * my * S[az * w + c + az] + kappa2 * (mx * my * mz);
+  return 1.0 / (m.J * s);
+}
+
+// r = b, u = 0, z = r / diag(A); partial b.b (= r.r) and r.z
+__global__ __launch_bounds__(256) void cg_start_kernel(const ScalMesh m, double kappa2, int64_t n,
+                                                       const double* __restrict__ b, double* __restrict__ u,
+                                                       double* __restrict__ r, double* __restrict__ z,
+                                                       double* __restrict__ red) {
+  __shared__ double sm[4];
+  double rr = 0.0, rz = 0.0;
+  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const int iyz = (int)(i / m.Nx), ix = (int)(i - (int64_t)iyz * m.Nx);
+    const double ri = b[i], zi = inv_diag(m, kappa2, ix % m.p, (iyz % m.Ny) % m.p, (iyz / m.Ny) % m.p) * ri;
+    u[i] = 0.0;
+    r[i] = ri;
+    z[i] = zi;
+    rr += ri * ri;
+    rz += ri * zi;
+  }
+  rr = block_sum(rr, sm);
+  rz = block_sum(rz, sm);
+  if (threadIdx.x == 0) {
+    red[kCgRr * kFieldRed + blockIdx.x] = rr;
+    red[kCgBb * kFieldRed + blockIdx.x] = rr;
+    red[kCgRz * kFieldRed + blockIdx.x] = rz;
+    if (blockIdx.x == 0) red[kCgDots * kFieldRed] = -1.0;
   }
 }
 
-// b[I(e, i)] += sum_q N[i][q] wJ[q] g[e][q] for the cells of one colour
-__global__ __launch_bounds__(256) void scal_project_kernel(const double* __restrict__ Nt,
-                                                           const double* __restrict__ wJ,
-                                                           const int32_t* __restrict__ cell_nodes,
-                                                           const int32_t* __restrict__ cells, int nloc, int nq3,
-                                                           const double* __restrict__ g, double* __restrict__ b) {
-  extern __shared__ double gs[];
-  const int e = cells[blockIdx.x];
-  for (int q = threadIdx.x; q < nq3; q += blockDim.x) gs[q] = wJ[q] * g[(size_t)e * nq3 + q];
-  __syncthreads();
-  const int32_t* nd = cell_nodes + (size_t)e * nloc;
-  for (int i = threadIdx.x; i < nloc; i += blockDim.x) {
-    const double* Ni = Nt + (size_t)i * nq3;
-    double s = 0.0;
-    for (int q = 0; q < nq3; ++q) s += Ni[q] * gs[q];
-    b[nd[i]] += s;
+// Step `it`, first half: stops everything once r.r is small enough, else
+// p = z + beta p (into the other buffer), q = A p, partial p.q.  A workgroup takes the
+// nodes owned by a cell (local index < p in each direction): the frame of
+// (2p + 1)^3 nodes around them is read into LDS and contracted with the row tables
+// along z, y and x; the mass and stiffness parts that the other directions need go
+// along, scaled at the end.
+__global__ __launch_bounds__(256) void cg_apply_kernel(const ScalMesh m, double kappa2, int n_cells, int n_part,
+                                                       int it, double tol, const double* __restrict__ z,
+                                                       const double* __restrict__ p_old, double* __restrict__ p_new,
+                                                       double* __restrict__ q, double* __restrict__ red) {
+  extern __shared__ double fsm[];
+  __shared__ double sm[4];
+  const int odd = it & 1;
+  if (cg_stopped(red, sm)) return;
+  const double rr = partial_sum(cg_dot(red, kCgRr + odd), n_part, sm);
+  const double bb = partial_sum(cg_dot(red, kCgBb), n_part, sm);
+  if (bb == 0.0 || (it > 0 && sqrt(rr) / sqrt(bb) <= tol)) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) red[kCgDots * kFieldRed] = (double)it;
+    return;
+  }
+  const double beta = it == 0 ? 0.0
+                              : partial_sum(cg_dot(red, kCgRz + odd), n_part, sm) /
+                                    partial_sum(cg_dot(red, kCgRz + 1 - odd), n_part, sm);
+  const int p = m.p, w = 2 * p + 1;
+  double* sR = fsm;                       // [2][p][w] row tables
+  double* sX = sR + 2 * p * w;            // [w][w][w] frame (x fastest), then [2][w (y)][w (x)][p (z)] ...
+  double* sM = sX + w * w * w;            // [p][w][w] mass part along z, then [p][p][w]
+  double* sS = sM + p * w * w;            // stiffness part, likewise
+  for (int t = threadIdx.x; t < 2 * p * w; t += 256) sR[t] = m.rows[t];
+  const double* rS = sR;
+  const double* rM = sR + p * w;
+  double pq = 0.0;
+  for (int e = blockIdx.x; e < n_cells; e += gridDim.x) {
+    const int cx = e % m.nx, cyz = e / m.nx, cy = cyz % m.ny, cz = cyz / m.ny;
+    __syncthreads();                      // the last cell's sX is read
+    for (int t = threadIdx.x; t < w * w * w; t += 256) {
+      const int fx = t % w, fy = (t / w) % w, fz = t / (w * w);
+      int ix = cx * p + fx - p, iy = cy * p + fy - p, iz = cz * p + fz - p;
+      ix = ix < 0 ? ix + m.Nx : ix >= m.Nx ? ix - m.Nx : ix;
+      iy = iy < 0 ? iy + m.Ny : iy >= m.Ny ? iy - m.Ny : iy;
+      iz = iz < 0 ? iz + m.Nz : iz >= m.Nz ? iz - m.Nz : iz;
+      const int64_t I = ix + (int64_t)m.Nx * (iy + (int64_t)m.Ny * iz);
+      const double v = it == 0 ? z[I] : fma(beta, p_old[I], z[I]);
+      sX[t] = v;
+      if (fx >= p && fx < 2 * p && fy >= p && fy < 2 * p && fz >= p && fz < 2 * p) p_new[I] = v;
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < p * w * w; t += 256) {          // along z: M, S
+      const int xy = t % (w * w), a = t / (w * w);
+      double vm = 0.0, vs = 0.0;
+      for (int j = a == 0 ? 0 : p; j < w; ++j) {                  // (rows a > 0 stay in the cell)
+        const double x = sX[xy + w * w * j];
+        vm = fma(rM[a * w + j], x, vm);
+        vs = fma(rS[a * w + j], x, vs);
+      }
+      sM[t] = vm;
+      sS[t] = vs;
+    }
+    __syncthreads();
+    double* tA = sX;                      // [p z][p y][w x]: M M
+    double* tB = sX + p * p * w;          // sy S M + sz M S (+ kappa^2 M M)
+    for (int t = threadIdx.x; t < p * p * w; t += 256) {          // along y
+      const int x = t % w, a = (t / w) % p, c = t / (w * p);
+      double mm = 0.0, sm_ = 0.0, ms = 0.0;
+      for (int j = a == 0 ? 0 : p; j < w; ++j) {
+        const double vm = sM[(c * w + j) * w + x], vs = sS[(c * w + j) * w + x];
+        mm = fma(rM[a * w + j], vm, mm);
+        sm_ = fma(rS[a * w + j], vm, sm_);
+        ms = fma(rM[a * w + j], vs, ms);
+      }
+      tA[t] = mm;
+      tB[t] = m.sy * sm_ + m.sz * ms + kappa2 * mm;
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < p * p * p; t += 256) {          // along x
+      const int a = t % p, bc = t / p;
+      double v = 0.0, vs = 0.0;
+      for (int j = a == 0 ? 0 : p; j < w; ++j) {
+        v = fma(rM[a * w + j], tB[bc * w + j], v);
+        vs = fma(rS[a * w + j], tA[bc * w + j], vs);
+      }
+      const int64_t I = cx * p + a + (int64_t)m.Nx * (cy * p + bc % p + (int64_t)m.Ny * (cz * p + bc / p));
+      const double y = m.J * fma(m.sx, vs, v);
+      q[I] = y;
+      pq = fma(it == 0 ? z[I] : fma(beta, p_old[I], z[I]), y, pq);
+    }
+  }
+  pq = block_sum(pq, sm);
+  if (threadIdx.x == 0) red[kCgPq * kFieldRed + blockIdx.x] = pq;
+}
+
+// Second half: u += alpha p, r -= alpha q, z = r / diag(A); partial r.r, r.z for the next step
+__global__ __launch_bounds__(256) void cg_update_kernel(const ScalMesh m, double kappa2, int64_t n, int n_part,
+                                                        int n_pq, int it, const double* __restrict__ p,
+                                                        const double* __restrict__ q, double* __restrict__ u,
+                                                        double* __restrict__ r, double* __restrict__ z,
+                                                        double* __restrict__ red) {
+  __shared__ double sm[4];
+  if (cg_stopped(red, sm)) return;
+  const int odd = it & 1;
+  const double al = partial_sum(cg_dot(red, kCgRz + odd), n_part, sm) / partial_sum(cg_dot(red, kCgPq), n_pq, sm);
+  double rr = 0.0, rz = 0.0;
+  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const int iyz = (int)(i / m.Nx), ix = (int)(i - (int64_t)iyz * m.Nx);
+    u[i] = fma(al, p[i], u[i]);
+    const double ri = fma(-al, q[i], r[i]);
+    const double zi = inv_diag(m, kappa2, ix % m.p, (iyz % m.Ny) % m.p, (iyz / m.Ny) % m.p) * ri;
+    r[i] = ri;
+    z[i] = zi;
+    rr += ri * ri;
+    rz += ri * zi;
+  }
+  rr = block_sum(rr, sm);
+  rz = block_sum(rz, sm);
+  if (threadIdx.x == 0) {
+    red[(kCgRr + 1 - odd) * kFieldRed + blockIdx.x] = rr;
+    red[(kCgRz + 1 - odd) * kFieldRed + blockIdx.x] = rz;
   }
 }
 
-// out[e][q] = sum_i N[i][q] u[I(e, i)]
-__global__ __launch_bounds__(256) void scal_interp_kernel(const double* __restrict__ Nt,
-                                                          const int32_t* __restrict__ cell_nodes, int nloc, int nq3,
+// One direction of a tensor contraction in LDS: out[.. o ..] = sum_i T(i, o) in[.. i ..]
+// with n_in values in, n_out out along the direction, inner values before it and outer after.
+template <class F>
+__device__ __forceinline__ void contract_dir(const double* in, double* out, int inner, int n_in, int n_out, int outer,
+                                             F T) {
+  for (int t = threadIdx.x; t < inner * n_out * outer; t += 256) {
+    const int i0 = t % inner, o = (t / inner) % n_out, k = t / (inner * n_out);
+    double s = 0.0;
+    for (int i = 0; i < n_in; ++i) s = fma(T(i, o), in[i0 + inner * (i + n_in * k)], s);
+    out[t] = s;
+  }
+  __syncthreads();
+}
+
+// be[e][i] = sum_q N_i(r_q) w_q J g[e][q], the cells' parts of the right-hand side
+__global__ __launch_bounds__(256) void scal_project_kernel(const ScalMesh m, int buf, const double* __restrict__ g,
+                                                           double* __restrict__ be) {
+  extern __shared__ double fsm[];
+  const int nq = m.nq, np = m.np1, nq3 = nq * nq * nq, nloc = np * np * np, e = blockIdx.x;
+  double* sB = fsm;                       // [np1][nq]
+  double* a = sB + np * nq;
+  double* b = a + buf;
+  for (int t = threadIdx.x; t < np * nq; t += 256) sB[t] = m.B[t];
+  for (int t = threadIdx.x; t < nq3; t += 256)
+    a[t] = m.wq[t % nq] * m.wq[(t / nq) % nq] * m.wq[t / (nq * nq)] * m.J * g[(size_t)e * nq3 + t];
+  __syncthreads();
+  const auto T = [&](int q, int i) { return sB[i * nq + q]; };
+  contract_dir(a, b, nq * nq, nq, np, 1, T);
+  contract_dir(b, a, nq, nq, np, np, T);
+  contract_dir(a, b, 1, nq, np, np * np, T);
+  for (int t = threadIdx.x; t < nloc; t += 256) be[(size_t)e * nloc + t] = b[t];
+}
+
+// b[I] = scale times the sum of be over the cells that hold node I (fixed order)
+__global__ __launch_bounds__(256) void scal_gather_kernel(const ScalMesh m, int64_t n, double scale,
+                                                          const double* __restrict__ be, double* __restrict__ b) {
+  const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
+  if (i >= n) return;
+  const int ix = (int)(i % m.Nx), iy = (int)((i / m.Nx) % m.Ny), iz = (int)(i / ((int64_t)m.Nx * m.Ny));
+  const int nloc = m.np1 * m.np1 * m.np1;
+  double s = 0.0;
+  for (int k = 0; k < 8; ++k) {
+    // (k & 1) etc.: the cell that ends at this node instead of the one it lies in
+    int cx = ix / m.p, ax = ix - cx * m.p, cy = iy / m.p, ay = iy - cy * m.p, cz = iz / m.p, az = iz - cz * m.p;
+    if ((k & 1) && ax != 0) continue;
+    if ((k & 2) && ay != 0) continue;
+    if ((k & 4) && az != 0) continue;
+    if (k & 1) ax = m.p, cx = cx == 0 ? m.nx - 1 : cx - 1;
+    if (k & 2) ay = m.p, cy = cy == 0 ? m.ny - 1 : cy - 1;
+    if (k & 4) az = m.p, cz = cz == 0 ? m.nz - 1 : cz - 1;
+    s += be[(size_t)(cx + m.nx * (cy + m.ny * cz)) * nloc + ax + m.np1 * (ay + m.np1 * az)];
+  }
+  b[i] = scale * s;
+}
+
+// out[e][q] = sum_i N_i(r_q) u[I(e, i)]
+__global__ __launch_bounds__(256) void scal_interp_kernel(const ScalMesh m, int buf,
+                                                          const int32_t* __restrict__ cell_nodes,
                                                           const double* __restrict__ u, double* __restrict__ out) {
-  extern __shared__ double us[];
-  const int e = blockIdx.x;
-  const int32_t* nd = cell_nodes + (size_t)e * nloc;
-  for (int i = threadIdx.x; i < nloc; i += blockDim.x) us[i] = u[nd[i]];
+  extern __shared__ double fsm[];
+  const int nq = m.nq, np = m.np1, nq3 = nq * nq * nq, nloc = np * np * np, e = blockIdx.x;
+  double* sB = fsm;
+  double* a = sB + np * nq;
+  double* b = a + buf;
+  for (int t = threadIdx.x; t < np * nq; t += 256) sB[t] = m.B[t];
+  for (int t = threadIdx.x; t < nloc; t += 256) a[t] = u[cell_nodes[(size_t)e * nloc + t]];
   __syncthreads();
-  for (int q = threadIdx.x; q < nq3; q += blockDim.x) {
-    double s = 0.0;
-    for (int i = 0; i < nloc; ++i) s += Nt[(size_t)i * nq3 + q] * us[i];
-    out[(size_t)e * nq3 + q] = s;
-  }
+  const auto T = [&](int i, int q) { return sB[i * nq + q]; };
+  contract_dir(a, b, np * np, np, nq, 1, T);
+  contract_dir(b, a, np, np, nq, nq, T);
+  contract_dir(a, b, 1, np, nq, nq * nq, T);
+  for (int t = threadIdx.x; t < nq3; t += 256) out[(size_t)e * nq3 + t] = b[t];
 }
 
 // partial[g] = sum over this group's strided range of x[i] * y[i] * (w ? w[i % nw] : 1)
@@ -99,12 +318,6 @@ __global__ void axpby_kernel(int64_t n, double a, const double* __restrict__ x, 
                              double* out) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     out[i] = a * x[i] + (y ? b * y[i] : 0.0);
-}
-
-__global__ void mul_kernel(int64_t n, const double* __restrict__ a, const double* __restrict__ x,
-                           double* __restrict__ out) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    out[i] = a[i] * x[i];
 }
 
 __global__ void fill_kernel(int64_t n, double v, double* __restrict__ out) {
@@ -177,18 +390,17 @@ int grid_for(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(cdi
 
 // ---------------------------------------------------------------- host side
 struct FieldOps {
-  DevBuf<double> Nt;       // [nloc][nq3] 3-D interpolation table
+  DevBuf<double> rows;     // row tables of the assembled 1-D stiffness and mass (ScalMesh)
   DevBuf<double> wJ;       // [nq3] w_q J
   DevBuf<double> wJ3;      // [3 nq3] w_q J repeated per vector component
   DevBuf<double> ones;     // [max(M, E nq3)] ones
   DevBuf<double> md;       // [M] lumped mass M_D
   DevBuf<double> gq;       // [E nq3] a field at the quadrature points
-  DevBuf<double> A;        // [nloc][nloc] shared cell matrix of the last kappa^2
-  DevBuf<double> dinv;     // [M] inverse assembled diagonal of A
-  DevBuf<double> red;      // reduction partials
-  DevBuf<double> v[5];     // CG vectors and a nodal right-hand side
+  DevBuf<double> red;      // reduction partials (and the CG's sums and state)
+  DevBuf<double> be;       // [E][nloc] cells' parts of a nodal right-hand side
+  DevBuf<double> v[7];     // u, r, z, p (two), q = A p, b
+  ScalMesh mesh;
   double md_sum = 0.0;
-  double kappa2 = -1.0;
   bool ready = false;
 };
 
@@ -200,14 +412,20 @@ static FieldOps& fops(chfsi_ctx* c) {
   FieldOps& f = *c->fields;
   if (!f.ready) {
     const int n = c->np1, nq = c->nq, nloc = c->nloc, nq3 = c->nq3;
-    std::vector<double> Nt((size_t)nloc * nq3), wJ(nq3);
-    for (int i = 0; i < nloc; ++i) {
-      const int ia[3] = {i % n, (i / n) % n, i / (n * n)};
-      for (int q = 0; q < nq3; ++q) {
-        const int qa[3] = {q % nq, (q / nq) % nq, q / (nq * nq)};
-        Nt[(size_t)i * nq3 + q] =
-            c->ref.B[ia[0] * nq + qa[0]] * c->ref.B[ia[1] * nq + qa[1]] * c->ref.B[ia[2] * nq + qa[2]];
-      }
+    std::vector<double> wJ(nq3);
+    // rows a = 0 .. p-1 of the assembled 1-D matrices over the nodes -p .. p: node 0 is
+    // shared with the cell before (its last row), the others lie inside the cell
+    const int p = c->p, w = 2 * p + 1;
+    std::vector<double> rows((size_t)2 * p * w, 0.0);
+    for (int k = 0; k < 2; ++k) {
+      const std::vector<double>& T = k == 0 ? c->ref.D : c->ref.B;
+      for (int a = 0; a < n; ++a)
+        for (int b = 0; b < n; ++b) {
+          double v = 0.0;
+          for (int q = 0; q < nq; ++q) v += c->ref.wq[q] * T[a * nq + q] * T[b * nq + q];
+          if (a < p) rows[((size_t)k * p + a) * w + p + b] += v;
+          else rows[(size_t)k * p * w + b] += v;      // node p of the cell before = node 0
+        }
     }
     for (int q = 0; q < nq3; ++q)
       wJ[q] = c->ref.wq[q % nq] * c->ref.wq[(q / nq) % nq] * c->ref.wq[q / (nq * nq)] * c->J;
@@ -219,34 +437,27 @@ static FieldOps& fops(chfsi_ctx* c) {
       f.md_sum += md[i];
     }
     const int64_t np = (int64_t)c->n_cells * nq3;
-    f.Nt.upload(Nt.data(), Nt.size(), c->stream);
+    f.rows.upload(rows.data(), rows.size(), c->stream);
+    if (c->ref_b1.n == 0) {
+      c->ref_b1.upload(c->ref.B.data(), c->ref.B.size(), c->stream);
+      c->ref_wq.upload(c->ref.wq.data(), c->ref.wq.size(), c->stream);
+    }
     f.wJ.upload(wJ.data(), wJ.size(), c->stream);
     f.wJ3.upload(wJ3.data(), wJ3.size(), c->stream);
     f.md.upload(md.data(), md.size(), c->stream);
     f.ones.alloc(std::max<int64_t>(c->n_nodes, np));
     fill(c, std::max<int64_t>(c->n_nodes, np), 1.0, f.ones.ptr);
     f.gq.alloc(np);
-    f.red.alloc(kFieldRed);
+    f.red.alloc(kCgDots * kFieldRed + 1);
+    f.be.alloc((size_t)c->n_cells * nloc);
+    f.mesh = ScalMesh{p, n, nq, c->nc[0], c->nc[1], c->nc[2], c->Nd[0], c->Nd[1], c->Nd[2], c->ref_b1.ptr,
+                      c->ref_wq.ptr, f.rows.ptr, c->J, 4.0 / (c->h[0] * c->h[0]), 4.0 / (c->h[1] * c->h[1]),
+                      4.0 / (c->h[2] * c->h[2])};
     for (auto& b : f.v) b.alloc(c->n_nodes);
     CHFSI_HIP(hipStreamSynchronize(c->stream));
     f.ready = true;
   }
   return f;
-}
-
-static void set_kappa(chfsi_ctx* c, FieldOps& f, double kappa2) {
-  if (f.kappa2 == kappa2) return;
-  const size_t nloc = c->nloc;
-  std::vector<double> A(nloc * nloc);
-  for (size_t i = 0; i < A.size(); ++i) A[i] = 2.0 * c->Kin[i] + kappa2 * c->Mcons[i];
-  std::vector<double> d(c->n_nodes, 0.0);
-  for (int e = 0; e < c->n_cells; ++e)
-    for (size_t a = 0; a < nloc; ++a) d[c->cell_nodes_h[(size_t)e * nloc + a]] += A[a * nloc + a];
-  for (auto& x : d) x = 1.0 / x;
-  f.A.upload(A.data(), A.size(), c->stream);
-  f.dinv.upload(d.data(), d.size(), c->stream);
-  CHFSI_HIP(hipStreamSynchronize(c->stream));
-  f.kappa2 = kappa2;
 }
 
 // sum_i x_i y_i (w_{i mod nw}); fixed grid, partials summed on the host in order
@@ -272,75 +483,70 @@ static void fill(chfsi_ctx* c, int64_t n, double v, double* out) {
   LAUNCH_CHECK();
 }
 
-// y = A x (nodal)
-static void scal_apply(chfsi_ctx* c, FieldOps& f, const double* x, double* y) {
-  fill(c, c->n_nodes, 0.0, y);
-  const size_t sh = c->nloc * sizeof(double);
-  for (int k = 0; k < c->n_colours; ++k) {
-    const int n_in = c->colour_off[k + 1] - c->colour_off[k];
-    if (n_in == 0) continue;
-    hipLaunchKernelGGL(scal_cell_op_kernel, dim3(n_in), dim3(256), sh, c->stream, f.A.ptr, c->cell_nodes.ptr,
-                       c->colour_cells.ptr + c->colour_off[k], c->nloc, x, y);
-    LAUNCH_CHECK();
-  }
+static int scal_buf(const chfsi_ctx* c) {        // largest stage of a cell's contractions
+  const int n = std::max(c->np1, c->nq);
+  return n * n * n;
 }
 
-// b = int N_I g (nodal, overwritten)
-static void scal_project(chfsi_ctx* c, FieldOps& f, const double* g, double* b) {
-  fill(c, c->n_nodes, 0.0, b);
-  const size_t sh = c->nq3 * sizeof(double);
-  for (int k = 0; k < c->n_colours; ++k) {
-    const int n_in = c->colour_off[k + 1] - c->colour_off[k];
-    if (n_in == 0) continue;
-    hipLaunchKernelGGL(scal_project_kernel, dim3(n_in), dim3(256), sh, c->stream, f.Nt.ptr, f.wJ.ptr,
-                       c->cell_nodes.ptr, c->colour_cells.ptr + c->colour_off[k], c->nloc, c->nq3, g, b);
-    LAUNCH_CHECK();
-  }
+// b = scale int N_I g (nodal, overwritten)
+static void scal_project(chfsi_ctx* c, FieldOps& f, double scale, const double* g, double* b) {
+  const int buf = scal_buf(c);
+  const size_t sh = (size_t)(c->np1 * c->nq + 2 * buf) * sizeof(double);
+  hipLaunchKernelGGL(scal_project_kernel, dim3(c->n_cells), dim3(256), sh, c->stream, f.mesh, buf, g, f.be.ptr);
+  LAUNCH_CHECK();
+  hipLaunchKernelGGL(scal_gather_kernel, dim3(cdiv(c->n_nodes, 256)), dim3(256), 0, c->stream, f.mesh, c->n_nodes,
+                     scale, f.be.ptr, b);
+  LAUNCH_CHECK();
 }
 
 static void scal_interp(chfsi_ctx* c, FieldOps& f, const double* u, double* out) {
-  hipLaunchKernelGGL(scal_interp_kernel, dim3(c->n_cells), dim3(256), c->nloc * sizeof(double), c->stream,
-                     f.Nt.ptr, c->cell_nodes.ptr, c->nloc, c->nq3, u, out);
+  const int buf = scal_buf(c);
+  const size_t sh = (size_t)(c->np1 * c->nq + 2 * buf) * sizeof(double);
+  hipLaunchKernelGGL(scal_interp_kernel, dim3(c->n_cells), dim3(256), sh, c->stream, f.mesh, buf,
+                     c->cell_nodes.ptr, u, out);
   LAUNCH_CHECK();
 }
 
-// A u = b by CG preconditioned with diag(A)^{-1}; b is v[4]; u returned in v[0].
-// Stops when ||r|| <= tol ||b||.  Returns the iteration count (negative if max_iter hit).
-static int pcg(chfsi_ctx* c, FieldOps& f, double tol, int max_iter, double* rel_out) {
+// A u = b by CG preconditioned with diag(A)^{-1}, A = K_s + kappa2 M_c; b is v[6]; u
+// returned in v[0].  Stops when ||r|| <= tol ||b||.  Returns the iteration count
+// (negative if max_iter hit).  The host looks every kCgBatch steps; the steps issued
+// past the end return at once.
+static int pcg(chfsi_ctx* c, FieldOps& f, double kappa2, double tol, int max_iter, double* rel_out) {
+  constexpr int kCgBatch = 16;
   const int64_t n = c->n_nodes;
-  double *u = f.v[0].ptr, *r = f.v[1].ptr, *z = f.v[2].ptr, *pp = f.v[3].ptr, *b = f.v[4].ptr;
-  double* Ap = z;   // z and A p are not live at the same time
-  fill(c, n, 0.0, u);
-  axpby(c, n, 1.0, b, 0.0, nullptr, r);
-  const double bn = std::sqrt(wdot(c, f, b, b, nullptr, 1, n));
-  if (bn == 0.0) {
-    if (rel_out) *rel_out = 0.0;
-    return 0;
-  }
-  hipLaunchKernelGGL(mul_kernel, dim3(grid_for(n)), dim3(256), 0, c->stream, n, f.dinv.ptr, r, pp);
+  double *u = f.v[0].ptr, *r = f.v[1].ptr, *z = f.v[2].ptr, *q = f.v[5].ptr, *b = f.v[6].ptr;
+  double* pp[2] = {f.v[3].ptr, f.v[4].ptr};
+  const int n_part = (int)std::min<int64_t>(kFieldRed, cdiv(n, 256));
+  const int n_pq = std::min(kFieldRed, c->n_cells);
+  const int p = c->p, w = 2 * p + 1;
+  const size_t sh = (size_t)(2 * p * w + w * w * w + 2 * p * w * w) * sizeof(double);
+  hipLaunchKernelGGL(cg_start_kernel, dim3(n_part), dim3(256), 0, c->stream, f.mesh, kappa2, n, b, u, r, z, f.red.ptr);
   LAUNCH_CHECK();
-  double rz = wdot(c, f, r, pp, nullptr, 1, n);
-  double rel = 1.0;
-  int it = 0;
-  for (; it < max_iter; ++it) {
-    scal_apply(c, f, pp, Ap);
-    const double pAp = wdot(c, f, pp, Ap, nullptr, 1, n);
-    const double al = rz / pAp;
-    axpby(c, n, al, pp, 1.0, u, u);
-    axpby(c, n, -al, Ap, 1.0, r, r);
-    rel = std::sqrt(wdot(c, f, r, r, nullptr, 1, n)) / bn;
-    if (rel <= tol) {
-      ++it;
-      break;
+  std::vector<double> h((size_t)kCgDots * kFieldRed + 1);
+  for (int it = 0;;) {
+    const int end = std::min(max_iter, it + kCgBatch);
+    for (; it < end; ++it) {
+      hipLaunchKernelGGL(cg_apply_kernel, dim3(n_pq), dim3(256), sh, c->stream, f.mesh, kappa2, c->n_cells, n_part,
+                         it, tol, z, pp[1 - (it & 1)], pp[it & 1], q, f.red.ptr);
+      LAUNCH_CHECK();
+      hipLaunchKernelGGL(cg_update_kernel, dim3(n_part), dim3(256), 0, c->stream, f.mesh, kappa2, n, n_part, n_pq, it,
+                         pp[it & 1], q, u, r, z, f.red.ptr);
+      LAUNCH_CHECK();
     }
-    hipLaunchKernelGGL(mul_kernel, dim3(grid_for(n)), dim3(256), 0, c->stream, n, f.dinv.ptr, r, z);
-    LAUNCH_CHECK();
-    const double rz1 = wdot(c, f, r, z, nullptr, 1, n);
-    axpby(c, n, 1.0, z, rz1 / rz, pp, pp);
-    rz = rz1;
+    CHFSI_HIP(hipMemcpyAsync(h.data(), f.red.ptr, h.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    CHFSI_HIP(hipStreamSynchronize(c->stream));
+    const double state = h.back();
+    const int done = state >= 0.0 ? (int)state : it;
+    double rr = 0.0, bb = 0.0;
+    for (int g = 0; g < n_part; ++g) {
+      rr += h[(size_t)(kCgRr + (done & 1)) * kFieldRed + g];
+      bb += h[(size_t)kCgBb * kFieldRed + g];
+    }
+    const double rel = bb == 0.0 ? 0.0 : std::sqrt(rr) / std::sqrt(bb);
+    if (state < 0.0 && it < max_iter) continue;
+    if (rel_out) *rel_out = rel;
+    return state >= 0.0 || rel <= tol ? done : -done;
   }
-  if (rel_out) *rel_out = rel;
-  return rel <= tol ? it : -it;
 }
 
 double field_integral(chfsi_ctx* c, const double* g) {
@@ -362,7 +568,6 @@ double field_inner(chfsi_ctx* c, const double* r1, const double* m1, const doubl
 int screened_poisson(chfsi_ctx* c, double kappa2, double scale, const double* g, double* u_q, double tol,
                      int max_iter, double* rel) {
   FieldOps& f = fops(c);
-  set_kappa(c, f, kappa2);
   const int64_t np = (int64_t)c->n_cells * c->nq3;
   const double vol = c->box[0] * c->box[1] * c->box[2];
   const double* src = g;
@@ -371,14 +576,13 @@ int screened_poisson(chfsi_ctx* c, double kappa2, double scale, const double* g,
     axpby(c, np, 1.0, g, -gbar, f.ones.ptr, f.gq.ptr);          // g - mean(g)
     src = f.gq.ptr;
   }
-  scal_project(c, f, src, f.v[4].ptr);
-  if (scale != 1.0) axpby(c, c->n_nodes, scale, f.v[4].ptr, 0.0, nullptr, f.v[4].ptr);
+  scal_project(c, f, scale, src, f.v[6].ptr);
   if (kappa2 == 0.0) {
     // the right-hand side's roundoff component along the constants (the null space)
-    const double bm = wdot(c, f, f.v[4].ptr, nullptr, nullptr, 1, c->n_nodes) / (double)c->n_nodes;
-    axpby(c, c->n_nodes, 1.0, f.v[4].ptr, -bm, f.ones.ptr, f.v[4].ptr);
+    const double bm = wdot(c, f, f.v[6].ptr, nullptr, nullptr, 1, c->n_nodes) / (double)c->n_nodes;
+    axpby(c, c->n_nodes, 1.0, f.v[6].ptr, -bm, f.ones.ptr, f.v[6].ptr);
   }
-  const int it = pcg(c, f, tol, max_iter, rel);
+  const int it = pcg(c, f, kappa2, tol, max_iter, rel);
   if (kappa2 == 0.0) {
     const double mean = wdot(c, f, f.v[0].ptr, f.md.ptr, nullptr, 1, c->n_nodes) / f.md_sum;
     axpby(c, c->n_nodes, 1.0, f.v[0].ptr, -mean, f.ones.ptr, f.v[0].ptr);
