@@ -2,9 +2,13 @@
 // a Monkhorst-Pack grid and independent systems of uneven size; the
 // eigenproblems of different k are independent, Sec. III.B).
 //
-// Per recurrence step the projector terms and the initialisation run per task;
-// the cell products of all tasks run as one persistent launch per colour phase
-// (and per tile shape / k-term variant) walking a static item list.  Column
+// Tasks whose applies run by cells (see products_scratch_bytes) go together: per
+// recurrence step one launch each for the projector contraction, the coefficients,
+// the cell products (per tile shape / k-term variant; matrix-free tasks one each) and
+// the gather with the recurrence terms.  32 systems of 3^3 cells, p = 4, 32 columns,
+// degree 10 were a graph of 1550 nodes and are one of 41: 18.3 -> 2.23 ms.  For
+// the larger tasks the projector terms and the initialisation run per task and the
+// cell products of all as one persistent launch per colour phase.  Column
 // tile widths are chosen per task by timing the candidates on the task's own
 // data.  The whole degree-m filter of all tasks is captured into a hipGraph once
 // and replayed for any bounds: every recurrence coefficient is read from device
@@ -13,6 +17,7 @@
 #include <chrono>
 #include <cmath>
 #include <map>
+#include <numeric>
 #include <tuple>
 
 #include "internal.h"
@@ -22,6 +27,7 @@ using namespace chfsi;
 struct BatchGroup {
   int cb;
   bool has_s;
+  bool small;                                // all cells in one phase, into the tasks' ye
   int chunk;                                 // tasks [chunk * kBatchLaunchTasks, +kBatchLaunchTasks)
   BatchTaskArgs args;                        // their descriptors, by value for the launch
   std::vector<int> n_items;                  // per colour
@@ -47,7 +53,11 @@ struct chfsi_batch {
   } alpha_tab, bg_tab;                       // views into coef_tab
   double* coef_h = nullptr;                  // pinned host copy of coef_tab
   hipEvent_t coef_done = nullptr;            // the last upload of coef_h has been read
-  DevBuf<unsigned char> nl_scratch;          // nonlocal partial sums, shared by the tasks (one stream)
+  DevBuf<unsigned char> nl_scratch;          // nonlocal partial sums, shared by the large tasks (one stream)
+  std::vector<char> small;                   // per task
+  std::unique_ptr<BatchSmall> smalls;
+  DevBuf<unsigned char> small_mem;           // their ye and nonlocal scratch, task after task
+  std::vector<unsigned char*> ye;            // per task, null for large ones
   std::vector<uint64_t> gen;                 // context generations at creation
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -76,11 +86,13 @@ static void build_items(chfsi_batch* b, BatchGroup& g) {
     std::vector<std::vector<int4>> per_xcd(8);
     int unit = 0;
     for (int t = t0; t < t1; ++t) {
-      if (b->cb[t] != g.cb || (!b->kps[t]->gamma) != g.has_s) continue;
+      if (b->cb[t] != g.cb || (!b->kps[t]->gamma) != g.has_s || (bool)b->small[t] != g.small) continue;
       chfsi_ctx* c = b->tasks[t].ctx;
-      if (col >= c->n_colours) continue;
-      std::vector<int32_t> cells(c->colour_off[col + 1] - c->colour_off[col]);
-      if (!cells.empty())
+      if (col >= (g.small ? 1 : c->n_colours)) continue;
+      std::vector<int32_t> cells(g.small ? c->n_cells : c->colour_off[col + 1] - c->colour_off[col]);
+      if (g.small)
+        std::iota(cells.begin(), cells.end(), 0);
+      else if (!cells.empty())
         CHFSI_HIP(hipMemcpy(cells.data(), c->colour_cells.ptr + c->colour_off[col], cells.size() * sizeof(int32_t),
                             hipMemcpyDeviceToHost));
       const int nrt = (c->nrb + 1) / 2;
@@ -123,7 +135,10 @@ static void run_filter(chfsi_batch* b) {
     const int prec = (b->prec == CHFSI_PREC_MIXED && k < m) ? CHFSI_PREC_MIXED : CHFSI_PREC_FP64;
     const double* al_k = b->alpha_tab.ptr + (size_t)(k - 1) * nt;
     const double* bg_k = b->bg_tab.ptr + (size_t)(k - 1) * nt * 2;
+    const bool fp64 = prec == CHFSI_PREC_FP64;
+    if (b->smalls) b->smalls->nonlocal(b->stream, fp64, src, al_k);
     for (int t = 0; t < nt; ++t) {
+      if (b->small[t]) continue;
       const auto& tk = b->tasks[t];
       double2* buf[2] = {(double2*)tk.X_d, (double2*)tk.work_d};
       const int64_t ld[2] = {tk.ldx, tk.ldw};
@@ -139,18 +154,25 @@ static void run_filter(chfsi_batch* b) {
                           g->n_items[col], al_k + g->chunk * kBatchLaunchTasks, src,
                           g->grid[prec == CHFSI_PREC_FP64]);
       }
-    // matrix-free tasks: their own colour launches, alpha read from the table
+    // matrix-free tasks: their own launches, by colours with alpha read from the table
+    // or all cells into ye
     for (int t = 0; t < nt; ++t) {
       if (b->cb[t] != 0) continue;
       const auto& tk = b->tasks[t];
       double2* buf[2] = {(double2*)tk.X_d, (double2*)tk.work_d};
       const int64_t ld[2] = {tk.ldx, tk.ldw};
-      launch_mf_products(tk.ctx, *b->kps[t], prec, buf[src], ld[src], buf[src ^ 1], ld[src ^ 1], tk.n_vec, 0.0,
-                         al_k + t);
+      if (b->small[t])
+        launch_mf_products(tk.ctx, *b->kps[t], prec, buf[src], ld[src], nullptr, 0, tk.n_vec, 1.0, nullptr, b->ye[t]);
+      else
+        launch_mf_products(tk.ctx, *b->kps[t], prec, buf[src], ld[src], buf[src ^ 1], ld[src ^ 1], tk.n_vec, 0.0,
+                           al_k + t);
     }
+    if (b->smalls) b->smalls->init(b->stream, fp64, src, k == 1, al_k, bg_k);
   }
+  if ((m & 1) && b->smalls) b->smalls->copy_back(b->stream);
   if (m & 1)
     for (int t = 0; t < nt; ++t) {
+      if (b->small[t]) continue;
       const auto& tk = b->tasks[t];
       launch_copy_rows(tk.ctx, (double2*)tk.X_d, tk.ldx, (const double2*)tk.work_d, tk.ldw, 2 * tk.ctx->n_nodes,
                        tk.n_vec);
@@ -245,16 +267,51 @@ int chfsi_batch_create(int n_tasks, const chfsi_batch_task* tasks, int degree, i
         }
       }
     }
-    std::map<std::tuple<int, int, bool>, int> gid;
+    // small tasks: their applies run by cells in the batch's precision, and their
+    // scratch (ye and the nonlocal sums, 256-byte aligned) fits kSmallBytes together
+    constexpr size_t kSmallBytes = (size_t)4 << 30;
+    b->small.assign(n_tasks, 0);
+    b->ye.assign(n_tasks, nullptr);
+    size_t small_bytes = 0;
+    std::vector<size_t> ye_off(n_tasks, 0), nl_off(n_tasks, 0);
+    const auto up = [](size_t n) { return (n + 255) / 256 * 256; };
+    for (int t = 0; t < n_tasks; ++t) {
+      const auto& tk = tasks[t];
+      // (ye holds either precision: the last step is FP64)
+      const size_t ye = up(products_scratch_bytes(tk.ctx, tk.n_vec, true));
+      const size_t nl = up(nonlocal_scratch_bytes(*b->kps[t], tk.n_vec));
+      if (ye == 0 || small_bytes + ye + nl > kSmallBytes) continue;
+      b->small[t] = 1;
+      ye_off[t] = small_bytes;
+      nl_off[t] = small_bytes + ye;
+      small_bytes += ye + nl;
+    }
+    if (!b->small_mem.try_alloc(small_bytes)) {      // each task by itself then
+      b->small.assign(n_tasks, 0);
+      small_bytes = 0;
+    }
+    if (small_bytes > 0) {
+      std::vector<SmallTask> st;
+      for (int t = 0; t < n_tasks; ++t) {
+        if (!b->small[t]) continue;
+        const auto& tk = tasks[t];
+        b->ye[t] = b->small_mem.ptr + ye_off[t];
+        st.push_back(SmallTask{tk.ctx, b->kps[t], {(double2*)tk.X_d, (double2*)tk.work_d}, {tk.ldx, tk.ldw},
+                               tk.n_vec, t, b->ye[t], b->small_mem.ptr + nl_off[t]});
+      }
+      b->smalls.reset(new BatchSmall(st, b->stream));
+    }
+    std::map<std::tuple<int, int, bool, bool>, int> gid;
     for (int t = 0; t < n_tasks; ++t) {
       if (b->cb[t] == 0) continue;
-      auto key = std::make_tuple(t / kBatchLaunchTasks, b->cb[t], !b->kps[t]->gamma);
+      auto key = std::make_tuple(t / kBatchLaunchTasks, b->cb[t], !b->kps[t]->gamma, (bool)b->small[t]);
       if (!gid.count(key)) {
         gid[key] = (int)b->groups.size();
         auto* g = new BatchGroup();
         g->chunk = std::get<0>(key);
         g->cb = std::get<1>(key);
         g->has_s = std::get<2>(key);
+        g->small = std::get<3>(key);
         b->groups.push_back(g);
       }
     }
@@ -278,7 +335,8 @@ int chfsi_batch_create(int n_tasks, const chfsi_batch_task* tasks, int degree, i
       dt[t].nkb = c->nkb;
       dt[t].nmat = kp.nmat;
       dt[t].pad = 0;
-      nl_bytes = std::max(nl_bytes, nonlocal_scratch_bytes(kp, tk.n_vec));
+      dt[t].ye = b->ye[t];
+      if (!b->small[t]) nl_bytes = std::max(nl_bytes, nonlocal_scratch_bytes(kp, tk.n_vec));
       b->gen.push_back(c->gen);
     }
     for (auto* g : b->groups) {

@@ -65,6 +65,16 @@ struct DevBuf {
     }
     n = count;
   }
+  // as alloc; false where the memory is not there (for buffers that a call can do without)
+  bool try_alloc(size_t count) {
+    try {
+      alloc(count);
+      return true;
+    } catch (const Error&) {
+      (void)hipGetLastError();
+      return false;
+    }
+  }
   void upload(const T* h, size_t count, hipStream_t s) {
     alloc(count);
     CHFSI_HIP(hipMemcpyAsync(ptr, h, count * sizeof(T), hipMemcpyHostToDevice, s));
@@ -147,6 +157,7 @@ struct BatchTaskDev {
   int64_t ld[2];
   int n_vec, nloc, nrb, nkb, nmat;
   int pad;
+  void* ye;                     // products of all cells go here (small tasks), or null
 };
 // Task descriptors of one persistent launch, passed by value in the kernel
 // arguments (pointers read from the argument segment compile to global, not
@@ -351,6 +362,29 @@ void noalloc_scratch_init();
 void apply_nonlocal_init(chfsi_ctx* c, KPoint& kp, const double2* X, int64_t ldx, double2* W, int64_t ldw,
                          int n_vec, int prec, double alpha, double beta, double gamma, const double* alpha_d,
                          const double* bg_d, void* scratch);
+// The small tasks of a batch (those whose applies run by cells): one launch per stage
+// for all of them.  The cell products of each step go to the tasks' ye between
+// nonlocal() and init().
+struct SmallTask {
+  chfsi_ctx* ctx;
+  KPoint* kp;
+  double2* buf[2];
+  int64_t ld[2];
+  int n_vec, index;
+  void *ye, *nl_scratch;        // owned by the batch
+};
+class BatchSmall {
+ public:
+  BatchSmall(const std::vector<SmallTask>& tasks, hipStream_t stream);
+  ~BatchSmall();
+  // src: which buffer holds Y_{k-1}; alpha, bg: the step's coefficient tables
+  void nonlocal(hipStream_t s, bool fp64, int src, const double* alpha);
+  void init(hipStream_t s, bool fp64, int src, bool first, const double* alpha, const double* bg);
+  void copy_back(hipStream_t s);          // buffer 1 -> buffer 0
+ private:
+  struct Impl;
+  std::unique_ptr<Impl> impl_;
+};
 void launch_fill_random(chfsi_ctx* c, double2* X, int64_t n_rows, int n_vec, int64_t ld,
                         uint64_t seed, int64_t row0, int col0, int64_t n_total_cols);
 }  // namespace chfsi

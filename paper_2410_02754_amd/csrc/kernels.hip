@@ -824,8 +824,7 @@ static void* ye_for_call(chfsi_ctx* c, int n_vec, bool fp64) {
   if (c->ye.n < n) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     CHFSI_HIP(hipStreamIsCapturing(c->stream, &st));
-    if (st != hipStreamCaptureStatusNone) return nullptr;
-    c->ye.alloc(n);
+    if (st != hipStreamCaptureStatusNone || !c->ye.try_alloc(n)) return nullptr;
   }
   return c->ye.ptr;
 }
@@ -919,6 +918,237 @@ void apply_nonlocal_init(chfsi_ctx* c, KPoint& kp, const double2* X, int64_t ldx
     nonlocal_init_t<float>(c, kp, kp.nl.proj32.ptr, X, ldx, W, ldw, n_vec, alpha, beta, gamma, alpha_d, bg_d, scratch);
   else
     nonlocal_init_t<double>(c, kp, kp.nl.proj.ptr, X, ldx, W, ldw, n_vec, alpha, beta, gamma, alpha_d, bg_d, scratch);
+}
+
+// ---- Small tasks of a batch: one launch per stage of an apply for all of them.  Per
+// task the same waves and blocks as in an apply by cells (bit for bit), with the
+// task in blockIdx.y and its arguments in device memory.
+template <class T>
+struct BatchNl {
+  NlContractArgs<T> c;
+  NlCoefArgs<T> f;
+  InitArgs<T> i;
+  double2* buf[2];
+  int64_t ld[2];
+  int64_t rows;
+  int index;                              // in the recurrence coefficient tables
+  int has_nl, realp, pack, n_atoms, coef_tiles;
+};
+constexpr int kBatchCopy = 4096;          // elements per workgroup of the copy
+
+// A pointer read from memory, as one to device memory (else its accesses are flat).
+template <class P>
+__device__ __forceinline__ P* global_ptr(P* p) {
+  return (P*)(__attribute__((address_space(1))) P*)p;
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void batch_contract_kernel(const BatchNl<T>* __restrict__ tasks,
+                                                             const int2* __restrict__ map, int src) {
+  const int2 w = map[blockIdx.x];
+  const BatchNl<T>& t = tasks[w.x];
+  const int wid = __builtin_amdgcn_readfirstlane(w.y * 4 + (int)(threadIdx.x >> 6));
+  if (wid >= t.c.n_work) return;      // no barrier in this kernel
+  NlContractArgs<T> g = t.c;
+  g.proj = global_ptr(g.proj);
+  g.sup_node = global_ptr(g.sup_node);
+  g.chunk_atom = global_ptr(g.chunk_atom);
+  g.chunk_begin = global_ptr(g.chunk_begin);
+  g.chunk_end = global_ptr(g.chunk_end);
+  g.chunk_order = global_ptr(g.chunk_order);
+  g.atom_npj = global_ptr(g.atom_npj);
+  g.partial = global_ptr(g.partial);
+  g.X = global_ptr(t.buf[src]);
+  g.ldx = t.ld[src];
+  if (t.realp) nl_contract_wave<T, true, false>(g, wid);
+  else if (t.pack) nl_contract_wave<T, false, true>(g, wid);
+  else nl_contract_wave<T, false, false>(g, wid);
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void batch_coef_kernel(const BatchNl<T>* __restrict__ tasks,
+                                                         const int2* __restrict__ map,
+                                                         const double* __restrict__ alpha) {
+  __shared__ NlCoefSmem<T> sm;
+  const int2 w = map[blockIdx.x];
+  const BatchNl<T>& t = tasks[w.x];
+  NlCoefArgs<T> g = t.f;
+  g.partial = global_ptr(g.partial);
+  g.atom_chunk0 = global_ptr(g.atom_chunk0);
+  g.atom_npj = global_ptr(g.atom_npj);
+  g.delta = global_ptr(g.delta);
+  g.Cp = global_ptr(g.Cp);
+  g.alpha_d = alpha + t.index;
+  nl_coef_block<T>(sm, g, w.y / t.coef_tiles, w.y % t.coef_tiles);
+}
+
+template <class T, int FL>
+__global__ __launch_bounds__(256) void batch_init_kernel(const BatchNl<T>* __restrict__ tasks,
+                                                         const int2* __restrict__ map, int src,
+                                                         const double* __restrict__ alpha,
+                                                         const double* __restrict__ bg) {
+  const int2 w = map[blockIdx.x];
+  const BatchNl<T>& t = tasks[w.x];
+  const int wid = __builtin_amdgcn_readfirstlane(w.y * 4 + (int)(threadIdx.x >> 6));
+  if (wid >= t.i.n_work) return;          // no barrier in this kernel
+  InitArgs<T> g = t.i;
+  g.proj = global_ptr(g.proj);
+  g.run_off = global_ptr(g.run_off);
+  g.pair_atom = global_ptr(g.pair_atom);
+  g.pair_ent = global_ptr(g.pair_ent);
+  g.atom_npj = global_ptr(g.atom_npj);
+  g.Cp = global_ptr(g.Cp);
+  g.ye = global_ptr(g.ye);
+  if (g.msc) g.msc = global_ptr(g.msc);
+  g.X = global_ptr(t.buf[src]);
+  g.ldx = t.ld[src];
+  g.W = global_ptr(t.buf[src ^ 1]);
+  g.ldw = t.ld[src ^ 1];
+  g.Wold = g.W;
+  g.ldo = g.ldw;
+  g.alpha_d = alpha + t.index;
+  g.bg_d = bg + 2 * t.index;
+  if (t.realp) init_nl_wave<T, FL, true, true>(g, wid);
+  else init_nl_wave<T, FL, false, true>(g, wid);
+}
+
+__global__ __launch_bounds__(256) void batch_copy_kernel(const BatchNl<double>* __restrict__ tasks,
+                                                         const int2* __restrict__ map) {
+  const int2 w = map[blockIdx.x];
+  const BatchNl<double>& t = tasks[w.x];
+  double2* d = global_ptr(t.buf[0]);
+  const double2* s = global_ptr(t.buf[1]);
+  const int n_vec = t.i.n_vec;
+  const int64_t i0 = (int64_t)w.y * kBatchCopy, total = t.rows * n_vec;
+  const int64_t i1 = i0 + kBatchCopy < total ? i0 + kBatchCopy : total;
+  for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) {
+    const int64_t r = i / n_vec, n = i - r * n_vec;
+    d[r * t.ld[0] + n] = s[r * t.ld[1] + n];
+  }
+}
+
+// (task, block of the task) of each workgroup of a launch
+struct BatchMap {
+  std::vector<int2> h;
+  DevBuf<int2> d;
+  int n = 0;
+  void add(int task, int64_t blocks) {
+    for (int64_t i = 0; i < blocks; ++i) h.push_back(int2{task, (int)i});
+  }
+  void upload(hipStream_t s) {
+    n = (int)h.size();
+    if (n > 0) d.upload(h.data(), h.size(), s);
+  }
+};
+template <class T>
+struct BatchStage {
+  std::vector<BatchNl<T>> h;
+  DevBuf<BatchNl<T>> d;
+  BatchMap contract, coef, init;
+  void add(const BatchNl<T>& b) {
+    const int t = (int)h.size();
+    h.push_back(b);
+    if (b.has_nl) {
+      contract.add(t, cdiv(b.c.n_work, 4));
+      coef.add(t, (int64_t)b.n_atoms * b.coef_tiles);
+    }
+    init.add(t, cdiv(b.i.n_work, 4));
+  }
+  void upload(hipStream_t s) {
+    d.upload(h.data(), h.size(), s);
+    contract.upload(s);
+    coef.upload(s);
+    init.upload(s);
+  }
+};
+struct BatchSmall::Impl {
+  BatchStage<double> s64;
+  BatchStage<float> s32;
+  BatchMap copy;
+};
+
+template <class T>
+static BatchNl<T> batch_nl(const SmallTask& s, const typename C2<T>::type* proj) {
+  typedef typename C2<T>::type CT;
+  chfsi_ctx* c = s.ctx;
+  NonlocalK& nl = s.kp->nl;
+  BatchNl<T> b{};
+  b.buf[0] = s.buf[0];
+  b.buf[1] = s.buf[1];
+  b.ld[0] = s.ld[0];
+  b.ld[1] = s.ld[1];
+  b.rows = 2 * c->n_nodes;
+  b.index = s.index;
+  b.has_nl = nl.n_atoms != 0 && nl.n_entries != 0;
+  CT* Cp = nullptr;
+  if (b.has_nl) {
+    const int nsub = nl_parts(nl, s.n_vec);
+    Cp = reinterpret_cast<CT*>(s.nl_scratch);
+    CT* partial = Cp + (size_t)nl.n_atoms * 2 * nl.max_pj * s.n_vec;
+    b.c = contract_args<T>(nl, proj, nullptr, 0, s.n_vec, nsub, partial);
+    b.f = NlCoefArgs<T>{partial, nl.atom_chunk0.ptr, nl.atom_npj.ptr, nl.delta.ptr, nl.max_pj, nsub,
+                        s.n_vec, 0,                  s.n_vec,         1.0,          nullptr,   Cp};
+    b.realp = nl.real_proj;
+    b.pack = pack_rows(nl);
+    b.n_atoms = nl.n_atoms;
+    b.coef_tiles = cdiv(s.n_vec, kCoefCols);
+  }
+  b.i = init_args<T>(c, nl, proj, Cp, nullptr, 0, nullptr, 0, nullptr, 0, s.n_vec, 1.0, 1.0);
+  b.i.ye = reinterpret_cast<const CT*>(s.ye);
+  b.i.msc = c->form == CHFSI_FORM_MATRIX_FREE ? c->minv_sqrt.ptr : nullptr;
+  return b;
+}
+
+BatchSmall::BatchSmall(const std::vector<SmallTask>& tasks, hipStream_t stream) : impl_(new Impl) {
+  Impl& m = *impl_;
+  for (size_t t = 0; t < tasks.size(); ++t) {
+    const SmallTask& s = tasks[t];
+    m.s64.add(batch_nl<double>(s, s.kp->nl.proj.ptr));
+    m.s32.add(batch_nl<float>(s, s.kp->nl.proj32.ptr));
+    m.copy.add((int)t, (2 * s.ctx->n_nodes * s.n_vec + kBatchCopy - 1) / kBatchCopy);
+  }
+  m.s64.upload(stream);
+  m.s32.upload(stream);
+  m.copy.upload(stream);
+  CHFSI_HIP(hipStreamSynchronize(stream));   // the host arrays have been read
+}
+
+BatchSmall::~BatchSmall() = default;
+
+template <class T>
+static void batch_nonlocal(hipStream_t s, const BatchStage<T>& b, int src, const double* alpha) {
+  if (b.contract.n == 0) return;          // no task has atoms
+  hipLaunchKernelGGL((batch_contract_kernel<T>), dim3(b.contract.n), dim3(256), 0, s, b.d.ptr, b.contract.d.ptr, src);
+  LAUNCH_CHECK();
+  hipLaunchKernelGGL((batch_coef_kernel<T>), dim3(b.coef.n), dim3(256), 0, s, b.d.ptr, b.coef.d.ptr, alpha);
+  LAUNCH_CHECK();
+}
+
+void BatchSmall::nonlocal(hipStream_t s, bool fp64, int src, const double* alpha) {
+  if (fp64) batch_nonlocal(s, impl_->s64, src, alpha);
+  else batch_nonlocal(s, impl_->s32, src, alpha);
+}
+
+template <class T>
+static void batch_init(hipStream_t s, const BatchStage<T>& b, int src, bool first, const double* alpha,
+                       const double* bg) {
+  if (first)
+    hipLaunchKernelGGL((batch_init_kernel<T, kInitGamma>), dim3(b.init.n), dim3(256), 0, s, b.d.ptr, b.init.d.ptr, src,
+                       alpha, bg);
+  else
+    hipLaunchKernelGGL((batch_init_kernel<T, kInitBeta | kInitGamma>), dim3(b.init.n), dim3(256), 0, s, b.d.ptr,
+                       b.init.d.ptr, src, alpha, bg);
+  LAUNCH_CHECK();
+}
+
+void BatchSmall::init(hipStream_t s, bool fp64, int src, bool first, const double* alpha, const double* bg) {
+  if (fp64) batch_init(s, impl_->s64, src, first, alpha, bg);
+  else batch_init(s, impl_->s32, src, first, alpha, bg);
+}
+
+void BatchSmall::copy_back(hipStream_t s) {
+  hipLaunchKernelGGL(batch_copy_kernel, dim3(impl_->copy.n), dim3(256), 0, s, impl_->s64.d.ptr, impl_->copy.d.ptr);
+  LAUNCH_CHECK();
 }
 
 size_t nonlocal_scratch_bytes_min(const KPoint& kp, int n_vec) {
