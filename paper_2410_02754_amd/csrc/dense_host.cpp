@@ -1,15 +1,10 @@
-// Small dense Hermitian linear algebra on the host for the T x T projected
-// problems of the Rayleigh-Ritz step and the Cholesky factor of the Gram
-// matrix (Sec. III.B.2).  T <= a few thousand; O(T^3) textbook algorithms:
-//  - Cholesky S = L L^H (lower, positive real diagonal),
-//  - forward-substitution inverse of a lower-triangular matrix,
-//  - Hermitian eigendecomposition: Householder reduction to a Hermitian
-//    tridiagonal matrix (Golub and Van Loan, Sec. 8.3), a diagonal phase
-//    change that makes it real, then the implicit QL iteration with shifts on
-//    the real tridiagonal (Bowdler, Martin, Reinsch and Wilkinson, 1968),
-//    accumulating the rotations, and back-transformation by blocks of
-//    reflectors in the compact WY form I - Y T Y^H (Schreiber and Van Loan,
-//    1989).
+// Hermitian eigendecomposition on the host for the T x T projected problems of
+// the Rayleigh-Ritz step (Sec. III.B.2), T <= a few thousand: Householder
+// reduction to a Hermitian tridiagonal matrix (Golub and Van Loan, Sec. 8.3), a
+// diagonal phase change that makes it real, then the implicit QL iteration with
+// shifts on the real tridiagonal (Bowdler, Martin, Reinsch and Wilkinson, 1968),
+// accumulating the rotations, and back-transformation by blocks of reflectors in
+// the compact WY form I - Y T Y^H (Schreiber and Van Loan, 1989).
 // All matrices are row-major std::vector<cplx> of size n*n.
 #include <algorithm>
 #include <atomic>
@@ -77,56 +72,6 @@ class Pool {
   std::atomic<bool> stop_{false};
   const std::function<void(int, int)>* f_ = nullptr;
 };
-
-int cholesky_lower(std::vector<cplx>& S, int n) {
-  // in place, left-looking by rows of columns: lower triangle of S becomes L,
-  // upper triangle zeroed; the updates of the rows below column j run in parallel
-  Pool pool((size_t)n * n * n / 3);
-  for (int j = 0; j < n; ++j) {
-    double d = S[(size_t)j * n + j].real();
-    for (int k = 0; k < j; ++k) d -= std::norm(S[(size_t)j * n + k]);
-    if (!(d > 0.0) || !std::isfinite(d)) return j;
-    const double ljj = std::sqrt(d);
-    S[(size_t)j * n + j] = ljj;
-    const int rows = n - j - 1;
-    auto body = [&](int t, int nt) {
-      int lo, hi;
-      Pool::range(rows, t, nt, lo, hi);
-      const cplx* Lj = &S[(size_t)j * n];
-      for (int i = j + 1 + lo; i < j + 1 + hi; ++i) {
-        cplx s = S[(size_t)i * n + j];
-        const cplx* Li = &S[(size_t)i * n];
-        for (int k = 0; k < j; ++k) s -= Li[k] * std::conj(Lj[k]);
-        S[(size_t)i * n + j] = s / ljj;
-      }
-    };
-    if ((size_t)rows * j > 4096) pool.run(body);
-    else body(0, 1);
-  }
-  for (int i = 0; i < n; ++i)
-    for (int j = i + 1; j < n; ++j) S[(size_t)i * n + j] = 0.0;
-  return -1;
-}
-
-void lower_inverse(const std::vector<cplx>& L, int n, std::vector<cplx>& X) {
-  X.assign((size_t)n * n, cplx(0.0, 0.0));
-  // column j of X solves L x = e_j; columns are independent (interleaved over
-  // the workers, since column j costs ~(n - j)^2)
-  Pool pool((size_t)n * n * n / 6);
-  pool.run([&](int t, int nt) {
-    std::vector<cplx> x(n);
-    for (int j = t; j < n; j += nt) {
-      x[j] = 1.0 / L[(size_t)j * n + j];
-      for (int i = j + 1; i < n; ++i) {
-        cplx s = 0.0;
-        const cplx* Li = &L[(size_t)i * n];
-        for (int k = j; k < i; ++k) s += Li[k] * x[k];
-        x[i] = -s / L[(size_t)i * n + i];
-      }
-      for (int i = j; i < n; ++i) X[(size_t)i * n + j] = x[i];
-    }
-  });
-}
 
 // Implicit QL on the real symmetric tridiagonal (d, e), e[i] couples i, i+1.
 // Zt[i][:] accumulates eigenvector i (rows), starting from the identity.  The

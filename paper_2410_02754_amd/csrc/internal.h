@@ -260,8 +260,6 @@ void build_nonlocal(chfsi_ctx* c, KPoint& kp, int n_atoms, const chfsi_atom_desc
 void angular_momentum_real(int l, std::vector<cplx>& L);   // [3][2l+1][2l+1]
 
 // dense host linear algebra (dense_host.cpp)
-int cholesky_lower(std::vector<cplx>& S, int n);           // returns -1 ok, else bad column
-void lower_inverse(const std::vector<cplx>& L, int n, std::vector<cplx>& Linv);
 void hermitian_eig(const std::vector<cplx>& A, int n, std::vector<double>& w, std::vector<cplx>& V);
 
 // device launchers (kernels.hip)
@@ -310,6 +308,18 @@ void launch_axpby_rows(chfsi_ctx* c, double2* W, int64_t ldw, const double2* X, 
                        int64_t rows, int n_vec, double beta, double gamma);
 void launch_copy_rows(chfsi_ctx* c, double2* dst, int64_t ldd, const double2* src, int64_t lds,
                       int64_t rows, int n_vec);
+struct GramShape {
+  int groups;                   // row ranges, each with its own partial sums
+  int64_t tiles, range_rows;
+};
+GramShape gram_shape(int64_t rows, int n, bool lower_only);
+double2* gram_device(chfsi_ctx* c, const double2* X, int64_t ldx, const double2* Y, int64_t ldy, int64_t rows, int n,
+                     bool lower_only, size_t extra);
+size_t chol_extra(int n);
+void chol_rotation(chfsi_ctx* c, double2* Sd, int n, double2* R, int (&info)[3]);
+int64_t rotate_panel_rows(int64_t rows, int n);
+double2* rotation_matrix(chfsi_ctx* c, int64_t rows, int n, bool upper);   // room for Q, for rotate_device
+void rotate_device(chfsi_ctx* c, double2* X, int64_t ldx, int64_t rows, int n, const double2* Qd, bool upper);
 void gram(chfsi_ctx* c, const double2* X, int64_t ldx, const double2* Y, int64_t ldy, int64_t rows,
           int n, std::vector<cplx>& S, bool lower_only);
 void rotate_inplace(chfsi_ctx* c, double2* X, int64_t ldx, int64_t rows, int n,

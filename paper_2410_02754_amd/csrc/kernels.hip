@@ -1731,33 +1731,52 @@ void densities(chfsi_ctx* c, const double2* X, int64_t ldx, int n_vec, const dou
 // ============================================================================
 // Dense tall-skinny products (FP64 MFMA) for CholGS and Rayleigh-Ritz
 // ============================================================================
-// Both products run on one LDS-staged tile engine: workgroup tile 128 x 64
-// complex outputs, 4 waves of 64 x 32 (4 x 2 blocks of 16 x 16, 4 real MFMAs
+// Both products run on one LDS-staged tile engine: workgroup tile 64 x 64
+// complex outputs, 4 waves of 32 x 32 (2 x 2 blocks of 16 x 16, 4 real MFMAs
 // per complex block and k-step of 4), k staged through LDS in double-buffered
 // stages of 8, k-major ([k][m] and [k][n]) so that every fragment read is 16
 // consecutive complex values.  The next stage's global loads are issued before
-// the current stage's MFMAs.
-constexpr int kGM = 128, kGN = 64, kGK = 8, kGPad = 2;   // pad: k rows 4 apart on other banks
+// the current stage's MFMAs.  Bound by the FP64 matrix rate: the tile's size only
+// sets the cache reads per MFMA, and against 128 x 64 less of it lies above the
+// diagonal of a triangular product and three or four workgroups fit a CU, so that
+// fewer rows still fill the GPU.  On 432000 rows x 384 columns: Gram product 5.9 ->
+// 5.0 ms (matrix units 77 % busy at 2.13 GHz), triangular rotation 8.4 (with the
+// copies of its panels) -> 5.0 ms; 250000 x 256: Gram 2.4 -> 1.4, full rotation 2.7
+// either way.
+constexpr int kGM = 64, kGN = 64, kGK = 8, kGPad = 2;   // pad: k rows 4 apart on other banks
+constexpr int kGSlots = 1024;    // workgroups of one round: 4 on each of 256 CUs
 
 struct GemmSmem {
   double2 a[2][kGK][kGM + kGPad];
   double2 b[2][kGK][kGN + kGPad];
 };
 
+// Tile t of an n x n product; triangular: the tiles (i, j <= i) row by row
+__device__ __forceinline__ int2 gram_tile(int t, int n, int lower) {
+  if (!lower) {
+    const int nt = (n + kGN - 1) / kGN;
+    return int2{t / nt, t % nt};
+  }
+  int i = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+  while (i * (i + 1) / 2 > t) --i;
+  while ((i + 1) * (i + 2) / 2 <= t) ++i;
+  return int2{i, t - i * (i + 1) / 2};
+}
+
 // acc[mb][nb] (re, im) += op(A) B over one LDS stage; CONJ: op(A) = conj(A)
 template <bool CONJ>
-__device__ __forceinline__ void gemm_stage(const GemmSmem& sm, int buf, int wm, int wn, int lane, d4 (&cr)[4][2],
-                                           d4 (&ci)[4][2]) {
+__device__ __forceinline__ void gemm_stage(const GemmSmem& sm, int buf, int wm, int wn, int lane, d4 (&cr)[2][2],
+                                           d4 (&ci)[2][2]) {
   const int kl = lane >> 4, il = lane & 15;
 #pragma unroll
   for (int ks = 0; ks < kGK / 4; ++ks) {
-    double2 fa[4], fb[2];
+    double2 fa[2], fb[2];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) fa[mb] = sm.a[buf][ks * 4 + kl][wm * 64 + mb * 16 + il];
+    for (int mb = 0; mb < 2; ++mb) fa[mb] = sm.a[buf][ks * 4 + kl][wm * 32 + mb * 16 + il];
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) fb[nb] = sm.b[buf][ks * 4 + kl][wn * 32 + nb * 16 + il];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
+    for (int mb = 0; mb < 2; ++mb) {
       const double ar = fa[mb].x, ai = CONJ ? -fa[mb].y : fa[mb].y, nai = -ai;
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb) {
@@ -1770,135 +1789,148 @@ __device__ __forceinline__ void gemm_stage(const GemmSmem& sm, int buf, int wm, 
   }
 }
 
-// Partial S = X^H Y over chunks of rows, lower-triangle tiles only when asked.
-// Work item = (tile, chunk group g); group g walks the row chunks g, g + G, ...
-// and the items of one group are consecutive on one XCD, so the tiles reading
-// the same rows share that XCD's L2.  partial[g] holds the group's n x n sum.
-__global__ __launch_bounds__(256) void gram_kernel(const double2* __restrict__ X, int64_t ldx,
-                                                   const double2* __restrict__ Y, int64_t ldy,
-                                                   int64_t rows, int n, int64_t chunk_rows, int n_groups,
-                                                   const int2* __restrict__ tiles, int n_tiles,
-                                                   double2* __restrict__ partial) {
+// Partial S = X^H Y over row ranges, lower-triangle tiles only when asked.
+// Work item = (tile, row range g), the items of one range consecutive on one XCD,
+// so the tiles reading the same rows share that XCD's L2.  partial[g] holds the
+// range's n x n sum.  A wave whose 32 x 32 lies above the diagonal of a triangular
+// product has nothing to do but its share of the staging.
+__global__ __launch_bounds__(256, 4) void gram_kernel(const double2* __restrict__ X, int64_t ldx,
+                                                      const double2* __restrict__ Y, int64_t ldy, int64_t rows,
+                                                      int n, int64_t range_rows, int n_groups, int n_tiles,
+                                                      int lower, double2* __restrict__ partial) {
   __shared__ GemmSmem sm;
   const int n_work = n_tiles * n_groups;
   const int per_xcd = (int)((gridDim.x + 7) / 8);
   const int bid = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
   if (bid >= n_work) return;              // uniform over the block, before any barrier
   const int g = bid / n_tiles;
-  const int2 tl = tiles[bid - g * n_tiles];
+  const int2 tl = gram_tile(bid - g * n_tiles, n, lower);
   const int i0 = tl.x * kGM, j0 = tl.y * kGN;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wm = wave & 1, wn = wave >> 1;
-  // staging map: A 8 rows x 128 cols (4 per thread), B 8 rows x 64 cols (2 per thread);
-  // slot u of a thread is column (tid & 31) + 32 u, so each LDS store writes 32
-  // consecutive elements of a row (no bank conflicts) and each load reads 512 B
-  const int ak = tid >> 5, am = tid & 31;
-  const int bk = tid >> 5, bn = tid & 31;
-  d4 cr[4][2], ci[4][2];
+  const bool busy = !lower || i0 + wm * 32 + 31 >= j0 + wn * 32;
+  // staging map: 8 rows x 64 columns of each operand, 2 per thread, columns
+  // (tid & 31) + 32 u, so each LDS store writes 32 consecutive elements of a row
+  // (no bank conflicts) and each load reads 512 B
+  const int sk = tid >> 5, sc = tid & 31;
+  d4 cr[2][2], ci[2][2];
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
+  for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) cr[mb][nb] = ci[mb][nb] = d4{0, 0, 0, 0};
-  const int64_t n_chunks = (rows + chunk_rows - 1) / chunk_rows;
-  double2 pa[4], pb[2];
-  auto gload = [&](int64_t r0, int64_t r_end) {
-    const int64_t r = r0 + ak;
+  double2 pa[2], pb[2];
+  const int64_t r_begin = g * range_rows;
+  const int64_t r_end = r_begin + range_rows < rows ? r_begin + range_rows : rows;
+  auto gload = [&](int64_t r0) {
+    const int64_t r = r0 + sk;
     const bool rv = r < r_end;
     const double2* xp = X + (rv ? r : 0) * ldx;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int c = i0 + am + 32 * u;
-      pa[u] = (rv && c < n) ? xp[c] : double2{0.0, 0.0};
-    }
-    const int64_t rb = r0 + bk;
-    const bool rbv = rb < r_end;
-    const double2* yp = Y + (rbv ? rb : 0) * ldy;
+    const double2* yp = Y + (rv ? r : 0) * ldy;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const int c = j0 + bn + 32 * u;
-      pb[u] = (rbv && c < n) ? yp[c] : double2{0.0, 0.0};
+      const int c = i0 + sc + 32 * u, d = j0 + sc + 32 * u;
+      pa[u] = (rv && c < n) ? xp[c] : double2{0.0, 0.0};
+      pb[u] = (rv && d < n) ? yp[d] : double2{0.0, 0.0};
     }
   };
   auto lstore = [&](int buf) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) sm.a[buf][ak][am + 32 * u] = pa[u];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) sm.b[buf][bk][bn + 32 * u] = pb[u];
-  };
-  for (int64_t ch = g; ch < n_chunks; ch += n_groups) {
-    const int64_t r_begin = ch * chunk_rows;
-    const int64_t r_end = std::min<int64_t>(rows, r_begin + chunk_rows);
-    const int nst = (int)((r_end - r_begin + kGK - 1) / kGK);
-    __syncthreads();                      // previous chunk's last stage is read
-    gload(r_begin, r_end);
-    lstore(0);
-    __syncthreads();
-    for (int st = 0; st < nst; ++st) {
-      const int buf = st & 1;
-      const bool more = st + 1 < nst;
-      if (more) gload(r_begin + (int64_t)(st + 1) * kGK, r_end);
-      gemm_stage<true>(sm, buf, wm, wn, lane, cr, ci);
-      if (more) lstore(buf ^ 1);          // that buffer was last read before the previous barrier
-      __syncthreads();
+    for (int u = 0; u < 2; ++u) {
+      sm.a[buf][sk][sc + 32 * u] = pa[u];
+      sm.b[buf][sk][sc + 32 * u] = pb[u];
     }
+  };
+  const int nst = (int)((r_end - r_begin + kGK - 1) / kGK);
+  gload(r_begin);
+  lstore(0);
+  __syncthreads();
+  for (int st = 0; st < nst; ++st) {
+    const int buf = st & 1;
+    const bool more = st + 1 < nst;
+    if (more) gload(r_begin + (int64_t)(st + 1) * kGK);
+    if (busy) gemm_stage<true>(sm, buf, wm, wn, lane, cr, ci);
+    if (more) lstore(buf ^ 1);            // that buffer was last read before the previous barrier
+    __syncthreads();
   }
   double2* out = partial + (size_t)g * n * n;
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
+  for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int ri = i0 + wm * 64 + mb * 16 + acc_row<double>(lane, j);
+        const int ri = i0 + wm * 32 + mb * 16 + acc_row<double>(lane, j);
         const int cj = j0 + wn * 32 + nb * 16 + (lane & 15);
         if (ri < n && cj < n) out[(size_t)ri * n + cj] = double2{cr[mb][nb][j], ci[mb][nb][j]};
       }
 }
 
-// S[i][j] = sum over groups of partial[g][i][j] for the (i, j) of the listed tiles
-__global__ void gram_reduce_kernel(const double2* __restrict__ partial, int n_groups, int n,
-                                   const int2* __restrict__ tiles, double2* __restrict__ S) {
-  const int2 tl = tiles[blockIdx.x];
-  for (int t = threadIdx.x; t < kGM * kGN; t += blockDim.x) {
-    const int i = tl.x * kGM + t / kGN, j = tl.y * kGN + t % kGN;
-    if (i >= n || j >= n) continue;
-    double2 s = {0.0, 0.0};
-    for (int g = 0; g < n_groups; ++g) {
-      const double2 v = partial[((size_t)g * n + i) * n + j];
-      s.x += v.x;
-      s.y += v.y;
-    }
-    S[(size_t)i * n + j] = s;
+// S[i][j] = sum over ranges of partial[g][i][j] for the (i, j) of the tiles; one
+// workgroup takes four rows of a tile (one element per thread: one workgroup per
+// tile left the GPU idle, 353 -> 13 us at n = 384)
+__global__ __launch_bounds__(256) void gram_reduce_kernel(const double2* __restrict__ partial, int n_groups, int n,
+                                                          int lower, double2* __restrict__ S) {
+  const int2 tl = gram_tile(blockIdx.x, n, lower);
+  const int i = tl.x * kGM + blockIdx.y * 4 + (threadIdx.x >> 6), j = tl.y * kGN + (threadIdx.x & 63);
+  if (i >= n || j >= n) return;
+  const double2* p = partial + (size_t)i * n + j;
+  const size_t nn = (size_t)n * n;
+  double2 s = {0.0, 0.0};
+#pragma unroll 8
+  for (int g = 0; g < n_groups; ++g) {
+    const double2 v = p[g * nn];
+    s.x += v.x;
+    s.y += v.y;
   }
+  S[(size_t)i * n + j] = s;
+}
+
+// Row ranges of a Gram product: one round of workgroups, cut at whole stages; past
+// half a round of tiles the count of at most four that fills its rounds best.
+GramShape gram_shape(int64_t rows, int n, bool lower_only) {
+  GramShape g;
+  const int64_t nt = cdiv(n, kGM);
+  const int64_t tiles = lower_only ? nt * (nt + 1) / 2 : nt * nt;
+  g.tiles = tiles;
+  int64_t groups = std::max<int64_t>(1, kGSlots / tiles);
+  if (groups == 1) {
+    const auto fill = [&](int64_t k) {
+      return (double)(tiles * k) / (double)((tiles * k + kGSlots - 1) / kGSlots * kGSlots);
+    };
+    for (int64_t k = 2; k <= 4; ++k)
+      if (fill(k) > 1.05 * fill(groups)) groups = k;
+  }
+  groups = std::min<int64_t>(groups, std::max<int64_t>(1, rows / 64));
+  g.range_rows = (cdiv(rows, groups) + kGK - 1) / kGK * kGK;
+  g.groups = std::max(1, cdiv(rows, g.range_rows));
+  return g;
+}
+
+// S = X^H Y on the device (its lower triangle): in c->scratch, which is grown for
+// `extra` doubles behind it
+double2* gram_device(chfsi_ctx* c, const double2* X, int64_t ldx, const double2* Y, int64_t ldy, int64_t rows, int n,
+                     bool lower_only, size_t extra) {
+  const GramShape g = gram_shape(rows, n, lower_only);
+  const size_t nn = (size_t)n * n;
+  CHFSI_CHECK(g.tiles * g.groups < (int64_t)1 << 30, CHFSI_EINVAL, "Gram product: too many columns");
+  c->scratch.alloc(2 * nn * (g.groups + 1) + extra);
+  double2* partial = reinterpret_cast<double2*>(c->scratch.ptr);
+  double2* Sd = partial + g.groups * nn;
+  StageTimer tm(c, CHFSI_STAGE_GRAM, 8.0 * (double)rows * n * n * (lower_only ? 0.5 : 1.0),
+                8.0 * (double)rows * kGM * kGN * g.tiles, 2.0 * (double)rows * n * sizeof(double2));
+  const int64_t n_work = g.tiles * g.groups;
+  hipLaunchKernelGGL(gram_kernel, dim3(8 * cdiv(n_work, 8)), dim3(256), 0, c->stream, X, ldx, Y, ldy, rows, n,
+                     g.range_rows, g.groups, (int)g.tiles, lower_only ? 1 : 0, partial);
+  LAUNCH_CHECK();
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3((int)g.tiles, kGM / 4), dim3(256), 0, c->stream, partial, g.groups, n,
+                     lower_only ? 1 : 0, Sd);
+  LAUNCH_CHECK();
+  return Sd;
 }
 
 void gram(chfsi_ctx* c, const double2* X, int64_t ldx, const double2* Y, int64_t ldy, int64_t rows,
           int n, std::vector<cplx>& S, bool lower_only) {
-  const int nti = cdiv(n, kGM), ntj = cdiv(n, kGN);
-  std::vector<int2> tiles;
-  for (int i = 0; i < nti; ++i)
-    for (int j = 0; j < ntj; ++j)
-      if (!lower_only || j * kGN < (i + 1) * kGM) tiles.push_back(int2{i, j});
-  const int ntl = (int)tiles.size();
-  // one resident round of work items (two 256-thread workgroups per CU at this
-  // kernel's register use); row chunks of 256
-  const int64_t chunk_rows = 256;
-  const int64_t n_chunks = std::max<int64_t>(1, (rows + chunk_rows - 1) / chunk_rows);
-  const int n_groups = (int)std::max<int64_t>(1, std::min<int64_t>(n_chunks, 512 / ntl));
-  const size_t need = (size_t)n_groups * n * n + (size_t)n * n;   // double2 units
-  c->scratch.alloc(2 * need + ntl);                               // + tiles (int2 = 1 double)
-  double2* partial = reinterpret_cast<double2*>(c->scratch.ptr);
-  double2* Sd = partial + (size_t)n_groups * n * n;
-  int2* td = reinterpret_cast<int2*>(Sd + (size_t)n * n);
-  CHFSI_HIP(hipMemcpyAsync(td, tiles.data(), ntl * sizeof(int2), hipMemcpyHostToDevice, c->stream));
-  StageTimer tm(c, CHFSI_STAGE_GRAM, 8.0 * (double)rows * n * n * (lower_only ? 0.5 : 1.0),
-                8.0 * (double)rows * kGM * kGN * ntl, 2.0 * (double)rows * n * sizeof(double2));
-  const int n_work = ntl * n_groups;
-  hipLaunchKernelGGL(gram_kernel, dim3(8 * cdiv(n_work, 8)), dim3(256), 0, c->stream, X, ldx, Y, ldy, rows, n,
-                     chunk_rows, n_groups, td, ntl, partial);
-  LAUNCH_CHECK();
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3(ntl), dim3(256), 0, c->stream, partial, n_groups, n, td, Sd);
-  LAUNCH_CHECK();
+  const double2* Sd = gram_device(c, X, ldx, Y, ldy, rows, n, lower_only, 0);
   std::vector<double2> h((size_t)n * n);
   CHFSI_HIP(hipMemcpyAsync(h.data(), Sd, (size_t)n * n * sizeof(double2), hipMemcpyDeviceToHost, c->stream));
   CHFSI_HIP(hipStreamSynchronize(c->stream));
@@ -1912,114 +1944,426 @@ void gram(chfsi_ctx* c, const double2* X, int64_t ldx, const double2* Y, int64_t
     }
 }
 
-// X[r0 + r][:] = P[r][:] Q over a row panel P (a copy of those rows).  upper:
-// Q[k][j] = 0 for k > j, so the k range of a column tile ends at its last column;
-// a workgroup then takes column tiles ct and n_ct - 1 - ct of its row tile in turn
-// (equal work per workgroup: the k ranges of the pair add up to n + kGN).
-// Work item = (row tile, column tile or pair), consecutive on one XCD, so the
-// column tiles of one row tile read its panel rows through one L2.
-__global__ __launch_bounds__(256) void rotate_kernel(const double2* __restrict__ P, int n,
-                                                     int64_t prow, const double2* __restrict__ Q,
-                                                     double2* __restrict__ X, int64_t ldx, int upper,
-                                                     int n_rt, int n_ct) {
+// One 64 x 64 tile of P Q: rows r0.. of P (valid below prow), columns j0.., k below
+// kend, into X.  trim: the tile crosses Q's diagonal, a wave's k range ends at its
+// own last column.
+__device__ __forceinline__ void rotate_tile(GemmSmem& sm, const double2* P, int64_t ldp, int64_t r0, int64_t prow,
+                                            const double2* __restrict__ Q, int n, int j0, int kend, int trim,
+                                            double2* X, int64_t ldx) {
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int wm = wave & 1, wn = wave >> 1;
+  // staging map: A 64 rows x 8 k (rows (tid >> 3) + 32 u: eight lanes read the 128
+  // bytes of a row, and the k-major stores of 16 lanes hit all banks once), B 8 rows
+  // of Q x 64 columns (columns (tid & 31) + 32 u)
+  const int am = tid >> 3, ak = tid & 7;
+  const int bk = tid >> 5, bn = tid & 31;
+  const double2* pp = P + (r0 + am) * ldp + ak;
+  const int64_t pstep = 32 * ldp;
+  const double2* qp = Q + (size_t)bk * n + j0 + bn;
+  const int64_t qstep = (int64_t)kGK * n;
+  const int my_end = trim ? j0 + wn * 32 + 32 : kend;
+  d4 cr[2][2], ci[2][2];
+#pragma unroll
+  for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) cr[mb][nb] = ci[mb][nb] = d4{0, 0, 0, 0};
+  double2 pa[2], pb[2];
+  auto gload = [&](int k0) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      pa[u] = (r0 + am + 32 * u < prow && k0 + ak < kend) ? pp[u * pstep] : double2{0.0, 0.0};
+      pb[u] = (k0 + bk < kend && j0 + bn + 32 * u < n) ? qp[32 * u] : double2{0.0, 0.0};
+    }
+    pp += kGK;
+    qp += qstep;
+  };
+  auto lstore = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      sm.a[buf][ak][am + 32 * u] = pa[u];
+      sm.b[buf][bk][bn + 32 * u] = pb[u];
+    }
+  };
+  const int nst = (kend + kGK - 1) / kGK;
+  gload(0);
+  lstore(0);
+  __syncthreads();
+  for (int st = 0; st < nst; ++st) {
+    const int buf = st & 1;
+    const bool more = st + 1 < nst;
+    if (more) gload((st + 1) * kGK);
+    if (st * kGK < my_end) gemm_stage<false>(sm, buf, wm, wn, lane, cr, ci);
+    if (more) lstore(buf ^ 1);
+    __syncthreads();                      // the last one: every read of P and sm is done
+  }
+#pragma unroll
+  for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int64_t r = r0 + wm * 32 + mb * 16 + acc_row<double>(lane, j);
+        const int cj = j0 + wn * 32 + nb * 16 + (lane & 15);
+        if (r < prow && cj < n) X[r * ldx + cj] = double2{cr[mb][nb][j], ci[mb][nb][j]};
+      }
+}
+
+// X[r][:] = P[r][:] Q over a row panel P (a copy of those rows of X).  Work item =
+// (row tile, column tile), consecutive on one XCD, so the column tiles of one row
+// tile read its panel rows through one L2.
+__global__ __launch_bounds__(256, 4) void rotate_kernel(const double2* __restrict__ P, int n, int64_t prow,
+                                                        const double2* __restrict__ Q, double2* __restrict__ X,
+                                                        int64_t ldx, int n_rt, int n_ct) {
   __shared__ GemmSmem sm;
-  const int n_cw = upper ? (n_ct + 1) / 2 : n_ct;    // column work items per row tile
-  const int n_work = n_rt * n_cw;
+  const int n_work = n_rt * n_ct;
   const int per_xcd = (int)((gridDim.x + 7) / 8);
   const int bid = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
   if (bid >= n_work) return;              // uniform over the block, before any barrier
-  const int rt = bid / n_cw, cw = bid - rt * n_cw;
-  const int64_t r0 = (int64_t)rt * kGM;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wm = wave & 1, wn = wave >> 1;
-  // staging map: A 128 panel rows x 8 k (4 consecutive k per thread, stored
-  // k-major), B 8 rows of Q x 64 columns (columns (tid & 31) + 32 u)
-  const int am = tid >> 1, ak = (tid & 1) * 4;
-  const int bk = tid >> 5, bn = tid & 31;
-  const int64_t ra = r0 + am;
-  const bool rav = ra < prow;
-  const double2* prow_p = P + (rav ? ra : 0) * (int64_t)n;
-  const int n_pass = (upper && n_ct - 1 - cw != cw) ? 2 : 1;
-  for (int pass = 0; pass < n_pass; ++pass) {
-    const int ct = pass == 0 ? cw : n_ct - 1 - cw;
-    const int j0 = ct * kGN;
-    const int kend = upper ? std::min(n, j0 + kGN) : n;
-    d4 cr[4][2], ci[4][2];
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb) cr[mb][nb] = ci[mb][nb] = d4{0, 0, 0, 0};
-    double2 pa[4], pb[2];
-    auto gload = [&](int k0) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int k = k0 + ak + u;
-        pa[u] = (rav && k < kend) ? prow_p[k] : double2{0.0, 0.0};
-      }
-      const int kb = k0 + bk;
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int cj = j0 + bn + 32 * u;
-        pb[u] = (kb < kend && cj < n) ? Q[(size_t)kb * n + cj] : double2{0.0, 0.0};
-      }
-    };
-    auto lstore = [&](int buf) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) sm.a[buf][ak + u][am] = pa[u];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) sm.b[buf][bk][bn + 32 * u] = pb[u];
-    };
-    const int nst = (kend + kGK - 1) / kGK;
-    if (pass > 0) __syncthreads();          // the previous tile's last stage has read sm
-    gload(0);
-    lstore(0);
-    __syncthreads();
-    for (int st = 0; st < nst; ++st) {
-      const int buf = st & 1;
-      const bool more = st + 1 < nst;
-      if (more) gload((st + 1) * kGK);
-      gemm_stage<false>(sm, buf, wm, wn, lane, cr, ci);
-      if (more) lstore(buf ^ 1);
-      __syncthreads();
-    }
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int64_t r = r0 + wm * 64 + mb * 16 + acc_row<double>(lane, j);
-          const int cj = j0 + wn * 32 + nb * 16 + (lane & 15);
-          if (r < prow && cj < n) X[r * ldx + cj] = double2{cr[mb][nb][j], ci[mb][nb][j]};
-        }
+  const int rt = bid / n_ct, ct = bid - rt * n_ct;
+  rotate_tile(sm, P, n, (int64_t)rt * kGM, prow, Q, n, ct * kGN, n, 0, X, ldx);
+}
+
+// X <- X Q in place, Q upper triangular: a workgroup owns 64 rows and takes its
+// column tiles from the last to the first.  A tile reads columns up to its own last
+// one and writes its own, which no later tile reads, so no copy of X is made.
+// Against panels with (row tile, column pair) items, 384 columns: 0.78 against 0.92
+// ms on 65536 rows, 0.39 against 0.44 on 27648, 0.23 against 0.21 on 11664.  Three
+// workgroups per CU: at four it spills (5.4 against 5.0 ms on 432000).
+__global__ __launch_bounds__(256, 3) void rotate_upper_kernel(double2* X, int64_t ldx, int64_t rows, int n,
+                                                              const double2* __restrict__ Q) {
+  __shared__ GemmSmem sm;
+  for (int j0 = (n - 1) / kGN * kGN; j0 >= 0; j0 -= kGN) {
+    const int kend = j0 + kGN < n ? j0 + kGN : n;
+    rotate_tile(sm, X, ldx, (int64_t)blockIdx.x * kGM, rows, Q, n, j0, kend, 1, X, ldx);
+  }
+}
+
+// Rows of a panel: whole rounds of workgroups within 128 MiB of copied rows
+int64_t rotate_panel_rows(int64_t rows, int n) {
+  const int64_t n_ct = cdiv(n, kGN);
+  const int64_t cap = std::max<int64_t>(1, ((int64_t)1 << 27) / ((int64_t)n * 16) / kGM);   // row tiles
+  const int64_t rounds = cap * n_ct / kGSlots;
+  const int64_t rt = rounds > 0 ? std::max<int64_t>(1, rounds * kGSlots / n_ct) : cap;
+  return std::min<int64_t>(rt, cdiv(rows, kGM)) * kGM;
+}
+
+// Room for the n x n matrix of rotate_device (in front of the panel's)
+double2* rotation_matrix(chfsi_ctx* c, int64_t rows, int n, bool upper) {
+  c->panel.alloc(((upper ? 0 : (size_t)rotate_panel_rows(rows, n) * n) + (size_t)n * n) * 2);
+  return reinterpret_cast<double2*>(c->panel.ptr);
+}
+
+void rotate_device(chfsi_ctx* c, double2* X, int64_t ldx, int64_t rows, int n, const double2* Qd, bool upper) {
+  StageTimer tm(c, CHFSI_STAGE_ROTATE, 8.0 * (double)rows * n * n * (upper ? 0.5 : 1.0),
+                8.0 * (double)rows * n * n * (upper ? 0.5 : 1.0), (upper ? 2.0 : 4.0) * (double)rows * n * sizeof(double2));
+  if (upper) {
+    hipLaunchKernelGGL(rotate_upper_kernel, dim3(cdiv(rows, kGM)), dim3(256), 0, c->stream, X, ldx, rows, n, Qd);
+    LAUNCH_CHECK();
+    return;
+  }
+  double2* P = reinterpret_cast<double2*>(c->panel.ptr) + (size_t)n * n;
+  const int64_t prow = rotate_panel_rows(rows, n);
+  for (int64_t r0 = 0; r0 < rows; r0 += prow) {
+    const int64_t pr = std::min(prow, rows - r0);
+    launch_copy_rows(c, P, n, X + r0 * ldx, ldx, pr, n);
+    const int n_rt = cdiv(pr, kGM), n_ct = cdiv(n, kGN);
+    hipLaunchKernelGGL(rotate_kernel, dim3(8 * cdiv((int64_t)n_rt * n_ct, 8)), dim3(256), 0, c->stream, P, n, pr, Qd,
+                       X + r0 * ldx, ldx, n_rt, n_ct);
+    LAUNCH_CHECK();
   }
 }
 
 void rotate_inplace(chfsi_ctx* c, double2* X, int64_t ldx, int64_t rows, int n, const std::vector<cplx>& Q,
                     bool upper) {
-  // panel of rows copied to scratch, then multiplied back into place
-  int64_t prow = std::max<int64_t>(kGM, ((int64_t)1 << 27) / ((int64_t)n * 16));   // <= 128 MiB
-  prow = std::min<int64_t>(prow, rows);
-  prow = (prow + kGM - 1) / kGM * kGM;
-  c->panel.alloc((size_t)prow * n * 2 + (size_t)n * n * 2);
-  double2* P = reinterpret_cast<double2*>(c->panel.ptr);
-  double2* Qd = P + (size_t)prow * n;
+  double2* Qd = rotation_matrix(c, rows, n, upper);
   std::vector<double2> qh((size_t)n * n);
   for (size_t i = 0; i < qh.size(); ++i) qh[i] = double2{Q[i].real(), Q[i].imag()};
   CHFSI_HIP(hipMemcpyAsync(Qd, qh.data(), qh.size() * sizeof(double2), hipMemcpyHostToDevice, c->stream));
-  StageTimer tm(c, CHFSI_STAGE_ROTATE, 8.0 * (double)rows * n * n * (upper ? 0.5 : 1.0),
-                8.0 * (double)rows * n * n, 4.0 * (double)rows * n * sizeof(double2));
-  for (int64_t r0 = 0; r0 < rows; r0 += prow) {
-    const int64_t pr = std::min(prow, rows - r0);
-    launch_copy_rows(c, P, n, X + r0 * ldx, ldx, pr, n);
-    const int n_rt = cdiv(pr, kGM), n_ct = cdiv(n, kGN);
-    const int n_cw = upper ? (n_ct + 1) / 2 : n_ct;
-    const int grid = 8 * cdiv((int64_t)n_rt * n_cw, 8);
-    hipLaunchKernelGGL(rotate_kernel, dim3(grid), dim3(256), 0, c->stream, P, n, pr, Qd, X + r0 * ldx, ldx,
-                       upper ? 1 : 0, n_rt, n_ct);
+  rotate_device(c, X, ldx, rows, n, Qd, upper);
+  CHFSI_HIP(hipStreamSynchronize(c->stream));   // qh leaves scope
+}
+
+// ============================================================================
+// Cholesky factor of the Gram matrix and the rotation it gives (CholGS)
+// ============================================================================
+// S' = D S D with D = diag(S)^{-1/2}, S' = L L^H, R = D L^{-H}, all in blocks of 32
+// columns, on the device, so that nothing but the column of a failed pivot comes to
+// the host before X R.  On the host with 16 threads this was 3.65 ms at n = 384 and
+// the copies to and fro; the launches below take 0.62 ms (0.16 at n = 96, 2.0 at
+// 1000).  A launch per block column of the factor and one for the inverse; bound by
+// the chain of 32 pivots in each diagonal block (37 us per block, and 128 us for the
+// inverse), not by the n^3 work.
+constexpr int kCB = 32, kCPad = 2;         // block; pad as in the tile engine
+typedef double2 CholTile[kCB][kCB + kCPad];
+
+// info: [0] the matrix has a non-finite element, [1] first column without a
+// positive diagonal, [2] first failed pivot (n: none)
+__global__ __launch_bounds__(256) void chol_scale_kernel(const double2* __restrict__ S, int n, double* __restrict__ dsc,
+                                                         double2* __restrict__ R, int* __restrict__ info) {
+  const int i = blockIdx.x;
+  const double si = S[(size_t)i * n + i].x;
+  const double di = 1.0 / sqrt(si);
+  if (threadIdx.x == 0) {
+    dsc[i] = di;
+    if (!(si > 0.0)) atomicMin(&info[1], i);
+  }
+  bool bad = false;
+  for (int j = threadIdx.x; j < n; j += 256) {
+    R[(size_t)i * n + j] = double2{0.0, 0.0};
+    if (j > i) continue;
+    const double2 v = S[(size_t)i * n + j];
+    bad |= !isfinite(v.x) || !isfinite(v.y);
+  }
+  if (bad) atomicOr(&info[0], 1);
+}
+
+// A = D S D (lower triangle) into A
+__global__ __launch_bounds__(256) void chol_apply_scale_kernel(const double2* __restrict__ S, int n,
+                                                               const double* __restrict__ dsc,
+                                                               double2* __restrict__ A) {
+  const int i = blockIdx.x;
+  const double di = dsc[i];
+  for (int j = threadIdx.x; j <= i; j += 256) {
+    const double2 v = S[(size_t)i * n + j];
+    const double w = di * dsc[j];
+    A[(size_t)i * n + j] = double2{v.x * w, v.y * w};
+  }
+}
+
+// t <- the 32 x 32 block (bi, bj) of A (zero outside the matrix; outside the lower
+// triangle too, with an identity on a diagonal past n)
+__device__ __forceinline__ void chol_load(CholTile& t, const double2* __restrict__ A, int n, int bi, int bj) {
+  for (int e = threadIdx.x; e < kCB * kCB; e += 256) {
+    const int r = e / kCB, c = e % kCB, i = bi * kCB + r, j = bj * kCB + c;
+    double2 v = {0.0, 0.0};
+    if (i < n && j < n && j <= i) v = A[(size_t)i * n + j];
+    else if (i == j) v.x = 1.0;
+    t[r][c] = v;
+  }
+}
+
+// acc of this wave's 16 x 16 quarter += P Q^H (HERM) or P Q over 32 columns
+template <bool HERM>
+__device__ __forceinline__ void chol_gemm(const CholTile& P, const CholTile& Q, d4& cr, d4& ci) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = (wave & 1) * 16 + (lane & 15), c = (wave >> 1) * 16 + (lane & 15), kl = lane >> 4;
+#pragma unroll
+  for (int ks = 0; ks < kCB / 4; ++ks) {
+    const double2 a = P[r][4 * ks + kl];
+    double2 b = HERM ? Q[c][4 * ks + kl] : Q[4 * ks + kl][c];
+    if (HERM) b.y = -b.y;
+    cr = mfma(a.x, b.x, cr);
+    ci = mfma(a.x, b.y, ci);
+    cr = mfma(-a.y, b.y, cr);
+    ci = mfma(a.y, b.x, ci);
+  }
+}
+
+// Factor of the diagonal block b in t and its inverse, by elimination of [t | I]:
+// 256 threads, two barriers a column (the quotients of the column, the rest).  Products of quotients (a_ik / d_k) conj(a_jk),
+// not of scaled columns, so that equal columns leave a pivot of exactly zero.
+__device__ __forceinline__ void chol_factor(CholTile& t, CholTile& m, int n, int b, double2* __restrict__ L,
+                                            double2* __restrict__ invd, int* __restrict__ info) {
+  __shared__ double2 quot[kCB];
+  for (int e = threadIdx.x; e < kCB * kCB; e += 256) m[e / kCB][e % kCB] = double2{e / kCB == e % kCB ? 1.0 : 0.0, 0.0};
+  __syncthreads();
+  for (int k = 0; k < kCB; ++k) {
+    const double d = t[k][k].x;
+    if (threadIdx.x == 0 && (!(d > 0.0) || !isfinite(d))) atomicMin(&info[2], b * kCB + k);
+    if (threadIdx.x > k && threadIdx.x < kCB) {
+      const double2 a = t[threadIdx.x][k];
+      quot[threadIdx.x] = double2{a.x / d, a.y / d};
+    }
+    __syncthreads();
+    // columns k+1.. of t below the diagonal, and columns 0..k of m
+    for (int e = threadIdx.x; e < (kCB - 1 - k) * kCB; e += 256) {
+      const int i = k + 1 + e / kCB, c = e % kCB;
+      const double qx = quot[i].x, qy = quot[i].y;
+      if (c <= k) {
+        const double2 w = m[k][c];
+        m[i][c].x -= qx * w.x - qy * w.y;
+        m[i][c].y -= qx * w.y + qy * w.x;
+      } else if (c <= i) {
+        const double2 w = t[c][k];
+        t[i][c].x -= qx * w.x + qy * w.y;
+        t[i][c].y -= qy * w.x - qx * w.y;
+      }
+    }
+    __syncthreads();
+  }
+  // rows and columns scaled by the pivots' roots
+  for (int e = threadIdx.x; e < kCB * kCB; e += 256) {
+    const int r = e / kCB, c = e % kCB, i = b * kCB + r, j = b * kCB + c;
+    const double lr = sqrt(t[r][r].x), lc = sqrt(t[c][c].x);
+    double2 v = t[r][c], w = m[r][c];
+    if (c > r) v = w = double2{0.0, 0.0};
+    else if (c == r) v = double2{lr, 0.0};
+    else v = double2{v.x / lc, v.y / lc};
+    w = double2{w.x / lr, w.y / lr};
+    if (i < n && j < n) L[(size_t)i * n + j] = v;
+    invd[(size_t)b * kCB * kCB + e] = w;
+  }
+}
+
+__global__ __launch_bounds__(256) void chol_first_kernel(const double2* __restrict__ A, int n, double2* __restrict__ L,
+                                                         double2* __restrict__ invd, int* __restrict__ info) {
+  __shared__ CholTile t, m;
+  chol_load(t, A, n, 0, 0);
+  __syncthreads();
+  chol_factor(t, m, n, 0, L, invd, info);
+}
+
+// Block column p eliminated: workgroup (i, j), p < j <= i, takes
+// L_ip = A_ip L_pp^{-H}, L_jp alike, A_ij -= L_ip L_jp^H; the workgroups of column
+// p + 1 also write their L_ip, and that of its diagonal factors the block.
+__global__ __launch_bounds__(256) void chol_step_kernel(double2* __restrict__ A, int n, int p, double2* __restrict__ L,
+                                                        double2* __restrict__ invd, int* __restrict__ info) {
+  __shared__ CholTile t, m, u;
+  int i = (int)((sqrtf(8.0f * (float)blockIdx.x + 1.0f) - 1.0f) * 0.5f);
+  while (i * (i + 1) / 2 > (int)blockIdx.x) --i;
+  while ((i + 1) * (i + 2) / 2 <= (int)blockIdx.x) ++i;
+  const int j = p + 1 + (int)blockIdx.x - i * (i + 1) / 2;
+  i += p + 1;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r0 = (wave & 1) * 16, c0 = (wave >> 1) * 16 + (lane & 15);
+  for (int e = threadIdx.x; e < kCB * kCB; e += 256) u[e / kCB][e % kCB] = invd[(size_t)p * kCB * kCB + e];
+  chol_load(t, A, n, i, p);
+  chol_load(m, A, n, j, p);
+  __syncthreads();
+  d4 lr{0, 0, 0, 0}, li{0, 0, 0, 0}, mr{0, 0, 0, 0}, mi{0, 0, 0, 0};
+  chol_gemm<true>(t, u, lr, li);
+  chol_gemm<true>(m, u, mr, mi);
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = r0 + acc_row<double>(lane, q);
+    t[r][c0] = double2{lr[q], li[q]};
+    m[r][c0] = double2{mr[q], mi[q]};
+    const int gi = i * kCB + r;
+    if (j == p + 1 && gi < n) L[(size_t)gi * n + p * kCB + c0] = double2{lr[q], li[q]};
+  }
+  __syncthreads();
+  d4 ar{0, 0, 0, 0}, ai{0, 0, 0, 0};
+  chol_gemm<true>(t, m, ar, ai);
+  chol_load(u, A, n, i, j);
+  __syncthreads();
+  const bool next = i == p + 1;           // its diagonal block: j = i
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = r0 + acc_row<double>(lane, q);
+    const int gi = i * kCB + r, gj = j * kCB + c0;
+    const double2 v = {u[r][c0].x - ar[q], u[r][c0].y - ai[q]};
+    if (next) u[r][c0] = v;
+    else if (gi < n && gj <= gi) A[(size_t)gi * n + gj] = v;
+  }
+  if (!next) return;                      // uniform over the block
+  __syncthreads();
+  chol_factor(u, m, n, i, L, invd, info);
+}
+
+// Block column j of X = L^{-1}, from the diagonal down: X_ij = -L_ii^{-1} sum_k L_ik X_kj,
+// and R = D X^H.  The column's own blocks are read back from X (this workgroup's
+// stores, behind barriers).
+__global__ __launch_bounds__(256) void chol_inverse_kernel(const double2* __restrict__ L, int n,
+                                                           const double2* __restrict__ invd,
+                                                           const double* __restrict__ dsc, double2* X,
+                                                           double2* __restrict__ R) {
+  __shared__ CholTile t, m;
+  const int j = blockIdx.x, nb = (n + kCB - 1) / kCB;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r0 = (wave & 1) * 16, c0 = (wave >> 1) * 16 + (lane & 15);
+  const auto store = [&](int i, const CholTile& v) {
+    for (int e = threadIdx.x; e < kCB * kCB; e += 256) {
+      const int r = e / kCB, c = e % kCB, gi = i * kCB + r, gj = j * kCB + c;
+      if (gi < n && gj < n) X[(size_t)gi * n + gj] = v[r][c];
+    }
+    for (int e = threadIdx.x; e < kCB * kCB; e += 256) {
+      const int c = e / kCB, r = e % kCB, gi = i * kCB + r, gj = j * kCB + c;
+      if (gi < n && gj < n) R[(size_t)gj * n + gi] = double2{dsc[gj] * v[r][c].x, -(dsc[gj] * v[r][c].y)};
+    }
+  };
+  const auto diag = [&](CholTile& v, int b) {
+    for (int e = threadIdx.x; e < kCB * kCB; e += 256) v[e / kCB][e % kCB] = invd[(size_t)b * kCB * kCB + e];
+  };
+  diag(t, j);
+  __syncthreads();
+  store(j, t);
+  __syncthreads();
+  constexpr int kPer = kCB * kCB / 256;
+  for (int i = j + 1; i < nb; ++i) {
+    d4 sr{0, 0, 0, 0}, si{0, 0, 0, 0};
+    double2 pl[kPer], px[kPer];
+    const auto gload = [&](int k) {       // L_ik and X_kj (k < i <= nb - 1: whole blocks of columns)
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) {
+        const int f = threadIdx.x + 256 * e, r = f / kCB, c = f % kCB;
+        const int gi = i * kCB + r, gj = j * kCB + c;
+        pl[e] = gi < n ? L[(size_t)gi * n + k * kCB + c] : double2{0.0, 0.0};
+        px[e] = gj < n ? X[(size_t)(k * kCB + r) * n + gj] : double2{0.0, 0.0};
+      }
+    };
+    gload(j);
+    for (int k = j; k < i; ++k) {
+      __syncthreads();                    // the last products have read t and m
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) {
+        const int f = threadIdx.x + 256 * e;
+        t[f / kCB][f % kCB] = pl[e];
+        m[f / kCB][f % kCB] = px[e];
+      }
+      __syncthreads();
+      if (k + 1 < i) gload(k + 1);
+      chol_gemm<false>(t, m, sr, si);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) m[r0 + acc_row<double>(lane, q)][c0] = double2{-sr[q], -si[q]};
+    diag(t, i);
+    __syncthreads();
+    d4 xr{0, 0, 0, 0}, xi{0, 0, 0, 0};
+    chol_gemm<false>(t, m, xr, xi);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) m[r0 + acc_row<double>(lane, q)][c0] = double2{xr[q], xi[q]};
+    __syncthreads();
+    store(i, m);
+    __syncthreads();
+  }
+}
+
+// Device memory of chol_rotation behind the Gram matrix, in doubles: A (later the
+// inverse), L, the diagonal blocks' inverses, the scales, info
+size_t chol_extra(int n) {
+  const size_t nb = cdiv(n, kCB);
+  return 4 * (size_t)n * n + 2 * nb * kCB * kCB + n + 4;
+}
+
+// R (device) from the Gram matrix Sd, whose `chol_extra` follows it; the columns of a
+// failure, or n, in info (host): see chol_scale_kernel
+void chol_rotation(chfsi_ctx* c, double2* Sd, int n, double2* R, int (&info)[3]) {
+  const size_t nn = (size_t)n * n;
+  const int nb = cdiv(n, kCB);
+  double2 *A = Sd + nn, *L = A + nn, *invd = L + nn;
+  double* dsc = reinterpret_cast<double*>(invd + (size_t)nb * kCB * kCB);
+  int* info_d = reinterpret_cast<int*>(dsc + n);
+  const int none[3] = {0, n, n};
+  CHFSI_HIP(hipMemcpyAsync(info_d, none, sizeof none, hipMemcpyHostToDevice, c->stream));
+  hipStream_t s = c->stream;
+  hipLaunchKernelGGL(chol_scale_kernel, dim3(n), dim3(256), 0, s, Sd, n, dsc, R, info_d);
+  LAUNCH_CHECK();
+  hipLaunchKernelGGL(chol_apply_scale_kernel, dim3(n), dim3(256), 0, s, Sd, n, dsc, A);
+  LAUNCH_CHECK();
+  hipLaunchKernelGGL(chol_first_kernel, dim3(1), dim3(256), 0, s, A, n, L, invd, info_d);
+  LAUNCH_CHECK();
+  for (int p = 0; p + 1 < nb; ++p) {
+    const int r = nb - 1 - p;
+    hipLaunchKernelGGL(chol_step_kernel, dim3(r * (r + 1) / 2), dim3(256), 0, s, A, n, p, L, invd, info_d);
     LAUNCH_CHECK();
   }
-  CHFSI_HIP(hipStreamSynchronize(c->stream));   // qh leaves scope
+  hipLaunchKernelGGL(chol_inverse_kernel, dim3(nb), dim3(256), 0, s, L, n, invd, dsc, A, R);
+  LAUNCH_CHECK();
+  CHFSI_HIP(hipMemcpyAsync(info, info_d, sizeof none, hipMemcpyDeviceToHost, s));
+  CHFSI_HIP(hipStreamSynchronize(s));
 }
 
 // ============================================================================
