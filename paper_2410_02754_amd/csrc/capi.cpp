@@ -521,18 +521,6 @@ int chfsi_lanczos_bounds(chfsi_ctx* c, int ik, int steps, const void* v0, double
   CHFSI_CHECK(v0 && lo && hi, CHFSI_EINVAL, "v0_d, lo and hi must be non-NULL");
   CHFSI_CHECK(steps >= 1 && steps <= 10000, CHFSI_EINVAL, "steps must be in [1, 10000]");
   KPoint& kp = kpoint(c, ik);
-  const int64_t rows = 2 * c->n_nodes;
-  DevBuf<double2> vb;
-  vb.alloc((size_t)3 * rows);
-  double2* v = vb.ptr;
-  double2* w = v + rows;
-  double2* vp = w + rows;
-  const double n0 = std::sqrt(dot_re(c, (const double2*)v0, (const double2*)v0, rows));
-  CHFSI_CHECK(n0 > 0.0 && std::isfinite(n0), CHFSI_EINVAL, "v0 must be finite and nonzero");
-  launch_axpby_rows(c, v, 1, (const double2*)v0, 1, rows, 1, 0.0, 1.0 / n0);
-  launch_axpby_rows(c, vp, 1, v, 1, rows, 1, 0.0, 0.0);
-  double beta = 0.0;
-  std::vector<double> al, be;
   // one column per apply: with the matrix-free data of the current fields at
   // hand the local part takes the matrix-free product (the same operator up to
   // rounding), which reads no cell matrices
@@ -542,25 +530,16 @@ int chfsi_lanczos_bounds(chfsi_ctx* c, int ik, int steps, const void* v0, double
     ~FormGuard() { c->form = form; }
   } fg{c, c->form};
   if (c->form == CHFSI_FORM_CELL_MATRIX && c->mf_gen == c->gen) c->form = CHFSI_FORM_MATRIX_FREE;
-  for (int j = 0; j < steps; ++j) {
-    apply_H(c, kp, v, 1, w, 1, 1, CHFSI_PREC_FP64, 1.0, 0.0, 0.0);
-    const double alpha = dot_re(c, v, w, rows);
-    launch_axpby_rows(c, w, 1, v, 1, rows, 1, 1.0, -alpha);
-    launch_axpby_rows(c, w, 1, vp, 1, rows, 1, 1.0, -beta);
-    const double bn = std::sqrt(dot_re(c, w, w, rows));
-    al.push_back(alpha);
-    if (j < steps - 1) be.push_back(bn);
-    std::swap(vp, v);                                   // vp <- v
-    if (bn > 0.0) launch_axpby_rows(c, v, 1, w, 1, rows, 1, 0.0, 1.0 / bn);
-    beta = bn;
-    if (!(bn > 0.0)) break;
-  }
-  be.resize(al.size() > 0 ? al.size() - 1 : 0);
+  double n0 = 0.0;
+  std::vector<double> al, be;
+  lanczos_steps(c, kp, (const double2*)v0, steps, n0, al, be);
+  CHFSI_CHECK(n0 > 0.0 && std::isfinite(n0), CHFSI_EINVAL, "v0 must be finite and nonzero");
+  const double beta = be.back();
+  be.pop_back();
   std::vector<double> th;
   tridiag_eigvals(al, be, th);
   *lo = th.front();
   *hi = th.back() + beta;
-  CHFSI_HIP(hipStreamSynchronize(c->stream));
   API_END(c)
 }
 

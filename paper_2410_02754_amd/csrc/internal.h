@@ -218,6 +218,7 @@ struct chfsi_ctx {
   size_t nl_fixed_bytes = 0;
   chfsi::DevBuf<double> ye;                   // cell products of one apply, cell by cell (small applies)
   chfsi::DevBuf<double> panel;                // row panel for in-place rotations
+  chfsi::DevBuf<double> lanczos;              // three vectors and the scalars of lanczos_steps
   chfsi::DevBuf<double> cd_partial;           // adjoint cross densities per column group
   chfsi::DevBuf<int32_t> den_order;           // cell order of the density kernels (4x4x4 tiles)
   chfsi::DevBuf<double> ref_b1, ref_wq;       // 1-D interpolation table and weights (device copy)
@@ -331,7 +332,8 @@ void rr_project(chfsi_ctx* c, int ik, const double2* X, int64_t ldx, double2* wo
                 std::vector<cplx>& Hp);
 void column_resid_norms(chfsi_ctx* c, const double2* W, int64_t ldw, const double2* X, int64_t ldx,
                         int64_t rows, int n, const double* theta, double* out);
-double dot_re(chfsi_ctx* c, const double2* x, const double2* y, int64_t rows);
+void lanczos_steps(chfsi_ctx* c, KPoint& kp, const double2* v0, int steps, double& n0, std::vector<double>& al,
+                   std::vector<double>& bn);
 // batched filter support (kernels.hip)
 void launch_cell_batch(hipStream_t s, bool fp64, int CB, bool has_s, const BatchTaskArgs& tasks, const int4* items,
                        int n_items, const double* alpha, int src, int grid);

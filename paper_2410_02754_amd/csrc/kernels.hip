@@ -110,8 +110,8 @@ constexpr int nl_col_blocks() { return sizeof(T) == 8 ? 1 : 2; }
 // j of the lane 32 above (FP32).
 // A chunk is cut into nsub parts (partial[chunk * nsub + part]) where whole
 // chunks are too few waves to fill the GPU: a wave walks its entries 16 at a
-// time, each step a trip to memory, so 512 entries of a narrow block were a
-// 97 us chain (16 atoms, one column) that eight parts cut to 17 us.
+// time, each step a trip to memory, so 512 entries of a narrow block are a chain
+// of 32 trips that eight parts cut to four (16 atoms, one column: 39 us).
 template <class T>
 struct NlContractArgs {
   const typename C2<T>::type* proj;
@@ -285,15 +285,14 @@ __global__ __launch_bounds__(256) void nl_contract_kernel(const NlContractArgs<T
   nl_contract_wave<T, REALP, PACK>(g, wid);
 }
 
-// Coefficients of one atom and 16 columns: the sum over the atom's parts,
+// Coefficients of one atom and COLS columns: the sum over the atom's parts,
 //   C[r][n] = sum_part partial[part][r][n],
 // and the coupling C'[r][n] = alpha sum_r' Delta[r][r'] C[r'][n] (r = 2 chi + spin).
-// 16 threads per column take every 16th part (in a fixed order), meet by lane
-// exchange and in LDS, and each then forms its rows of C'.  Serial chains of
-// loads set its time: the sum over parts is 16 times shorter than with one
-// thread per row, and one launch takes the place of two (together 103 us for 33
-// atoms, 128 columns and 9200 parts).  alpha_d (device, or null) overrides alpha
-// at run time (graph replays with new filter bounds).
+// 256 / COLS threads per column take every (256 / COLS)th part (in a fixed order),
+// meet by lane exchange and in LDS, and each then forms its rows of C'.  Serial
+// chains of loads set its time, so the columns of a workgroup are few where the
+// atoms and columns alone give few workgroups (coef_cols).  alpha_d (device, or
+// null) overrides alpha at run time (graph replays with new filter bounds).
 template <class T>
 struct NlCoefArgs {
   const typename C2<T>::type* partial;
@@ -304,25 +303,26 @@ struct NlCoefArgs {
   const double* alpha_d;
   typename C2<T>::type* Cp;
 };
-constexpr int kCoefCols = 16;
 
 template <class T>
 struct NlCoefSmem {
-  typename C2<T>::type w[4][2 * kMaxPj][kCoefCols];
+  typename C2<T>::type w[4][2 * kMaxPj * 16];
+  typename C2<T>::type c[2 * kMaxPj * 16];
 };
 
-template <class T>
+template <class T, int COLS>
 __device__ __forceinline__ void nl_coef_block(NlCoefSmem<T>& sm, const NlCoefArgs<T>& g, int a, int ctile) {
   typedef typename C2<T>::type CT;
-  const int tid = threadIdx.x, il = tid & 15, slot = tid >> 4, wave = tid >> 6;
-  const int col = ctile * kCoefCols + il;
+  constexpr int SLOTS = 256 / COLS;
+  const int tid = threadIdx.x, il = tid % COLS, slot = tid / COLS, wave = tid >> 6;
+  const int col = ctile * COLS + il;
   const int mr = 2 * g.max_pj, nr = 2 * g.atom_npj[a];
   const int p0 = g.atom_chunk0[a] * g.nsub, p1 = g.atom_chunk0[a + 1] * g.nsub;
   const CT* __restrict__ part = g.partial + min(col, g.n_part - 1);
   T sr[2 * kMaxPj], si[2 * kMaxPj];
 #pragma unroll
   for (int r = 0; r < 2 * kMaxPj; ++r) sr[r] = si[r] = (T)0;
-  for (int p = p0 + slot; p < p1; p += 16) {
+  for (int p = p0 + slot; p < p1; p += SLOTS) {
     CT v[2 * kMaxPj];
 #pragma unroll
     for (int r = 0; r < 2 * kMaxPj; ++r)
@@ -336,27 +336,34 @@ __device__ __forceinline__ void nl_coef_block(NlCoefSmem<T>& sm, const NlCoefArg
   }
 #pragma unroll
   for (int r = 0; r < 2 * kMaxPj; ++r) {
-    sr[r] += __shfl_xor(sr[r], 16);
-    si[r] += __shfl_xor(si[r], 16);
-    sr[r] += __shfl_xor(sr[r], 32);
-    si[r] += __shfl_xor(si[r], 32);
-    if ((tid & 63) < 16) {
+#pragma unroll
+    for (int d = COLS; d < 64; d *= 2) {
+      sr[r] += __shfl_xor(sr[r], d);
+      si[r] += __shfl_xor(si[r], d);
+    }
+    if ((tid & 63) < COLS) {
       CT o;
       o.x = sr[r];
       o.y = si[r];
-      sm.w[wave][r][il] = o;
+      sm.w[wave][r * COLS + il] = o;
     }
   }
   __syncthreads();
+  for (int e = tid; e < nr * COLS; e += 256) {
+    CT o;
+    o.x = (sm.w[0][e].x + sm.w[1][e].x) + (sm.w[2][e].x + sm.w[3][e].x);
+    o.y = (sm.w[0][e].y + sm.w[1][e].y) + (sm.w[2][e].y + sm.w[3][e].y);
+    sm.c[e] = o;
+  }
+  __syncthreads();
   const double alpha = g.alpha_d ? *g.alpha_d : g.alpha;
-  for (int r = slot; r < nr; r += 16) {
+  for (int r = slot; r < nr; r += SLOTS) {
     T xr = 0, xi = 0;
     for (int q = 0; q < nr; ++q) {
       const double2 d = g.delta[((size_t)a * mr + r) * mr + q];
-      const T cr = (sm.w[0][q][il].x + sm.w[1][q][il].x) + (sm.w[2][q][il].x + sm.w[3][q][il].x);
-      const T ci = (sm.w[0][q][il].y + sm.w[1][q][il].y) + (sm.w[2][q][il].y + sm.w[3][q][il].y);
-      xr += (T)d.x * cr - (T)d.y * ci;
-      xi += (T)d.x * ci + (T)d.y * cr;
+      const CT c = sm.c[q * COLS + il];
+      xr += (T)d.x * c.x - (T)d.y * c.y;
+      xi += (T)d.x * c.y + (T)d.y * c.x;
     }
     if (col < g.n_part) {
       CT o;
@@ -367,10 +374,10 @@ __device__ __forceinline__ void nl_coef_block(NlCoefSmem<T>& sm, const NlCoefArg
   }
 }
 
-template <class T>
+template <class T, int COLS>
 __global__ __launch_bounds__(256) void nl_coef_kernel(const NlCoefArgs<T> g) {
   __shared__ NlCoefSmem<T> sm;
-  nl_coef_block<T>(sm, g, blockIdx.x, blockIdx.y);
+  nl_coef_block<T, COLS>(sm, g, blockIdx.x, blockIdx.y);
 }
 
 // Recurrence initialisation fused with the nonlocal back-product, one wave per
@@ -644,6 +651,18 @@ static int nl_parts(const NonlocalK& nl, int n_vec) {
   return need <= (size_t)CHFSI_NOALLOC_SCRATCH_BYTES ? s : 1;
 }
 
+// Columns per workgroup of the coefficient kernel.  A function of the whole block's
+// width, so that column groups sum alike: 1 where columns are one or two (16 atoms of
+// about 970 parts: 48 us with 16, 13 with 1), 4 where an atom has more than 64 parts
+// and the workgroups still fit the GPU at once (4 atoms, 128 columns, about 130 parts
+// each: 50 against 31 us), else 16 (32 tasks of 2 atoms with about 32 parts: 8.9
+// against 12.1 us with 4).
+static int coef_cols(const NonlocalK& nl, int n_vec) {
+  if (n_vec <= 2) return 1;
+  const int64_t parts = (int64_t)nl.n_chunks * nl_parts(nl, n_vec);
+  return parts > 64 * (int64_t)nl.n_atoms && (int64_t)nl.n_atoms * cdiv(n_vec, 4) <= 1024 ? 4 : 16;
+}
+
 template <class T>
 static NlContractArgs<T> contract_args(const NonlocalK& nl, const typename C2<T>::type* proj, const double2* X,
                                        int64_t ldx, int n_vec, int nsub, typename C2<T>::type* partial) {
@@ -717,7 +736,11 @@ static const typename C2<T>::type* nonlocal_coeffs(chfsi_ctx* c, NonlocalK& nl,
     LAUNCH_CHECK();
     const NlCoefArgs<T> co{partial, nl.atom_chunk0.ptr, nl.atom_npj.ptr, nl.delta.ptr, nl.max_pj, nsub,
                            gc,      c0,                 n_vec,           alpha,        alpha_d,   Cp};
-    hipLaunchKernelGGL((nl_coef_kernel<T>), dim3(nl.n_atoms, cdiv(gc, kCoefCols)), dim3(256), 0, c->stream, co);
+    const int cols = coef_cols(nl, n_vec);
+    const dim3 fgrid(nl.n_atoms, cdiv(gc, cols));
+    if (cols == 1) hipLaunchKernelGGL((nl_coef_kernel<T, 1>), fgrid, dim3(256), 0, c->stream, co);
+    else if (cols == 4) hipLaunchKernelGGL((nl_coef_kernel<T, 4>), fgrid, dim3(256), 0, c->stream, co);
+    else hipLaunchKernelGGL((nl_coef_kernel<T, 16>), fgrid, dim3(256), 0, c->stream, co);
     LAUNCH_CHECK();
   }
   return Cp;
@@ -932,7 +955,7 @@ struct BatchNl {
   int64_t ld[2];
   int64_t rows;
   int index;                              // in the recurrence coefficient tables
-  int has_nl, realp, pack, n_atoms, coef_tiles;
+  int has_nl, realp, pack, n_atoms, coef_cols, coef_tiles;
 };
 constexpr int kBatchCopy = 4096;          // elements per workgroup of the copy
 
@@ -979,7 +1002,10 @@ __global__ __launch_bounds__(256) void batch_coef_kernel(const BatchNl<T>* __res
   g.delta = global_ptr(g.delta);
   g.Cp = global_ptr(g.Cp);
   g.alpha_d = alpha + t.index;
-  nl_coef_block<T>(sm, g, w.y / t.coef_tiles, w.y % t.coef_tiles);
+  const int a = w.y / t.coef_tiles, ct = w.y % t.coef_tiles;
+  if (t.coef_cols == 1) nl_coef_block<T, 1>(sm, g, a, ct);
+  else if (t.coef_cols == 4) nl_coef_block<T, 4>(sm, g, a, ct);
+  else nl_coef_block<T, 16>(sm, g, a, ct);
 }
 
 template <class T, int FL>
@@ -1091,7 +1117,8 @@ static BatchNl<T> batch_nl(const SmallTask& s, const typename C2<T>::type* proj)
     b.realp = nl.real_proj;
     b.pack = pack_rows(nl);
     b.n_atoms = nl.n_atoms;
-    b.coef_tiles = cdiv(s.n_vec, kCoefCols);
+    b.coef_cols = coef_cols(nl, s.n_vec);
+    b.coef_tiles = cdiv(s.n_vec, b.coef_cols);
   }
   b.i = init_args<T>(c, nl, proj, Cp, nullptr, 0, nullptr, 0, nullptr, 0, s.n_vec, 1.0, 1.0);
   b.i.ye = reinterpret_cast<const CT*>(s.ye);
@@ -2429,16 +2456,119 @@ __global__ __launch_bounds__(256) void dot_kernel(const double2* __restrict__ x,
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-double dot_re(chfsi_ctx* c, const double2* x, const double2* y, int64_t rows) {
-  c->scratch.alloc(kRedGroups);
-  hipLaunchKernelGGL(dot_kernel, dim3(kRedGroups), dim3(256), 0, c->stream, x, y, rows, c->scratch.ptr);
-  LAUNCH_CHECK();
-  double h[kRedGroups];
-  CHFSI_HIP(hipMemcpyAsync(h, c->scratch.ptr, sizeof(h), hipMemcpyDeviceToHost, c->stream));
-  CHFSI_HIP(hipStreamSynchronize(c->stream));
-  double s = 0.0;
-  for (int g = 0; g < kRedGroups; ++g) s += h[g];
+// ---- Lanczos recurrence with its scalars on the device: a step's kernels sum the
+// partial products they need themselves, so that no step waits for the host.
+// sc: alpha_j at [0, steps), |w_j| at [steps, 2 steps), |v_0| at [2 steps].
+__device__ __forceinline__ double red_sum(const double* __restrict__ partial, double* red) {
+  red[threadIdx.x] = partial[threadIdx.x];
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
+  }
+  const double s = red[0];
+  __syncthreads();                        // red is free again
   return s;
+}
+static_assert(kRedGroups == 256, "red_sum takes one partial sum per thread");
+
+// w <- w - alpha v - |w_{j-1}| vp (vp: none at j = 0), alpha from its partial sums,
+// and the partial sums of |w|^2
+__global__ __launch_bounds__(256) void lanczos_update_kernel(double2* __restrict__ w, const double2* __restrict__ v,
+                                                             const double2* __restrict__ vp, int64_t rows,
+                                                             const double* __restrict__ dots, int j, int steps,
+                                                             double* __restrict__ sc, double* __restrict__ norms) {
+  __shared__ double red[256];
+  const double alpha = red_sum(dots, red);
+  const double beta = j > 0 ? sc[steps + j - 1] : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) sc[j] = alpha;
+  double s = 0.0;
+  for (int64_t r = blockIdx.x * 256 + threadIdx.x; r < rows; r += (int64_t)kRedGroups * 256) {
+    double2 x = w[r];
+    const double2 y = v[r];
+    x.x -= alpha * y.x;
+    x.y -= alpha * y.y;
+    if (j > 0) {
+      const double2 z = vp[r];
+      x.x -= beta * z.x;
+      x.y -= beta * z.y;
+    }
+    w[r] = x;
+    s += x.x * x.x + x.y * x.y;
+  }
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int h = 128; h > 0; h >>= 1) {
+    if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) norms[blockIdx.x] = red[0];
+}
+
+// v <- w / |w| from the partial sums of |w|^2 (zero where that is not positive); the
+// norm to out
+__global__ __launch_bounds__(256) void lanczos_scale_kernel(double2* __restrict__ v, const double2* __restrict__ w,
+                                                            int64_t rows, const double* __restrict__ norms,
+                                                            double* __restrict__ out) {
+  __shared__ double red[256];
+  const double nrm = sqrt(red_sum(norms, red));
+  const bool pos = nrm > 0.0;
+  const double f = 1.0 / nrm;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *out = nrm;
+  for (int64_t r = blockIdx.x * 256 + threadIdx.x; r < rows; r += (int64_t)kRedGroups * 256) {
+    const double2 x = w[r];
+    v[r] = pos ? double2{f * x.x, f * x.y} : double2{0.0, 0.0};
+  }
+}
+
+// alpha_j and |w_j| of up to `steps` steps from v0 (those up to the first |w_j| that is
+// not positive), and |v0|.  20 steps on 250000 rows with 16 atoms were 4.0 ms with two
+// trips to the host and five vector kernels a step, 2.4 ms with these three (and the
+// narrower coefficient tiles); the product with H is 105 of a step's 120 us.
+void lanczos_steps(chfsi_ctx* c, KPoint& kp, const double2* v0, int steps, double& n0, std::vector<double>& al,
+                   std::vector<double>& bn) {
+  const int64_t rows = 2 * c->n_nodes;
+  const size_t n_sc = 2 * (size_t)steps + 1;
+  c->lanczos.alloc((size_t)6 * rows + 2 * kRedGroups + n_sc);
+  double2* v = reinterpret_cast<double2*>(c->lanczos.ptr);
+  double2 *w = v + rows, *vp = w + rows;
+  double* dots = reinterpret_cast<double*>(vp + rows);
+  double *norms = dots + kRedGroups, *sc = norms + kRedGroups;
+  hipStream_t s = c->stream;
+  const auto dot = [&](const double2* x, const double2* y, double* out) {
+    hipLaunchKernelGGL(dot_kernel, dim3(kRedGroups), dim3(256), 0, s, x, y, rows, out);
+    LAUNCH_CHECK();
+  };
+  std::vector<double> h(n_sc);
+  dot(v0, v0, norms);
+  hipLaunchKernelGGL(lanczos_scale_kernel, dim3(kRedGroups), dim3(256), 0, s, v, v0, rows, norms, sc + 2 * steps);
+  LAUNCH_CHECK();
+  constexpr int kLook = 32;               // steps between the host's looks at a breakdown
+  int done = 0;
+  bool ended = false;
+  while (done < steps && !ended) {
+    const int j1 = std::min(steps, done + kLook);
+    for (int j = done; j < j1; ++j) {
+      apply_H(c, kp, v, 1, w, 1, 1, CHFSI_PREC_FP64, 1.0, 0.0, 0.0);
+      dot(v, w, dots);
+      hipLaunchKernelGGL(lanczos_update_kernel, dim3(kRedGroups), dim3(256), 0, s, w, v, vp, rows, dots, j, steps, sc,
+                         norms);
+      LAUNCH_CHECK();
+      std::swap(vp, v);                   // vp <- v
+      hipLaunchKernelGGL(lanczos_scale_kernel, dim3(kRedGroups), dim3(256), 0, s, v, w, rows, norms, sc + steps + j);
+      LAUNCH_CHECK();
+    }
+    CHFSI_HIP(hipMemcpyAsync(h.data(), sc, n_sc * sizeof(double), hipMemcpyDeviceToHost, s));
+    CHFSI_HIP(hipStreamSynchronize(s));
+    n0 = h[2 * steps];
+    if (!(n0 > 0.0 && std::isfinite(n0))) return;
+    for (int j = done; j < j1 && !ended; ++j) {
+      al.push_back(h[j]);
+      bn.push_back(h[steps + j]);
+      ended = !(h[steps + j] > 0.0);
+    }
+    done = j1;
+  }
 }
 
 // ============================================================================

@@ -61,3 +61,30 @@ def test_split_contraction_matches_whole_chunks(lmax, k):
         err = (y[:, 0] - Y[:, c]).abs().max() / Y[:, c].abs().max()
         assert float(err) <= 64 * np.finfo(float).eps, float(err)
     op.close()
+
+
+@pytest.mark.parametrize("n", [2, 3, 33, 2100])
+def test_coefficient_tiles_match_single_columns(n):
+    """1, 4 and 16 columns per workgroup of the coefficient sums (2100: 16), last
+    tiles ragged; the bound of the module's text."""
+    op = _op((4, 4, 3), 3, 0.2, "cell")
+    X = torch.tensor(synth.random_block(7, op.n_dof, n), device="cuda")
+    Y = op.apply_H(X, torch.empty_like(X))
+    for c in {0, n // 2, n - 1}:
+        x = X[:, c:c + 1].contiguous()
+        y = op.apply_H(x, torch.empty_like(x))
+        torch.cuda.synchronize()
+        assert torch.max((y - Y[:, c:c + 1]).abs()) <= 64 * np.finfo(float).eps * torch.max(Y.abs())
+    op.close()
+
+
+def test_lanczos_start_vector_checks():
+    from paper_2410_02754_amd import ChfsiError
+    op = _op((2, 2, 2), 3, 0.0, "cell")
+    for bad in (0.0, float("nan"), float("inf")):
+        with pytest.raises(ChfsiError):
+            op.lanczos_bounds(torch.full((op.n_dof,), bad, dtype=torch.complex128, device="cuda"), 40)
+    v = torch.tensor(synth.random_block(8, op.n_dof, 1)[:, 0], device="cuda")
+    lo, hi = op.lanczos_bounds(v, 33)
+    assert lo < hi and op.lanczos_bounds(v, 33) == (lo, hi)
+    op.close()
