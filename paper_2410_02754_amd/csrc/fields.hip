@@ -43,24 +43,31 @@ __device__ __forceinline__ double block_sum(double v, double* sm) {
   __syncthreads();
   return (sm[0] + sm[1]) + (sm[2] + sm[3]);
 }
-__device__ __forceinline__ double partial_sum(const double* __restrict__ p, int n, double* sm) {
-  double v = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) v += p[i];
-  return block_sum(v, sm);
+// NS such sums at once: the 256 threads' v[k], to every thread in v[k]
+template <int NS>
+__device__ __forceinline__ void block_sums(double (&v)[NS], double* sm) {
+#pragma unroll
+  for (int k = 32; k > 0; k >>= 1)
+#pragma unroll
+    for (int i = 0; i < NS; ++i) v[i] += __shfl_xor(v[i], k);
+  __syncthreads();                        // sm is free
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int i = 0; i < NS; ++i) sm[4 * i + (threadIdx.x >> 6)] = v[i];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NS; ++i) v[i] = (sm[4 * i] + sm[4 * i + 1]) + (sm[4 * i + 2] + sm[4 * i + 3]);
 }
 
 // ---- Conjugate gradients, two kernels per step, scalars on the device.  A step was
 // a fill, a launch per colour, ten vector kernels and three round trips to the host
-// (about 130 us on 4^3 cells, p = 4); these two take 12.4 us.  red: [kCgDots][kFieldRed]
+// (about 130 us on 4^3 cells, p = 4); these two take 9.4 us.  red: [kCgDots][kFieldRed]
 // partial sums (p.Ap; r.r and r.z of even and odd steps; b.b), then the state: the
 // number of steps when r.r reached the tolerance, or -1.
 constexpr int kCgDots = 6, kCgPq = 0, kCgRr = 1, kCgRz = 3, kCgBb = 5;
-__device__ __forceinline__ const double* cg_dot(const double* red, int k) { return red + k * kFieldRed; }
-// whether a step before has stopped the iteration, the same for the whole workgroup
-__device__ __forceinline__ bool cg_stopped(const double* red, double* sm) {
-  if (threadIdx.x == 0) sm[0] = red[kCgDots * kFieldRed];
-  __syncthreads();
-  return sm[0] >= 0.0;
+// this thread's partial sum of dot k (n <= kFieldRed = 256 parts)
+__device__ __forceinline__ double cg_part(const double* __restrict__ red, int k, int n) {
+  return (int)threadIdx.x < n ? red[k * kFieldRed + threadIdx.x] : 0.0;
 }
 
 // 1 / diag(A) at node (ax, ay, az) of a cell's frame (a < p in each direction)
@@ -105,52 +112,86 @@ __global__ __launch_bounds__(256) void cg_start_kernel(const ScalMesh m, double 
 // nodes owned by a cell (local index < p in each direction): the frame of
 // (2p + 1)^3 nodes around them is read into LDS and contracted with the row tables
 // along z, y and x; the mass and stiffness parts that the other directions need go
-// along, scaled at the end.
+// along, scaled at the end.  On a small mesh a step is a chain of trips to memory: the
+// state, the partial sums and the first cell's frame are all asked for at once
+// (5.9 us on 4^3 cells, p = 4, and the update 3.5; 8.8 and 4.1 one after the other).
+template <int P>
 __global__ __launch_bounds__(256) void cg_apply_kernel(const ScalMesh m, double kappa2, int n_cells, int n_part,
                                                        int it, double tol, const double* __restrict__ z,
                                                        const double* __restrict__ p_old, double* __restrict__ p_new,
                                                        double* __restrict__ q, double* __restrict__ red) {
   extern __shared__ double fsm[];
-  __shared__ double sm[4];
+  __shared__ double sm[16];
   const int odd = it & 1;
-  if (cg_stopped(red, sm)) return;
-  const double rr = partial_sum(cg_dot(red, kCgRr + odd), n_part, sm);
-  const double bb = partial_sum(cg_dot(red, kCgBb), n_part, sm);
+  constexpr int p = P, w = 2 * p + 1, w3 = w * w * w;
+  constexpr int kCgPre = w3 <= 1024 ? (w3 + 255) / 256 : 4;       // frame values per thread fetched ahead
+  const double state = red[kCgDots * kFieldRed];
+  double d[4] = {cg_part(red, kCgRr + odd, n_part), cg_part(red, kCgBb, n_part), cg_part(red, kCgRz + odd, n_part),
+                 it > 0 ? cg_part(red, kCgRz + 1 - odd, n_part) : 0.0};
+  const auto node = [&](int e, int t) {   // frame entry t of cell e
+    const int cx = e % m.nx, cyz = e / m.nx, cy = cyz % m.ny, cz = cyz / m.ny;
+    const int fx = t % w, fy = (t / w) % w, fz = t / (w * w);
+    int ix = cx * p + fx - p, iy = cy * p + fy - p, iz = cz * p + fz - p;
+    ix = ix < 0 ? ix + m.Nx : ix >= m.Nx ? ix - m.Nx : ix;
+    iy = iy < 0 ? iy + m.Ny : iy >= m.Ny ? iy - m.Ny : iy;
+    iz = iz < 0 ? iz + m.Nz : iz >= m.Nz ? iz - m.Nz : iz;
+    return ix + (int64_t)m.Nx * (iy + (int64_t)m.Ny * iz);
+  };
+  double zf[kCgPre], pf[kCgPre];
+#pragma unroll
+  for (int k = 0; k < kCgPre; ++k) {
+    const int t = threadIdx.x + 256 * k;
+    const int64_t I = node(blockIdx.x, t < w3 ? t : 0);
+    zf[k] = z[I];
+    pf[k] = it > 0 ? p_old[I] : 0.0;
+  }
+  double* sR = fsm;                       // [2][p][w] row tables
+  double* sX = sR + 2 * p * w;            // [w][w][w] frame (x fastest), then [2][w (y)][w (x)][p (z)] ...
+  double* sM = sX + w3;                   // [p][w][w] mass part along z, then [p][p][w]
+  double* sS = sM + p * w * w;            // stiffness part, likewise
+  for (int t = threadIdx.x; t < 2 * p * w; t += 256) sR[t] = m.rows[t];
+  block_sums(d, sm);
+  if (state >= 0.0) return;               // a step before has stopped the iteration
+  const double rr = d[0], bb = d[1];
   if (bb == 0.0 || (it > 0 && sqrt(rr) / sqrt(bb) <= tol)) {
     if (blockIdx.x == 0 && threadIdx.x == 0) red[kCgDots * kFieldRed] = (double)it;
     return;
   }
-  const double beta = it == 0 ? 0.0
-                              : partial_sum(cg_dot(red, kCgRz + odd), n_part, sm) /
-                                    partial_sum(cg_dot(red, kCgRz + 1 - odd), n_part, sm);
-  const int p = m.p, w = 2 * p + 1;
-  double* sR = fsm;                       // [2][p][w] row tables
-  double* sX = sR + 2 * p * w;            // [w][w][w] frame (x fastest), then [2][w (y)][w (x)][p (z)] ...
-  double* sM = sX + w * w * w;            // [p][w][w] mass part along z, then [p][p][w]
-  double* sS = sM + p * w * w;            // stiffness part, likewise
-  for (int t = threadIdx.x; t < 2 * p * w; t += 256) sR[t] = m.rows[t];
+  const double beta = it == 0 ? 0.0 : d[2] / d[3];
   const double* rS = sR;
   const double* rM = sR + p * w;
   double pq = 0.0;
   for (int e = blockIdx.x; e < n_cells; e += gridDim.x) {
-    const int cx = e % m.nx, cyz = e / m.nx, cy = cyz % m.ny, cz = cyz / m.ny;
-    __syncthreads();                      // the last cell's sX is read
-    for (int t = threadIdx.x; t < w * w * w; t += 256) {
+    const bool first = e == (int)blockIdx.x;
+    if (!first) __syncthreads();          // the last cell's sX is read
+    const auto put = [&](int t, double zv, double pv) {
+      const double v = it == 0 ? zv : fma(beta, pv, zv);
       const int fx = t % w, fy = (t / w) % w, fz = t / (w * w);
-      int ix = cx * p + fx - p, iy = cy * p + fy - p, iz = cz * p + fz - p;
-      ix = ix < 0 ? ix + m.Nx : ix >= m.Nx ? ix - m.Nx : ix;
-      iy = iy < 0 ? iy + m.Ny : iy >= m.Ny ? iy - m.Ny : iy;
-      iz = iz < 0 ? iz + m.Nz : iz >= m.Nz ? iz - m.Nz : iz;
-      const int64_t I = ix + (int64_t)m.Nx * (iy + (int64_t)m.Ny * iz);
-      const double v = it == 0 ? z[I] : fma(beta, p_old[I], z[I]);
       sX[t] = v;
-      if (fx >= p && fx < 2 * p && fy >= p && fy < 2 * p && fz >= p && fz < 2 * p) p_new[I] = v;
+      if (fx >= p && fx < 2 * p && fy >= p && fy < 2 * p && fz >= p && fz < 2 * p) p_new[node(e, t)] = v;
+    };
+    if (first) {
+#pragma unroll
+      for (int k = 0; k < kCgPre; ++k)
+        if ((int)threadIdx.x + 256 * k < w3) put(threadIdx.x + 256 * k, zf[k], pf[k]);
+    }
+    for (int t = threadIdx.x + (first ? 256 * kCgPre : 0); t < w3; t += 256) {
+      const int64_t I = node(e, t);
+      put(t, z[I], it > 0 ? p_old[I] : 0.0);
     }
     __syncthreads();
+    double own[2];                        // the values of this thread's own nodes
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int t = min((int)threadIdx.x + 256 * k, p * p * p - 1), a = t % p, bc = t / p;
+      own[k] = sX[p + a + w * (p + bc % p + w * (p + bc / p))];
+    }
     for (int t = threadIdx.x; t < p * w * w; t += 256) {          // along z: M, S
       const int xy = t % (w * w), a = t / (w * w);
       double vm = 0.0, vs = 0.0;
-      for (int j = a == 0 ? 0 : p; j < w; ++j) {                  // (rows a > 0 stay in the cell)
+#pragma unroll
+      for (int j = 0; j < w; ++j) {
+        if (j < p && a > 0) continue;     // (rows a > 0 stay in the cell)
         const double x = sX[xy + w * w * j];
         vm = fma(rM[a * w + j], x, vm);
         vs = fma(rS[a * w + j], x, vs);
@@ -164,7 +205,9 @@ __global__ __launch_bounds__(256) void cg_apply_kernel(const ScalMesh m, double 
     for (int t = threadIdx.x; t < p * p * w; t += 256) {          // along y
       const int x = t % w, a = (t / w) % p, c = t / (w * p);
       double mm = 0.0, sm_ = 0.0, ms = 0.0;
-      for (int j = a == 0 ? 0 : p; j < w; ++j) {
+#pragma unroll
+      for (int j = 0; j < w; ++j) {
+        if (j < p && a > 0) continue;
         const double vm = sM[(c * w + j) * w + x], vs = sS[(c * w + j) * w + x];
         mm = fma(rM[a * w + j], vm, mm);
         sm_ = fma(rS[a * w + j], vm, sm_);
@@ -174,17 +217,23 @@ __global__ __launch_bounds__(256) void cg_apply_kernel(const ScalMesh m, double 
       tB[t] = m.sy * sm_ + m.sz * ms + kappa2 * mm;
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < p * p * p; t += 256) {          // along x
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {                                 // along x (p^3 <= 512)
+      const int t = threadIdx.x + 256 * k;
+      if (t >= p * p * p) break;
       const int a = t % p, bc = t / p;
       double v = 0.0, vs = 0.0;
-      for (int j = a == 0 ? 0 : p; j < w; ++j) {
+#pragma unroll
+      for (int j = 0; j < w; ++j) {
+        if (j < p && a > 0) continue;
         v = fma(rM[a * w + j], tB[bc * w + j], v);
         vs = fma(rS[a * w + j], tA[bc * w + j], vs);
       }
+      const int cx = e % m.nx, cyz = e / m.nx, cy = cyz % m.ny, cz = cyz / m.ny;
       const int64_t I = cx * p + a + (int64_t)m.Nx * (cy * p + bc % p + (int64_t)m.Ny * (cz * p + bc / p));
       const double y = m.J * fma(m.sx, vs, v);
       q[I] = y;
-      pq = fma(it == 0 ? z[I] : fma(beta, p_old[I], z[I]), y, pq);
+      pq = fma(own[k], y, pq);
     }
   }
   pq = block_sum(pq, sm);
@@ -197,26 +246,38 @@ __global__ __launch_bounds__(256) void cg_update_kernel(const ScalMesh m, double
                                                         const double* __restrict__ q, double* __restrict__ u,
                                                         double* __restrict__ r, double* __restrict__ z,
                                                         double* __restrict__ red) {
-  __shared__ double sm[4];
-  if (cg_stopped(red, sm)) return;
+  __shared__ double sm[8];
   const int odd = it & 1;
-  const double al = partial_sum(cg_dot(red, kCgRz + odd), n_part, sm) / partial_sum(cg_dot(red, kCgPq), n_pq, sm);
-  double rr = 0.0, rz = 0.0;
-  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+  const double state = red[kCgDots * kFieldRed];
+  double d[2] = {cg_part(red, kCgRz + odd, n_part), cg_part(red, kCgPq, n_pq)};
+  const int64_t i0 = blockIdx.x * (int64_t)256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+  // this thread's first values, asked for with the sums
+  const int64_t ic = i0 < n ? i0 : n - 1;
+  double pv = p[ic], qv = q[ic], uv = u[ic], rv = r[ic];
+  block_sums(d, sm);
+  if (state >= 0.0) return;
+  const double al = d[0] / d[1];
+  double s[2] = {0.0, 0.0};
+  for (int64_t i = i0; i < n; i += step) {
+    if (i != i0) {
+      pv = p[i];
+      qv = q[i];
+      uv = u[i];
+      rv = r[i];
+    }
     const int iyz = (int)(i / m.Nx), ix = (int)(i - (int64_t)iyz * m.Nx);
-    u[i] = fma(al, p[i], u[i]);
-    const double ri = fma(-al, q[i], r[i]);
+    u[i] = fma(al, pv, uv);
+    const double ri = fma(-al, qv, rv);
     const double zi = inv_diag(m, kappa2, ix % m.p, (iyz % m.Ny) % m.p, (iyz / m.Ny) % m.p) * ri;
     r[i] = ri;
     z[i] = zi;
-    rr += ri * ri;
-    rz += ri * zi;
+    s[0] += ri * ri;
+    s[1] += ri * zi;
   }
-  rr = block_sum(rr, sm);
-  rz = block_sum(rz, sm);
+  block_sums(s, sm);
   if (threadIdx.x == 0) {
-    red[(kCgRr + 1 - odd) * kFieldRed + blockIdx.x] = rr;
-    red[(kCgRz + 1 - odd) * kFieldRed + blockIdx.x] = rz;
+    red[(kCgRr + 1 - odd) * kFieldRed + blockIdx.x] = s[0];
+    red[(kCgRz + 1 - odd) * kFieldRed + blockIdx.x] = s[1];
   }
 }
 
@@ -520,13 +581,17 @@ static int pcg(chfsi_ctx* c, FieldOps& f, double kappa2, double tol, int max_ite
   const int n_pq = std::min(kFieldRed, c->n_cells);
   const int p = c->p, w = 2 * p + 1;
   const size_t sh = (size_t)(2 * p * w + w * w * w + 2 * p * w * w) * sizeof(double);
+  static constexpr decltype(&cg_apply_kernel<1>) kApply[] = {cg_apply_kernel<1>, cg_apply_kernel<2>, cg_apply_kernel<3>,
+                                                             cg_apply_kernel<4>, cg_apply_kernel<5>, cg_apply_kernel<6>,
+                                                             cg_apply_kernel<7>, cg_apply_kernel<8>};
+  static_assert(sizeof kApply / sizeof *kApply == kMaxP, "one per order");
   hipLaunchKernelGGL(cg_start_kernel, dim3(n_part), dim3(256), 0, c->stream, f.mesh, kappa2, n, b, u, r, z, f.red.ptr);
   LAUNCH_CHECK();
   std::vector<double> h((size_t)kCgDots * kFieldRed + 1);
   for (int it = 0;;) {
     const int end = std::min(max_iter, it + kCgBatch);
     for (; it < end; ++it) {
-      hipLaunchKernelGGL(cg_apply_kernel, dim3(n_pq), dim3(256), sh, c->stream, f.mesh, kappa2, c->n_cells, n_part,
+      hipLaunchKernelGGL(kApply[p - 1], dim3(n_pq), dim3(256), sh, c->stream, f.mesh, kappa2, c->n_cells, n_part,
                          it, tol, z, pp[1 - (it & 1)], pp[it & 1], q, f.red.ptr);
       LAUNCH_CHECK();
       hipLaunchKernelGGL(cg_update_kernel, dim3(n_part), dim3(256), 0, c->stream, f.mesh, kappa2, n, n_part, n_pq, it,
