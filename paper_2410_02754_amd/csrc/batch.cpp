@@ -268,7 +268,10 @@ int chfsi_batch_create(int n_tasks, const chfsi_batch_task* tasks, int degree, i
       }
     }
     // small tasks: their applies run by cells in the batch's precision, and their
-    // scratch (ye and the nonlocal sums, 256-byte aligned) fits kSmallBytes together
+    // scratch (ye and the nonlocal sums, 256-byte aligned) fits kSmallBytes together.
+    // Not those of one column: their kernels (nl_contract_one, init_one) beside the
+    // others in the joint ones would cost those registers (127 against 110, 109
+    // against 97) for a batch that filters single columns.
     constexpr size_t kSmallBytes = (size_t)4 << 30;
     b->small.assign(n_tasks, 0);
     b->ye.assign(n_tasks, nullptr);
@@ -280,7 +283,7 @@ int chfsi_batch_create(int n_tasks, const chfsi_batch_task* tasks, int degree, i
       // (ye holds either precision: the last step is FP64)
       const size_t ye = up(products_scratch_bytes(tk.ctx, tk.n_vec, true));
       const size_t nl = up(nonlocal_scratch_bytes(*b->kps[t], tk.n_vec));
-      if (ye == 0 || small_bytes + ye + nl > kSmallBytes) continue;
+      if (ye == 0 || tk.n_vec == 1 || small_bytes + ye + nl > kSmallBytes) continue;
       b->small[t] = 1;
       ye_off[t] = small_bytes;
       nl_off[t] = small_bytes + ye;

@@ -111,7 +111,7 @@ constexpr int nl_col_blocks() { return sizeof(T) == 8 ? 1 : 2; }
 // A chunk is cut into nsub parts (partial[chunk * nsub + part]) where whole
 // chunks are too few waves to fill the GPU: a wave walks its entries 16 at a
 // time, each step a trip to memory, so 512 entries of a narrow block are a chain
-// of 32 trips that eight parts cut to four (16 atoms, one column: 39 us).
+// of 32 trips that eight parts cut to four.
 template <class T>
 struct NlContractArgs {
   const typename C2<T>::type* proj;
@@ -272,6 +272,77 @@ __device__ __forceinline__ void nl_contract_wave(const NlContractArgs<T>& g, int
       }
     }
   }
+}
+
+// The same for a block of one column: 64 entries at a time, one per lane, and the sums
+// over the lanes by halving (32 lanes keep one half of the values, 32 the other, and
+// so on), so that four projectors take 17 exchanges.  The matrix-unit form loads each
+// x sixteen times over, 12 wave loads for 16 entries against 6 for 64: 16 atoms,
+// 250000 rows 39 -> 19 us.
+template <class T, bool REALP>
+__device__ __forceinline__ void nl_contract_one(const NlContractArgs<T>& g, int wid) {
+  typedef typename C2<T>::type CT;
+  const int lane = threadIdx.x & 63, max_pj = g.max_pj;
+  const int oi = wid / g.nsub, sub = wid - oi * g.nsub;
+  const int ch = g.chunk_order[oi];
+  const int a = g.chunk_atom[ch], cb0 = g.chunk_begin[ch], ce0 = g.chunk_end[ch];
+  const int part = ((ce0 - cb0 + g.nsub - 1) / g.nsub + 15) / 16 * 16;   // as in the block form
+  const int b = cb0 + sub * part, e = min(ce0, b + part);
+  const int npj = g.atom_npj[a];
+  T s[kMaxPj][4];                         // [chi][spin][re, im]
+#pragma unroll
+  for (int x = 0; x < kMaxPj; ++x) s[x][0] = s[x][1] = s[x][2] = s[x][3] = (T)0;
+  for (int j = b + lane; j < e; j += 64) {
+    const double2* __restrict__ xr = g.X + 2 * (int64_t)g.sup_node[j] * g.ldx;
+    const CT* __restrict__ pr = g.proj + (size_t)j * max_pj;
+    CT pv[kMaxPj];
+#pragma unroll
+    for (int x = 0; x < kMaxPj; ++x)
+      if (x < npj) pv[x] = pr[x];
+    const double2 u = xr[0], d = xr[g.ldx];
+    const T v[4] = {(T)u.x, (T)u.y, (T)d.x, (T)d.y};
+#pragma unroll
+    for (int x = 0; x < kMaxPj; ++x)
+      if (x < npj) {
+#pragma unroll
+        for (int sp = 0; sp < 2; ++sp) {
+          s[x][2 * sp] += pv[x].x * v[2 * sp];
+          s[x][2 * sp + 1] += pv[x].x * v[2 * sp + 1];
+          if (!REALP) {
+            s[x][2 * sp] += pv[x].y * v[2 * sp + 1];
+            s[x][2 * sp + 1] -= pv[x].y * v[2 * sp];
+          }
+        }
+      }
+  }
+  T* out = reinterpret_cast<T*>(g.partial + ((size_t)ch * g.nsub + sub) * 2 * max_pj);
+#pragma unroll
+  for (int x0 = 0; x0 < kMaxPj; x0 += 4) {
+    if (x0 >= npj) break;
+    T v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = x0 + k / 4 < kMaxPj ? s[x0 + k / 4 < kMaxPj ? x0 + k / 4 : 0][k % 4] : (T)0;
+#pragma unroll
+    for (int h = 8, d = 32; h > 0; h /= 2, d /= 2) {
+      const bool up = lane & d;
+#pragma unroll
+      for (int k = 0; k < h; ++k) {
+        const T keep = up ? v[k + h] : v[k], send = up ? v[k] : v[k + h];
+        v[k] = keep + __shfl_xor(send, d);
+      }
+    }
+    v[0] += __shfl_xor(v[0], 2);
+    v[0] += __shfl_xor(v[0], 1);
+    // lane bits 5..2, the highest first, are the value's index
+    const int k = lane >> 2;
+    if ((lane & 3) == 0 && x0 + k / 4 < npj) out[4 * x0 + k] = v[0];
+  }
+}
+
+template <class T, bool REALP>
+__global__ __launch_bounds__(256) void nl_contract_one_kernel(const NlContractArgs<T> g) {
+  const int wid = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  if (wid < g.n_work) nl_contract_one<T, REALP>(g, wid);
 }
 
 template <class T, bool REALP, bool PACK = false>
@@ -627,6 +698,104 @@ __device__ __forceinline__ void init_nl_wave(const InitArgs<T>& g, int wid) {
   }
 }
 
+// The same for a block of one column, on the vector units: lane = (half of the run's
+// atoms, node, spin), the halves meet by lane exchange.  The matrix-unit form spends
+// 15 of 16 columns of every load on copies: 16 atoms, 250000 rows 40 -> 23 us.
+template <class T>
+__device__ __forceinline__ void init_one(const InitArgs<T>& g, int wid, int fl, bool realp) {
+  typedef typename C2<T>::type CT;
+  const int lane = threadIdx.x & 63, half = lane >> 5, il = (lane & 31) >> 1, sp = lane & 1;
+  const int64_t node = (int64_t)wid * kNlRun + il;
+  const bool nv = node < g.n_nodes;
+  const int64_t nd = nv ? node : g.n_nodes - 1, row = 2 * nd + sp;
+  const double beta = g.bg_d ? g.bg_d[0] : g.beta, gamma = g.bg_d ? g.bg_d[1] : g.gamma;
+  double2 o = {0.0, 0.0}, xv = {0.0, 0.0}, rv = {0.0, 0.0};
+  if (fl & kInitBeta) o = g.Wold[row * g.ldo];
+  if (fl & kInitGamma) xv = g.X[row * g.ldx];
+  if (fl & kInitRs) rv = g.Rs[row * g.ldr];
+  CT s = {(T)0, (T)0};
+  if (g.has_nl) {
+    const int p1 = g.run_off[wid + 1];
+    int pr = g.run_off[wid] + half;
+    int a = pr < p1 ? g.pair_atom[pr] : 0, ent = pr < p1 ? g.pair_ent[(size_t)pr * kNlRun + il] : -1;
+    for (; pr < p1; pr += 2) {
+      const int npj = g.atom_npj[a];
+      const CT* __restrict__ cp = g.Cp + (size_t)a * 2 * g.max_pj + sp;
+      const CT* __restrict__ pp = g.proj + (size_t)(ent < 0 ? 0 : ent) * g.max_pj;
+      const bool in = ent >= 0;
+      CT pv[kMaxPj], cv[kMaxPj];
+#pragma unroll
+      for (int x = 0; x < kMaxPj; ++x)
+        if (x < npj) {
+          pv[x] = pp[x];
+          cv[x] = cp[2 * x];
+        }
+      if (pr + 2 < p1) {                  // the next atom, with these in flight
+        a = g.pair_atom[pr + 2];
+        ent = g.pair_ent[(size_t)(pr + 2) * kNlRun + il];
+      }
+      if (in)
+#pragma unroll
+        for (int x = 0; x < kMaxPj; ++x)
+          if (x < npj) {
+            s.x += pv[x].x * cv[x].x;
+            s.y += pv[x].x * cv[x].y;
+            if (!realp) {
+              s.x -= pv[x].y * cv[x].y;
+              s.y += pv[x].y * cv[x].x;
+            }
+          }
+    }
+    s.x += __shfl_xor(s.x, 32);
+    s.y += __shfl_xor(s.y, 32);
+  }
+  if (half != 0) return;
+  double2 t = {(double)s.x, (double)s.y};
+  if (fl & kInitBeta) {
+    t.x += beta * o.x;
+    t.y += beta * o.y;
+  }
+  if (fl & kInitGamma) {
+    t.x += gamma * xv.x;
+    t.y += gamma * xv.y;
+  }
+  if (fl & kInitRs) {
+    t.x += g.rscale[0] * rv.x;
+    t.y += g.rscale[0] * rv.y;
+  }
+  if (g.ye) {                             // as in the block form
+    const MeshShape& ms = g.mesh;
+    const int n = (int)nd, nloc = ms.np1 * ms.np1 * ms.np1;
+    const double alpha = g.alpha_d ? *g.alpha_d : g.alpha;
+    const double sc = g.msc ? alpha * g.msc[n] : alpha;
+    const int iyz = n / ms.Nx, ix = n - iyz * ms.Nx;
+    const int iz = iyz / ms.Ny, iy = iyz - iz * ms.Ny;
+    int rx[2], ry[2], rz[2];
+    const int kx = dir_rows(ix, ms.p, ms.nx, nloc, 1, rx);
+    const int ky = dir_rows(iy, ms.p, ms.ny, nloc * ms.nx, ms.np1, ry);
+    const int kz = dir_rows(iz, ms.p, ms.nz, nloc * ms.nx * ms.ny, ms.np1 * ms.np1, rz);
+    CT yv[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {         // all in flight (x fastest; absent ones repeat another)
+      const int x = (k & 1) < kx ? k & 1 : 0, y = (k >> 1 & 1) < ky ? k >> 1 & 1 : 0, z = k >> 2 < kz ? k >> 2 : 0;
+      yv[k] = g.ye[(size_t)(rx[x] + ry[y] + rz[z]) * 2 + sp];
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if ((k & 1) < kx && (k >> 1 & 1) < ky && k >> 2 < kz) {
+        t.x = fma(sc, (double)yv[k].x, t.x);
+        t.y = fma(sc, (double)yv[k].y, t.y);
+      }
+  }
+  if (nv) g.W[row * g.ldw] = t;
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void init_one_kernel(const InitArgs<T> g, int fl, int realp) {
+  const int wid = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  if (wid < g.n_work) init_one<T>(g, wid, fl, realp);
+}
+
 template <class T, int FL, bool REALP, bool GATHER>
 __global__ __launch_bounds__(256) void init_nl_kernel(const InitArgs<T> g) {
   const int wid = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
@@ -727,7 +896,11 @@ static const typename C2<T>::type* nonlocal_coeffs(chfsi_ctx* c, NonlocalK& nl,
     const int gc = std::min(group, n_vec - c0);
     const NlContractArgs<T> ca = contract_args<T>(nl, proj, X + c0, ldx, gc, nsub, partial);
     const dim3 cgrid(8 * cdiv(cdiv(ca.n_work, 4), 8));
-    if (nl.real_proj)
+    if (n_vec == 1 && nl.real_proj)
+      hipLaunchKernelGGL((nl_contract_one_kernel<T, true>), cgrid, dim3(256), 0, c->stream, ca);
+    else if (n_vec == 1)
+      hipLaunchKernelGGL((nl_contract_one_kernel<T, false>), cgrid, dim3(256), 0, c->stream, ca);
+    else if (nl.real_proj)
       hipLaunchKernelGGL((nl_contract_kernel<T, true>), cgrid, dim3(256), 0, c->stream, ca);
     else if (pack_rows(nl))
       hipLaunchKernelGGL((nl_contract_kernel<T, false, true>), cgrid, dim3(256), 0, c->stream, ca);
@@ -788,6 +961,11 @@ static void launch_init(chfsi_ctx* c, const InitArgs<T>& g, const NonlocalK& nl)
                     (1.0 + (g.beta != 0.0) + (g.gamma != 0.0)));
   const int fl = (g.beta != 0.0 ? kInitBeta : 0) | (g.gamma != 0.0 ? kInitGamma : 0) | (g.Rs ? kInitRs : 0);
   const dim3 grid(cdiv(g.n_work, 4)), blk(256);
+  if (g.n_vec == 1) {
+    hipLaunchKernelGGL((init_one_kernel<T>), grid, blk, 0, c->stream, g, fl, realp ? 1 : 0);
+    LAUNCH_CHECK();
+    return;
+  }
 #define INIT_NL_LAUNCH(F, RP, GA) hipLaunchKernelGGL((init_nl_kernel<T, F, RP, GA>), grid, blk, 0, c->stream, g)
 #define INIT_NL_CASE(F)                     \
   case F:                                   \
@@ -2523,8 +2701,8 @@ __global__ __launch_bounds__(256) void lanczos_scale_kernel(double2* __restrict_
 
 // alpha_j and |w_j| of up to `steps` steps from v0 (those up to the first |w_j| that is
 // not positive), and |v0|.  20 steps on 250000 rows with 16 atoms were 4.0 ms with two
-// trips to the host and five vector kernels a step, 2.4 ms with these three (and the
-// narrower coefficient tiles); the product with H is 105 of a step's 120 us.
+// trips to the host and five vector kernels a step, 2.4 ms with these three and the
+// narrower coefficient tiles, 1.6 ms with the one-column product; the product with H is 68 of a step's 82 us.
 void lanczos_steps(chfsi_ctx* c, KPoint& kp, const double2* v0, int steps, double& n0, std::vector<double>& al,
                    std::vector<double>& bn) {
   const int64_t rows = 2 * c->n_nodes;

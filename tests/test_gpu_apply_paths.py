@@ -88,3 +88,33 @@ def test_lanczos_start_vector_checks():
     lo, hi = op.lanczos_bounds(v, 33)
     assert lo < hi and op.lanczos_bounds(v, 33) == (lo, hi)
     op.close()
+
+
+@pytest.mark.parametrize("lmax,k,form,prec", [(0, 0.0, "cell", "fp64"), (1, 0.2, "matrix_free", "mixed"),
+                                              (2, 0.0, "matrix_free", "fp64"), (2, 0.2, "cell", "mixed")])
+def test_one_column_matches_block(lmax, k, form, prec):
+    """The one-column kernels against a column of a block, with and without the gather
+    and the residual term.  Single precision rounds sums of at most 2000 terms: 64
+    units of its last place, as in double; the residual filter of degree 3 multiplies
+    by three growth factors below 4."""
+    op = _op((3, 4, 2), 4, k, form, lmax)
+    ulp = np.finfo(np.float32 if prec == "mixed" else np.float64).eps
+    X = torch.tensor(synth.random_block(9, op.n_dof, 20), device="cuda")
+    R = torch.tensor(synth.random_block(10, op.n_dof, 20), device="cuda")
+    x, r = X[:, 3:4].contiguous(), R[:, 3:4].contiguous()
+    Y, y = op.apply_H(X, torch.empty_like(X), prec=prec), op.apply_H(x, torch.empty_like(x), prec=prec)
+    assert torch.max((y - Y[:, 3:4]).abs()) <= 64 * ulp * torch.max(Y.abs())
+    Z, z, w = X.clone(), x.clone(), torch.empty_like(x)
+    op.cheb_filter(z, w, 3, 8.0, 900.0, -6.0, prec=prec)
+    zn = x.clone()
+    op.cheb_filter_noalloc(zn, w, 3, 8.0, 900.0, -6.0, prec=prec)
+    assert torch.equal(z, zn)
+    th = np.linspace(0.5, 4.0, 20)
+    op.cheb_filter_resid(Z, R, th, torch.empty((op.n_dof, 40), dtype=X.dtype, device="cuda"), 3, 8.0, 900.0, -6.0,
+                         prec=prec)
+    z = x.clone()
+    op.cheb_filter_resid(z, r, th[3:4].copy(), torch.empty((op.n_dof, 2), dtype=X.dtype, device="cuda"), 3, 8.0, 900.0,
+                         -6.0, prec=prec)
+    torch.cuda.synchronize()
+    assert torch.max((z - Z[:, 3:4]).abs()) <= 64 * 64 * ulp * torch.max(Z.abs())
+    op.close()

@@ -16,7 +16,9 @@ KINDS = [((2, 2, 2), 3, 1, 0.2, 5, "cell"),
          ((2, 3, 3), 2, 2, 0.0, 33, "cell"),
          ((2, 2, 3), 5, None, 0.1, 1, "cell"),
          ((3, 3, 2), 3, 1, 0.1, 20, "matrix_free"),
-         ((2, 2, 2), 6, 2, 0.0, 130, "matrix_free")]
+         ((2, 2, 2), 6, 2, 0.0, 130, "matrix_free"),
+         ((2, 2, 2), 4, 2, 0.1, 1, "cell"),
+         ((2, 3, 2), 3, 1, 0.0, 1, "matrix_free")]
 LARGE = ((41, 41, 41), 1, 0, 0.0, 2, "cell")     # 68921 workgroups in eight colours
 
 
@@ -43,8 +45,8 @@ def test_small_tasks_equal_per_task_bitwise(prec, degree, graph, large):
         kinds = KINDS + ([LARGE] if large else [])
         ops = [_op(k, stream) for k in kinds]
         tasks = []
-        for t in range(6 * 6 + len(kinds)):                # 42 or 43
-            j = t % 6 if t < 42 else 6
+        for t in range(5 * len(KINDS) + (1 if large else 0)):       # more than 32
+            j = t % len(KINDS) if t < 5 * len(KINDS) else len(KINDS)
             X = torch.tensor(synth.random_block(t, ops[j].n_dof, kinds[j][4]), device="cuda")
             tasks.append((ops[j], 0, X, torch.empty_like(X)))
         X0 = [t[2].clone() for t in tasks]
