@@ -10,6 +10,7 @@
 #include <atomic>
 #include <cmath>
 #include <functional>
+#include <memory>
 #include <numeric>
 #include <thread>
 
@@ -73,20 +74,187 @@ class Pool {
   const std::function<void(int, int)>* f_ = nullptr;
 };
 
-// Implicit QL on the real symmetric tridiagonal (d, e), e[i] couples i, i+1.
-// Zt[i][:] accumulates eigenvector i (rows), starting from the identity.  The
-// rotations only act on Zt, so they are recorded in order and applied after the
-// iteration, each worker applying all of them to its own range of columns.  One
-// QL step is a chain of rotations of rows (i, i+1), i = m-1 down to l; along the
-// chain the updated row i is the next rotation's row i+1, so it stays in
-// registers ("carry") and each rotation costs one row load and one row store.
-static void tridiag_ql(std::vector<double>& d, std::vector<double>& e, std::vector<double>* Zt, int n,
-                       Pool* pool) {
+// Inner loops, compiled twice: for processors with AVX2 and FMA and for any (chosen
+// at run time).  Complex numbers are interleaved (re, im), a vector holds two.
+typedef double v4 __attribute__((vector_size(32), aligned(8), may_alias));
+
+#define CHFSI_DENSE_KERNELS(NAME, ATTR)                                                                               \
+  struct NAME {                                                                                                       \
+    /* A -= (a + i b) conj(q) + (e + i f) conj(v); out = sum of the new A times x */                                  \
+    ATTR static void update_dot(double* __restrict__ A, int n2, const double* q, const double* v, const double* x,    \
+                                double a, double b, double e, double f, double* out) {                                \
+      const v4 a4 = {a, -a, a, -a}, e4 = {e, -e, e, -e};                                                              \
+      v4 s1[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}}, s2[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};                                  \
+      int j = 0;                                                                                                      \
+      for (; j + 8 <= n2; j += 8)                                                                                     \
+        for (int u = 0; u < 2; ++u) {                                                                                 \
+          const int k = j + 4 * u;                                                                                    \
+          const v4 qk = *(const v4*)(q + k), vk = *(const v4*)(v + k), xk = *(const v4*)(x + k);                      \
+          const v4 y = *(const v4*)(A + k) - (a4 * qk + b * __builtin_shufflevector(qk, qk, 1, 0, 3, 2) + e4 * vk +   \
+                                              f * __builtin_shufflevector(vk, vk, 1, 0, 3, 2));                       \
+          *(v4*)(A + k) = y;                                                                                          \
+          s1[u] += y * __builtin_shufflevector(xk, xk, 0, 0, 2, 2);                                                   \
+          s2[u] += y * __builtin_shufflevector(xk, xk, 1, 1, 3, 3);                                                   \
+        }                                                                                                             \
+      const v4 t1 = s1[0] + s1[1], t2 = s2[0] + s2[1];                                                                \
+      double r1 = t1[0] + t1[2], i1 = t1[1] + t1[3], r2 = t2[0] + t2[2], i2 = t2[1] + t2[3];                          \
+      for (; j < n2; j += 2) {                                                                                        \
+        const double yr = A[j] - (a * q[j] + b * q[j + 1] + e * v[j] + f * v[j + 1]);                                 \
+        const double yi = A[j + 1] - (b * q[j] - a * q[j + 1] + f * v[j] - e * v[j + 1]);                             \
+        A[j] = yr;                                                                                                    \
+        A[j + 1] = yi;                                                                                                \
+        r1 += yr * x[j];                                                                                              \
+        i1 += yi * x[j];                                                                                              \
+        r2 += yr * x[j + 1];                                                                                          \
+        i2 += yi * x[j + 1];                                                                                          \
+      }                                                                                                               \
+      out[0] = r1 - i2;                                                                                               \
+      out[1] = i1 + r2;                                                                                               \
+    }                                                                                                                 \
+    /* y += (ar + i ai) x over n2 doubles */                                                                          \
+    ATTR static void caxpy(double* __restrict__ y, const double* __restrict__ x, double ar, double ai, int n2) {      \
+      const v4 w = {-ai, ai, -ai, ai};                                                                                \
+      int j = 0;                                                                                                      \
+      for (; j + 4 <= n2; j += 4) {                                                                                   \
+        const v4 u = *(const v4*)(x + j);                                                                             \
+        *(v4*)(y + j) += ar * u + w * __builtin_shufflevector(u, u, 1, 0, 3, 2);                                      \
+      }                                                                                                               \
+      for (; j < n2; j += 2) {                                                                                        \
+        y[j] += ar * x[j] - ai * x[j + 1];                                                                            \
+        y[j + 1] += ar * x[j + 1] + ai * x[j];                                                                        \
+      }                                                                                                               \
+    }                                                                                                                 \
+    /* a chain of len rotations of rows (i, i + 1), i = m - 1 down, on eight columns */                               \
+    ATTR static void rotate8(double* Z, int m, int len, const double* rc, const double* rs) {                         \
+      double* z = Z + (size_t)m * 8;                                                                                  \
+      v4 c0 = *(const v4*)z, c1 = *(const v4*)(z + 4);                                                                \
+      for (int r = 0; r < len; ++r) {                                                                                 \
+        double* up = z - 8;                                                                                           \
+        const v4 a0 = *(const v4*)up, a1 = *(const v4*)(up + 4);                                                      \
+        *(v4*)z = rs[r] * a0 + rc[r] * c0;                                                                            \
+        *(v4*)(z + 4) = rs[r] * a1 + rc[r] * c1;                                                                      \
+        c0 = rc[r] * a0 - rs[r] * c0;                                                                                 \
+        c1 = rc[r] * a1 - rs[r] * c1;                                                                                 \
+        z = up;                                                                                                       \
+      }                                                                                                               \
+      *(v4*)z = c0;                                                                                                   \
+      *(v4*)(z + 4) = c1;                                                                                             \
+    }                                                                                                                 \
+  };
+CHFSI_DENSE_KERNELS(DenseAny, )
+CHFSI_DENSE_KERNELS(DenseAvx2, __attribute__((target("avx2,fma"))))
+#undef CHFSI_DENSE_KERNELS
+
+struct DenseOps {
+  decltype(&DenseAny::update_dot) update_dot;
+  decltype(&DenseAny::caxpy) caxpy;
+  decltype(&DenseAny::rotate8) rotate8;
+};
+static DenseOps dense_ops() {
+  if (__builtin_cpu_supports("avx2") && __builtin_cpu_supports("fma"))
+    return {DenseAvx2::update_dot, DenseAvx2::caxpy, DenseAvx2::rotate8};
+  return {DenseAny::update_dot, DenseAny::caxpy, DenseAny::rotate8};
+}
+
+// sqrt(f^2 + g^2); hypot only where the squares could leave the range
+static inline double hyp(double f, double g) {
+  const double s = f * f + g * g;
+  return s > 1e-280 && s < 1e280 ? std::sqrt(s) : std::hypot(f, g);
+}
+
+// The rotations of the QL iteration on their way from the thread that finds them to
+// those that apply them, a chain (of rows (i, i + 1), i = m - 1 .. m - len) at a time.
+// When the room is used up the producer waits until every consumer has taken all.
+class RotQueue {
+ public:
+  // consumers: those at work beside the producer (0: one afterwards; the room grows)
+  RotQueue(int n, int consumers) : taken_(std::max(1, consumers)), alone_(consumers == 0) {
+    cap_ = std::max<size_t>(n, std::min<size_t>((size_t)1 << 20, 4 * (size_t)n * n + 1024));
+    rc_.reset(new double[cap_]);
+    rs_.reset(new double[cap_]);
+    chains_.reserve(cap_);
+  }
+  // room for a chain of at most n rotations
+  void open(int n) {
+    if (used_ + n <= cap_) return;
+    if (alone_) {
+      for (auto* a : {&rc_, &rs_}) {
+        std::unique_ptr<double[]> b(new double[2 * cap_]);
+        std::copy(a->get(), a->get() + used_, b.get());
+        *a = std::move(b);
+      }
+      cap_ *= 2;
+      return;
+    }
+    const int64_t all = published_.load(std::memory_order_relaxed);
+    for (auto& t : taken_)
+      for (int spin = 0; t.v.load(std::memory_order_acquire) < all; ++spin)
+        if (spin > 4096) std::this_thread::yield();
+    used_ = 0;
+    chains_.clear();
+    base_ = all;
+  }
+  void push(double c, double s) {
+    rc_[used_ + len_] = c;
+    rs_[used_ + len_] = s;
+    ++len_;
+  }
+  void close(int m) {
+    if (len_ == 0) return;
+    chains_.push_back({m, len_, used_});
+    used_ += len_;
+    len_ = 0;
+    published_.fetch_add(1, std::memory_order_release);
+  }
+  void finish() { finished_.store(true, std::memory_order_release); }
+  // f(m, len, c, s) for every chain in order, until the producer has finished
+  template <class F>
+  void consume(int who, F f) {
+    for (int64_t g = 0;;) {
+      int64_t p;
+      for (int spin = 0; (p = published_.load(std::memory_order_acquire)) == g; ++spin) {
+        if (finished_.load(std::memory_order_acquire) && published_.load(std::memory_order_acquire) == g) return;
+        if (spin > 4096) std::this_thread::yield();
+      }
+      for (; g < p; ++g) {
+        const Chain& c = chains_.data()[g - base_];
+        f(c.m, c.len, &rc_[c.off], &rs_[c.off]);
+      }
+      taken_[who].v.store(g, std::memory_order_release);
+    }
+  }
+
+ private:
+  struct Chain {
+    int m, len;
+    size_t off;
+  };
+  struct alignas(64) Count {
+    std::atomic<int64_t> v{0};
+    Count() = default;
+    Count(const Count& o) : v(o.v.load()) {}
+    Count& operator=(const Count& o) {
+      v.store(o.v.load());
+      return *this;
+    }
+  };
+  size_t cap_, used_ = 0;
+  int len_ = 0;
+  int64_t base_ = 0;
+  std::unique_ptr<double[]> rc_, rs_;
+  std::vector<Chain> chains_;   // with consumers beside the producer it never outgrows its first room
+  std::vector<Count> taken_;
+  const bool alone_;
+  std::atomic<int64_t> published_{0};
+  std::atomic<bool> finished_{false};
+};
+
+// Implicit QL on the real symmetric tridiagonal (d, e), e[i] couples i, i+1: the
+// eigenvalues in d.  out: takes the rotations, in order, or null.
+static void tridiag_ql(std::vector<double>& d, std::vector<double>& e, int n, RotQueue* out) {
   if (n == 0) return;
   e.resize(n);
   e[n - 1] = 0.0;
-  std::vector<int> ch_m, ch_len;           // chain: rotations of rows (i, i+1), i = m-1 .. m-len
-  std::vector<double> rc, rs;
   for (int l = 0; l < n; ++l) {
     int iter = 0;
     while (true) {
@@ -103,10 +271,10 @@ static void tridiag_ql(std::vector<double>& d, std::vector<double>& e, std::vect
       double s = 1.0, c = 1.0, p = 0.0;
       int i = m - 1;
       bool deflated = false;
-      const size_t first = rc.size();
+      if (out) out->open(n);
       for (; i >= l; --i) {
         double f = s * e[i], b = c * e[i];
-        r = std::hypot(f, g);
+        r = hyp(f, g);
         e[i + 1] = r;
         if (r == 0.0) {
           d[i + 1] -= p;
@@ -121,65 +289,61 @@ static void tridiag_ql(std::vector<double>& d, std::vector<double>& e, std::vect
         p = s * r;
         d[i + 1] = g + p;
         g = c * r - b;
-        if (Zt) {
-          rc.push_back(c);
-          rs.push_back(s);
-        }
+        if (out) out->push(c, s);
       }
-      if (Zt && rc.size() > first) {
-        ch_m.push_back(m);
-        ch_len.push_back((int)(rc.size() - first));
-      }
+      if (out) out->close(m);
       if (deflated) continue;
       d[l] -= p;
       e[l] = g;
       e[m] = 0.0;
     }
   }
-  if (!Zt || rc.empty()) return;
-  auto body = [&](int t, int nt) {
-    int lo, hi;
-    Pool::range(n, t, nt, lo, hi);
-    double* Z = Zt->data();
-    constexpr int B = 8;
-    for (int k0 = lo; k0 < hi; k0 += B) {
-      const int w = std::min(B, hi - k0);
-      size_t q = 0;
-      for (size_t ch = 0; ch < ch_m.size(); ++ch) {
-        const int m = ch_m[ch], len = ch_len[ch];
-        double carry[B];
-        const double* zm = Z + (size_t)m * n + k0;
-        for (int u = 0; u < B; ++u) carry[u] = u < w ? zm[u] : 0.0;
-        for (int r = 0; r < len; ++r, ++q) {
-          const int i = m - 1 - r;
-          double* __restrict__ zi = Z + (size_t)i * n + k0;
-          double* __restrict__ zj = zi + n;
-          const double c = rc[q], s = rs[q];
-          if (w == B) {
-            for (int u = 0; u < B; ++u) {
-              const double a = zi[u];
-              zj[u] = s * a + c * carry[u];
-              carry[u] = c * a - s * carry[u];
-            }
-          } else {
-            for (int u = 0; u < w; ++u) {
-              const double a = zi[u];
-              zj[u] = s * a + c * carry[u];
-              carry[u] = c * a - s * carry[u];
-            }
-          }
-        }
-        double* zl = Z + (size_t)(m - len) * n + k0;
-        for (int u = 0; u < w; ++u) zl[u] = carry[u];
-      }
-    }
-  };
-  if (pool) pool->run(body);
-  else body(0, 1);
 }
 
+// The same with eigenvector i in row i of Z, in blocks of eight columns ([block][n][8],
+// so that a block stays in the first cache), from the identity.  The rotations only act
+// on Z: the first worker finds them, the others apply them as they come, each to its
+// own blocks (alone: afterwards).  Along a chain the updated row i is the next
+// rotation's row i+1 and stays in registers.
+static void tridiag_vectors(std::vector<double>& d, std::vector<double>& e, std::vector<double>& Z, int n, Pool& pool,
+                            const DenseOps& ops) {
+  const int consumers = std::max(1, pool.size() - 1), blocks = (n + 7) / 8;
+  Z.resize((size_t)blocks * n * 8);
+  RotQueue q(n, pool.size() - 1);
+  const auto apply = [&](int who) {
+    int lo, hi;
+    Pool::range(blocks, who, consumers, lo, hi);
+    for (int b = lo; b < hi; ++b)
+      for (int u = 0; u < 8 && 8 * b + u < n; ++u) Z[((size_t)b * n + 8 * b + u) * 8 + u] = 1.0;
+    q.consume(who, [&](int m, int len, const double* rc, const double* rs) {
+      for (int b = lo; b < hi; ++b) ops.rotate8(&Z[(size_t)b * n * 8], m, len, rc, rs);
+    });
+  };
+  if (pool.size() > 1) {
+    pool.run([&](int t, int) {
+      if (t > 0) {
+        apply(t - 1);
+        return;
+      }
+      tridiag_ql(d, e, n, &q);
+      q.finish();
+    });
+    return;
+  }
+  tridiag_ql(d, e, n, &q);
+  q.finish();
+  apply(0);
+}
+
+// One pass over the trailing block per reflector: the update of the one before and the
+// product with the new vector, every row by the same thread throughout.  Bound by the
+// threads' meetings and the vectors they pass, and in the QL iteration by its chain of
+// square roots and quotients.  16 threads, n = 256: reduction 3.0 -> 1.6 ms (two passes
+// before, and column k read across all rows), QL with its rotations 2.5 -> 1.9,
+// back-transformation 2.2 -> 0.6, in all 7.8 -> 4.4 ms; n = 512 33 -> 14 ms.
 void hermitian_eig(const std::vector<cplx>& Ain, int n, std::vector<double>& w, std::vector<cplx>& V) {
   Pool pool((size_t)n * n * n);
+  const DenseOps ops = dense_ops();
   std::vector<cplx> A = Ain;
   // use the lower triangle; make A exactly Hermitian from it
   for (int i = 0; i < n; ++i) {
@@ -188,80 +352,60 @@ void hermitian_eig(const std::vector<cplx>& Ain, int n, std::vector<double>& w, 
   }
   std::vector<std::vector<cplx>> vs(std::max(0, n - 2));
   std::vector<cplx> offd(std::max(0, n - 1), 0.0);
-  std::vector<cplx> p(n), q(n);
+  std::vector<double> d(n), e(std::max(1, n));
+  // the pending update A -= 2 (v q^H + q v^H), v the vector of the reflector before, and
+  // the new vector x: two buffers in turn, so that v is in the threads' caches already
+  std::vector<cplx> buf[2] = {std::vector<cplx>(n, 0.0), std::vector<cplx>(n, 0.0)}, q(n, 0.0), p(n);
+  const auto row = [&](int i, int from, const std::vector<cplx>& v, const std::vector<cplx>& x, cplx* out) {
+    ops.update_dot(reinterpret_cast<double*>(&A[(size_t)i * n + from]), 2 * (n - from),
+                   reinterpret_cast<const double*>(&q[from]), reinterpret_cast<const double*>(&v[from]),
+                   reinterpret_cast<const double*>(&x[from]), 2.0 * v[i].real(), 2.0 * v[i].imag(), 2.0 * q[i].real(),
+                   2.0 * q[i].imag(), reinterpret_cast<double*>(out));
+  };
+  cplx unused;
   for (int k = 0; k + 2 < n; ++k) {
-    const int m = n - k - 1;         // size of the trailing block
-    std::vector<cplx> v(m);
+    std::vector<cplx>&v = buf[(k & 1) ^ 1], &x = buf[k & 1];
+    row(k, k, v, x, &unused);
+    d[k] = A[(size_t)k * n + k].real();
+    const int m = n - k - 1;               // size of the trailing block
+    const cplx* Ak = &A[(size_t)k * n];
     double xn2 = 0.0;
-    for (int i = 0; i < m; ++i) {
-      v[i] = A[(size_t)(k + 1 + i) * n + k];
-      xn2 += std::norm(v[i]);
+    for (int i = k + 1; i < n; ++i) {
+      x[i] = std::conj(Ak[i]);             // column k
+      xn2 += std::norm(x[i]);
     }
     const double xn = std::sqrt(xn2);
-    if (xn == 0.0) {
-      offd[k] = 0.0;
-      continue;
-    }
-    const cplx phase = (std::abs(v[0]) > 0.0) ? v[0] / std::abs(v[0]) : cplx(1.0, 0.0);
-    const cplx alpha = -phase * xn;
-    v[0] -= alpha;
-    double vn = 0.0;
-    for (int i = 0; i < m; ++i) vn += std::norm(v[i]);
-    vn = std::sqrt(vn);
-    for (int i = 0; i < m; ++i) v[i] /= vn;
-    // p = A_sub v ; rho = v^H p ; q = p - rho v ; A_sub -= 2 (v q^H + q v^H)
-    const bool par = (size_t)m * m > 8192;
-    auto matvec = [&](int t, int nt) {
-      int lo, hi;
-      Pool::range(m, t, nt, lo, hi);
-      const double* vv = reinterpret_cast<const double*>(v.data());
-      for (int i = lo; i < hi; ++i) {
-        const double* Ai = reinterpret_cast<const double*>(&A[(size_t)(k + 1 + i) * n + k + 1]);
-        double sr = 0.0, si = 0.0;
-        for (int j = 0; j < m; ++j) {
-          sr += Ai[2 * j] * vv[2 * j] - Ai[2 * j + 1] * vv[2 * j + 1];
-          si += Ai[2 * j] * vv[2 * j + 1] + Ai[2 * j + 1] * vv[2 * j];
-        }
-        p[i] = cplx(sr, si);
+    if (xn != 0.0) {
+      const cplx x0 = x[k + 1];
+      const cplx phase = (std::abs(x0) > 0.0) ? x0 / std::abs(x0) : cplx(1.0, 0.0);
+      const cplx alpha = -phase * xn;
+      x[k + 1] -= alpha;
+      double vn = 0.0;
+      for (int i = k + 1; i < n; ++i) vn += std::norm(x[i]);
+      vn = std::sqrt(vn);
+      for (int i = k + 1; i < n; ++i) x[i] /= vn;
+      offd[k] = alpha;
+      vs[k].assign(x.begin() + k + 1, x.end());
+    }                                      // (else x = 0: the pass only updates)
+    const auto pass = [&](int t, int nt) {
+      // rows by eights, so that no two threads write one line of p
+      for (int b = (k + 1) / 8; 8 * b < n; ++b) {
+        if (b % nt != t) continue;
+        for (int i = std::max(k + 1, 8 * b); i < std::min(n, 8 * b + 8); ++i) row(i, k + 1, v, x, &p[i]);
       }
     };
-    if (par) pool.run(matvec);
-    else matvec(0, 1);
-    cplx rho = 0.0;
-    for (int i = 0; i < m; ++i) rho += std::conj(v[i]) * p[i];
-    for (int i = 0; i < m; ++i) q[i] = p[i] - rho.real() * v[i];
-    auto update = [&](int t, int nt) {
-      int lo, hi;
-      Pool::range(m, t, nt, lo, hi);
-      const double* vv = reinterpret_cast<const double*>(v.data());
-      const double* qq = reinterpret_cast<const double*>(q.data());
-      for (int i = lo; i < hi; ++i) {
-        double* Ai = reinterpret_cast<double*>(&A[(size_t)(k + 1 + i) * n + k + 1]);
-        const double vr = 2.0 * v[i].real(), vim = 2.0 * v[i].imag();
-        const double qr = 2.0 * q[i].real(), qim = 2.0 * q[i].imag();
-        for (int j = 0; j < m; ++j) {
-          // vi conj(q_j) + qi conj(v_j)
-          const double ar = vr * qq[2 * j] + vim * qq[2 * j + 1] + qr * vv[2 * j] + qim * vv[2 * j + 1];
-          const double ai = vim * qq[2 * j] - vr * qq[2 * j + 1] + qim * vv[2 * j] - qr * vv[2 * j + 1];
-          Ai[2 * j] -= ar;
-          Ai[2 * j + 1] -= ai;
-        }
-      }
-    };
-    if (par) pool.run(update);
-    else update(0, 1);
-    offd[k] = alpha;
-    for (int i = 1; i < m; ++i) {
-      A[(size_t)(k + 1 + i) * n + k] = 0.0;
-      A[(size_t)k * n + k + 1 + i] = 0.0;
-    }
-    A[(size_t)(k + 1) * n + k] = alpha;
-    A[(size_t)k * n + k + 1] = std::conj(alpha);
-    vs[k].swap(v);
+    if ((size_t)m * m > 8192) pool.run(pass);
+    else pass(0, 1);
+    // the new pending update: rho = x^H p, q = p - rho x
+    double rho = 0.0;
+    for (int i = k + 1; i < n; ++i) rho += x[i].real() * p[i].real() + x[i].imag() * p[i].imag();
+    for (int i = k + 1; i < n; ++i) q[i] = cplx(p[i].real() - rho * x[i].real(), p[i].imag() - rho * x[i].imag());
+  }
+  for (int i = std::max(0, n - 2); i < n; ++i) {
+    row(i, std::max(0, n - 2), buf[(n & 1) ^ 1], buf[n & 1], &unused);    // the last x was buf[(n - 3) & 1]
+    d[i] = A[(size_t)i * n + i].real();
   }
   if (n >= 2) offd[n - 2] = A[(size_t)(n - 1) * n + n - 2];
-  std::vector<double> d(n), e(std::max(1, n));
-  for (int i = 0; i < n; ++i) d[i] = A[(size_t)i * n + i].real();
   // phases phi_0 = 1, phi_{k+1} = phi_k e_k / |e_k| make the tridiagonal real
   std::vector<cplx> phi(n, 1.0);
   for (int k = 0; k + 1 < n; ++k) {
@@ -269,21 +413,16 @@ void hermitian_eig(const std::vector<cplx>& Ain, int n, std::vector<double>& w, 
     e[k] = a;
     phi[k + 1] = (a > 0.0) ? phi[k] * offd[k] / a : phi[k];
   }
-  std::vector<double> Zt((size_t)n * n, 0.0);
-  for (int i = 0; i < n; ++i) Zt[(size_t)i * n + i] = 1.0;
-  tridiag_ql(d, e, &Zt, n, &pool);
+  std::vector<double> Z;
+  tridiag_vectors(d, e, Z, n, pool, ops);
   // sort ascending
   std::vector<int> order(n);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return d[a] < d[b]; });
   w.resize(n);
-  // V[:, j] = Q (phi .* z_order[j]); build Y = D Z column-sorted, then apply Q
-  V.assign((size_t)n * n, 0.0);
-  for (int j = 0; j < n; ++j) {
-    w[j] = d[order[j]];
-    const double* z = &Zt[(size_t)order[j] * n];
-    for (int i = 0; i < n; ++i) V[(size_t)i * n + j] = phi[i] * z[i];
-  }
+  // V[:, j] = Q (phi .* z_order[j])
+  V.resize((size_t)n * n);
+  for (int j = 0; j < n; ++j) w[j] = d[order[j]];
   // Q = H_0 H_1 ... H_{n-3} applied to V, H_k = I - 2 v_k v_k^H (v_k unit, nonzero
   // from row k+1).  The reflectors go in blocks of kWY consecutive ones, each block
   // H_k1 ... H_k2 = I - Y T Y^H (compact WY form: Y = [v_k1 .. v_k2], T upper
@@ -297,9 +436,8 @@ void hermitian_eig(const std::vector<cplx>& Ain, int n, std::vector<double>& w, 
     std::vector<cplx> Y;        // [m1][nb], rows k1+1 .. n-1 (zero above each v's start)
     std::vector<cplx> T;        // [nb][nb] upper
   };
-  std::vector<Blk> blks;
-  for (int k1 = 0; k1 < nref; k1 += kWY) {
-    Blk B;
+  std::vector<Blk> blks((nref + kWY - 1) / kWY);
+  const auto build = [&](Blk& B, int k1) {
     B.k1 = k1;
     B.k2 = std::min(nref, k1 + kWY) - 1;
     const int nb = B.k2 - B.k1 + 1, m1 = n - k1 - 1;
@@ -314,10 +452,12 @@ void hermitian_eig(const std::vector<cplx>& Ain, int n, std::vector<double>& w, 
     for (int i = 0; i < nb; ++i) {
       if (vs[k1 + i].empty()) continue;      // H = I: zero column of Y, T_ii = 0
       // g[0:i] = Y[:, 0:i]^H v_i
-      for (int j = 0; j < i; ++j) {
-        cplx acc = 0.0;
-        for (int r = i; r < m1; ++r) acc += std::conj(B.Y[(size_t)r * nb + j]) * B.Y[(size_t)r * nb + i];
-        g[j] = acc;
+      std::fill(g.begin(), g.end(), 0.0);
+      for (int r = i; r < m1; ++r) {
+        const cplx* Yr = &B.Y[(size_t)r * nb];
+        const double a = Yr[i].real(), b = Yr[i].imag();
+        for (int j = 0; j < i; ++j)
+          g[j] += cplx(Yr[j].real() * a + Yr[j].imag() * b, Yr[j].real() * b - Yr[j].imag() * a);
       }
       for (int j = 0; j < i; ++j) {
         cplx acc = 0.0;
@@ -326,13 +466,20 @@ void hermitian_eig(const std::vector<cplx>& Ain, int n, std::vector<double>& w, 
       }
       B.T[(size_t)i * nb + i] = 2.0;
     }
-    blks.push_back(std::move(B));
-  }
+  };
+  pool.run([&](int t, int nt) {
+    for (size_t b = t; b < blks.size(); b += nt) build(blks[b], (int)b * kWY);
+  });
   pool.run([&](int t, int nt) {
     int lo, hi;
     Pool::range(n, t, nt, lo, hi);
     if (lo >= hi) return;
-    const int w = hi - lo, w2 = 2 * w;
+    const int nc = hi - lo, w2 = 2 * nc;
+    // this worker's columns together (rows of V are a multiple of the cache's period apart)
+    std::vector<cplx> U((size_t)n * nc);
+    for (int i = 0; i < n; ++i)
+      for (int j = 0; j < nc; ++j)
+        U[(size_t)i * nc + j] = phi[i] * Z[((size_t)(i / 8) * n + order[lo + j]) * 8 + i % 8];
     std::vector<double> W((size_t)kWY * w2), W2((size_t)kWY * w2);
     for (int bi = (int)blks.size() - 1; bi >= 0; --bi) {
       const Blk& B = blks[bi];
@@ -340,52 +487,35 @@ void hermitian_eig(const std::vector<cplx>& Ain, int n, std::vector<double>& w, 
       // W = Y^H V_sub (interleaved re, im)
       std::fill(W.begin(), W.begin() + (size_t)nb * w2, 0.0);
       for (int r = 0; r < m1; ++r) {
-        const double* __restrict__ Vr = reinterpret_cast<const double*>(&V[(size_t)(r0 + r) * n + lo]);
+        const double* __restrict__ Vr = reinterpret_cast<const double*>(&U[(size_t)(r0 + r) * nc]);
         const cplx* Yr = &B.Y[(size_t)r * nb];
         const int jmax = std::min(nb, r + 1);      // v_{k1+j} starts at row j of the block
-        for (int j = 0; j < jmax; ++j) {
-          const double yr = Yr[j].real(), yi = -Yr[j].imag();
-          double* __restrict__ Wj = &W[(size_t)j * w2];
-          for (int c = 0; c < w2; c += 2) {
-            Wj[c] += yr * Vr[c] - yi * Vr[c + 1];
-            Wj[c + 1] += yr * Vr[c + 1] + yi * Vr[c];
-          }
-        }
+        for (int j = 0; j < jmax; ++j) ops.caxpy(&W[(size_t)j * w2], Vr, Yr[j].real(), -Yr[j].imag(), w2);
       }
       // W2 = T W
       for (int j = 0; j < nb; ++j) {
         double* __restrict__ W2j = &W2[(size_t)j * w2];
         std::fill(W2j, W2j + w2, 0.0);
         for (int l = j; l < nb; ++l) {
-          const double tr = B.T[(size_t)j * nb + l].real(), ti = B.T[(size_t)j * nb + l].imag();
-          const double* __restrict__ Wl = &W[(size_t)l * w2];
-          for (int c = 0; c < w2; c += 2) {
-            W2j[c] += tr * Wl[c] - ti * Wl[c + 1];
-            W2j[c + 1] += tr * Wl[c + 1] + ti * Wl[c];
-          }
+          const cplx tl = B.T[(size_t)j * nb + l];
+          ops.caxpy(W2j, &W[(size_t)l * w2], tl.real(), tl.imag(), w2);
         }
       }
       // V_sub -= Y W2
       for (int r = 0; r < m1; ++r) {
-        double* __restrict__ Vr = reinterpret_cast<double*>(&V[(size_t)(r0 + r) * n + lo]);
+        double* __restrict__ Vr = reinterpret_cast<double*>(&U[(size_t)(r0 + r) * nc]);
         const cplx* Yr = &B.Y[(size_t)r * nb];
         const int jmax = std::min(nb, r + 1);
-        for (int j = 0; j < jmax; ++j) {
-          const double yr = Yr[j].real(), yi = Yr[j].imag();
-          const double* __restrict__ W2j = &W2[(size_t)j * w2];
-          for (int c = 0; c < w2; c += 2) {
-            Vr[c] -= yr * W2j[c] - yi * W2j[c + 1];
-            Vr[c + 1] -= yr * W2j[c + 1] + yi * W2j[c];
-          }
-        }
+        for (int j = 0; j < jmax; ++j) ops.caxpy(Vr, &W2[(size_t)j * w2], -Yr[j].real(), -Yr[j].imag(), w2);
       }
     }
+    for (int i = 0; i < n; ++i) std::copy(&U[(size_t)i * nc], &U[(size_t)i * nc] + nc, &V[(size_t)i * n + lo]);
   });
 }
 
 void tridiag_eigvals(std::vector<double> d, std::vector<double> e, std::vector<double>& w) {
   const int n = (int)d.size();
-  tridiag_ql(d, e, nullptr, n, nullptr);
+  tridiag_ql(d, e, n, nullptr);
   std::sort(d.begin(), d.end());
   w = d;
 }

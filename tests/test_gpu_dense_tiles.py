@@ -25,14 +25,12 @@ def _block(rows, n, pad, seed):
     return X
 
 
-@pytest.mark.parametrize("cells,p", [((3, 3, 2), 2), ((33, 33, 33), 1)])
+@pytest.mark.parametrize("cells,p", [((3, 3, 3), 2), ((33, 33, 33), 1)])
 @pytest.mark.parametrize("n,pad", [(1, 0), (31, 3), (64, 0), (65, 7), (130, 0), (193, 1)])
 def test_gram_and_triangular_rotation(cells, p, n, pad):
     from paper_2410_02754_amd import Operator
     op = Operator(cells, tuple(1.1 * c for c in cells), p, "gll", p + 1, [(0.0, 0.0, 0.0)])
     rows = op.n_dof
-    if n > rows // 2:
-        pytest.skip("more columns than half the rows")
     X, Y = _block(rows, n, pad, 1), _block(rows, n, pad, 2)
     x, y = X[:, :n], Y[:, :n]
     S = op.overlap(x, y)
@@ -76,4 +74,30 @@ def test_failed_pivot_and_bad_values(n, dup):
             op.chol_gs(X)
         assert e.value.bad_col == col
         assert torch.equal(torch.view_as_real(X).nan_to_num(7.0), torch.view_as_real(Y).nan_to_num(7.0))
+    op.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 40, 41, 133])
+def test_rayleigh_ritz_against_dense_eigenvalues(n):
+    """One thread (n <= 40) and several, widths beside multiples of eight: Ritz values
+    against numpy's of the same projected matrix, and the rotated block's projection
+    diagonal, both to n^(3/2) roundings of the matrix' norm."""
+    from paper_2410_02754_amd import Operator
+    s = synth.make_system("rr", n_cells=(4, 3, 3), box=(4.8, 3.6, 3.6), p=3, kpts=[(0.1, 0.2, 0.0)], n_atoms=1, lmax=1,
+                          rcut_sigmas=4.0, n_vec=1)
+    op = Operator(s.n_cells, s.box, s.p, s.quad, s.n_q, s.kpts)
+    pts = op.quad_points().reshape(-1, 3)
+    op.set_local(torch.tensor(synth.veff(s, pts).reshape(op.n_cells, op.nq3), device="cuda"),
+                 torch.tensor(synth.bxc(s, pts).reshape(op.n_cells, op.nq3, 3), device="cuda"))
+    op.set_atoms(s.atoms)
+    X = _block(op.n_dof, n, 0, 11)
+    op.chol_gs(X)
+    W = torch.empty_like(X)
+    H = op.overlap(X, op.apply_H(X, W))
+    want = np.linalg.eigvalsh((H + H.conj().T) / 2)
+    theta, _ = op.rayleigh_ritz(X, W)
+    tol = 4 * max(n, 4)**1.5 * np.finfo(float).eps * np.abs(want).max()
+    assert np.max(np.abs(np.asarray(theta) - want)) < tol
+    G = op.overlap(X, op.apply_H(X, W))
+    assert np.max(np.abs(G - np.diag(np.asarray(theta)))) < 4 * tol
     op.close()
