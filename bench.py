@@ -753,7 +753,7 @@ def bench_matfree(args, s, X, W, Wf, b, theta_ref, torch, tables=None, theta_cmp
            "filter_s_per_pass": round(sum(ftimes) / k2, 3),
            "filter_tflops_cell_count": round(fst["flops"] / sum(ftimes) / 1e12, 4),
            "setup_s": round(t_setup, 2),
-           "kernel": "mf_apply_kernel<7, false> (gather, 12 line contractions per spin, scatter-add)",
+           "kernel": "mf_apply_kernel<7, false> (gather, 9 line contractions per spin, scatter-add)",
            "mean_launch_ms": round(ms, 4),
            # 12 dense 1-D contractions per spin (96 n_p^4 per cell and column); the even-odd
            # form issues about half of these multiply-adds

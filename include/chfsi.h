@@ -214,9 +214,9 @@ int chfsi_cheb_filter_resid(chfsi_ctx* ctx, int ik, void* X_d, int64_t ldx, cons
 /* Cholesky-Gram-Schmidt: S = X^H X (FP64), S = L L^H, X <- X L^{-H}, so that
  * the columns become orthonormal with the same span (the orthonormalisation
  * before the Rayleigh-Ritz step, Sec. III.B.2).  The factorisation runs on the
- * unit-diagonal D S D, D = diag(S)^{-1/2} (same result in exact arithmetic).  On CHFSI_ENOTPD *bad_col (if
- * non-NULL) is the first column whose pivot is not positive and X is left
- * unchanged. */
+ * device, on the unit-diagonal D S D, D = diag(S)^{-1/2} (same result in exact
+ * arithmetic).  On CHFSI_ENOTPD *bad_col (if non-NULL) is the first column whose
+ * pivot is not positive and X is left unchanged.  Synchronises the stream. */
 int chfsi_chol_gs(chfsi_ctx* ctx, void* X_d, int64_t ldx, int n_vec, int* bad_col);
 
 /* Rayleigh-Ritz on an orthonormal block (Sec. III.B.2): W = H_hat^k X,
@@ -248,7 +248,8 @@ size_t chfsi_workspace_bytes(const chfsi_ctx* ctx, int ik, int n_vec, int op);
  * tridiagonal, *hi = largest Ritz value + ||f_steps|| (an upper bound of the
  * spectrum, Sec. III.B.2).  In the cell-matrix form (when n_q = p + 1) the
  * single-column applies run the matrix-free product of the same operator, which
- * does not stream the cell matrices for one column. */
+ * does not stream the cell matrices for one column.  Synchronises the stream; the
+ * context keeps the three vectors. */
 int chfsi_lanczos_bounds(chfsi_ctx* ctx, int ik, int steps, const void* v0_d, double* lo,
                          double* hi);
 
@@ -436,10 +437,14 @@ int chfsi_scf_run(chfsi_ctx* fine, chfsi_ctx* coarse, const chfsi_scf_params* pa
 /* ---- Batched filtering of independent operators (the k-points of a grid and
  * independent systems: the eigenproblems of different k are independent,
  * Sec. III.B).  One task = one (context, k-point, block): X_d [2M][ldx] is
- * filtered in place with work_d [2M][ldw].  Per recurrence step the projector
- * terms run per task and the cell products of all tasks run as one persistent
- * launch per colour phase (per tile width and k-term variant).  Tasks may share
- * a context (k-points of one mesh) but not X or work buffers. */
+ * filtered in place with work_d [2M][ldw].  Small tasks (those whose colours
+ * alone would leave the GPU idle) go together: per recurrence step one launch
+ * for all of them of each of the projector contraction, its coefficients, the
+ * cell products (per tile width and k-term variant; matrix-free tasks one each)
+ * and their sum with the recurrence terms.  For the others the projector terms
+ * run per task and the cell products of all as one persistent launch per colour
+ * phase.  Tasks may share a context (k-points of one mesh) but not X or work
+ * buffers. */
 typedef struct chfsi_batch chfsi_batch;
 typedef struct {
   chfsi_ctx* ctx;
@@ -464,7 +469,9 @@ enum chfsi_batch_flags {
  * bound at creation.  With CHFSI_BATCH_AUTOTUNE the work buffers are used as
  * scratch during creation.  The batch owns the device memory its kernels use
  * besides the task buffers (projector partial sums, recurrence coefficient
- * tables), so other calls on the same contexts (chfsi_chol_gs,
+ * tables, and the cell products of the small tasks, at most 4 GiB in all; tasks
+ * beyond that, or all where the memory is not there, run like the large ones), so
+ * other calls on the same contexts (chfsi_chol_gs,
  * chfsi_rayleigh_ritz, ...) may run between filters. */
 int chfsi_batch_create(int n_tasks, const chfsi_batch_task* tasks, int degree, int prec_mode, int flags,
                        chfsi_batch** out);
@@ -486,7 +493,7 @@ int chfsi_batch_graph_info(const chfsi_batch* batch, int* n_captures, int* n_rep
                            double* instantiate_ms);
 
 /* Chosen column tile width per task (cols_out[n_tasks]; 0 for a task whose
- * context uses the matrix-free form, which runs its own per-colour launches) and,
+ * context uses the matrix-free form, which runs its own launches) and,
  * if tune_ms is not NULL, the timed cell-stage milliseconds for widths 32, 64,
  * 128 (-1 = not run). */
 int chfsi_batch_tiles(const chfsi_batch* batch, int* cols_out, double* tune_ms);
@@ -513,7 +520,8 @@ enum chfsi_stage {
   CHFSI_STAGE_AXPY = 3,       /* recurrence initialisation / element-wise passes                  */
   CHFSI_STAGE_GRAM = 4,       /* X^H Y overlap and projected-Hamiltonian products                 */
   CHFSI_STAGE_ROTATE = 5,     /* in-place subspace rotations X <- X Q                             */
-  CHFSI_STAGE_HOST_DENSE = 6, /* host Cholesky / inverse / Hermitian eigensolver (wall time)      */
+  CHFSI_STAGE_HOST_DENSE = 6, /* n x n algebra: the host's Hermitian eigensolver (wall time) and
+                                 the device's Cholesky factor and inverse                         */
   CHFSI_N_STAGES = 7
 };
 /* Accumulated totals of one stage since the last reset.  flops: algorithmic

@@ -397,8 +397,9 @@ __global__ __launch_bounds__((cell_threads<T, TW>()), (cell_min_waves<T, TW>()))
 
 // Batched form: one persistent grid walks a static list of (task, cell, row
 // tile, column tile) items across many independent operators (k-points, systems):
-// those of one colour phase, or all cells of small tasks (into their ye).  Items were ordered on the host so that item
-// i runs on XCD i % 8 and the row tiles of a cell share an XCD.
+// those of one colour phase, or all cells of small tasks (into their ye).  Items were
+// ordered on the host so that item i runs on XCD i % 8 and the row tiles of a cell
+// share an XCD.
 template <class T, int TW, bool HAS_S>
 __global__ __launch_bounds__((cell_threads<T, TW>()), (cell_min_waves<T, TW>())) void cell_batch_kernel(const BatchTaskArgs tasks,
                                                          const int4* __restrict__ items, int n_items,
@@ -410,7 +411,8 @@ __global__ __launch_bounds__((cell_threads<T, TW>()), (cell_min_waves<T, TW>()))
     const BatchTaskDev& t = tasks.t[w.x];
     const T* cm = sizeof(T) == 8 ? (const T*)t.cm64 : (const T*)t.cm32;
     cell_tile<T, TW, HAS_S>(sm, cm, t.cell_nodes, w.y, w.z, w.w, t.nloc, t.nrb, t.nkb, t.nmat, t.buf[src],
-                                t.ld[src], t.buf[src ^ 1], t.ld[src ^ 1], t.n_vec, alpha[w.x], (typename CellC2<T>::type*)t.ye);
+                            t.ld[src], t.buf[src ^ 1], t.ld[src ^ 1], t.n_vec, alpha[w.x],
+                            (typename CellC2<T>::type*)t.ye);
   }
 }
 
@@ -442,7 +444,7 @@ static void launch_cells(chfsi_ctx* c, const T* cm, int nmat, const double2* X, 
 }
 
 // 64-column tiles for every block wider than 32: at p = 5..6 they run 1-4 %
-// faster than 128-column tiles in both precisions (three workgroups per CU
+// faster than 128-column tiles in both precisions (four workgroups per CU
 // instead of one hide the epilogue and barrier latencies; the two column tiles
 // of a cell read its operator through the same L2).  The per-column arithmetic
 // does not depend on the tile width, so results are bitwise the same.

@@ -226,7 +226,8 @@ struct chfsi_ctx {
   // form of the local operator: CHFSI_FORM_CELL_MATRIX (stored cell matrices)
   // or CHFSI_FORM_MATRIX_FREE (sum factorisation from the quadrature data)
   int form = 0;
-  chfsi::DevBuf<double> mf_tab;               // [B: np1^2][Dq: np1^2][w: np1]
+  chfsi::DevBuf<double> mf_tab;               // [B: np1^2][Dq: np1^2][w: np1], then even-odd blocks of B, B^T,
+                                              // Dq, Dq^T and K = Dq^T diag(w) Dq
   chfsi::DevBuf<double> mf_qd;                // [E][x][y + nq z][4]: w_q J (V, Bx, By, Bz)
   chfsi::DevBuf<float> mf_tab32, mf_qd32;     // FP32 copies for mixed precision
   chfsi::DevBuf<float> mf_kin32;              // [3][point on the line][line] FP32 kinetic weights

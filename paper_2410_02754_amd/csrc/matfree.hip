@@ -85,7 +85,18 @@ __device__ __forceinline__ void grad_line(const T* __restrict__ eoDf, const T* _
     const T c = a_d * wl;
 #pragma unroll
     for (int r = 0; r < NP; ++r) w[r] = C2{fma(c, dw[r].x, w[r].x), fma(c, dw[r].y, w[r].y)};
-    if constexpr (KT) sf_eo<T, NP, true>(eoDf, u, g);
+    if constexpr (KT) {
+      // (the barriers keep the two contractions' registers apart)
+      __builtin_amdgcn_sched_barrier(0);
+      sf_eo<T, NP, true>(eoDf, u, g);
+#pragma unroll
+      for (int r = 0; r < NP; ++r) {      // -i b wJ g = b wJ g.y - i b wJ g.x
+        const T s = b_d * wl * w1[r];
+        w[r].x = fma(s, g[r].y, w[r].x);
+        w[r].y = fma(-s, g[r].x, w[r].y);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
   } else {
     sf_eo<T, NP, true>(eoDf, u, g);
     C2 fk[NP];
@@ -98,10 +109,9 @@ __device__ __forceinline__ void grad_line(const T* __restrict__ eoDf, const T* _
 #pragma unroll
     for (int r = 0; r < NP; ++r) w[r] = C2{w[r].x + dw[r].x, w[r].y + dw[r].y};
   }
-  if constexpr (KT) {
+  if constexpr (KT && sizeof(T) == 4) {
 #pragma unroll
     for (int r = 0; r < NP; ++r) {
-      // -i b wJ g = b wJ g.y - i b wJ g.x
       const T s = b_d * wl * w1[r];
       w[r].x = fma(s, g[r].y, w[r].x);
       w[r].y = fma(-s, g[r].x, w[r].y);
@@ -264,6 +274,28 @@ __global__ __launch_bounds__(MfT<T>::NT, mf_waves<T>(NP)) void mf_apply_kernel(
       s1[q].x = (s - d.w) * u1[q].x + d.y * u0[q].x - d.z * u0[q].y;
       s1[q].y = (s - d.w) * u1[q].y + d.y * u0[q].y + d.z * u0[q].x;
     }
+    if constexpr (KT && sizeof(T) == 8) {
+      // one spin's lines after the other's, the second from LDS again: with both in
+      // registers beside the k-term's derivative they spilled or cost a resident
+      // workgroup (p = 5, 256 columns on 10^3 cells 2.14 ms, now 1.80; p = 7, 128
+      // columns on 8^3 1.69 and 1.17)
+#pragma unroll
+      for (int q = 0; q < NP; ++q) bufW[base + N3 + q] = s1[q];
+      asm volatile("" ::: "memory");      // (not forwarded to the loads below)
+      grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, wl, a0, b0, kin + l, u0, s0);
+#pragma unroll
+      for (int q = 0; q < NP; ++q) bufW[base + q] = s0[q];
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        u1[q] = bufU[base + N3 + q];
+        s1[q] = bufW[base + N3 + q];
+      }
+      grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, wl, a0, b0, kin + l, u1, s1);
+#pragma unroll
+      for (int q = 0; q < NP; ++q) bufW[base + N3 + q] = s1[q];
+      continue;
+    }
     grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, wl, a0, b0, kin + l, u0, s0);
     grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, wl, a0, b0, kin + l, u1, s1);
 #pragma unroll
@@ -276,8 +308,10 @@ __global__ __launch_bounds__(MfT<T>::NT, mf_waves<T>(NP)) void mf_apply_kernel(
   // the output rows of phase 7's x-line, in flight while the next phases run
   const int I7 = fx + mesh.Nx * wrap(fy + ta, mesh.Ny) + mesh.Nxy * wrap(fz + tb, mesh.Nz);
   double2* __restrict__ y0 = Y + ((2 * (int64_t)I7 + ts) * ldy + col);
-  // (FP64; in FP32 their registers would cost a resident workgroup)
-  constexpr bool kEarly = sizeof(T) == 8;
+  // (FP64; in FP32, and with the k-term from n_p = 7 on, their registers cost more:
+  // p = 6, k != 0, 128 columns on 12^3 cells 2.50 ms with them, 2.42 without; p = 5
+  // 1.80 and 1.85)
+  constexpr bool kEarly = sizeof(T) == 8 && !(KT && NP >= 7);
   double2 yo[NP];
   if (kEarly && ok && !ye) {
 #pragma unroll
