@@ -873,7 +873,7 @@ def bench_scale(args, torch):
             tables[key] = (thetam, dth)
             m_l = max(1, mst["cell_launches"])
             m_roof = cell_roofline(mst["cell_flops"] / m_l, mst["cell_exec"] / m_l, mst["cell_ms"] / m_l, gamma,
-                                   PEAK_FP32)
+                                   PEAK_FP32, KERNEL_PRODUCTS)
             conv = rm < 1e-4
             out[key] = {
                 "form": ("FP32 cell/projector products in applies 1..m-1, FP64 apply m" if not resid_form else
