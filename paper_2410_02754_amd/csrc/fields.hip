@@ -61,13 +61,18 @@ __device__ __forceinline__ void block_sums(double (&v)[NS], double* sm) {
 
 // ---- Conjugate gradients, two kernels per step, scalars on the device.  A step was
 // a fill, a launch per colour, ten vector kernels and three round trips to the host
-// (about 130 us on 4^3 cells, p = 4); these two take 9.4 us.  red: [kCgDots][kFieldRed]
-// partial sums (p.Ap; r.r and r.z of even and odd steps; b.b), then the state: the
-// number of steps when r.r reached the tolerance, or -1.
-constexpr int kCgDots = 6, kCgPq = 0, kCgRr = 1, kCgRz = 3, kCgBb = 5;
-// this thread's partial sum of dot k (n <= kFieldRed = 256 parts)
-__device__ __forceinline__ double cg_part(const double* __restrict__ red, int k, int n) {
-  return (int)threadIdx.x < n ? red[k * kFieldRed + threadIdx.x] : 0.0;
+// (about 130 us on 4^3 cells, p = 4); these two take 9.4 us.  red: [kCgDots][stride]
+// partial sums (p.Ap; r.r and r.z of even and odd steps; b.b), a part per workgroup,
+// then the state: the number of steps when r.r reached the tolerance, or -1.
+// Up to kCgParts workgroups, eight per CU: with one per CU large meshes of low order
+// waited for each other's trips to memory (128 steps: p = 3, 48^3 cells 121 ms, now 40;
+// p = 6, 16^3 17.6 and 10.4).
+constexpr int kCgDots = 6, kCgPq = 0, kCgRr = 1, kCgRz = 3, kCgBb = 5, kCgParts = 2048;
+// this thread's share of the n parts of dot k
+__device__ __forceinline__ double cg_part(const double* __restrict__ red, int stride, int k, int n) {
+  double s = (int)threadIdx.x < n ? red[k * stride + threadIdx.x] : 0.0;
+  for (int i = threadIdx.x + 256; i < n; i += 256) s += red[k * stride + i];
+  return s;
 }
 
 // 1 / diag(A) at node (ax, ay, az) of a cell's frame (a < p in each direction)
@@ -84,7 +89,7 @@ __device__ __forceinline__ double inv_diag(const ScalMesh& m, double kappa2, int
 // r = b, u = 0, z = r / diag(A); partial b.b (= r.r) and r.z
 __global__ __launch_bounds__(256) void cg_start_kernel(const ScalMesh m, double kappa2, int64_t n,
                                                        const double* __restrict__ b, double* __restrict__ u,
-                                                       double* __restrict__ r, double* __restrict__ z,
+                                                       double* __restrict__ r, double* __restrict__ z, int stride,
                                                        double* __restrict__ red) {
   __shared__ double sm[4];
   double rr = 0.0, rz = 0.0;
@@ -100,11 +105,36 @@ __global__ __launch_bounds__(256) void cg_start_kernel(const ScalMesh m, double 
   rr = block_sum(rr, sm);
   rz = block_sum(rz, sm);
   if (threadIdx.x == 0) {
-    red[kCgRr * kFieldRed + blockIdx.x] = rr;
-    red[kCgBb * kFieldRed + blockIdx.x] = rr;
-    red[kCgRz * kFieldRed + blockIdx.x] = rz;
-    if (blockIdx.x == 0) red[kCgDots * kFieldRed] = -1.0;
+    red[kCgRr * stride + blockIdx.x] = rr;
+    red[kCgBb * stride + blockIdx.x] = rr;
+    red[kCgRz * stride + blockIdx.x] = rz;
+    if (blockIdx.x == 0) red[kCgDots * stride] = -1.0;
   }
+}
+
+// Head of step `it`: the state and the sums it needs, asked for ...
+struct CgHead {
+  double state, d[4];
+};
+__device__ __forceinline__ CgHead cg_ask(const double* __restrict__ red, int stride, int n_part, int it) {
+  const int odd = it & 1;
+  return CgHead{red[kCgDots * stride],
+                {cg_part(red, stride, kCgRr + odd, n_part), cg_part(red, stride, kCgBb, n_part),
+                 cg_part(red, stride, kCgRz + odd, n_part),
+                 it > 0 ? cg_part(red, stride, kCgRz + 1 - odd, n_part) : 0.0}};
+}
+// ... and beta from them, or false if the iteration has ended (a step before, or now)
+__device__ __forceinline__ bool cg_go(CgHead& h, double* sm, double* __restrict__ red, int stride, int it, double tol,
+                                      double& beta) {
+  block_sums(h.d, sm);
+  if (h.state >= 0.0) return false;
+  const double rr = h.d[0], bb = h.d[1];
+  if (bb == 0.0 || (it > 0 && sqrt(rr) / sqrt(bb) <= tol)) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) red[kCgDots * stride] = (double)it;
+    return false;
+  }
+  beta = it == 0 ? 0.0 : h.d[2] / h.d[3];
+  return true;
 }
 
 // Step `it`, first half: stops everything once r.r is small enough, else
@@ -116,18 +146,16 @@ __global__ __launch_bounds__(256) void cg_start_kernel(const ScalMesh m, double 
 // state, the partial sums and the first cell's frame are all asked for at once
 // (5.9 us on 4^3 cells, p = 4, and the update 3.5; 8.8 and 4.1 one after the other).
 template <int P>
-__global__ __launch_bounds__(256) void cg_apply_kernel(const ScalMesh m, double kappa2, int n_cells, int n_part,
+__global__ __launch_bounds__(256) void cg_apply_kernel(const ScalMesh m, double kappa2, int64_t n, int n_part,
                                                        int it, double tol, const double* __restrict__ z,
                                                        const double* __restrict__ p_old, double* __restrict__ p_new,
-                                                       double* __restrict__ q, double* __restrict__ red) {
+                                                       double* __restrict__ q, int stride,
+                                                       double* __restrict__ red) {
   extern __shared__ double fsm[];
   __shared__ double sm[16];
-  const int odd = it & 1;
   constexpr int p = P, w = 2 * p + 1, w3 = w * w * w;
   constexpr int kCgPre = w3 <= 1024 ? (w3 + 255) / 256 : 4;       // frame values per thread fetched ahead
-  const double state = red[kCgDots * kFieldRed];
-  double d[4] = {cg_part(red, kCgRr + odd, n_part), cg_part(red, kCgBb, n_part), cg_part(red, kCgRz + odd, n_part),
-                 it > 0 ? cg_part(red, kCgRz + 1 - odd, n_part) : 0.0};
+  CgHead head = cg_ask(red, stride, n_part, it);
   const auto node = [&](int e, int t) {   // frame entry t of cell e
     const int cx = e % m.nx, cyz = e / m.nx, cy = cyz % m.ny, cz = cyz / m.ny;
     const int fx = t % w, fy = (t / w) % w, fz = t / (w * w);
@@ -150,18 +178,12 @@ __global__ __launch_bounds__(256) void cg_apply_kernel(const ScalMesh m, double 
   double* sM = sX + w3;                   // [p][w][w] mass part along z, then [p][p][w]
   double* sS = sM + p * w * w;            // stiffness part, likewise
   for (int t = threadIdx.x; t < 2 * p * w; t += 256) sR[t] = m.rows[t];
-  block_sums(d, sm);
-  if (state >= 0.0) return;               // a step before has stopped the iteration
-  const double rr = d[0], bb = d[1];
-  if (bb == 0.0 || (it > 0 && sqrt(rr) / sqrt(bb) <= tol)) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) red[kCgDots * kFieldRed] = (double)it;
-    return;
-  }
-  const double beta = it == 0 ? 0.0 : d[2] / d[3];
+  double beta;
+  if (!cg_go(head, sm, red, stride, it, tol, beta)) return;
   const double* rS = sR;
   const double* rM = sR + p * w;
   double pq = 0.0;
-  for (int e = blockIdx.x; e < n_cells; e += gridDim.x) {
+  for (int e = blockIdx.x; e < n; e += gridDim.x) {
     const bool first = e == (int)blockIdx.x;
     if (!first) __syncthreads();          // the last cell's sX is read
     const auto put = [&](int t, double zv, double pv) {
@@ -237,19 +259,84 @@ __global__ __launch_bounds__(256) void cg_apply_kernel(const ScalMesh m, double 
     }
   }
   pq = block_sum(pq, sm);
-  if (threadIdx.x == 0) red[kCgPq * kFieldRed + blockIdx.x] = pq;
+  if (threadIdx.x == 0) red[kCgPq * stride + blockIdx.x] = pq;
+}
+
+// The same first half for orders 1 and 2, a thread per node: its row of A reaches 27 to
+// 125 nodes, read through the caches, where a workgroup per cell would have one or eight
+// nodes to share its barriers: 128 steps on 64^3 cells with p = 1 4 and 34 ms, p = 2 36
+// and 51; on 16^3 with p = 2 3.3 and 2.9.  From p = 3 a node reads too many.
+template <int P>
+__global__ __launch_bounds__(256) void cg_apply_node_kernel(const ScalMesh m, double kappa2, int64_t n, int n_part,
+                                                            int it, double tol, const double* __restrict__ z,
+                                                            const double* __restrict__ p_old,
+                                                            double* __restrict__ p_new, double* __restrict__ q,
+                                                            int stride, double* __restrict__ red) {
+  __shared__ double sm[16];
+  constexpr int w = 2 * P + 1;
+  __shared__ double sR[2 * P * w];
+  for (int t = threadIdx.x; t < 2 * P * w; t += 256) sR[t] = m.rows[t];
+  CgHead head = cg_ask(red, stride, n_part, it);
+  double beta;
+  if (!cg_go(head, sm, red, stride, it, tol, beta)) return;   // (its barriers order sR)
+  double pq = 0.0;
+  for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const int iyz = (int)(i / m.Nx), ix = (int)(i - (int64_t)iyz * m.Nx), iz = iyz / m.Ny, iy = iyz - iz * m.Ny;
+    const int a = ix % P, b = iy % P, c = iz % P;
+    // rows of the three directions: entry j at node offset j - P from the cell's first node
+    const double *Sx = sR + a * w, *Sy = sR + b * w, *Sz = sR + c * w;
+    const double *Mx = Sx + P * w, *My = Sy + P * w, *Mz = Sz + P * w;
+    int off[w];
+#pragma unroll
+    for (int j = 0; j < w; ++j) {
+      const int x = ix - a + j - P;
+      off[j] = x < 0 ? x + m.Nx : x >= m.Nx ? x - m.Nx : x;
+    }
+    double y = 0.0, own = 0.0;
+#pragma unroll
+    for (int jz = 0; jz < w; ++jz) {
+      if (jz < P && c > 0) continue;      // (rows a > 0 stay in the cell)
+      int kz = iz - c + jz - P;
+      kz = kz < 0 ? kz + m.Nz : kz >= m.Nz ? kz - m.Nz : kz;
+#pragma unroll
+      for (int jy = 0; jy < w; ++jy) {
+        if (jy < P && b > 0) continue;
+        int ky = iy - b + jy - P;
+        ky = ky < 0 ? ky + m.Ny : ky >= m.Ny ? ky - m.Ny : ky;
+        const int64_t r0 = (int64_t)m.Nx * (ky + (int64_t)m.Ny * kz);
+        double vs = 0.0, vm = 0.0;
+#pragma unroll
+        for (int j = 0; j < w; ++j) {     // (entries left of the cell are zero in rows a > 0)
+          double v = z[r0 + off[j]];
+          if (it > 0) v = fma(beta, p_old[r0 + off[j]], v);
+          vs = fma(Sx[j], v, vs);
+          vm = fma(Mx[j], v, vm);
+          if (jz == P + c && jy == P + b && j == P + a) own = v;
+        }
+        const double mm = My[jy] * Mz[jz];
+        y = fma(m.sx * mm, vs, y);
+        y = fma(m.sy * Sy[jy] * Mz[jz] + m.sz * My[jy] * Sz[jz] + kappa2 * mm, vm, y);
+      }
+    }
+    y *= m.J;
+    p_new[i] = own;
+    q[i] = y;
+    pq = fma(own, y, pq);
+  }
+  pq = block_sum(pq, sm);
+  if (threadIdx.x == 0) red[kCgPq * stride + blockIdx.x] = pq;
 }
 
 // Second half: u += alpha p, r -= alpha q, z = r / diag(A); partial r.r, r.z for the next step
 __global__ __launch_bounds__(256) void cg_update_kernel(const ScalMesh m, double kappa2, int64_t n, int n_part,
                                                         int n_pq, int it, const double* __restrict__ p,
                                                         const double* __restrict__ q, double* __restrict__ u,
-                                                        double* __restrict__ r, double* __restrict__ z,
+                                                        double* __restrict__ r, double* __restrict__ z, int stride,
                                                         double* __restrict__ red) {
   __shared__ double sm[8];
   const int odd = it & 1;
-  const double state = red[kCgDots * kFieldRed];
-  double d[2] = {cg_part(red, kCgRz + odd, n_part), cg_part(red, kCgPq, n_pq)};
+  const double state = red[kCgDots * stride];
+  double d[2] = {cg_part(red, stride, kCgRz + odd, n_part), cg_part(red, stride, kCgPq, n_pq)};
   const int64_t i0 = blockIdx.x * (int64_t)256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
   // this thread's first values, asked for with the sums
   const int64_t ic = i0 < n ? i0 : n - 1;
@@ -276,8 +363,8 @@ __global__ __launch_bounds__(256) void cg_update_kernel(const ScalMesh m, double
   }
   block_sums(s, sm);
   if (threadIdx.x == 0) {
-    red[(kCgRr + 1 - odd) * kFieldRed + blockIdx.x] = s[0];
-    red[(kCgRz + 1 - odd) * kFieldRed + blockIdx.x] = s[1];
+    red[(kCgRr + 1 - odd) * stride + blockIdx.x] = s[0];
+    red[(kCgRz + 1 - odd) * stride + blockIdx.x] = s[1];
   }
 }
 
@@ -509,7 +596,7 @@ static FieldOps& fops(chfsi_ctx* c) {
     f.ones.alloc(std::max<int64_t>(c->n_nodes, np));
     fill(c, std::max<int64_t>(c->n_nodes, np), 1.0, f.ones.ptr);
     f.gq.alloc(np);
-    f.red.alloc(kCgDots * kFieldRed + 1);
+    f.red.alloc(kCgDots * kCgParts + 1);
     f.be.alloc((size_t)c->n_cells * nloc);
     f.mesh = ScalMesh{p, n, nq, c->nc[0], c->nc[1], c->nc[2], c->Nd[0], c->Nd[1], c->Nd[2], c->ref_b1.ptr,
                       c->ref_wq.ptr, f.rows.ptr, c->J, 4.0 / (c->h[0] * c->h[0]), 4.0 / (c->h[1] * c->h[1]),
@@ -577,25 +664,29 @@ static int pcg(chfsi_ctx* c, FieldOps& f, double kappa2, double tol, int max_ite
   const int64_t n = c->n_nodes;
   double *u = f.v[0].ptr, *r = f.v[1].ptr, *z = f.v[2].ptr, *q = f.v[5].ptr, *b = f.v[6].ptr;
   double* pp[2] = {f.v[3].ptr, f.v[4].ptr};
-  const int n_part = (int)std::min<int64_t>(kFieldRed, cdiv(n, 256));
-  const int n_pq = std::min(kFieldRed, c->n_cells);
   const int p = c->p, w = 2 * p + 1;
-  const size_t sh = (size_t)(2 * p * w + w * w * w + 2 * p * w * w) * sizeof(double);
-  static constexpr decltype(&cg_apply_kernel<1>) kApply[] = {cg_apply_kernel<1>, cg_apply_kernel<2>, cg_apply_kernel<3>,
-                                                             cg_apply_kernel<4>, cg_apply_kernel<5>, cg_apply_kernel<6>,
-                                                             cg_apply_kernel<7>, cg_apply_kernel<8>};
+  // a thread per node or, from p = 3 on, a workgroup per cell
+  const bool by_node = p <= 2;
+  const int n_part = std::min(kCgParts, cdiv(n, 256));
+  const int n_pq = by_node ? n_part : std::min(kCgParts, c->n_cells);
+  const int stride = std::max(n_part, n_pq);
+  const size_t sh = by_node ? 0 : (size_t)(2 * p * w + w * w * w + 2 * p * w * w) * sizeof(double);
+  static constexpr decltype(&cg_apply_kernel<3>) kApply[] = {
+      cg_apply_node_kernel<1>, cg_apply_node_kernel<2>, cg_apply_kernel<3>, cg_apply_kernel<4>,
+      cg_apply_kernel<5>,      cg_apply_kernel<6>,      cg_apply_kernel<7>, cg_apply_kernel<8>};
   static_assert(sizeof kApply / sizeof *kApply == kMaxP, "one per order");
-  hipLaunchKernelGGL(cg_start_kernel, dim3(n_part), dim3(256), 0, c->stream, f.mesh, kappa2, n, b, u, r, z, f.red.ptr);
+  hipLaunchKernelGGL(cg_start_kernel, dim3(n_part), dim3(256), 0, c->stream, f.mesh, kappa2, n, b, u, r, z, stride,
+                     f.red.ptr);
   LAUNCH_CHECK();
-  std::vector<double> h((size_t)kCgDots * kFieldRed + 1);
+  std::vector<double> h((size_t)kCgDots * stride + 1);
   for (int it = 0;;) {
     const int end = std::min(max_iter, it + kCgBatch);
     for (; it < end; ++it) {
-      hipLaunchKernelGGL(kApply[p - 1], dim3(n_pq), dim3(256), sh, c->stream, f.mesh, kappa2, c->n_cells, n_part,
-                         it, tol, z, pp[1 - (it & 1)], pp[it & 1], q, f.red.ptr);
+      hipLaunchKernelGGL(kApply[p - 1], dim3(n_pq), dim3(256), sh, c->stream, f.mesh, kappa2,
+                         by_node ? n : c->n_cells, n_part, it, tol, z, pp[1 - (it & 1)], pp[it & 1], q, stride, f.red.ptr);
       LAUNCH_CHECK();
       hipLaunchKernelGGL(cg_update_kernel, dim3(n_part), dim3(256), 0, c->stream, f.mesh, kappa2, n, n_part, n_pq, it,
-                         pp[it & 1], q, u, r, z, f.red.ptr);
+                         pp[it & 1], q, u, r, z, stride, f.red.ptr);
       LAUNCH_CHECK();
     }
     CHFSI_HIP(hipMemcpyAsync(h.data(), f.red.ptr, h.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
@@ -604,8 +695,8 @@ static int pcg(chfsi_ctx* c, FieldOps& f, double kappa2, double tol, int max_ite
     const int done = state >= 0.0 ? (int)state : it;
     double rr = 0.0, bb = 0.0;
     for (int g = 0; g < n_part; ++g) {
-      rr += h[(size_t)(kCgRr + (done & 1)) * kFieldRed + g];
-      bb += h[(size_t)kCgBb * kFieldRed + g];
+      rr += h[(size_t)(kCgRr + (done & 1)) * stride + g];
+      bb += h[(size_t)kCgBb * stride + g];
     }
     const double rel = bb == 0.0 ? 0.0 : std::sqrt(rr) / std::sqrt(bb);
     if (state < 0.0 && it < max_iter) continue;
