@@ -59,7 +59,7 @@ struct MfMesh {
 // far as the registers do not spill much (FP64 at n_p = 6 and five waves: 54 ms for
 // an adjoint that takes 42 at four)
 template <class T>
-constexpr int mf_waves(int NP) { return sizeof(T) == 8 ? (NP <= 6 ? 4 : NP == 7 ? 3 : 2) : (NP <= 7 ? 6 : 3); }
+constexpr int mf_waves(int NP) { return sizeof(T) == 8 ? (NP <= 6 ? 4 : NP == 8 ? 2 : 3) : (NP <= 7 ? 6 : 3); }
 // columns per workgroup: the same LDS bytes in both precisions
 template <class T>
 constexpr int mf_cw(int NP) { return sizeof(T) == 8 ? sf_cols(NP) : 2 * sf_cols(NP); }
@@ -79,42 +79,44 @@ __device__ __forceinline__ void grad_line(const T* __restrict__ eoDf, const T* _
                                           const T* __restrict__ kin, const typename MfT<T>::C2 (&u)[NP],
                                           typename MfT<T>::C2 (&w)[NP]) {
   typedef typename MfT<T>::C2 C2;
-  C2 g[NP], dw[NP];
-  if constexpr (sizeof(T) == 8) {
+  if constexpr (sizeof(T) == 8 && !KT) {
+    const T c = a_d * wl;
+    sf_eo_each<T, NP, false>(eoK, u, [&](int r, C2 v) {
+      w[r] = C2{fma(c, v.x, w[r].x), fma(c, v.y, w[r].y)};
+      if (r >= NP / 2) __builtin_amdgcn_sched_barrier(0);   // (one pair's sums at a time in registers)
+    });
+  } else if constexpr (sizeof(T) == 8) {
+    C2 g[NP], dw[NP];
     sf_eo<T, NP, false>(eoK, u, dw);
     const T c = a_d * wl;
 #pragma unroll
     for (int r = 0; r < NP; ++r) w[r] = C2{fma(c, dw[r].x, w[r].x), fma(c, dw[r].y, w[r].y)};
-    if constexpr (KT) {
-      // (the barriers keep the two contractions' registers apart)
-      __builtin_amdgcn_sched_barrier(0);
-      sf_eo<T, NP, true>(eoDf, u, g);
-#pragma unroll
-      for (int r = 0; r < NP; ++r) {      // -i b wJ g = b wJ g.y - i b wJ g.x
-        const T s = b_d * wl * w1[r];
-        w[r].x = fma(s, g[r].y, w[r].x);
-        w[r].y = fma(-s, g[r].x, w[r].y);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  } else {
+    // (the barriers keep the two contractions' registers apart)
+    __builtin_amdgcn_sched_barrier(0);
     sf_eo<T, NP, true>(eoDf, u, g);
-    C2 fk[NP];
+#pragma unroll
+    for (int r = 0; r < NP; ++r) {        // -i b wJ g = b wJ g.y - i b wJ g.x
+      const T s = b_d * wl * w1[r];
+      w[r].x = fma(s, g[r].y, w[r].x);
+      w[r].y = fma(-s, g[r].x, w[r].y);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  } else {
+    C2 g[NP], fk[NP];
+    sf_eo<T, NP, true>(eoDf, u, g);
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
       const T k = kin[q * NP * NP];
       fk[q] = C2{k * g[q].x, k * g[q].y};
     }
-    sf_eo<T, NP, true>(eoDb, fk, dw);
+    sf_eo_each<T, NP, true>(eoDb, fk, [&](int r, C2 v) { w[r] = C2{w[r].x + v.x, w[r].y + v.y}; });
+    if constexpr (KT) {
 #pragma unroll
-    for (int r = 0; r < NP; ++r) w[r] = C2{w[r].x + dw[r].x, w[r].y + dw[r].y};
-  }
-  if constexpr (KT && sizeof(T) == 4) {
-#pragma unroll
-    for (int r = 0; r < NP; ++r) {
-      const T s = b_d * wl * w1[r];
-      w[r].x = fma(s, g[r].y, w[r].x);
-      w[r].y = fma(-s, g[r].x, w[r].y);
+      for (int r = 0; r < NP; ++r) {
+        const T s = b_d * wl * w1[r];
+        w[r].x = fma(s, g[r].y, w[r].x);
+        w[r].y = fma(-s, g[r].x, w[r].y);
+      }
     }
   }
 }
@@ -125,6 +127,22 @@ __device__ __forceinline__ void grad_line(const T* __restrict__ eoDf, const T* _
 // orders keep consecutive lines.
 template <int NP>
 constexpr int mf_ypitch() { return NP == 6 || NP == 7 ? 8 : NP; }
+
+// Points between neighbouring x-lines in LDS: n_p = 8 would put every line of an x pass
+// on the same banks (degree-6 filter, k = 0, FP64, 128 columns on 8^3 cells: 10.2 against 10.4 ms).
+template <int NP>
+constexpr int mf_pitch() { return NP == 8 ? 9 : NP; }
+
+// Phase 3 in two parts, the x-lines of each spin by themselves (each thread reads the other
+// spin's values from LDS), instead of both spins' lines in one thread.  Together saves
+// a pass over the LDS, but takes the registers of four lines and half the threads (a
+// quarter of them at n_p >= 8).  With the k-term that never pays: against together,
+// FP64 degree-6 filter, 128 columns: p = 5, 14^3 cells 17.3 and 17.8 ms, p = 6, 12^3
+// 17.8 and 18.4, p = 7, 8^3 9.9 and 11.8, p = 8, 8^3 17.7 and 20.0; FP32, p = 6, 15.9 and 17.5.
+// At k = 0 it pays for n_p = 8 (9.9 and 10.4, FP32 8.3 and 9.2) and in FP32 for 7 (15.8
+// and 16.2), not elsewhere (FP64 p = 6 17.7 and 17.3, p = 8 18.9 and 17.7).
+template <class T, int NP, bool KT>
+constexpr bool mf_split() { return KT || NP == 8 || (sizeof(T) == 4 && NP == 7); }
 
 // tab: [B: NP*NP][Dq: NP*NP][w: NP][even-odd tables of B, B^T, Dq, Dq^T, K], qd:
 // [E][x][y + NP z] of (wJ V, wJ Bx, wJ By, wJ Bz), kin: [3][point on the line][line],
@@ -140,7 +158,7 @@ constexpr int mf_ypitch() { return NP == 6 || NP == 7 ? 8 : NP; }
 //   2. y: B                                6. B^T along y
 //   3. x: B -> U; potential, kinetic x     7. B^T along x, y scattered
 //   4. + kinetic y
-// (phase 3 takes the x-lines of both spins together, as the field couples them).
+// (phase 3 takes the x-lines of both spins together or one by one, see mf_split).
 // Nothing saturates: the vector units (38 % busy), the requests of 32-byte row
 // pieces to L2 (45 %), the LDS and the waits for rows each take a share at the
 // three workgroups per CU that 44 KB of LDS allow, so each is kept short: one
@@ -166,11 +184,12 @@ __global__ __launch_bounds__(MfT<T>::NT, mf_waves<T>(NP)) void mf_apply_kernel(
   constexpr int CW = mf_cw<T>(NP);
   constexpr int N2 = NP * NP, N3 = N2 * NP;
   constexpr int YP = mf_ypitch<NP>(), NY = YP * NP;
+  constexpr int SY = mf_pitch<NP>(), SZ = SY * NP, SF = SZ * NP;   // point (x, y, z): x + SY y + SZ z
   static_assert(2 * CW * N2 <= NT, "one edge task per thread");
   extern __shared__ double2 mf_sm_raw[];
-  C2* bufU = reinterpret_cast<C2*>(mf_sm_raw);   // [CW][2][N3]
-  C2* bufW = bufU + CW * 2 * N3;
-  T* w2 = reinterpret_cast<T*>(bufW + CW * 2 * N3);  // [N2] J w_a w_b
+  C2* bufU = reinterpret_cast<C2*>(mf_sm_raw);   // [CW][2][SF]
+  C2* bufW = bufU + CW * 2 * SF;
+  T* w2 = reinterpret_cast<T*>(bufW + CW * 2 * SF);  // [N2] J w_a w_b
   const T* w1 = tab + 2 * N2;
   const T* eoBf = tab + 2 * N2 + NP;
   const T* eoBb = eoBf + sf_eo_size(NP);
@@ -187,7 +206,7 @@ __global__ __launch_bounds__(MfT<T>::NT, mf_waves<T>(NP)) void mf_apply_kernel(
   const bool edge = tid < 2 * CW * N2;
   const int tc = tid % CW, ts = (tid / CW) % 2, tl = tid / (2 * CW);
   const int ta = tl % NP, tb = tl / NP;          // the line's two fixed indices
-  const int tf = (tc * 2 + ts) * N3;
+  const int tf = (tc * 2 + ts) * SF;
   const int e = cells ? cells[item / n_chunks] : item / n_chunks;
   const int col = (item % n_chunks) * CW + tc;
   const int cx = e % mesh.nx, cyz = e / mesh.nx;
@@ -223,7 +242,7 @@ __global__ __launch_bounds__(MfT<T>::NT, mf_waves<T>(NP)) void mf_apply_kernel(
     }
     sf_eo<T, NP, false>(eoBf, u, r);
 #pragma unroll
-    for (int o = 0; o < NP; ++o) bufU[tf + tl + o * N2] = r[o];
+    for (int o = 0; o < NP; ++o) bufU[tf + ta + SY * tb + o * SZ] = r[o];
   }
   lds_barrier();
 
@@ -231,7 +250,7 @@ __global__ __launch_bounds__(MfT<T>::NT, mf_waves<T>(NP)) void mf_apply_kernel(
   const auto yline = [&](int t, int& f, int& l) {
     const int g = t % NY, fi = t / NY, x = g % YP, z = g / YP;
     l = x + NP * z;
-    f = fi * N3 + x + z * N2;
+    f = fi * SF + x + z * SZ;
     return x < NP;
   };
   // 2. y
@@ -240,78 +259,88 @@ __global__ __launch_bounds__(MfT<T>::NT, mf_waves<T>(NP)) void mf_apply_kernel(
     if (!yline(t, p, l)) continue;
     C2 v[NP], r[NP];
 #pragma unroll
-    for (int j = 0; j < NP; ++j) v[j] = bufU[p + j * NP];
+    for (int j = 0; j < NP; ++j) v[j] = bufU[p + j * SY];
     sf_eo<T, NP, false>(eoBf, v, r);
 #pragma unroll
-    for (int o = 0; o < NP; ++o) bufU[p + o * NP] = r[o];
+    for (int o = 0; o < NP; ++o) bufU[p + o * SY] = r[o];
   }
   lds_barrier();
 
-  // 3. x-lines of both spins: U, potential and field, kinetic x
-  for (int t = tid; t < N2 * CW; t += NT) {
-    const int l = t % N2, base = (t / N2) * 2 * N3 + l * NP;
-    const Q4* __restrict__ dq = qd + (size_t)e * N3 + l;
-    const T wl = w2[l];
-    C2 u0[NP], u1[NP], s0[NP], s1[NP];
-    {
-      C2 v[NP];
+  // 3. x-lines: U, potential and field, kinetic x
+  if constexpr (mf_split<T, NP, KT>()) {
+    for (int t = tid; t < N2 * 2 * CW; t += NT) {
+      const int l = t % N2, base = (t / N2) * SF + l * SY;
+      C2 v[NP], r[NP];
 #pragma unroll
       for (int j = 0; j < NP; ++j) v[j] = bufU[base + j];
-      sf_eo<T, NP, false>(eoBf, v, u0);
+      sf_eo<T, NP, false>(eoBf, v, r);
 #pragma unroll
-      for (int j = 0; j < NP; ++j) v[j] = bufU[base + N3 + j];
-      sf_eo<T, NP, false>(eoBf, v, u1);
+      for (int o = 0; o < NP; ++o) bufU[base + o] = r[o];
     }
-#pragma unroll
-    for (int q = 0; q < NP; ++q) {
-      bufU[base + q] = u0[q];
-      bufU[base + N3 + q] = u1[q];
-      // up:   (s + Bz) u0 + (Bx - i By) u1;  down: (s - Bz) u1 + (Bx + i By) u0
-      const Q4 d = dq[q * N2];
-      const T s = KT ? d.x + half_k2 * (wl * w1[q]) : d.x;
-      s0[q].x = (s + d.w) * u0[q].x + d.y * u1[q].x + d.z * u1[q].y;
-      s0[q].y = (s + d.w) * u0[q].y + d.y * u1[q].y - d.z * u1[q].x;
-      s1[q].x = (s - d.w) * u1[q].x + d.y * u0[q].x - d.z * u0[q].y;
-      s1[q].y = (s - d.w) * u1[q].y + d.y * u0[q].y + d.z * u0[q].x;
-    }
-    if constexpr (KT && sizeof(T) == 8) {
-      // one spin's lines after the other's, the second from LDS again: with both in
-      // registers beside the k-term's derivative they spilled or cost a resident
-      // workgroup (p = 5, 256 columns on 10^3 cells 2.14 ms, now 1.80; p = 7, 128
-      // columns on 8^3 1.69 and 1.17)
-#pragma unroll
-      for (int q = 0; q < NP; ++q) bufW[base + N3 + q] = s1[q];
-      asm volatile("" ::: "memory");      // (not forwarded to the loads below)
-      grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, wl, a0, b0, kin + l, u0, s0);
-#pragma unroll
-      for (int q = 0; q < NP; ++q) bufW[base + q] = s0[q];
-      asm volatile("" ::: "memory");
+    lds_barrier();
+    for (int t = tid; t < N2 * 2 * CW; t += NT) {
+      const int l = t % N2, f = t / N2, base = f * SF + l * SY, other = (f ^ 1) * SF + l * SY;
+      const Q4* __restrict__ dq = qd + (size_t)e * N3 + l;
+      const T wl = w2[l], sg = (f & 1) ? (T)-1 : (T)1;
+      C2 u[NP], s[NP];
 #pragma unroll
       for (int q = 0; q < NP; ++q) {
-        u1[q] = bufU[base + N3 + q];
-        s1[q] = bufW[base + N3 + q];
+        u[q] = bufU[base + q];
+        // up:   (s + Bz) u0 + (Bx - i By) u1;  down: (s - Bz) u1 + (Bx + i By) u0
+        const C2 o = bufU[other + q];
+        const Q4 d = dq[q * N2];
+        const T sv = (KT ? d.x + half_k2 * (wl * w1[q]) : d.x) + sg * d.w, dz = sg * d.z;
+        s[q].x = sv * u[q].x + d.y * o.x + dz * o.y;
+        s[q].y = sv * u[q].y + d.y * o.y - dz * o.x;
       }
+      grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, wl, a0, b0, kin + l, u, s);
+#pragma unroll
+      for (int q = 0; q < NP; ++q) bufW[base + q] = s[q];
+    }
+  } else {
+    for (int t = tid; t < N2 * CW; t += NT) {
+      const int l = t % N2, base = (t / N2) * 2 * SF + l * SY;
+      const Q4* __restrict__ dq = qd + (size_t)e * N3 + l;
+      const T wl = w2[l];
+      C2 u0[NP], u1[NP], s0[NP], s1[NP];
+      {
+        C2 v[NP];
+#pragma unroll
+        for (int j = 0; j < NP; ++j) v[j] = bufU[base + j];
+        sf_eo<T, NP, false>(eoBf, v, u0);
+#pragma unroll
+        for (int j = 0; j < NP; ++j) v[j] = bufU[base + SF + j];
+        sf_eo<T, NP, false>(eoBf, v, u1);
+      }
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        bufU[base + q] = u0[q];
+        bufU[base + SF + q] = u1[q];
+        // up:   (s + Bz) u0 + (Bx - i By) u1;  down: (s - Bz) u1 + (Bx + i By) u0
+        const Q4 d = dq[q * N2];
+        const T s = d.x;
+        s0[q].x = (s + d.w) * u0[q].x + d.y * u1[q].x + d.z * u1[q].y;
+        s0[q].y = (s + d.w) * u0[q].y + d.y * u1[q].y - d.z * u1[q].x;
+        s1[q].x = (s - d.w) * u1[q].x + d.y * u0[q].x - d.z * u0[q].y;
+        s1[q].y = (s - d.w) * u1[q].y + d.y * u0[q].y + d.z * u0[q].x;
+      }
+      grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, wl, a0, b0, kin + l, u0, s0);
       grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, wl, a0, b0, kin + l, u1, s1);
 #pragma unroll
-      for (int q = 0; q < NP; ++q) bufW[base + N3 + q] = s1[q];
-      continue;
-    }
-    grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, wl, a0, b0, kin + l, u0, s0);
-    grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, wl, a0, b0, kin + l, u1, s1);
-#pragma unroll
-    for (int q = 0; q < NP; ++q) {
-      bufW[base + q] = s0[q];
-      bufW[base + N3 + q] = s1[q];
+      for (int q = 0; q < NP; ++q) {
+        bufW[base + q] = s0[q];
+        bufW[base + SF + q] = s1[q];
+      }
     }
   }
 
   // the output rows of phase 7's x-line, in flight while the next phases run
   const int I7 = fx + mesh.Nx * wrap(fy + ta, mesh.Ny) + mesh.Nxy * wrap(fz + tb, mesh.Nz);
   double2* __restrict__ y0 = Y + ((2 * (int64_t)I7 + ts) * ldy + col);
-  // (FP64; in FP32, and with the k-term from n_p = 7 on, their registers cost more:
-  // p = 6, k != 0, 128 columns on 12^3 cells 2.50 ms with them, 2.42 without; p = 5
-  // 1.80 and 1.85)
-  constexpr bool kEarly = sizeof(T) == 8 && !(KT && NP >= 7);
+  // (FP64; in FP32, with the k-term from n_p = 7 on, and at n_p = 9 their registers cost
+  // more: p = 6, k != 0, 128 columns on 12^3 cells 2.50 ms with them, 2.42 without; p = 5
+  // 1.80 and 1.85; p = 8, k = 0, degree-6 filter on 8^3 18.5 and 17.9)
+  constexpr bool kEarly = sizeof(T) == 8 && NP <= (KT ? 6 : 8);
   double2 yo[NP];
   if (kEarly && ok && !ye) {
 #pragma unroll
@@ -325,27 +354,27 @@ __global__ __launch_bounds__(MfT<T>::NT, mf_waves<T>(NP)) void mf_apply_kernel(
     if (!yline(t, p, l)) continue;
     C2 u[NP], w[NP];
 #pragma unroll
-    for (int j = 0; j < NP; ++j) u[j] = bufU[p + j * NP];
+    for (int j = 0; j < NP; ++j) u[j] = bufU[p + j * SY];
 #pragma unroll
-    for (int j = 0; j < NP; ++j) w[j] = bufW[p + j * NP];
+    for (int j = 0; j < NP; ++j) w[j] = bufW[p + j * SY];
     grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, w2[l], a1, b1, kin + N3 + l, u, w);
 #pragma unroll
-    for (int j = 0; j < NP; ++j) bufW[p + j * NP] = w[j];
+    for (int j = 0; j < NP; ++j) bufW[p + j * SY] = w[j];
   }
   lds_barrier();
 
   // 5. kinetic z; W is then complete, and goes back along z
   for (int t = tid; t < N2 * 2 * CW; t += NT) {
-    const int l = t % N2, base = (t / N2) * N3 + l;
+    const int l = t % N2, base = (t / N2) * SF + l % NP + SY * (l / NP);
     C2 u[NP], w[NP], r[NP];
 #pragma unroll
-    for (int j = 0; j < NP; ++j) u[j] = bufU[base + j * N2];
+    for (int j = 0; j < NP; ++j) u[j] = bufU[base + j * SZ];
 #pragma unroll
-    for (int j = 0; j < NP; ++j) w[j] = bufW[base + j * N2];
+    for (int j = 0; j < NP; ++j) w[j] = bufW[base + j * SZ];
     grad_line<T, NP, KT>(eoDf, eoDb, eoK, w1, w2[l], a2, b2, kin + 2 * N3 + l, u, w);
     sf_eo<T, NP, false>(eoBb, w, r);
 #pragma unroll
-    for (int j = 0; j < NP; ++j) bufW[base + j * N2] = r[j];
+    for (int j = 0; j < NP; ++j) bufW[base + j * SZ] = r[j];
   }
   lds_barrier();
 
@@ -355,10 +384,10 @@ __global__ __launch_bounds__(MfT<T>::NT, mf_waves<T>(NP)) void mf_apply_kernel(
     if (!yline(t, p, l)) continue;
     C2 v[NP], r[NP];
 #pragma unroll
-    for (int j = 0; j < NP; ++j) v[j] = bufW[p + j * NP];
+    for (int j = 0; j < NP; ++j) v[j] = bufW[p + j * SY];
     sf_eo<T, NP, false>(eoBb, v, r);
 #pragma unroll
-    for (int o = 0; o < NP; ++o) bufW[p + o * NP] = r[o];
+    for (int o = 0; o < NP; ++o) bufW[p + o * SY] = r[o];
   }
   lds_barrier();
 
@@ -366,7 +395,7 @@ __global__ __launch_bounds__(MfT<T>::NT, mf_waves<T>(NP)) void mf_apply_kernel(
   if (ok) {
     C2 v[NP], y[NP];
 #pragma unroll
-    for (int j = 0; j < NP; ++j) v[j] = bufW[tf + tl * NP + j];
+    for (int j = 0; j < NP; ++j) v[j] = bufW[tf + tl * SY + j];
     sf_eo<T, NP, false>(eoBb, v, y);
     if (ye) {                             // all cells in one launch: gathered by the caller
       C2* __restrict__ yr = ye + (((size_t)e * N3 + tl * NP) * 2 + ts) * n_vec + col;
@@ -410,7 +439,7 @@ void launch_mf_t(chfsi_ctx* c, const KPoint& kp, const double2* X, int64_t ldx, 
   typedef typename MfT<T>::C2 C2;
   typedef typename MfT<T>::Q4 Q4;
   constexpr int CW = mf_cw<T>(NP);
-  const size_t sh = 2 * (size_t)CW * 2 * NP * NP * NP * sizeof(C2) + NP * NP * sizeof(T);
+  const size_t sh = 2 * (size_t)CW * 2 * mf_pitch<NP>() * NP * NP * sizeof(C2) + NP * NP * sizeof(T);
   const MfMesh mesh{c->nc[0], c->nc[1], c->Nd[0], c->Nd[1], c->Nd[2], c->Nd[0] * c->Nd[1]};
   const int n_chunks = cdiv(n_vec, CW);
   T a[3], b[3];

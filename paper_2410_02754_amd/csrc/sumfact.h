@@ -49,9 +49,10 @@ template <> struct SfC2<float> { typedef float2 type; };
 // h][M[i][h]: h][M[h][h]].
 constexpr int sf_eo_size(int NP) { return 2 * (NP / 2) * (NP / 2) + 2 * (NP / 2) + 1; }
 
-template <class T, int N, bool SK>
-__device__ __forceinline__ void sf_eo(const T* __restrict__ tb, const typename SfC2<T>::type* in,
-                                      typename SfC2<T>::type* out) {
+// f(o, value) for every output, in pairs (o, n-1-o), then the middle one: what is done
+// with a value at once needs no registers for a whole line of them
+template <class T, int N, bool SK, class F>
+__device__ __forceinline__ void sf_eo_each(const T* __restrict__ tb, const typename SfC2<T>::type* in, F f) {
   typedef typename SfC2<T>::type C2;
   constexpr int h = N / 2;
   constexpr bool odd = (N % 2) != 0;
@@ -86,8 +87,8 @@ __device__ __forceinline__ void sf_eo(const T* __restrict__ tb, const typename S
         si = fma(mrow[o], in[h].y, si);
       }
     }
-    out[o] = C2{sr + dr, si + di};
-    out[N - 1 - o] = C2{sr - dr, si - di};
+    f(o, C2{sr + dr, si + di});
+    f(N - 1 - o, C2{sr - dr, si - di});
   }
   if constexpr (odd) {
     T r = 0, im = 0;
@@ -101,8 +102,15 @@ __device__ __forceinline__ void sf_eo(const T* __restrict__ tb, const typename S
       r = fma(mcol[h], in[h].x, r);
       im = fma(mcol[h], in[h].y, im);
     }
-    out[h] = C2{r, im};
+    f(h, C2{r, im});
   }
+}
+
+template <class T, int N, bool SK>
+__device__ __forceinline__ void sf_eo(const T* __restrict__ tb, const typename SfC2<T>::type* in,
+                                      typename SfC2<T>::type* out) {
+  typedef typename SfC2<T>::type C2;
+  sf_eo_each<T, N, SK>(tb, in, [&](int o, C2 v) { out[o] = v; });
 }
 
 // First point of line l along DIM in a padded field (point (x, y, z) at
