@@ -1016,17 +1016,19 @@ size_t products_scratch_bytes(const chfsi_ctx* c, int n_vec, bool fp64) {
 }
 
 // The context's ye for this apply, or null: per-colour launches (which also serve
-// where nothing may be allocated, the fixed-scratch filter or a capture that
-// comes before the first such apply).
+// where nothing may be allocated, the fixed-scratch filter).  Under stream capture
+// always null: a graph would keep ye's address, and a wider apply after the capture
+// moves ye.  (The default stream cannot be captured.)
 static void* ye_for_call(chfsi_ctx* c, int n_vec, bool fp64) {
   const size_t bytes = c->nl_fixed ? 0 : products_scratch_bytes(c, n_vec, fp64);
   if (bytes == 0) return nullptr;
-  const size_t n = (bytes + sizeof(double) - 1) / sizeof(double);
-  if (c->ye.n < n) {
+  if (c->stream) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     CHFSI_HIP(hipStreamIsCapturing(c->stream, &st));
-    if (st != hipStreamCaptureStatusNone || !c->ye.try_alloc(n)) return nullptr;
+    if (st != hipStreamCaptureStatusNone) return nullptr;
   }
+  const size_t n = (bytes + sizeof(double) - 1) / sizeof(double);
+  if (c->ye.n < n && !c->ye.try_alloc(n)) return nullptr;
   return c->ye.ptr;
 }
 
