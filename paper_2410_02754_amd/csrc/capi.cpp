@@ -196,6 +196,8 @@ int chfsi_set_apply_form(chfsi_ctx* c, int form) {
   }
   c->mf_qd.release();
   c->mf_qd32.release();
+  c->ye.release();
+  c->ye.retry();
   c->form = form;
   c->have_local = false;
   ++c->gen;
@@ -211,6 +213,7 @@ int chfsi_set_local(chfsi_ctx* c, const double* V, const double* B) {
   CHFSI_CHECK(!(bad & 1), CHFSI_ENONFINITE, "veff has NaN/Inf");
   CHFSI_CHECK(!(bad & 2), CHFSI_ENONFINITE, "bxc has NaN/Inf");
   ++c->gen;
+  c->ye.retry();
   if (c->form == CHFSI_FORM_MATRIX_FREE) {
     mf_set_local(c, V, B);
     c->have_local = true;
@@ -252,6 +255,7 @@ int chfsi_set_atoms(chfsi_ctx* c, int n_atoms, const chfsi_atom_desc* atoms) {
     }
   }
   ++c->gen;
+  c->ye.retry();
   for (auto* kp : c->kp) build_nonlocal(c, *kp, n_atoms, atoms);
   API_END(c)
 }

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "../../include/chfsi.h"
+#include "spare.h"
 
 namespace chfsi {
 
@@ -216,7 +217,7 @@ struct chfsi_ctx {
   // columns per launch as fit (the allocation-free filter entry point)
   void* nl_fixed = nullptr;
   size_t nl_fixed_bytes = 0;
-  chfsi::DevBuf<double> ye;                   // cell products of one apply, cell by cell (small applies)
+  chfsi::SpareBuf ye;                         // cell products of one apply, cell by cell (small applies)
   chfsi::DevBuf<double> panel;                // row panel for in-place rotations
   chfsi::DevBuf<double> lanczos;              // three vectors and the scalars of lanczos_steps
   chfsi::DevBuf<double> cd_partial;           // adjoint cross densities per column group

@@ -1027,9 +1027,7 @@ static void* ye_for_call(chfsi_ctx* c, int n_vec, bool fp64) {
     CHFSI_HIP(hipStreamIsCapturing(c->stream, &st));
     if (st != hipStreamCaptureStatusNone) return nullptr;
   }
-  const size_t n = (bytes + sizeof(double) - 1) / sizeof(double);
-  if (c->ye.n < n && !c->ye.try_alloc(n)) return nullptr;
-  return c->ye.ptr;
+  return c->ye.get(bytes);
 }
 
 template <class T>
@@ -1043,7 +1041,7 @@ static void apply_t(chfsi_ctx* c, KPoint& kp, const typename C2<T>::type* proj, 
   g.Rs = Rs;
   g.ldr = ldr;
   g.rscale = rscale;
-  CT* ye = reinterpret_cast<CT*>(ye_for_call(c, n_vec, sizeof(T) == 8));
+  CT* ye = static_cast<CT*>(ye_for_call(c, n_vec, sizeof(T) == 8));
   if (ye) {
     g.ye = ye;
     g.alpha = alpha;

@@ -1,0 +1,31 @@
+// Device memory that a call can do without: with it a faster route runs, without it
+// another one with the same results.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstddef>
+#include <cstdint>
+
+namespace chfsi {
+
+class SpareBuf {
+ public:
+  SpareBuf() = default;
+  SpareBuf(const SpareBuf&) = delete;
+  SpareBuf& operator=(const SpareBuf&) = delete;
+  ~SpareBuf() { release(); }
+  // At least `bytes`, or null.  A growing buffer takes its new memory beside the old and
+  // keeps the old where that fails (its address stays good); a size that failed is not
+  // asked for again, nor any larger one, until retry().
+  void* get(size_t bytes);
+  void retry() { refused_ = SIZE_MAX; }
+  void release();
+  size_t bytes() const { return bytes_; }
+
+ private:
+  void* ptr_ = nullptr;
+  size_t bytes_ = 0, refused_ = SIZE_MAX;
+};
+
+}  // namespace chfsi
