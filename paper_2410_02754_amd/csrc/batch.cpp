@@ -56,7 +56,7 @@ struct chfsi_batch {
   DevBuf<unsigned char> nl_scratch;          // nonlocal partial sums, shared by the large tasks (one stream)
   std::vector<char> small;                   // per task
   std::unique_ptr<BatchSmall> smalls;
-  DevBuf<unsigned char> small_mem;           // their ye and nonlocal scratch, task after task
+  SpareBuf small_mem;                        // their ye and nonlocal scratch, task after task
   std::vector<unsigned char*> ye;            // per task, null for large ones
   std::vector<uint64_t> gen;                 // context generations at creation
   hipGraph_t graph = nullptr;
@@ -210,8 +210,9 @@ static void upload_coeffs(chfsi_batch* b, const std::vector<double>& bounds) {
 
 extern "C" {
 
-int chfsi_batch_create(int n_tasks, const chfsi_batch_task* tasks, int degree, int prec_mode, int flags,
-                       chfsi_batch** out) {
+// (joint: the small tasks go together)
+static int batch_create(int n_tasks, const chfsi_batch_task* tasks, int degree, int prec_mode, int flags, bool joint,
+                        chfsi_batch** out) {
   chfsi_batch* b = nullptr;
   try {
     CHFSI_CHECK(n_tasks >= 1 && tasks && out, CHFSI_EINVAL, "need n_tasks >= 1, tasks and out");
@@ -283,13 +284,14 @@ int chfsi_batch_create(int n_tasks, const chfsi_batch_task* tasks, int degree, i
       // (ye holds either precision: the last step is FP64)
       const size_t ye = up(products_scratch_bytes(tk.ctx, tk.n_vec, true));
       const size_t nl = up(nonlocal_scratch_bytes(*b->kps[t], tk.n_vec));
-      if (ye == 0 || tk.n_vec == 1 || small_bytes + ye + nl > kSmallBytes) continue;
+      if (!joint || ye == 0 || tk.n_vec == 1 || small_bytes + ye + nl > kSmallBytes) continue;
       b->small[t] = 1;
       ye_off[t] = small_bytes;
       nl_off[t] = small_bytes + ye;
       small_bytes += ye + nl;
     }
-    if (!b->small_mem.try_alloc(small_bytes)) {      // each task by itself then
+    unsigned char* mem = static_cast<unsigned char*>(b->small_mem.get(small_bytes));
+    if (!mem) {                                      // each task by itself then
       b->small.assign(n_tasks, 0);
       small_bytes = 0;
     }
@@ -298,9 +300,9 @@ int chfsi_batch_create(int n_tasks, const chfsi_batch_task* tasks, int degree, i
       for (int t = 0; t < n_tasks; ++t) {
         if (!b->small[t]) continue;
         const auto& tk = tasks[t];
-        b->ye[t] = b->small_mem.ptr + ye_off[t];
+        b->ye[t] = mem + ye_off[t];
         st.push_back(SmallTask{tk.ctx, b->kps[t], {(double2*)tk.X_d, (double2*)tk.work_d}, {tk.ldx, tk.ldw},
-                               tk.n_vec, t, b->ye[t], b->small_mem.ptr + nl_off[t]});
+                               tk.n_vec, t, b->ye[t], mem + nl_off[t]});
       }
       b->smalls.reset(new BatchSmall(st, b->stream));
     }
@@ -369,6 +371,17 @@ int chfsi_batch_create(int n_tasks, const chfsi_batch_task* tasks, int degree, i
     delete b;
     return CHFSI_ENOMEM;
   }
+}
+
+int chfsi_batch_create(int n_tasks, const chfsi_batch_task* tasks, int degree, int prec_mode, int flags,
+                       chfsi_batch** out) {
+  const int rc = batch_create(n_tasks, tasks, degree, prec_mode, flags, true, out);
+  if (rc != CHFSI_ENOMEM) return rc;
+  // once more without the memory that it can do without
+  (void)hipGetLastError();
+  for (int t = 0; t < n_tasks; ++t)
+    if (tasks[t].ctx) tasks[t].ctx->ye.release();
+  return batch_create(n_tasks, tasks, degree, prec_mode, flags, false, out);
 }
 
 int chfsi_batch_filter(chfsi_batch* b, const double* a, const double* bb, const double* a0) {

@@ -113,6 +113,8 @@ int chfsi_create(const chfsi_mesh_desc* d, void* stream, chfsi_ctx** out) {
     const int64_t nodes = (int64_t)d->n_cells[0] * d->p * d->n_cells[1] * d->p * d->n_cells[2] * d->p;
     CHFSI_CHECK(nodes < ((int64_t)1 << 30), CHFSI_EINVAL, "mesh too large for 32-bit node ids");
     c = new chfsi_ctx();
+    for (auto* b : {&c->scratch, &c->panel, &c->lanczos, &c->cd_partial, &c->occ, &c->mf_qd}) b->spare = &c->ye;
+    c->mf_qd32.spare = &c->ye;
     for (int k = 0; k < 3; ++k) {
       c->nc[k] = d->n_cells[k];
       c->box[k] = d->box[k];
@@ -132,6 +134,8 @@ int chfsi_create(const chfsi_mesh_desc* d, void* stream, chfsi_ctx** out) {
       for (int k = 0; k < 3; ++k) kp->k[k] = d->kpts[3 * ik + k];
       kp->gamma = kp->k[0] == 0.0 && kp->k[1] == 0.0 && kp->k[2] == 0.0;
       kp->nmat = kp->gamma ? 4 : 5;
+      kp->cell64.spare = kp->U0.spare = kp->S.spare = kp->cell32.spare = &c->ye;
+      kp->nl.proj.spare = kp->nl.proj32.spare = kp->nl.pair_ent.spare = &c->ye;
       c->kp.push_back(kp);
     }
     CHFSI_HIP(hipStreamSynchronize(c->stream));

@@ -559,6 +559,8 @@ static FieldOps& fops(chfsi_ctx* c) {
   if (!c->fields) c->fields = std::make_shared<FieldOps>();
   FieldOps& f = *c->fields;
   if (!f.ready) {
+    for (auto* b : {&f.wJ, &f.wJ3, &f.ones, &f.md, &f.gq, &f.red, &f.be, &f.rows}) b->spare = &c->ye;
+    for (auto& b : f.v) b.spare = &c->ye;
     const int n = c->np1, nq = c->nq, nloc = c->nloc, nq3 = c->nq3;
     std::vector<double> wJ(nq3);
     // rows a = 0 .. p-1 of the assembled 1-D matrices over the nodes -p .. p: node 0 is

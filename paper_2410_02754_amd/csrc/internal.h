@@ -46,6 +46,7 @@ template <class T>
 struct DevBuf {
   T* ptr = nullptr;
   size_t n = 0;
+  SpareBuf* spare = nullptr;    // given back if an allocation fails (not in use by the caller then)
   DevBuf() = default;
   DevBuf(const DevBuf&) = delete;
   DevBuf& operator=(const DevBuf&) = delete;
@@ -60,21 +61,16 @@ struct DevBuf {
     release();
     if (count == 0) return;
     hipError_t e = hipMalloc(&ptr, count * sizeof(T));
+    if (e != hipSuccess && spare && spare->bytes() > 0) {
+      (void)hipGetLastError();
+      spare->release();
+      e = hipMalloc(&ptr, count * sizeof(T));
+    }
     if (e != hipSuccess) {
       ptr = nullptr;
       throw Error{CHFSI_ENOMEM, "hipMalloc of " + std::to_string(count * sizeof(T)) + " bytes failed"};
     }
     n = count;
-  }
-  // as alloc; false where the memory is not there (for buffers that a call can do without)
-  bool try_alloc(size_t count) {
-    try {
-      alloc(count);
-      return true;
-    } catch (const Error&) {
-      (void)hipGetLastError();
-      return false;
-    }
   }
   void upload(const T* h, size_t count, hipStream_t s) {
     alloc(count);

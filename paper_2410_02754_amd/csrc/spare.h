@@ -1,5 +1,8 @@
 // Device memory that a call can do without: with it a faster route runs, without it
-// another one with the same results.
+// another one with the same results.  So it is never taken where it could be missed:
+// all such buffers of a device hold at most kSpareMax together, one is only taken where a
+// sixteenth of the device's memory stays free beside it, and an allocation that fails
+// takes its context's back (DevBuf::spare).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -8,6 +11,8 @@
 #include <cstdint>
 
 namespace chfsi {
+
+constexpr size_t kSpareMax = (size_t)8 << 30;
 
 class SpareBuf {
  public:
@@ -26,6 +31,7 @@ class SpareBuf {
  private:
   void* ptr_ = nullptr;
   size_t bytes_ = 0, refused_ = SIZE_MAX;
+  int device_ = -1;
 };
 
 }  // namespace chfsi

@@ -13,12 +13,15 @@ DEVICE = r"""
 #include <cstdio>
 #include <cstdlib>
 #include <map>
+#include <mutex>
 #include "spare.h"
 static size_t g_total = 0, g_used = 0;
 static int g_mallocs = 0, g_frees = 0, g_dev = 0;
+static std::mutex g_lock;
 static std::map<void*, size_t> g_live;
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
+  std::lock_guard<std::mutex> lk(g_lock);
   ++g_mallocs;
   if (g_used + n > g_total) return hipErrorOutOfMemory;
   *p = malloc(1);
@@ -27,6 +30,7 @@ hipError_t hipMalloc(void** p, size_t n) {
   return hipSuccess;
 }
 hipError_t hipFree(void* p) {
+  std::lock_guard<std::mutex> lk(g_lock);
   assert(g_live.count(p));
   ++g_frees;
   g_used -= g_live[p];
@@ -69,6 +73,67 @@ int main() {
 }
 """
 
+BOUNDS = r"""
+#include <memory>
+#include <thread>
+#include <vector>
+#include "internal.h"
+int main() {
+  g_total = 288 * GB;
+  {
+    std::vector<std::unique_ptr<SpareBuf>> v;         // many owners: bounded together
+    int got = 0;
+    for (int i = 0; i < 50; ++i) {
+      v.emplace_back(new SpareBuf);
+      got += v.back()->get(GB) != nullptr;
+    }
+    assert(got == 8 && g_used == kSpareMax);
+    assert(v[0]->get(GB / 2) && !v[1]->get(GB + 1));
+    g_dev = 1;                                        // another device has its own share
+    SpareBuf o;
+    assert(o.get(2 * GB));
+    g_dev = 0;
+    v.clear();
+    assert(g_used == 2 * GB);
+  }
+  {
+    SpareBuf a, b;                                    // a sixteenth of the device stays free
+    void* hog;
+    assert(hipMalloc(&hog, 269 * GB) == hipSuccess);
+    assert(!a.get(2 * GB) && a.get(GB) && !b.get(GB));
+    // an allocation that fails takes its context's back
+    DevBuf<double> d;
+    bool threw = false;
+    try {
+      d.alloc(19 * GB / 8);
+    } catch (const Error& e) {
+      threw = e.code == CHFSI_ENOMEM;
+    }
+    assert(threw && d.ptr == nullptr && a.bytes() == GB);
+    d.spare = &a;
+    d.alloc(19 * GB / 8);
+    assert(d.ptr && a.bytes() == 0 && g_used == 288 * GB);
+    hipFree(hog);
+  }
+  assert(g_used == 0);
+  {
+    std::vector<std::thread> t;                       // several threads
+    for (int i = 0; i < 8; ++i)
+      t.emplace_back([]() {
+        for (int r = 0; r < 200; ++r) {
+          SpareBuf s;
+          s.get(64 * MB);
+          s.get(128 * MB);
+        }
+      });
+    for (auto& x : t) x.join();
+    SpareBuf s;
+    assert(s.get(kSpareMax));                         // all given back
+  }
+  puts("ok");
+}
+"""
+
 
 def _run(tmp_path, body):
     cxx = shutil.which("g++")
@@ -83,3 +148,7 @@ def _run(tmp_path, body):
 
 def test_growth_and_failure(tmp_path):
     _run(tmp_path, GROWTH)
+
+
+def test_bounds_and_giving_back(tmp_path):
+    _run(tmp_path, BOUNDS)
