@@ -237,8 +237,14 @@ int chfsi_overlap(chfsi_ctx* ctx, const void* X_d, int64_t ldx, const void* Y_d,
 
 /* Device memory the library itself holds for one call of the given kind on a
  * block of n_vec columns at k-point ik (its growable scratch, the rotation panel,
- * partial sums), excluding the caller's buffers (X, work, the backward
- * workspace): the peak of the call, in bytes; 0 for invalid arguments. */
+ * partial sums, the cells' products of an apply), excluding the caller's buffers
+ * (X, work, the backward workspace): the peak of the call on a fresh context in either
+ * precision, in bytes; 0 for invalid arguments.  The buffer of the cells' products is one
+ * that applies can do without: the library takes it only where a sixteenth of the
+ * device's memory stays free beside it and all contexts and batches of the device hold at
+ * most 8 GiB of such buffers, and gives it back where another allocation of the context
+ * fails and in chfsi_set_apply_form; a larger one is taken before the one it replaces
+ * goes. */
 enum chfsi_op { CHFSI_OP_APPLY = 0, CHFSI_OP_FILTER = 1, CHFSI_OP_CHOL_GS = 2, CHFSI_OP_RAYLEIGH_RITZ = 3,
                 CHFSI_OP_DENSITY = 4 };
 size_t chfsi_workspace_bytes(const chfsi_ctx* ctx, int ik, int n_vec, int op);

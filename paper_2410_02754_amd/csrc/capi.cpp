@@ -465,15 +465,18 @@ size_t chfsi_workspace_bytes(const chfsi_ctx* c, int ik, int n_vec, int op) {
   // the n x n rotation
   const size_t rot_b = ((size_t)rotate_panel_rows(rows, n_vec) * n + n * n) * sizeof(double2);
   const size_t resid_b = (256 * n + n) * sizeof(double);
-  const size_t nl_b = nonlocal_scratch_bytes(*c->kp[ik], n_vec) + products_scratch_bytes(c, n_vec, true);
+  // the applies' coefficients share the scratch of the others, the cells' products (of
+  // either precision: one may use them where the other does not) are a buffer of their own
+  const size_t nl_b = nonlocal_scratch_bytes(*c->kp[ik], n_vec);
+  const size_t ye_b = std::max(products_scratch_bytes(c, n_vec, true), products_scratch_bytes(c, n_vec, false));
   switch (op) {
     case CHFSI_OP_APPLY:
     case CHFSI_OP_FILTER:
-      return nl_b;
+      return nl_b + ye_b;
     case CHFSI_OP_CHOL_GS:
       return gram_b + chol_extra(n_vec) * sizeof(double) + n * n * sizeof(double2);
     case CHFSI_OP_RAYLEIGH_RITZ:
-      return std::max(std::max(nl_b, gram_b), resid_b) + rot_b;
+      return std::max(std::max(nl_b, gram_b), resid_b) + ye_b + rot_b;
     case CHFSI_OP_DENSITY: {
       const int want = std::max(1, cdiv(4096, std::max(1, c->n_cells)));
       int64_t groups;
