@@ -170,6 +170,7 @@ struct StageRec {
   int stage;
   hipEvent_t start, stop;
   double flops, exec_flops, bytes;
+  double share;                 // of the time between the events
 };
 
 }  // namespace chfsi
@@ -239,10 +240,13 @@ struct chfsi_ctx {
 };
 
 namespace chfsi {
-// Records HIP events around a stage's launches when timing is enabled.
+// Records HIP events around a stage's launches when timing is enabled.  share: the part
+// of their time that is this context's, where launches serve several contexts.
 class StageTimer {
  public:
-  StageTimer(chfsi_ctx* c, int stage, double flops, double exec_flops, double bytes);
+  StageTimer(chfsi_ctx* c, int stage, double flops, double exec_flops, double bytes, double share = 1.0);
+  StageTimer(const StageTimer&) = delete;
+  StageTimer& operator=(const StageTimer&) = delete;
   ~StageTimer();
  private:
   chfsi_ctx* c_;

@@ -856,6 +856,22 @@ static NlContractArgs<T> contract_args(const NonlocalK& nl, const typename C2<T>
   return g;
 }
 
+// Work of the stages, as the timers count it
+struct StageWork {
+  double flops, bytes;
+};
+static StageWork nonlocal_work(const NonlocalK& nl, int n_vec, size_t elem) {
+  StageWork w{0.0, (double)nl.n_entries * (2.0 * n_vec * sizeof(double2) + nl.max_pj * elem)};
+  for (const auto& at : nl.atoms)
+    w.flops += 2.0 * 8.0 * at.n_sup * at.n_pj * 2.0 * n_vec + 8.0 * 4.0 * at.n_pj * at.n_pj * n_vec;
+  return w;
+}
+// terms: recurrence terms read, beside the rows written
+static StageWork init_work(const NonlocalK* nl, int64_t n_nodes, int n_vec, int terms) {
+  return StageWork{nl ? 8.0 * 2.0 * nl->n_entries * nl->max_pj * n_vec : 0.0,
+                   2.0 * (double)n_nodes * n_vec * sizeof(double2) * (1.0 + terms)};
+}
+
 // Nonlocal coefficients C' = alpha Delta P^H X for every atom; returns the
 // device array [n_atoms][2 max_pj][n_vec] (in the scratch buffer), or null.
 // Scratch: the caller's buffer (scratch, at least nonlocal_scratch_bytes(nl,
@@ -887,11 +903,8 @@ static const typename C2<T>::type* nonlocal_coeffs(chfsi_ctx* c, NonlocalK& nl,
   }
   CT* Cp = reinterpret_cast<CT*>(scratch);
   CT* partial = Cp + n_cp;
-  double nl_flops = 0.0;
-  for (const auto& at : nl.atoms)
-    nl_flops += 2.0 * 8.0 * at.n_sup * at.n_pj * 2.0 * n_vec + 8.0 * 4.0 * at.n_pj * at.n_pj * n_vec;
-  const double nl_bytes = (double)nl.n_entries * (2.0 * n_vec * sizeof(double2) + nl.max_pj * sizeof(CT));
-  StageTimer tm(c, CHFSI_STAGE_NONLOCAL, nl_flops, nl_flops, nl_bytes);
+  const StageWork nw = nonlocal_work(nl, n_vec, sizeof(CT));
+  StageTimer tm(c, CHFSI_STAGE_NONLOCAL, nw.flops, nw.flops, nw.bytes);
   for (int c0 = 0; c0 < n_vec; c0 += group) {
     const int gc = std::min(group, n_vec - c0);
     const NlContractArgs<T> ca = contract_args<T>(nl, proj, X + c0, ldx, gc, nsub, partial);
@@ -956,9 +969,8 @@ static InitArgs<T> init_args(chfsi_ctx* c, NonlocalK& nl, const typename C2<T>::
 template <class T>
 static void launch_init(chfsi_ctx* c, const InitArgs<T>& g, const NonlocalK& nl) {
   const bool realp = g.has_nl && nl.real_proj;
-  StageTimer tm(c, CHFSI_STAGE_AXPY, g.has_nl ? 8.0 * 2.0 * nl.n_entries * nl.max_pj * g.n_vec : 0.0, 0.0,
-                2.0 * (double)g.n_nodes * g.n_vec * sizeof(double2) *
-                    (1.0 + (g.beta != 0.0) + (g.gamma != 0.0)));
+  const StageWork iw = init_work(g.has_nl ? &nl : nullptr, g.n_nodes, g.n_vec, (g.beta != 0.0) + (g.gamma != 0.0));
+  StageTimer tm(c, CHFSI_STAGE_AXPY, iw.flops, 0.0, iw.bytes);
   const int fl = (g.beta != 0.0 ? kInitBeta : 0) | (g.gamma != 0.0 ? kInitGamma : 0) | (g.Rs ? kInitRs : 0);
   const dim3 grid(cdiv(g.n_work, 4)), blk(256);
   if (g.n_vec == 1) {
@@ -1265,10 +1277,31 @@ struct BatchStage {
     init.upload(s);
   }
 };
+// one context's part of the joint launches, for its stage timers
+struct BatchShare {
+  chfsi_ctx* ctx;
+  StageWork nl[2], init[2];               // [precision: FP32, FP64], [step: the first, later ones]
+};
 struct BatchSmall::Impl {
   BatchStage<double> s64;
   BatchStage<float> s32;
   BatchMap copy;
+  std::vector<BatchShare> shares;
+  // The timers of the contexts that record: the launches' time goes to all contexts by
+  // their flops (nonlocal) or bytes (init).
+  typedef std::vector<std::unique_ptr<StageTimer>> Timers;
+  Timers time(int stage, bool nonlocal, int which) const {
+    Timers t;
+    double total = 0.0;
+    for (const auto& s : shares) total += nonlocal ? s.nl[which].flops : s.init[which].bytes;
+    for (const auto& s : shares) {
+      const StageWork& w = nonlocal ? s.nl[which] : s.init[which];
+      const double part = nonlocal ? w.flops : w.bytes;
+      if (s.ctx->stats_on && part > 0.0)
+        t.emplace_back(new StageTimer(s.ctx, stage, w.flops, nonlocal ? w.flops : 0.0, w.bytes, part / total));
+    }
+    return t;
+  }
 };
 
 template <class T>
@@ -1311,6 +1344,18 @@ BatchSmall::BatchSmall(const std::vector<SmallTask>& tasks, hipStream_t stream) 
     m.s64.add(batch_nl<double>(s, s.kp->nl.proj.ptr));
     m.s32.add(batch_nl<float>(s, s.kp->nl.proj32.ptr));
     m.copy.add((int)t, (2 * s.ctx->n_nodes * s.n_vec + kBatchCopy - 1) / kBatchCopy);
+    auto sh = std::find_if(m.shares.begin(), m.shares.end(), [&](const BatchShare& x) { return x.ctx == s.ctx; });
+    if (sh == m.shares.end()) sh = m.shares.insert(sh, BatchShare{s.ctx, {}, {}});
+    const NonlocalK& nl = s.kp->nl;
+    const bool has = nl.n_atoms != 0 && nl.n_entries != 0;
+    const auto add = [](StageWork& a, const StageWork& b) {
+      a.flops += b.flops;
+      a.bytes += b.bytes;
+    };
+    for (int k = 0; k < 2; ++k) {
+      if (has) add(sh->nl[k], nonlocal_work(nl, s.n_vec, k ? sizeof(double2) : sizeof(float2)));
+      add(sh->init[k], init_work(has ? &nl : nullptr, s.ctx->n_nodes, s.n_vec, 1 + k));
+    }
   }
   m.s64.upload(stream);
   m.s32.upload(stream);
@@ -1330,6 +1375,7 @@ static void batch_nonlocal(hipStream_t s, const BatchStage<T>& b, int src, const
 }
 
 void BatchSmall::nonlocal(hipStream_t s, bool fp64, int src, const double* alpha) {
+  const auto tm = impl_->time(CHFSI_STAGE_NONLOCAL, true, fp64);
   if (fp64) batch_nonlocal(s, impl_->s64, src, alpha);
   else batch_nonlocal(s, impl_->s32, src, alpha);
 }
@@ -1347,6 +1393,7 @@ static void batch_init(hipStream_t s, const BatchStage<T>& b, int src, bool firs
 }
 
 void BatchSmall::init(hipStream_t s, bool fp64, int src, bool first, const double* alpha, const double* bg) {
+  const auto tm = impl_->time(CHFSI_STAGE_AXPY, false, first ? 0 : 1);
   if (fp64) batch_init(s, impl_->s64, src, first, alpha, bg);
   else batch_init(s, impl_->s32, src, first, alpha, bg);
 }

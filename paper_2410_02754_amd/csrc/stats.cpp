@@ -14,13 +14,14 @@ static hipEvent_t take_event(chfsi_ctx* c) {
   return e;
 }
 
-StageTimer::StageTimer(chfsi_ctx* c, int stage, double flops, double exec_flops, double bytes)
+StageTimer::StageTimer(chfsi_ctx* c, int stage, double flops, double exec_flops, double bytes, double share)
     : c_(c), on_(c->stats_on) {
   if (!on_) return;
   rec_.stage = stage;
   rec_.flops = flops;
   rec_.exec_flops = exec_flops;
   rec_.bytes = bytes;
+  rec_.share = share;
   rec_.start = take_event(c);
   rec_.stop = take_event(c);
   CHFSI_HIP(hipEventRecord(rec_.start, c->stream));
@@ -39,7 +40,7 @@ void stats_resolve(chfsi_ctx* c) {
     CHFSI_HIP(hipEventElapsedTime(&ms, r.start, r.stop));
     auto& s = c->stats[r.stage];
     s.launches += 1;
-    s.ms += ms;
+    s.ms += ms * r.share;
     s.flops += r.flops;
     s.exec_flops += r.exec_flops;
     s.bytes += r.bytes;
