@@ -755,7 +755,7 @@ def bench_matfree(args, s, X, W, Wf, b, theta_ref, torch, tables=None, theta_cmp
            "setup_s": round(t_setup, 2),
            "kernel": "mf_apply_kernel<7, false> (gather, 9 line contractions per spin, scatter-add)",
            "mean_launch_ms": round(ms, 4),
-           # 12 dense 1-D contractions per spin (96 n_p^4 per cell and column); the even-odd
+           # 9 dense 1-D contractions per spin (72 n_p^4 per cell and column); the even-odd
            # form issues about half of these multiply-adds
            "sumfact_flops_per_launch": exec_per,
            "sumfact_fp64_tflops": round(exec_per / (ms * 1e-3) / 1e12, 3) if ms > 0 else None,

@@ -428,9 +428,10 @@ static void launch_cells(chfsi_ctx* c, const T* cm, int nmat, const double2* X, 
     const int nblk = n_in * n_rowtiles * n_coltiles;
     const double n2 = 2.0 * c->nloc;
     const double flops = 8.0 * n2 * n2 * n_vec * n_in;
-    // issued MFMA flops: per cell nrb row blocks x 2 TW 16-column blocks per column
-    // tile, each nkb k-steps of (8 | 12) MFMAs of 16x16x4 (2048 flops)
-    const double exec = (double)n_in * c->nrb * 2.0 * TW * n_coltiles * c->nkb * (HAS_S ? 12 : 8) * 2048.0;
+    // issued MFMA flops: per cell nrb row blocks x the 16-column blocks of the waves that
+    // have a column, each nkb k-steps of (8 | 12) MFMAs of 16x16x4 (2048 flops)
+    const int col_blocks = cdiv(n_vec, 16 * cell_cb<T, TW>()) * cell_cb<T, TW>();
+    const double exec = (double)n_in * c->nrb * col_blocks * c->nkb * (HAS_S ? 12 : 8) * 2048.0;
     const double bytes = (double)n_in * ((double)nmat * c->nloc * c->nloc * sizeof(T) +
                                          3.0 * c->nloc * 2.0 * n_vec * sizeof(double2));
     StageTimer tm(c, sizeof(T) == 8 ? CHFSI_STAGE_CELL_FP64 : CHFSI_STAGE_CELL_FP32, flops, exec, bytes);

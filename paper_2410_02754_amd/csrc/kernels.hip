@@ -866,10 +866,12 @@ static StageWork nonlocal_work(const NonlocalK& nl, int n_vec, size_t elem) {
     w.flops += 2.0 * 8.0 * at.n_sup * at.n_pj * 2.0 * n_vec + 8.0 * 4.0 * at.n_pj * at.n_pj * n_vec;
   return w;
 }
-// terms: recurrence terms read, beside the rows written
-static StageWork init_work(const NonlocalK* nl, int64_t n_nodes, int n_vec, int terms) {
+// terms: recurrence terms read, beside the rows written; ye_elem: bytes of a gathered
+// cell product (0: none are)
+static StageWork init_work(const chfsi_ctx* c, const NonlocalK* nl, int n_vec, int terms, size_t ye_elem) {
   return StageWork{nl ? 8.0 * 2.0 * nl->n_entries * nl->max_pj * n_vec : 0.0,
-                   2.0 * (double)n_nodes * n_vec * sizeof(double2) * (1.0 + terms)};
+                   2.0 * (double)c->n_nodes * n_vec * sizeof(double2) * (1.0 + terms) +
+                       2.0 * (double)c->n_cells * c->nloc * n_vec * ye_elem};
 }
 
 // Nonlocal coefficients C' = alpha Delta P^H X for every atom; returns the
@@ -969,7 +971,8 @@ static InitArgs<T> init_args(chfsi_ctx* c, NonlocalK& nl, const typename C2<T>::
 template <class T>
 static void launch_init(chfsi_ctx* c, const InitArgs<T>& g, const NonlocalK& nl) {
   const bool realp = g.has_nl && nl.real_proj;
-  const StageWork iw = init_work(g.has_nl ? &nl : nullptr, g.n_nodes, g.n_vec, (g.beta != 0.0) + (g.gamma != 0.0));
+  const StageWork iw = init_work(c, g.has_nl ? &nl : nullptr, g.n_vec, (g.beta != 0.0) + (g.gamma != 0.0),
+                                 g.ye ? 2 * sizeof(T) : 0);
   StageTimer tm(c, CHFSI_STAGE_AXPY, iw.flops, 0.0, iw.bytes);
   const int fl = (g.beta != 0.0 ? kInitBeta : 0) | (g.gamma != 0.0 ? kInitGamma : 0) | (g.Rs ? kInitRs : 0);
   const dim3 grid(cdiv(g.n_work, 4)), blk(256);
@@ -1280,7 +1283,7 @@ struct BatchStage {
 // one context's part of the joint launches, for its stage timers
 struct BatchShare {
   chfsi_ctx* ctx;
-  StageWork nl[2], init[2];               // [precision: FP32, FP64], [step: the first, later ones]
+  StageWork nl[2], init[2][2];            // [precision: FP32, FP64], [step: the first, later ones][precision]
 };
 struct BatchSmall::Impl {
   BatchStage<double> s64;
@@ -1290,12 +1293,13 @@ struct BatchSmall::Impl {
   // The timers of the contexts that record: the launches' time goes to all contexts by
   // their flops (nonlocal) or bytes (init).
   typedef std::vector<std::unique_ptr<StageTimer>> Timers;
-  Timers time(int stage, bool nonlocal, int which) const {
+  Timers time(bool nonlocal, bool first, bool fp64) const {
     Timers t;
+    const int stage = nonlocal ? CHFSI_STAGE_NONLOCAL : CHFSI_STAGE_AXPY;
     double total = 0.0;
-    for (const auto& s : shares) total += nonlocal ? s.nl[which].flops : s.init[which].bytes;
+    for (const auto& s : shares) total += nonlocal ? s.nl[fp64].flops : s.init[!first][fp64].bytes;
     for (const auto& s : shares) {
-      const StageWork& w = nonlocal ? s.nl[which] : s.init[which];
+      const StageWork& w = nonlocal ? s.nl[fp64] : s.init[!first][fp64];
       const double part = nonlocal ? w.flops : w.bytes;
       if (s.ctx->stats_on && part > 0.0)
         t.emplace_back(new StageTimer(s.ctx, stage, w.flops, nonlocal ? w.flops : 0.0, w.bytes, part / total));
@@ -1354,7 +1358,9 @@ BatchSmall::BatchSmall(const std::vector<SmallTask>& tasks, hipStream_t stream) 
     };
     for (int k = 0; k < 2; ++k) {
       if (has) add(sh->nl[k], nonlocal_work(nl, s.n_vec, k ? sizeof(double2) : sizeof(float2)));
-      add(sh->init[k], init_work(has ? &nl : nullptr, s.ctx->n_nodes, s.n_vec, 1 + k));
+      for (int later = 0; later < 2; ++later)
+        add(sh->init[later][k],
+            init_work(s.ctx, has ? &nl : nullptr, s.n_vec, 1 + later, k ? sizeof(double2) : sizeof(float2)));
     }
   }
   m.s64.upload(stream);
@@ -1375,7 +1381,7 @@ static void batch_nonlocal(hipStream_t s, const BatchStage<T>& b, int src, const
 }
 
 void BatchSmall::nonlocal(hipStream_t s, bool fp64, int src, const double* alpha) {
-  const auto tm = impl_->time(CHFSI_STAGE_NONLOCAL, true, fp64);
+  const auto tm = impl_->time(true, false, fp64);
   if (fp64) batch_nonlocal(s, impl_->s64, src, alpha);
   else batch_nonlocal(s, impl_->s32, src, alpha);
 }
@@ -1393,7 +1399,7 @@ static void batch_init(hipStream_t s, const BatchStage<T>& b, int src, bool firs
 }
 
 void BatchSmall::init(hipStream_t s, bool fp64, int src, bool first, const double* alpha, const double* bg) {
-  const auto tm = impl_->time(CHFSI_STAGE_AXPY, false, first ? 0 : 1);
+  const auto tm = impl_->time(false, first, fp64);
   if (fp64) batch_init(s, impl_->s64, src, first, alpha, bg);
   else batch_init(s, impl_->s32, src, first, alpha, bg);
 }

@@ -467,12 +467,12 @@ void launch_mf_t(chfsi_ctx* c, const KPoint& kp, const double2* X, int64_t ldx, 
     if (n_in == 0) continue;
     const int64_t total = (int64_t)n_in * n_chunks;
     CHFSI_CHECK(total < (int64_t)1 << 30, CHFSI_EINVAL, "matrix-free apply: too many work items");
-    // algorithmic flops of the dense cell product (the filter's count), flops of
-    // 12 dense line contractions per spin (as by the formula; the even-odd form issues about half of
-    // those multiply-adds), and the rows moved
+    // algorithmic flops of the dense cell product (the filter's count), flops of the
+    // kernel's line contractions taken as dense, 9 or 12 per spin (the even-odd form
+    // issues about half of those multiply-adds), and the rows moved
     const double n2 = 2.0 * c->nloc;
     const double flops = 8.0 * n2 * n2 * n_vec * n_in;
-    const double exec = 96.0 * np3 * NP * (double)n_vec * n_in;
+    const double exec = (sizeof(T) == 8 && !KT ? 72.0 : 96.0) * np3 * NP * (double)n_vec * n_in;
     const double bytes = (double)n_in * 3.0 * c->nloc * 2.0 * n_vec * sizeof(double2);
     StageTimer tm(c, sizeof(T) == 8 ? CHFSI_STAGE_CELL_FP64 : CHFSI_STAGE_CELL_FP32, flops, exec, bytes);
     const int grid = (int)(8 * ((total + 7) / 8));
