@@ -461,9 +461,9 @@ size_t chfsi_workspace_bytes(const chfsi_ctx* c, int ik, int n_vec, int op) {
   const int64_t rows = 2 * c->n_nodes;
   // gram(): partial sums of every row range + the reduced matrix
   const size_t gram_b = (gram_shape(rows, n_vec, true).groups + 1) * n * n * sizeof(double2);
-  // rotate_inplace(): a row panel of at most 128 MiB (none where it is triangular) and
-  // the n x n rotation
-  const size_t rot_b = ((size_t)rotate_panel_rows(rows, n_vec) * n + n * n) * sizeof(double2);
+  // rotate_inplace(): a row panel of at most 128 MiB (a triangular one mostly needs none)
+  // and the n x n rotation
+  const size_t rot_b = rotation_doubles(rows, n_vec, false) * sizeof(double);
   const size_t resid_b = (256 * n + n) * sizeof(double);
   // the applies' coefficients share the scratch of the others, the cells' products (of
   // either precision: one may use them where the other does not) are a buffer of their own
@@ -474,7 +474,7 @@ size_t chfsi_workspace_bytes(const chfsi_ctx* c, int ik, int n_vec, int op) {
     case CHFSI_OP_FILTER:
       return nl_b + ye_b;
     case CHFSI_OP_CHOL_GS:
-      return gram_b + chol_extra(n_vec) * sizeof(double) + n * n * sizeof(double2);
+      return gram_b + (chol_extra(n_vec) + rotation_doubles(rows, n_vec, true)) * sizeof(double);
     case CHFSI_OP_RAYLEIGH_RITZ:
       return std::max(std::max(nl_b, gram_b), resid_b) + ye_b + rot_b;
     case CHFSI_OP_DENSITY: {

@@ -320,7 +320,7 @@ double2* gram_device(chfsi_ctx* c, const double2* X, int64_t ldx, const double2*
                      bool lower_only, size_t extra);
 size_t chol_extra(int n);
 void chol_rotation(chfsi_ctx* c, double2* Sd, int n, double2* R, int (&info)[3]);
-int64_t rotate_panel_rows(int64_t rows, int n);
+size_t rotation_doubles(int64_t rows, int n, bool upper);
 double2* rotation_matrix(chfsi_ctx* c, int64_t rows, int n, bool upper);   // room for Q, for rotate_device
 void rotate_device(chfsi_ctx* c, double2* X, int64_t ldx, int64_t rows, int n, const double2* Qd, bool upper);
 void gram(chfsi_ctx* c, const double2* X, int64_t ldx, const double2* Y, int64_t ldy, int64_t rows,

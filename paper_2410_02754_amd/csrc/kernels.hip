@@ -2267,26 +2267,35 @@ __device__ __forceinline__ void rotate_tile(GemmSmem& sm, const double2* P, int6
 }
 
 // X[r][:] = P[r][:] Q over a row panel P (a copy of those rows of X).  Work item =
-// (row tile, column tile), consecutive on one XCD, so the column tiles of one row
-// tile read its panel rows through one L2.
+// (row tile, column tile), the column tiles of one row tile on one XCD, so that they read
+// its panel rows through one L2.  UPPER (Q upper triangular): a column tile's k range ends
+// with it; an XCD takes its row tiles' last column tiles first, the long ranges before the
+// short ones.
+template <bool UPPER>
 __global__ __launch_bounds__(256, 4) void rotate_kernel(const double2* __restrict__ P, int n, int64_t prow,
                                                         const double2* __restrict__ Q, double2* __restrict__ X,
                                                         int64_t ldx, int n_rt, int n_ct) {
   __shared__ GemmSmem sm;
-  const int n_work = n_rt * n_ct;
-  const int per_xcd = (int)((gridDim.x + 7) / 8);
-  const int bid = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
-  if (bid >= n_work) return;              // uniform over the block, before any barrier
-  const int rt = bid / n_ct, ct = bid - rt * n_ct;
-  rotate_tile(sm, P, n, (int64_t)rt * kGM, prow, Q, n, ct * kGN, n, 0, X, ldx);
+  const int xcd = (int)(blockIdx.x % 8), i = (int)(blockIdx.x / 8);
+  int rt, ct;
+  if (UPPER) {
+    const int per_rt = (n_rt + 7) / 8;
+    rt = xcd * per_rt + i % per_rt;
+    ct = n_ct - 1 - i / per_rt;
+  } else {
+    const int bid = xcd * (int)((gridDim.x + 7) / 8) + i;
+    rt = bid / n_ct;
+    ct = bid - rt * n_ct;
+  }
+  if (rt >= n_rt || ct < 0) return;       // uniform over the block, before any barrier
+  const int kend = UPPER && (ct + 1) * kGN < n ? (ct + 1) * kGN : n;
+  rotate_tile(sm, P, n, (int64_t)rt * kGM, prow, Q, n, ct * kGN, kend, UPPER, X, ldx);
 }
 
 // X <- X Q in place, Q upper triangular: a workgroup owns 64 rows and takes its
 // column tiles from the last to the first.  A tile reads columns up to its own last
-// one and writes its own, which no later tile reads, so no copy of X is made.
-// Against panels with (row tile, column pair) items, 384 columns: 0.78 against 0.92
-// ms on 65536 rows, 0.39 against 0.44 on 27648, 0.23 against 0.21 on 11664.  Three
-// workgroups per CU: at four it spills (5.4 against 5.0 ms on 432000).
+// one and writes its own, which no later tile reads, so no copy of X is made.  Three
+// workgroups per CU: at four it spills (5.4 against 5.0 ms on 432000 x 384).
 __global__ __launch_bounds__(256, 3) void rotate_upper_kernel(double2* X, int64_t ldx, int64_t rows, int n,
                                                               const double2* __restrict__ Q) {
   __shared__ GemmSmem sm;
@@ -2296,8 +2305,18 @@ __global__ __launch_bounds__(256, 3) void rotate_upper_kernel(double2* X, int64_
   }
 }
 
+// In place a triangular rotation has a workgroup per 64 rows, each walking all column
+// tiles; fewer than there are CUs leave the GPU idle, and the copy of the rows costs less
+// than that: 54 row tiles, 1000 columns 1.34 ms in place and 0.35 by panels; 128, 384: 0.22
+// and 0.12, 128 columns 0.038 and 0.035; 182, 512: 0.37 and 0.29; 215, 800: 0.95 and 0.81,
+// 128 columns 0.040 and 0.045; 250, 384: 0.22 and 0.26, 512: 0.38 and 0.35; 432, 384: 0.37
+// and 0.43.
+static bool rotate_by_panels(int64_t rows, int n, bool upper) {
+  return !upper || (n > kGN && cdiv(rows, kGM) <= (n <= 2 * kGN ? 128 : 216));
+}
+
 // Rows of a panel: whole rounds of workgroups within 128 MiB of copied rows
-int64_t rotate_panel_rows(int64_t rows, int n) {
+static int64_t rotate_panel_rows(int64_t rows, int n) {
   const int64_t n_ct = cdiv(n, kGN);
   const int64_t cap = std::max<int64_t>(1, ((int64_t)1 << 27) / ((int64_t)n * 16) / kGM);   // row tiles
   const int64_t rounds = cap * n_ct / kGSlots;
@@ -2305,16 +2324,22 @@ int64_t rotate_panel_rows(int64_t rows, int n) {
   return std::min<int64_t>(rt, cdiv(rows, kGM)) * kGM;
 }
 
-// Room for the n x n matrix of rotate_device (in front of the panel's)
+// Doubles of the n x n matrix of a rotation and the panel behind it
+size_t rotation_doubles(int64_t rows, int n, bool upper) {
+  return ((rotate_by_panels(rows, n, upper) ? (size_t)rotate_panel_rows(rows, n) * n : 0) + (size_t)n * n) * 2;
+}
+
+// Room for the n x n matrix of rotate_device
 double2* rotation_matrix(chfsi_ctx* c, int64_t rows, int n, bool upper) {
-  c->panel.alloc(((upper ? 0 : (size_t)rotate_panel_rows(rows, n) * n) + (size_t)n * n) * 2);
+  c->panel.alloc(rotation_doubles(rows, n, upper));
   return reinterpret_cast<double2*>(c->panel.ptr);
 }
 
 void rotate_device(chfsi_ctx* c, double2* X, int64_t ldx, int64_t rows, int n, const double2* Qd, bool upper) {
+  const bool panels = rotate_by_panels(rows, n, upper);
   StageTimer tm(c, CHFSI_STAGE_ROTATE, 8.0 * (double)rows * n * n * (upper ? 0.5 : 1.0),
-                8.0 * (double)rows * n * n * (upper ? 0.5 : 1.0), (upper ? 2.0 : 4.0) * (double)rows * n * sizeof(double2));
-  if (upper) {
+                8.0 * (double)rows * n * n * (upper ? 0.5 : 1.0), (panels ? 4.0 : 2.0) * (double)rows * n * sizeof(double2));
+  if (!panels) {
     hipLaunchKernelGGL(rotate_upper_kernel, dim3(cdiv(rows, kGM)), dim3(256), 0, c->stream, X, ldx, rows, n, Qd);
     LAUNCH_CHECK();
     return;
@@ -2325,8 +2350,12 @@ void rotate_device(chfsi_ctx* c, double2* X, int64_t ldx, int64_t rows, int n, c
     const int64_t pr = std::min(prow, rows - r0);
     launch_copy_rows(c, P, n, X + r0 * ldx, ldx, pr, n);
     const int n_rt = cdiv(pr, kGM), n_ct = cdiv(n, kGN);
-    hipLaunchKernelGGL(rotate_kernel, dim3(8 * cdiv((int64_t)n_rt * n_ct, 8)), dim3(256), 0, c->stream, P, n, pr, Qd,
-                       X + r0 * ldx, ldx, n_rt, n_ct);
+    if (upper)
+      hipLaunchKernelGGL(rotate_kernel<true>, dim3(8 * cdiv(n_rt, 8) * n_ct), dim3(256), 0, c->stream, P, n, pr, Qd,
+                         X + r0 * ldx, ldx, n_rt, n_ct);
+    else
+      hipLaunchKernelGGL(rotate_kernel<false>, dim3(8 * cdiv((int64_t)n_rt * n_ct, 8)), dim3(256), 0, c->stream, P, n,
+                         pr, Qd, X + r0 * ldx, ldx, n_rt, n_ct);
     LAUNCH_CHECK();
   }
 }
