@@ -216,7 +216,11 @@ int chfsi_cheb_filter_resid(chfsi_ctx* ctx, int ik, void* X_d, int64_t ldx, cons
  * before the Rayleigh-Ritz step, Sec. III.B.2).  The factorisation runs on the
  * device, on the unit-diagonal D S D, D = diag(S)^{-1/2} (same result in exact
  * arithmetic).  On CHFSI_ENOTPD *bad_col (if non-NULL) is the first column whose
- * pivot is not positive and X is left unchanged.  Synchronises the stream. */
+ * pivot is not positive and X is left unchanged.  The pivot of a linearly dependent
+ * column is zero up to rounding, of either sign, and only refused where it is not
+ * positive: surely for a zero column and for two equal columns of one block of 32
+ * (columns 32 b .. 32 b + 31), not for dependent columns in general.  Synchronises the
+ * stream. */
 int chfsi_chol_gs(chfsi_ctx* ctx, void* X_d, int64_t ldx, int n_vec, int* bad_col);
 
 /* Rayleigh-Ritz on an orthonormal block (Sec. III.B.2): W = H_hat^k X,

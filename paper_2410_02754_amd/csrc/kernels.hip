@@ -2447,8 +2447,10 @@ __device__ __forceinline__ void chol_gemm(const CholTile& P, const CholTile& Q, 
 }
 
 // Factor of the diagonal block b in t and its inverse, by elimination of [t | I]:
-// 256 threads, two barriers a column (the quotients of the column, the rest).  Products of quotients (a_ik / d_k) conj(a_jk),
-// not of scaled columns, so that equal columns leave a pivot of exactly zero.
+// 256 threads, two barriers a column (the quotients of the column, the rest).  Products of
+// quotients (a_ik / d_k) conj(a_jk), not of scaled columns, so that two equal columns of
+// one block leave a pivot of exactly zero (in different blocks the pivot is a rounding,
+// of either sign: L_jp = A_jp L_pp^{-H} rounds).
 __device__ __forceinline__ void chol_factor(CholTile& t, CholTile& m, int n, int b, double2* __restrict__ L,
                                             double2* __restrict__ invd, int* __restrict__ info) {
   __shared__ double2 quot[kCB];
