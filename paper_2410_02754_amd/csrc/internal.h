@@ -314,6 +314,8 @@ void launch_copy_rows(chfsi_ctx* c, double2* dst, int64_t ldd, const double2* sr
 struct GramShape {
   int groups;                   // row ranges, each with its own partial sums
   int64_t tiles, range_rows;
+  bool high;                    // tiles of 128 rows, else 64
+  double cost;                  // tiles over the share of the rounds' places that they fill
 };
 GramShape gram_shape(int64_t rows, int n, bool lower_only);
 double2* gram_device(chfsi_ctx* c, const double2* X, int64_t ldx, const double2* Y, int64_t ldy, int64_t rows, int n,

@@ -2004,12 +2004,15 @@ void densities(chfsi_ctx* c, const double2* X, int64_t ldx, int n_vec, const dou
 constexpr int kGM = 64, kGN = 64, kGK = 8, kGPad = 2;   // pad: k rows 4 apart on other banks
 constexpr int kGSlots = 1024;    // workgroups of one round: 4 on each of 256 CUs
 
+// MB: 16-row blocks per wave (2: the tile of 64 rows)
+template <int MB = 2>
 struct GemmSmem {
-  double2 a[2][kGK][kGM + kGPad];
+  double2 a[2][kGK][32 * MB + kGPad];
   double2 b[2][kGK][kGN + kGPad];
 };
 
 // Tile t of an n x n product; triangular: the tiles (i, j <= i) row by row
+// (whole products: any height of tile)
 __device__ __forceinline__ int2 gram_tile(int t, int n, int lower) {
   if (!lower) {
     const int nt = (n + kGN - 1) / kGN;
@@ -2022,19 +2025,19 @@ __device__ __forceinline__ int2 gram_tile(int t, int n, int lower) {
 }
 
 // acc[mb][nb] (re, im) += op(A) B over one LDS stage; CONJ: op(A) = conj(A)
-template <bool CONJ>
-__device__ __forceinline__ void gemm_stage(const GemmSmem& sm, int buf, int wm, int wn, int lane, d4 (&cr)[2][2],
-                                           d4 (&ci)[2][2]) {
+template <bool CONJ, int MB>
+__device__ __forceinline__ void gemm_stage(const GemmSmem<MB>& sm, int buf, int wm, int wn, int lane, d4 (&cr)[MB][2],
+                                           d4 (&ci)[MB][2]) {
   const int kl = lane >> 4, il = lane & 15;
 #pragma unroll
   for (int ks = 0; ks < kGK / 4; ++ks) {
-    double2 fa[2], fb[2];
+    double2 fa[MB], fb[2];
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb) fa[mb] = sm.a[buf][ks * 4 + kl][wm * 32 + mb * 16 + il];
+    for (int mb = 0; mb < MB; ++mb) fa[mb] = sm.a[buf][ks * 4 + kl][wm * (16 * MB) + mb * 16 + il];
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) fb[nb] = sm.b[buf][ks * 4 + kl][wn * 32 + nb * 16 + il];
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
+    for (int mb = 0; mb < MB; ++mb) {
       const double ar = fa[mb].x, ai = CONJ ? -fa[mb].y : fa[mb].y, nai = -ai;
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb) {
@@ -2050,33 +2053,34 @@ __device__ __forceinline__ void gemm_stage(const GemmSmem& sm, int buf, int wm, 
 // Partial S = X^H Y over row ranges, lower-triangle tiles only when asked.
 // Work item = (tile, row range g), the items of one range consecutive on one XCD,
 // so the tiles reading the same rows share that XCD's L2.  partial[g] holds the
-// range's n x n sum.  A wave whose 32 x 32 lies above the diagonal of a triangular
+// range's n x n sum.  A wave whose block lies above the diagonal of a triangular
 // product has nothing to do but its share of the staging.
-__global__ __launch_bounds__(256, 4) void gram_kernel(const double2* __restrict__ X, int64_t ldx,
+template <int MB>
+__global__ __launch_bounds__(256, MB == 2 ? 4 : 2) void gram_kernel(const double2* __restrict__ X, int64_t ldx,
                                                       const double2* __restrict__ Y, int64_t ldy, int64_t rows,
                                                       int n, int64_t range_rows, int n_groups, int n_tiles,
                                                       int lower, double2* __restrict__ partial) {
-  __shared__ GemmSmem sm;
+  __shared__ GemmSmem<MB> sm;
   const int n_work = n_tiles * n_groups;
   const int per_xcd = (int)((gridDim.x + 7) / 8);
   const int bid = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
   if (bid >= n_work) return;              // uniform over the block, before any barrier
   const int g = bid / n_tiles;
   const int2 tl = gram_tile(bid - g * n_tiles, n, lower);
-  const int i0 = tl.x * kGM, j0 = tl.y * kGN;
+  const int i0 = tl.x * (32 * MB), j0 = tl.y * kGN;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wm = wave & 1, wn = wave >> 1;
-  const bool busy = !lower || i0 + wm * 32 + 31 >= j0 + wn * 32;
-  // staging map: 8 rows x 64 columns of each operand, 2 per thread, columns
+  const bool busy = !lower || i0 + (wm + 1) * (16 * MB) - 1 >= j0 + wn * 32;
+  // staging map: 8 rows x 32 MB or 64 columns of the operands, MB or 2 per thread, columns
   // (tid & 31) + 32 u, so each LDS store writes 32 consecutive elements of a row
   // (no bank conflicts) and each load reads 512 B
   const int sk = tid >> 5, sc = tid & 31;
-  d4 cr[2][2], ci[2][2];
+  d4 cr[MB][2], ci[MB][2];
 #pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
+  for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) cr[mb][nb] = ci[mb][nb] = d4{0, 0, 0, 0};
-  double2 pa[2], pb[2];
+  double2 pa[MB], pb[2];
   const int64_t r_begin = g * range_rows;
   const int64_t r_end = r_begin + range_rows < rows ? r_begin + range_rows : rows;
   auto gload = [&](int64_t r0) {
@@ -2085,18 +2089,21 @@ __global__ __launch_bounds__(256, 4) void gram_kernel(const double2* __restrict_
     const double2* xp = X + (rv ? r : 0) * ldx;
     const double2* yp = Y + (rv ? r : 0) * ldy;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int c = i0 + sc + 32 * u, d = j0 + sc + 32 * u;
+    for (int u = 0; u < MB; ++u) {
+      const int c = i0 + sc + 32 * u;
       pa[u] = (rv && c < n) ? xp[c] : double2{0.0, 0.0};
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int d = j0 + sc + 32 * u;
       pb[u] = (rv && d < n) ? yp[d] : double2{0.0, 0.0};
     }
   };
   auto lstore = [&](int buf) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      sm.a[buf][sk][sc + 32 * u] = pa[u];
-      sm.b[buf][sk][sc + 32 * u] = pb[u];
-    }
+    for (int u = 0; u < MB; ++u) sm.a[buf][sk][sc + 32 * u] = pa[u];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) sm.b[buf][sk][sc + 32 * u] = pb[u];
   };
   const int nst = (int)((r_end - r_begin + kGK - 1) / kGK);
   gload(r_begin);
@@ -2106,18 +2113,18 @@ __global__ __launch_bounds__(256, 4) void gram_kernel(const double2* __restrict_
     const int buf = st & 1;
     const bool more = st + 1 < nst;
     if (more) gload(r_begin + (int64_t)(st + 1) * kGK);
-    if (busy) gemm_stage<true>(sm, buf, wm, wn, lane, cr, ci);
+    if (busy) gemm_stage<true, MB>(sm, buf, wm, wn, lane, cr, ci);
     if (more) lstore(buf ^ 1);            // that buffer was last read before the previous barrier
     __syncthreads();
   }
   double2* out = partial + (size_t)g * n * n;
 #pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
+  for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int ri = i0 + wm * 32 + mb * 16 + acc_row<double>(lane, j);
+        const int ri = i0 + wm * (16 * MB) + mb * 16 + acc_row<double>(lane, j);
         const int cj = j0 + wn * 32 + nb * 16 + (lane & 15);
         if (ri < n && cj < n) out[(size_t)ri * n + cj] = double2{cr[mb][nb][j], ci[mb][nb][j]};
       }
@@ -2143,25 +2150,36 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double2* __restr
   S[(size_t)i * n + j] = s;
 }
 
-// Row ranges of a Gram product: one round of workgroups, cut at whole stages; past
-// half a round of tiles the count of at most four that fills its rounds best.
-GramShape gram_shape(int64_t rows, int n, bool lower_only) {
+// Tiles and row ranges of a Gram product.  Ranges: one round of workgroups, cut at whole
+// stages; past half a round of tiles the count of at most four that fills its rounds best.
+// Whole products of many columns take tiles of 128 rows, 2 workgroups on a CU, where the
+// columns past n and the last round's idle places do not undo a twentieth less per element
+// (a quarter less LDS traffic per MFMA): on 432000 rows 600 columns 23.0 against 24.5 ms,
+// 1000 59.0 and 62.2, but 800, seven tiles of 128 for 6.25, 41.6 with tiles of 64.
+// Triangular products would lose more above the diagonal.
+static GramShape gram_ranges(int64_t rows, int64_t tiles, int64_t slots) {
   GramShape g;
-  const int64_t nt = cdiv(n, kGM);
-  const int64_t tiles = lower_only ? nt * (nt + 1) / 2 : nt * nt;
-  g.tiles = tiles;
-  int64_t groups = std::max<int64_t>(1, kGSlots / tiles);
-  if (groups == 1) {
-    const auto fill = [&](int64_t k) {
-      return (double)(tiles * k) / (double)((tiles * k + kGSlots - 1) / kGSlots * kGSlots);
-    };
+  const auto fill = [&](int64_t k) { return (double)(tiles * k) / (double)((tiles * k + slots - 1) / slots * slots); };
+  int64_t groups = std::max<int64_t>(1, slots / tiles);
+  if (groups == 1)
     for (int64_t k = 2; k <= 4; ++k)
       if (fill(k) > 1.05 * fill(groups)) groups = k;
-  }
   groups = std::min<int64_t>(groups, std::max<int64_t>(1, rows / 64));
+  g.high = false;
+  g.tiles = tiles;
   g.range_rows = (cdiv(rows, groups) + kGK - 1) / kGK * kGK;
   g.groups = std::max(1, cdiv(rows, g.range_rows));
+  g.cost = (double)tiles / fill(g.groups);
   return g;
+}
+
+GramShape gram_shape(int64_t rows, int n, bool lower_only) {
+  const int64_t nt = cdiv(n, kGM);
+  const GramShape g = gram_ranges(rows, lower_only ? nt * (nt + 1) / 2 : nt * nt, kGSlots);
+  if (lower_only || n < 512) return g;
+  GramShape h = gram_ranges(rows, cdiv(n, 2 * kGM) * nt, kGSlots / 2);
+  h.high = true;
+  return 2.0 * 0.95 * h.cost < g.cost ? h : g;
 }
 
 // S = X^H Y on the device (its lower triangle): in c->scratch, which is grown for
@@ -2175,13 +2193,19 @@ double2* gram_device(chfsi_ctx* c, const double2* X, int64_t ldx, const double2*
   double2* partial = reinterpret_cast<double2*>(c->scratch.ptr);
   double2* Sd = partial + g.groups * nn;
   StageTimer tm(c, CHFSI_STAGE_GRAM, 8.0 * (double)rows * n * n * (lower_only ? 0.5 : 1.0),
-                8.0 * (double)rows * kGM * kGN * g.tiles, 2.0 * (double)rows * n * sizeof(double2));
+                8.0 * (double)rows * kGM * kGN * g.tiles * (g.high ? 2 : 1), 2.0 * (double)rows * n * sizeof(double2));
   const int64_t n_work = g.tiles * g.groups;
-  hipLaunchKernelGGL(gram_kernel, dim3(8 * cdiv(n_work, 8)), dim3(256), 0, c->stream, X, ldx, Y, ldy, rows, n,
-                     g.range_rows, g.groups, (int)g.tiles, lower_only ? 1 : 0, partial);
+  const dim3 grid(8 * cdiv(n_work, 8));
+  if (g.high)
+    hipLaunchKernelGGL(gram_kernel<4>, grid, dim3(256), 0, c->stream, X, ldx, Y, ldy, rows, n, g.range_rows, g.groups,
+                       (int)g.tiles, 0, partial);
+  else
+    hipLaunchKernelGGL(gram_kernel<2>, grid, dim3(256), 0, c->stream, X, ldx, Y, ldy, rows, n, g.range_rows, g.groups,
+                       (int)g.tiles, lower_only ? 1 : 0, partial);
   LAUNCH_CHECK();
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3((int)g.tiles, kGM / 4), dim3(256), 0, c->stream, partial, g.groups, n,
-                     lower_only ? 1 : 0, Sd);
+  const int nt = cdiv(n, kGN);
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3(lower_only ? nt * (nt + 1) / 2 : nt * nt, kGM / 4), dim3(256), 0, c->stream,
+                     partial, g.groups, n, lower_only ? 1 : 0, Sd);
   LAUNCH_CHECK();
   return Sd;
 }
@@ -2205,7 +2229,7 @@ void gram(chfsi_ctx* c, const double2* X, int64_t ldx, const double2* Y, int64_t
 // One 64 x 64 tile of P Q: rows r0.. of P (valid below prow), columns j0.., k below
 // kend, into X.  trim: the tile crosses Q's diagonal, a wave's k range ends at its
 // own last column.
-__device__ __forceinline__ void rotate_tile(GemmSmem& sm, const double2* P, int64_t ldp, int64_t r0, int64_t prow,
+__device__ __forceinline__ void rotate_tile(GemmSmem<>& sm, const double2* P, int64_t ldp, int64_t r0, int64_t prow,
                                             const double2* __restrict__ Q, int n, int j0, int kend, int trim,
                                             double2* X, int64_t ldx) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -2250,7 +2274,7 @@ __device__ __forceinline__ void rotate_tile(GemmSmem& sm, const double2* P, int6
     const int buf = st & 1;
     const bool more = st + 1 < nst;
     if (more) gload((st + 1) * kGK);
-    if (st * kGK < my_end) gemm_stage<false>(sm, buf, wm, wn, lane, cr, ci);
+    if (st * kGK < my_end) gemm_stage<false, 2>(sm, buf, wm, wn, lane, cr, ci);
     if (more) lstore(buf ^ 1);
     __syncthreads();                      // the last one: every read of P and sm is done
   }
@@ -2275,7 +2299,7 @@ template <bool UPPER>
 __global__ __launch_bounds__(256, 4) void rotate_kernel(const double2* __restrict__ P, int n, int64_t prow,
                                                         const double2* __restrict__ Q, double2* __restrict__ X,
                                                         int64_t ldx, int n_rt, int n_ct) {
-  __shared__ GemmSmem sm;
+  __shared__ GemmSmem<> sm;
   const int xcd = (int)(blockIdx.x % 8), i = (int)(blockIdx.x / 8);
   int rt, ct;
   if (UPPER) {
@@ -2298,7 +2322,7 @@ __global__ __launch_bounds__(256, 4) void rotate_kernel(const double2* __restric
 // workgroups per CU: at four it spills (5.4 against 5.0 ms on 432000 x 384).
 __global__ __launch_bounds__(256, 3) void rotate_upper_kernel(double2* X, int64_t ldx, int64_t rows, int n,
                                                               const double2* __restrict__ Q) {
-  __shared__ GemmSmem sm;
+  __shared__ GemmSmem<> sm;
   for (int j0 = (n - 1) / kGN * kGN; j0 >= 0; j0 -= kGN) {
     const int kend = j0 + kGN < n ? j0 + kGN : n;
     rotate_tile(sm, X, ldx, (int64_t)blockIdx.x * kGM, rows, Q, n, j0, kend, 1, X, ldx);
