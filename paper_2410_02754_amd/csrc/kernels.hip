@@ -820,6 +820,16 @@ static int nl_parts(const NonlocalK& nl, int n_vec) {
   return need <= (size_t)CHFSI_NOALLOC_SCRATCH_BYTES ? s : 1;
 }
 
+// Rows of partial sums per projector row: parts times columns, or what a narrower block in
+// more parts takes, so that scratch grown for one block serves every narrower one (under
+// stream capture it cannot grow).  Widths of one 16-column tile count share their parts.
+static size_t nl_partial_rows(const NonlocalK& nl, int n_vec) {
+  size_t m = (size_t)nl_parts(nl, n_vec) * n_vec;
+  for (int w = 16; w < n_vec && (int64_t)nl.n_chunks * (w / 16) <= 8192; w += 16)     // (beyond: whole chunks)
+    m = std::max(m, (size_t)nl_parts(nl, w) * w);
+  return m * nl.n_chunks;
+}
+
 // Columns per workgroup of the coefficient kernel.  A function of the whole block's
 // width, so that column groups sum alike: 1 where columns are one or two (16 atoms of
 // about 970 parts: 48 us with 16, 13 with 1), 4 where an atom has more than 64 parts
@@ -887,9 +897,7 @@ static const typename C2<T>::type* nonlocal_coeffs(chfsi_ctx* c, NonlocalK& nl,
   if (nl.n_atoms == 0 || nl.n_entries == 0) return nullptr;
   const int mr = 2 * nl.max_pj;
   const int nsub = nl_parts(nl, n_vec);
-  const size_t n_part = (size_t)nl.n_chunks * nsub * mr * n_vec;
   const size_t n_cp = (size_t)nl.n_atoms * mr * n_vec;
-  const size_t bytes = (n_part + n_cp) * sizeof(CT);
   int group = n_vec;                      // columns per contraction launch
   if (!scratch && c->nl_fixed) {
     // fixed buffer: whole coefficient arrays, then as many columns of
@@ -900,6 +908,7 @@ static const typename C2<T>::type* nonlocal_coeffs(chfsi_ctx* c, NonlocalK& nl,
     group = (int)std::min<size_t>(n_vec, (c->nl_fixed_bytes - head) / per_col);
     scratch = c->nl_fixed;
   } else if (!scratch) {
+    const size_t bytes = (nl_partial_rows(nl, n_vec) * mr + n_cp) * sizeof(CT);
     c->scratch.alloc((bytes + sizeof(double) - 1) / sizeof(double));
     scratch = c->scratch.ptr;
   }
@@ -1420,7 +1429,7 @@ size_t nonlocal_scratch_bytes(const KPoint& kp, int n_vec) {
   const NonlocalK& nl = kp.nl;
   if (nl.n_atoms == 0 || nl.n_entries == 0) return 0;
   const size_t mr = 2 * nl.max_pj;
-  const size_t n = (size_t)nl.n_chunks * nl_parts(nl, n_vec) * mr * n_vec + (size_t)nl.n_atoms * mr * n_vec;
+  const size_t n = nl_partial_rows(nl, n_vec) * mr + (size_t)nl.n_atoms * mr * n_vec;
   return n * sizeof(double2);  // the larger of the two precisions
 }
 

@@ -43,3 +43,39 @@ def test_captured_product_survives_wider_ones(form, k, prec, first):
             assert torch.equal(Y, want), n
             del fill, Z
     op.close()
+
+
+def test_captured_narrower_block_after_a_wider_warm_up():
+    """With atoms the scratch cannot grow under capture: what a wide product has taken serves
+    every narrower one, whose sums are cut into more parts."""
+    from paper_2410_02754_amd import Operator
+    s = synth.make_system("many", n_cells=(4, 4, 4), box=(4.0, 4.0, 4.0), p=6, n_atoms=40, lmax=1, rcut_sigmas=8.0,
+                          n_vec=1)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        op = Operator(s.n_cells, s.box, s.p, s.quad, s.n_q, s.kpts, stream=stream.cuda_stream, form="matrix_free")
+        op.set_local(torch.rand((op.n_cells, op.nq3), dtype=torch.float64, device="cuda"),
+                     torch.rand((op.n_cells, op.nq3, 3), dtype=torch.float64, device="cuda"))
+        op.set_atoms(s.atoms)
+        W = torch.tensor(synth.random_block(1, op.n_dof, 144), device="cuda")
+        op.apply_H(W, torch.empty_like(W))
+        widths = {n: W[:, :n].contiguous() for n in (3, 16, 64, 100)}
+        out = {n: torch.zeros_like(x) for n, x in widths.items()}
+        stream.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream, capture_error_mode="thread_local"):
+        for n, x in widths.items():
+            op.apply_H(x, out[n])
+    torch.cuda.synchronize()
+    for rep in range(3):
+        with torch.cuda.stream(stream):
+            for n, x in widths.items():
+                x.mul_(1.5)
+                out[n].zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            for n, x in widths.items():
+                want = op.apply_H(x, torch.empty_like(x))
+                torch.cuda.synchronize()
+                assert torch.equal(out[n], want), n
+    op.close()
