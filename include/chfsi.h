@@ -139,7 +139,8 @@ enum chfsi_form { CHFSI_FORM_CELL_MATRIX = 0, CHFSI_FORM_MATRIX_FREE = 1 };
  * n_q = p + 1 (GL with n_q = p + 1, or GLL).  CHFSI_PREC_MIXED runs the same
  * contractions in FP32 (tables, quadrature data and fields in FP32, rows
  * converted on gather and added into the FP64 output).  In a batch (below),
- * tasks of this form run their own per-colour launches.  The call clears the local operator (CHFSI_ESTATE until
+ * tasks of this form run their own cell launches, all cells in one (small tasks)
+ * or colour by colour.  The call clears the local operator (CHFSI_ESTATE until
  * the next chfsi_set_local builds it in the chosen form).  CHFSI_EINVAL for an
  * unknown form or unsupported mesh. */
 int chfsi_set_apply_form(chfsi_ctx* ctx, int form);
@@ -524,7 +525,7 @@ int chfsi_fill_random(chfsi_ctx* ctx, void* X_d, int64_t n_rows, int n_vec, int6
 /* Per-stage timing (HIP events recorded on the context's stream around each
  * launch of a stage; off by default).  Stages: */
 enum chfsi_stage {
-  CHFSI_STAGE_CELL_FP64 = 0,  /* gather + FP64 cell products + scatter-add, one launch per colour */
+  CHFSI_STAGE_CELL_FP64 = 0,  /* gather + FP64 cell products + scatter-add (per colour or at once) */
   CHFSI_STAGE_CELL_FP32 = 1,  /* the same in FP32 (mixed precision)                              */
   CHFSI_STAGE_NONLOCAL = 2,   /* projector contraction, coupling and back-product                 */
   CHFSI_STAGE_AXPY = 3,       /* recurrence initialisation / element-wise passes                  */

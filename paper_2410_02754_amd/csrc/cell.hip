@@ -1,7 +1,8 @@
 // Cell-level operator: setup of the Pauli-form cell matrices and the fused
 // gather / MFMA cell product / scatter-add kernels (Sec. IV.B, the
 // cell-level dense products of the FE matrix-multivector product), per
-// colour for one operator or as a persistent grid over a batch.
+// colour for one operator, for all its cells with the products written out, or as a
+// persistent grid over a batch.
 //
 // Cell operator storage ("Pauli form"): the spinor cell matrix of
 // eqn:FEHlocEl with the k-terms of eqn:FEHloc is, with every term scaled by
@@ -151,7 +152,7 @@ void launch_cell_setup(chfsi_ctx* c, KPoint& kp, const double* V, const double* 
 }
 
 // ============================================================================
-// Fused gather / cell product / scatter-add, one launch per colour
+// Fused gather / cell product / scatter-add, one launch per colour (or all cells)
 // ============================================================================
 // Block = 2 (row blocks) x WC (column groups) waves of 16 rows x 16*CB columns:
 // block tile 32 local rows x BN = 16*CB*WC columns of one cell.  K loop over
@@ -166,8 +167,8 @@ void launch_cell_setup(chfsi_ctx* c, KPoint& kp, const double* V, const double* 
 //   yu = Pu u,  yd = Pd d,  tx = Bx (u + d),  ty = By (u - i d)     (+ S: 4 more)
 //   Y_up = yu + tx + ty,    Y_dn = yd + tx + i ty
 // instead of the 12 of the products entry by entry.  The MFMAs bound the kernel
-// (80 % of its wave cycles wait for them), so the four extra accumulators and the
-// additions on the fragments are paid for.  FP64 filter of 128 columns on 8^3
+// (matrix units 75 % busy, 64 % of the wave cycles wait for issue), so the four extra
+// accumulators and the additions on the fragments are paid for.  FP64 filter of 128 columns on 8^3
 // cells, p = 6, degree 24: 97.2 -> 74.0 ms; with FP32 products and the k-term, 200
 // columns on 10^3 cells, p = 5, degree 16: 80.5 -> 68.7 ms.
 template <class T> struct CellC2;

@@ -138,7 +138,7 @@ constexpr int kNlRun = 16;
 struct KPoint {
   double k[3];
   bool gamma;
-  int nmat;                     // 4 at Gamma (Hp, Hm, Bx, By), 5 with the k-term S
+  int nmat;                     // 4 at Gamma (Pu, Pd, Bx, By: see cell.hip), 5 with the k-term S
   DevBuf<double> cell64;        // tiled cell operators, FP64
   DevBuf<float> cell32;         // FP32 copy
   DevBuf<double> U0, S;         // uniform parts of the cell operator at this k (built by the first set_local)

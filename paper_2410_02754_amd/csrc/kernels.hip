@@ -3,17 +3,19 @@
 // Operator action (Sec. IV.B, "FE discretized matrix multivector product"):
 // extraction X_e = R_e X, cell products H_e X_e, nonlocal projector terms,
 // assembly Y = sum_e R_e^T Y_e.  The four steps run as
-//   1. an element-wise pass that initialises the output with the recurrence
-//      terms (beta W + gamma X),
-//   2. the projector contraction C_a = P_a^H X, the coupling C'_a = Delta_a C_a
-//      and the node-centric back-product W += P_a C'_a (eqn:FEHnloc),
-//   3. one launch per cell colour of the fused gather / MFMA cell product /
-//      scatter-add kernel; cells of one colour share no node, so the
-//      read-add-write of the epilogue needs no atomics and the result is
-//      bitwise reproducible.
+//   1. the projector contraction C_a = P_a^H X and the coupling C'_a = Delta_a C_a
+//      (eqn:FEHnloc),
+//   2. an initialisation pass over the nodes: the recurrence terms (beta W + gamma X)
+//      and the back-product P_a C'_a,
+//   3. one launch per cell colour of the fused gather / cell product / scatter-add
+//      kernel; cells of one colour share no node, so the read-add-write of the
+//      epilogue needs no atomics and the result is bitwise reproducible.
+// Small applies run step 3 first, for all cells in one launch that writes the cells'
+// products (ye), and step 2 adds those of each node in the colour order
+// (products_scratch_bytes).
 //
-// The cell products (step 3) live in cell.hip; this file holds the element-wise,
-// nonlocal, adjoint and dense-block kernels.
+// The cell products live in cell.hip and matfree.hip; this file holds the
+// element-wise, nonlocal, adjoint and dense-block kernels.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1146,8 +1148,8 @@ void apply_nonlocal_init(chfsi_ctx* c, KPoint& kp, const double2* X, int64_t ldx
 }
 
 // ---- Small tasks of a batch: one launch per stage of an apply for all of them.  Per
-// task the same waves and blocks as in an apply by cells (bit for bit), with the
-// task in blockIdx.y and its arguments in device memory.
+// task the same waves and blocks as in an apply by cells (bit for bit); a table gives
+// each workgroup its task and block, and the tasks' arguments are in device memory.
 template <class T>
 struct BatchNl {
   NlContractArgs<T> c;
@@ -2007,9 +2009,8 @@ void densities(chfsi_ctx* c, const double2* X, int64_t ldx, int n_vec, const dou
 // sets the cache reads per MFMA, and against 128 x 64 less of it lies above the
 // diagonal of a triangular product and three or four workgroups fit a CU, so that
 // fewer rows still fill the GPU.  On 432000 rows x 384 columns: Gram product 5.9 ->
-// 5.0 ms (matrix units 77 % busy at 2.13 GHz), triangular rotation 8.4 (with the
-// copies of its panels) -> 5.0 ms; 250000 x 256: Gram 2.4 -> 1.4, full rotation 2.7
-// either way.
+// 5.0 ms (matrix units 77 % busy), triangular rotation 8.4 (with the copies of its
+// panels) -> 5.0 ms; 250000 x 256: Gram 2.4 -> 1.4, full rotation 2.7 either way.
 constexpr int kGM = 64, kGN = 64, kGK = 8, kGPad = 2;   // pad: k rows 4 apart on other banks
 constexpr int kGSlots = 1024;    // workgroups of one round: 4 on each of 256 CUs
 

@@ -25,11 +25,12 @@
 // arithmetic in FP32, rows converted on gather and added into the FP64 output).
 //
 // Launch: one workgroup of 256 (FP64) or 512 (FP32) threads per (cell of one
-// colour, chunk of CW columns).  Both spins of CW columns live in two LDS buffers of n_p^3 complex
-// values per field; each thread owns one line (along the pass direction) of
-// one (column, spin) field, keeps it in registers and writes the contracted
+// colour, chunk of CW columns).  Both spins of CW columns live in two LDS buffers of
+// n_p^3 complex values per field; each thread owns one line (along the pass direction)
+// of one (column, spin) field, keeps it in registers and writes the contracted
 // line, so every LDS value read feeds n_p multiply-adds.  Within a colour no
-// two cells share a node, so the scatter is a plain read-add-write.
+// two cells share a node, so the scatter is a plain read-add-write.  Or one launch for
+// all cells, which writes the products out cell by cell (ye).
 #include <functional>
 
 #include "mfma.h"
@@ -123,13 +124,14 @@ __device__ __forceinline__ void grad_line(const T* __restrict__ eoDf, const T* _
 
 // Lines of a pass along y: groups of 8 lanes share one z, so that the lanes of a
 // 128-bit LDS access hit distinct banks (consecutive lines of n_p = 6, 7 overlap by
-// the pitch of a plane: 37 % of the kernel's LDS cycles were conflicts); other
+// the pitch of a plane: conflicts per LDS cycle 0.37 with them, 0.34 so, at n_p = 7); other
 // orders keep consecutive lines.
 template <int NP>
 constexpr int mf_ypitch() { return NP == 6 || NP == 7 ? 8 : NP; }
 
 // Points between neighbouring x-lines in LDS: n_p = 8 would put every line of an x pass
-// on the same banks (degree-6 filter, k = 0, FP64, 128 columns on 8^3 cells: 10.2 against 10.4 ms).
+// on the same banks (degree-6 filter, k = 0, FP64, 128 columns on 8^3 cells: 10.2 against
+// 10.4 ms).
 template <int NP>
 constexpr int mf_pitch() { return NP == 8 ? 9 : NP; }
 
@@ -138,8 +140,8 @@ constexpr int mf_pitch() { return NP == 8 ? 9 : NP; }
 // a pass over the LDS, but takes the registers of four lines and half the threads (a
 // quarter of them at n_p >= 8).  With the k-term that never pays: against together,
 // FP64 degree-6 filter, 128 columns: p = 5, 14^3 cells 17.3 and 17.8 ms, p = 6, 12^3
-// 17.8 and 18.4, p = 7, 8^3 9.9 and 11.8, p = 8, 8^3 17.7 and 20.0; FP32, p = 6, 15.9 and 17.5.
-// At k = 0 it pays for n_p = 8 (9.9 and 10.4, FP32 8.3 and 9.2) and in FP32 for 7 (15.8
+// 17.8 and 18.4, p = 7, 8^3 9.9 and 11.8, p = 8, 8^3 17.7 and 20.0; FP32, p = 6, 15.9 and
+// 17.5.  At k = 0 it pays for n_p = 8 (9.9 and 10.4, FP32 8.3 and 9.2) and in FP32 for 7 (15.8
 // and 16.2), not elsewhere (FP64 p = 6 17.7 and 17.3, p = 8 18.9 and 17.7).
 template <class T, int NP, bool KT>
 constexpr bool mf_split() { return KT || NP == 8 || (sizeof(T) == 4 && NP == 7); }
@@ -159,11 +161,11 @@ constexpr bool mf_split() { return KT || NP == 8 || (sizeof(T) == 4 && NP == 7);
 //   3. x: B -> U; potential, kinetic x     7. B^T along x, y scattered
 //   4. + kinetic y
 // (phase 3 takes the x-lines of both spins together or one by one, see mf_split).
-// Nothing saturates: the vector units (38 % busy), the requests of 32-byte row
-// pieces to L2 (45 %), the LDS and the waits for rows each take a share at the
-// three workgroups per CU that 44 KB of LDS allow, so each is kept short: one
-// contraction per kinetic term (FP64), one 64-bit multiplication per line's
-// addresses, quadrature data in the order of the lanes, the old values of the
+// Nothing saturates: the vector units (36 % busy), the requests of 32-byte row
+// pieces to L2 (42 % of one per clock and channel), the LDS and the waits for rows (41 %
+// of the wave cycles; p = 6, k = 0, FP64) each take a share at the three workgroups per
+// CU that 44 KB of LDS allow, so each is kept short: one contraction per kinetic term
+// (FP64), one 64-bit multiplication per line's addresses, quadrature data in the order of the lanes, the old values of the
 // output rows loaded right after phase 3 and used in phase 7, barriers that order
 // LDS only.  Per colour launch of 512 cells, p = 6, 128 columns: 0.73 -> 0.61 ms; filter
 // of 16^3 cells, degree 24: 225 -> 205 ms.
