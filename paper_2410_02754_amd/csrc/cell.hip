@@ -167,7 +167,7 @@ void launch_cell_setup(chfsi_ctx* c, KPoint& kp, const double* V, const double* 
 //   yu = Pu u,  yd = Pd d,  tx = Bx (u + d),  ty = By (u - i d)     (+ S: 4 more)
 //   Y_up = yu + tx + ty,    Y_dn = yd + tx + i ty
 // instead of the 12 of the products entry by entry.  The MFMAs bound the kernel
-// (matrix units 75 % busy, 64 % of the wave cycles wait for issue), so the four extra
+// (matrix units 74 % busy, 64 % of the wave cycles wait for issue), so the four extra
 // accumulators and the additions on the fragments are paid for.  FP64 filter of 128 columns on 8^3
 // cells, p = 6, degree 24: 97.2 -> 74.0 ms; with FP32 products and the k-term, 200
 // columns on 10^3 cells, p = 5, degree 16: 80.5 -> 68.7 ms.
