@@ -68,9 +68,14 @@ static void uniform_parts(chfsi_ctx* c, KPoint& kp) {
         }
         S[(size_t)i * N + j] = -0.5 * (cij - cji);
       }
-  kp.S.upload(S.data(), S.size(), c->stream);
-  kp.U0.upload(U0.data(), U0.size(), c->stream);
-  CHFSI_HIP(hipStreamSynchronize(c->stream));   // the host arrays end here
+  try {
+    kp.S.upload(S.data(), S.size(), c->stream);
+    kp.U0.upload(U0.data(), U0.size(), c->stream);
+    CHFSI_HIP(hipStreamSynchronize(c->stream));   // the host arrays end here
+  } catch (...) {
+    kp.U0.release();                              // (not filled: built by the next call)
+    throw;
+  }
 }
 
 static void require_operator(const chfsi_ctx* c) {
@@ -197,6 +202,8 @@ int chfsi_set_apply_form(chfsi_ctx* c, int form) {
   for (auto* kp : c->kp) {
     kp->cell64.release();
     kp->cell32.release();
+    kp->U0.release();
+    kp->S.release();
   }
   c->mf_qd.release();
   c->mf_qd32.release();
