@@ -245,8 +245,8 @@ int chfsi_overlap(chfsi_ctx* ctx, const void* X_d, int64_t ldx, const void* Y_d,
  * partial sums, the cells' products of an apply), excluding the caller's buffers
  * (X, work, the backward workspace): the peak of the call on a fresh context in either
  * precision, in bytes; 0 for invalid arguments.  The buffer of the cells' products is one
- * that applies can do without: the library takes it only where a sixteenth of the
- * device's memory stays free beside it and all contexts and batches of the device hold at
+ * that applies can do without: the library takes it only where (above 32 MiB) a sixteenth
+ * of the device's memory stays free beside it and all contexts and batches of the device hold at
  * most 8 GiB of such buffers, and gives it back where another allocation of the context
  * fails and in chfsi_set_apply_form; a larger one is taken before the one it replaces
  * goes. */

@@ -18,10 +18,13 @@ void* SpareBuf::get(size_t bytes) {
   {
     std::lock_guard<std::mutex> lk(g_mu);
     size_t avail = 0, total = 0;
-    const bool known = hipGetDevice(&dev) == hipSuccess && hipMemGetInfo(&avail, &total) == hipSuccess;
+    const bool known = hipGetDevice(&dev) == hipSuccess;
     const size_t mine = dev == device_ ? bytes_ : 0;      // given back once p is there
-    if (known && g_held[dev] - mine + bytes <= kSpareMax && avail >= bytes + total / 16 &&
-        hipMalloc(&p, bytes) == hipSuccess)
+    const auto room = [&]() {
+      return bytes <= kSpareSmall ||
+             (hipMemGetInfo(&avail, &total) == hipSuccess && avail >= bytes + total / 16);
+    };
+    if (known && g_held[dev] - mine + bytes <= kSpareMax && room() && hipMalloc(&p, bytes) == hipSuccess)
       g_held[dev] += bytes;
     else
       p = nullptr;

@@ -1,8 +1,9 @@
 // Device memory that a call can do without: with it a faster route runs, without it
 // another one with the same results.  So it is never taken where it could be missed:
-// all such buffers of a device hold at most kSpareMax together, one is only taken where a
-// sixteenth of the device's memory stays free beside it, and an allocation that fails
-// takes its context's back (DevBuf::spare).
+// all such buffers of a device hold at most kSpareMax together, one above kSpareSmall is
+// only taken where a sixteenth of the device's memory stays free beside it (asking cost
+// a context's first pass 9 to 10 us of 218 and 289), and an allocation that fails takes
+// its context's back (DevBuf::spare).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -12,7 +13,7 @@
 
 namespace chfsi {
 
-constexpr size_t kSpareMax = (size_t)8 << 30;
+constexpr size_t kSpareMax = (size_t)8 << 30, kSpareSmall = (size_t)32 << 20;
 
 class SpareBuf {
  public:

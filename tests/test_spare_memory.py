@@ -101,6 +101,9 @@ int main() {
     void* hog;
     assert(hipMalloc(&hog, 269 * GB) == hipSuccess);
     assert(!a.get(2 * GB) && a.get(GB) && !b.get(GB));
+    SpareBuf s;                                       // (small ones are not asked about)
+    assert(s.get(32 * MB) && !s.get(33 * MB));
+    s.release();
     // an allocation that fails takes its context's back
     DevBuf<double> d;
     bool threw = false;
