@@ -68,10 +68,19 @@ __device__ __forceinline__ void block_sums(double (&v)[NS], double* sm) {
 // waited for each other's trips to memory (128 steps: p = 3, 48^3 cells 121 ms, now 40;
 // p = 6, 16^3 17.6 and 10.4).
 constexpr int kCgDots = 6, kCgPq = 0, kCgRr = 1, kCgRz = 3, kCgBb = 5, kCgParts = 2048;
-// this thread's share of the n parts of dot k
+// Where part i of dot k lies, and this thread's share of the n parts.  Up to 256 of them
+// (MANY = false) a fixed stride and one part per thread: with the run's stride and the
+// loop small meshes took 1 to 2 % longer (128 steps: 3^3 cells, p = 4 1.755 ms and 1.725;
+// 4^3, p = 4 1.747 and 1.716, p = 7 2.772 and 2.731).
+template <bool MANY>
+__device__ __forceinline__ int cg_at(int stride, int k, int i) {
+  return k * (MANY ? stride : 256) + i;
+}
+template <bool MANY>
 __device__ __forceinline__ double cg_part(const double* __restrict__ red, int stride, int k, int n) {
-  double s = (int)threadIdx.x < n ? red[k * stride + threadIdx.x] : 0.0;
-  for (int i = threadIdx.x + 256; i < n; i += 256) s += red[k * stride + i];
+  double s = (int)threadIdx.x < n ? red[cg_at<MANY>(stride, k, threadIdx.x)] : 0.0;
+  if constexpr (MANY)
+    for (int i = threadIdx.x + 256; i < n; i += 256) s += red[cg_at<MANY>(stride, k, i)];
   return s;
 }
 
@@ -87,6 +96,7 @@ __device__ __forceinline__ double inv_diag(const ScalMesh& m, double kappa2, int
 }
 
 // r = b, u = 0, z = r / diag(A); partial b.b (= r.r) and r.z
+template <bool MANY>
 __global__ __launch_bounds__(256) void cg_start_kernel(const ScalMesh m, double kappa2, int64_t n,
                                                        const double* __restrict__ b, double* __restrict__ u,
                                                        double* __restrict__ r, double* __restrict__ z, int stride,
@@ -105,10 +115,10 @@ __global__ __launch_bounds__(256) void cg_start_kernel(const ScalMesh m, double 
   rr = block_sum(rr, sm);
   rz = block_sum(rz, sm);
   if (threadIdx.x == 0) {
-    red[kCgRr * stride + blockIdx.x] = rr;
-    red[kCgBb * stride + blockIdx.x] = rr;
-    red[kCgRz * stride + blockIdx.x] = rz;
-    if (blockIdx.x == 0) red[kCgDots * stride] = -1.0;
+    red[cg_at<MANY>(stride, kCgRr, blockIdx.x)] = rr;
+    red[cg_at<MANY>(stride, kCgBb, blockIdx.x)] = rr;
+    red[cg_at<MANY>(stride, kCgRz, blockIdx.x)] = rz;
+    if (blockIdx.x == 0) red[cg_at<MANY>(stride, kCgDots, 0)] = -1.0;
   }
 }
 
@@ -116,21 +126,23 @@ __global__ __launch_bounds__(256) void cg_start_kernel(const ScalMesh m, double 
 struct CgHead {
   double state, d[4];
 };
+template <bool MANY>
 __device__ __forceinline__ CgHead cg_ask(const double* __restrict__ red, int stride, int n_part, int it) {
   const int odd = it & 1;
-  return CgHead{red[kCgDots * stride],
-                {cg_part(red, stride, kCgRr + odd, n_part), cg_part(red, stride, kCgBb, n_part),
-                 cg_part(red, stride, kCgRz + odd, n_part),
-                 it > 0 ? cg_part(red, stride, kCgRz + 1 - odd, n_part) : 0.0}};
+  return CgHead{red[cg_at<MANY>(stride, kCgDots, 0)],
+                {cg_part<MANY>(red, stride, kCgRr + odd, n_part), cg_part<MANY>(red, stride, kCgBb, n_part),
+                 cg_part<MANY>(red, stride, kCgRz + odd, n_part),
+                 it > 0 ? cg_part<MANY>(red, stride, kCgRz + 1 - odd, n_part) : 0.0}};
 }
 // ... and beta from them, or false if the iteration has ended (a step before, or now)
+template <bool MANY>
 __device__ __forceinline__ bool cg_go(CgHead& h, double* sm, double* __restrict__ red, int stride, int it, double tol,
                                       double& beta) {
   block_sums(h.d, sm);
   if (h.state >= 0.0) return false;
   const double rr = h.d[0], bb = h.d[1];
   if (bb == 0.0 || (it > 0 && sqrt(rr) / sqrt(bb) <= tol)) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) red[kCgDots * stride] = (double)it;
+    if (blockIdx.x == 0 && threadIdx.x == 0) red[cg_at<MANY>(stride, kCgDots, 0)] = (double)it;
     return false;
   }
   beta = it == 0 ? 0.0 : h.d[2] / h.d[3];
@@ -145,7 +157,7 @@ __device__ __forceinline__ bool cg_go(CgHead& h, double* sm, double* __restrict_
 // along, scaled at the end.  On a small mesh a step is a chain of trips to memory: the
 // state, the partial sums and the first cell's frame are all asked for at once
 // (5.9 us on 4^3 cells, p = 4, and the update 3.5; 8.8 and 4.1 one after the other).
-template <int P>
+template <int P, bool MANY>
 __global__ __launch_bounds__(256) void cg_apply_kernel(const ScalMesh m, double kappa2, int64_t n, int n_part,
                                                        int it, double tol, const double* __restrict__ z,
                                                        const double* __restrict__ p_old, double* __restrict__ p_new,
@@ -155,7 +167,7 @@ __global__ __launch_bounds__(256) void cg_apply_kernel(const ScalMesh m, double 
   __shared__ double sm[16];
   constexpr int p = P, w = 2 * p + 1, w3 = w * w * w;
   constexpr int kCgPre = w3 <= 1024 ? (w3 + 255) / 256 : 4;       // frame values per thread fetched ahead
-  CgHead head = cg_ask(red, stride, n_part, it);
+  CgHead head = cg_ask<MANY>(red, stride, n_part, it);
   const auto node = [&](int e, int t) {   // frame entry t of cell e
     const int cx = e % m.nx, cyz = e / m.nx, cy = cyz % m.ny, cz = cyz / m.ny;
     const int fx = t % w, fy = (t / w) % w, fz = t / (w * w);
@@ -179,11 +191,11 @@ __global__ __launch_bounds__(256) void cg_apply_kernel(const ScalMesh m, double 
   double* sS = sM + p * w * w;            // stiffness part, likewise
   for (int t = threadIdx.x; t < 2 * p * w; t += 256) sR[t] = m.rows[t];
   double beta;
-  if (!cg_go(head, sm, red, stride, it, tol, beta)) return;
+  if (!cg_go<MANY>(head, sm, red, stride, it, tol, beta)) return;
   const double* rS = sR;
   const double* rM = sR + p * w;
   double pq = 0.0;
-  for (int e = blockIdx.x; e < n; e += gridDim.x) {
+  for (int e = blockIdx.x; e < (int)n; e += gridDim.x) {
     const bool first = e == (int)blockIdx.x;
     if (!first) __syncthreads();          // the last cell's sX is read
     const auto put = [&](int t, double zv, double pv) {
@@ -259,14 +271,14 @@ __global__ __launch_bounds__(256) void cg_apply_kernel(const ScalMesh m, double 
     }
   }
   pq = block_sum(pq, sm);
-  if (threadIdx.x == 0) red[kCgPq * stride + blockIdx.x] = pq;
+  if (threadIdx.x == 0) red[cg_at<MANY>(stride, kCgPq, blockIdx.x)] = pq;
 }
 
 // The same first half for orders 1 and 2, a thread per node: its row of A reaches 27 to
 // 125 nodes, read through the caches, where a workgroup per cell would have one or eight
 // nodes to share its barriers: 128 steps on 64^3 cells with p = 1 4 and 34 ms, p = 2 36
 // and 51; on 16^3 with p = 2 3.3 and 2.9.  From p = 3 a node reads too many.
-template <int P>
+template <int P, bool MANY>
 __global__ __launch_bounds__(256) void cg_apply_node_kernel(const ScalMesh m, double kappa2, int64_t n, int n_part,
                                                             int it, double tol, const double* __restrict__ z,
                                                             const double* __restrict__ p_old,
@@ -276,9 +288,9 @@ __global__ __launch_bounds__(256) void cg_apply_node_kernel(const ScalMesh m, do
   constexpr int w = 2 * P + 1;
   __shared__ double sR[2 * P * w];
   for (int t = threadIdx.x; t < 2 * P * w; t += 256) sR[t] = m.rows[t];
-  CgHead head = cg_ask(red, stride, n_part, it);
+  CgHead head = cg_ask<MANY>(red, stride, n_part, it);
   double beta;
-  if (!cg_go(head, sm, red, stride, it, tol, beta)) return;   // (its barriers order sR)
+  if (!cg_go<MANY>(head, sm, red, stride, it, tol, beta)) return;   // (its barriers order sR)
   double pq = 0.0;
   for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
     const int iyz = (int)(i / m.Nx), ix = (int)(i - (int64_t)iyz * m.Nx), iz = iyz / m.Ny, iy = iyz - iz * m.Ny;
@@ -324,10 +336,11 @@ __global__ __launch_bounds__(256) void cg_apply_node_kernel(const ScalMesh m, do
     pq = fma(own, y, pq);
   }
   pq = block_sum(pq, sm);
-  if (threadIdx.x == 0) red[kCgPq * stride + blockIdx.x] = pq;
+  if (threadIdx.x == 0) red[cg_at<MANY>(stride, kCgPq, blockIdx.x)] = pq;
 }
 
 // Second half: u += alpha p, r -= alpha q, z = r / diag(A); partial r.r, r.z for the next step
+template <bool MANY>
 __global__ __launch_bounds__(256) void cg_update_kernel(const ScalMesh m, double kappa2, int64_t n, int n_part,
                                                         int n_pq, int it, const double* __restrict__ p,
                                                         const double* __restrict__ q, double* __restrict__ u,
@@ -335,8 +348,8 @@ __global__ __launch_bounds__(256) void cg_update_kernel(const ScalMesh m, double
                                                         double* __restrict__ red) {
   __shared__ double sm[8];
   const int odd = it & 1;
-  const double state = red[kCgDots * stride];
-  double d[2] = {cg_part(red, stride, kCgRz + odd, n_part), cg_part(red, stride, kCgPq, n_pq)};
+  const double state = red[cg_at<MANY>(stride, kCgDots, 0)];
+  double d[2] = {cg_part<MANY>(red, stride, kCgRz + odd, n_part), cg_part<MANY>(red, stride, kCgPq, n_pq)};
   const int64_t i0 = blockIdx.x * (int64_t)256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
   // this thread's first values, asked for with the sums
   const int64_t ic = i0 < n ? i0 : n - 1;
@@ -363,8 +376,8 @@ __global__ __launch_bounds__(256) void cg_update_kernel(const ScalMesh m, double
   }
   block_sums(s, sm);
   if (threadIdx.x == 0) {
-    red[(kCgRr + 1 - odd) * stride + blockIdx.x] = s[0];
-    red[(kCgRz + 1 - odd) * stride + blockIdx.x] = s[1];
+    red[cg_at<MANY>(stride, kCgRr + 1 - odd, blockIdx.x)] = s[0];
+    red[cg_at<MANY>(stride, kCgRz + 1 - odd, blockIdx.x)] = s[1];
   }
 }
 
@@ -657,6 +670,21 @@ static void scal_interp(chfsi_ctx* c, FieldOps& f, const double* u, double* out)
   LAUNCH_CHECK();
 }
 
+// The kernels of order p (see cg_at)
+struct CgKernels {
+  decltype(&cg_start_kernel<true>) start;
+  decltype(&cg_apply_kernel<3, true>) apply;
+  decltype(&cg_update_kernel<true>) update;
+};
+template <bool MANY>
+static CgKernels cg_kernels(int p) {
+  static constexpr decltype(&cg_apply_kernel<3, MANY>) kApply[] = {
+      cg_apply_node_kernel<1, MANY>, cg_apply_node_kernel<2, MANY>, cg_apply_kernel<3, MANY>, cg_apply_kernel<4, MANY>,
+      cg_apply_kernel<5, MANY>,      cg_apply_kernel<6, MANY>,      cg_apply_kernel<7, MANY>, cg_apply_kernel<8, MANY>};
+  static_assert(sizeof kApply / sizeof *kApply == kMaxP, "one per order");
+  return {cg_start_kernel<MANY>, kApply[p - 1], cg_update_kernel<MANY>};
+}
+
 // A u = b by CG preconditioned with diag(A)^{-1}, A = K_s + kappa2 M_c; b is v[6]; u
 // returned in v[0].  Stops when ||r|| <= tol ||b||.  Returns the iteration count
 // (negative if max_iter hit).  The host looks every kCgBatch steps; the steps issued
@@ -671,23 +699,21 @@ static int pcg(chfsi_ctx* c, FieldOps& f, double kappa2, double tol, int max_ite
   const bool by_node = p <= 2;
   const int n_part = std::min(kCgParts, cdiv(n, 256));
   const int n_pq = by_node ? n_part : std::min(kCgParts, c->n_cells);
-  const int stride = std::max(n_part, n_pq);
+  const bool many = std::max(n_part, n_pq) > 256;
+  const int stride = many ? std::max(n_part, n_pq) : 256;
   const size_t sh = by_node ? 0 : (size_t)(2 * p * w + w * w * w + 2 * p * w * w) * sizeof(double);
-  static constexpr decltype(&cg_apply_kernel<3>) kApply[] = {
-      cg_apply_node_kernel<1>, cg_apply_node_kernel<2>, cg_apply_kernel<3>, cg_apply_kernel<4>,
-      cg_apply_kernel<5>,      cg_apply_kernel<6>,      cg_apply_kernel<7>, cg_apply_kernel<8>};
-  static_assert(sizeof kApply / sizeof *kApply == kMaxP, "one per order");
-  hipLaunchKernelGGL(cg_start_kernel, dim3(n_part), dim3(256), 0, c->stream, f.mesh, kappa2, n, b, u, r, z, stride,
-                     f.red.ptr);
+  const CgKernels k = many ? cg_kernels<true>(p) : cg_kernels<false>(p);
+  hipLaunchKernelGGL(k.start, dim3(n_part), dim3(256), 0, c->stream, f.mesh, kappa2, n, b, u, r, z, stride, f.red.ptr);
   LAUNCH_CHECK();
   std::vector<double> h((size_t)kCgDots * stride + 1);
   for (int it = 0;;) {
     const int end = std::min(max_iter, it + kCgBatch);
     for (; it < end; ++it) {
-      hipLaunchKernelGGL(kApply[p - 1], dim3(n_pq), dim3(256), sh, c->stream, f.mesh, kappa2,
-                         by_node ? n : c->n_cells, n_part, it, tol, z, pp[1 - (it & 1)], pp[it & 1], q, stride, f.red.ptr);
+      hipLaunchKernelGGL(k.apply, dim3(n_pq), dim3(256), sh, c->stream, f.mesh, kappa2,
+                         by_node ? n : c->n_cells, n_part, it, tol, z, pp[1 - (it & 1)], pp[it & 1], q, stride,
+                         f.red.ptr);
       LAUNCH_CHECK();
-      hipLaunchKernelGGL(cg_update_kernel, dim3(n_part), dim3(256), 0, c->stream, f.mesh, kappa2, n, n_part, n_pq, it,
+      hipLaunchKernelGGL(k.update, dim3(n_part), dim3(256), 0, c->stream, f.mesh, kappa2, n, n_part, n_pq, it,
                          pp[it & 1], q, u, r, z, stride, f.red.ptr);
       LAUNCH_CHECK();
     }

@@ -63,3 +63,9 @@ def test_residual_of_the_nodal_solution(p, nc):
     b = scf.project(m, rho[idx])
     r = b - scf.scalar_operator(m, K0**2) @ u
     assert np.linalg.norm(r) < 1e-11 * np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("p,nc", [(1, (64, 32, 32)), (1, (65, 32, 32)), (3, (8, 8, 4)), (3, (43, 3, 2))])
+def test_around_256_parts(p, nc):
+    """256 parts of the sums and a few more, by nodes and by cells."""
+    test_residual_of_the_nodal_solution(p, nc)
